@@ -125,6 +125,8 @@ static void free_ensemble(rid_ensemble_impl& e) {
   dev_free(e.d_wo);
   dev_free(e.d_bo);
   dev_free(e.d_vscale);
+  dev_free(e.split.frag);
+  dev_free(e.split.vec);
   dev_free(e.d_raw);
   dev_free(e.d_cvw);
   dev_free(e.d_bounds);
@@ -169,10 +171,7 @@ rid_status bias_force_core(rid_system_impl& s, rid_ensemble_impl& e, const float
                            float* d_force, float* d_energy, float* d_eps, float* d_sigma,
                            uint8_t* d_flags, hipStream_t st) {
   rid_status r;
-  if (e.frag_dirty) {
-    if ((r = pack_ensemble_weights(e, st)) != RID_OK) return r;
-    e.frag_dirty = false;
-  }
+  if ((r = ensure_packed(e, st)) != RID_OK) return r;
   const TorsionInput tin{&s, d_pos};
   r = B <= RID_FROM_POS_MAX_B ? launch_mlp_from_pos(e, tin, B, A, g, st) : RID_EUNSUPPORTED;
   if (r == RID_EUNSUPPORTED) {
@@ -349,6 +348,24 @@ rid_status rid_ensemble_create(int n_cv, int n_models, int n_hidden,
   }
   e.frag_bytes_per_model = off;
   rid_status st = RID_OK;
+  if (prec == RID_FP32) {
+    split_layout(e);
+    SplitDev& s = e.split;
+    const size_t KL = (size_t)n_models * n_hidden;
+    const size_t n_bias = KL * s.NP, n_rs = KL * 2 * s.RW, n_bound = KL * 2 * 32,
+                 n_wo = (size_t)n_models * s.NP;
+    if ((st = dev_alloc(&s.frag, s.frag_bytes * n_models)) != RID_OK ||
+        (st = dev_alloc(&s.vec, n_bias + n_rs + n_bound + n_wo + n_models)) != RID_OK) {
+      free_ensemble(e);
+      delete h;
+      return st;
+    }
+    s.bias = s.vec;
+    s.rs = s.bias + n_bias;
+    s.bound = s.rs + n_rs;
+    s.wo = s.bound + n_bound;
+    s.bo = s.wo + n_wo;
+  }
   if ((st = dev_alloc(&e.d_master, e.n_params)) != RID_OK ||
       (st = dev_alloc(&e.d_m, e.n_params)) != RID_OK ||
       (st = dev_alloc(&e.d_v, e.n_params)) != RID_OK ||
@@ -563,10 +580,7 @@ rid_status rid_model_dev(rid_ensemble ens, const float* d_s, int B, float* d_eps
   if ((r = e.ws_A.ensure(sizeof(float) * e.K * (size_t)B)) != RID_OK) return r;
   if ((r = e.ws_g.ensure(sizeof(float) * e.K * (size_t)B * e.n_cv)) != RID_OK) return r;
   if ((r = launch_embed(d_s, B, e.n_cv, e.d_raw, e.ws_x.as<float>(), st)) != RID_OK) return r;
-  if (e.frag_dirty) {
-    if ((r = pack_ensemble_weights(e, st)) != RID_OK) return r;
-    e.frag_dirty = false;
-  }
+  if ((r = ensure_packed(e, st)) != RID_OK) return r;
   if ((r = launch_mlp(e, e.ws_x.as<float>(), B, e.ws_A.as<float>(), e.ws_g.as<float>(), st)) != RID_OK)
     return r;
   return launch_ensemble_reduce(e.K, e.n_cv, B, e.ws_A.as<float>(), e.ws_g.as<float>(),

@@ -166,10 +166,7 @@ rid_status launch_bias_conservative(const rid_system_impl& s, rid_ensemble_impl&
   if ((r = e.ws_A.ensure(sizeof(float) * K * (size_t)B)) != RID_OK) return r;
   if ((r = e.ws_g.ensure(sizeof(float) * K * nb)) != RID_OK) return r;
   if ((r = e.ws_x.ensure(sizeof(float) * 2 * nb)) != RID_OK) return r;
-  if (e.frag_dirty) {
-    if ((r = pack_ensemble_weights(e, st)) != RID_OK) return r;
-    e.frag_dirty = false;
-  }
+  if ((r = ensure_packed(e, st)) != RID_OK) return r;
   float* A = e.ws_A.as<float>();
   float* g = e.ws_g.as<float>();
   if ((r = launch_cv_eval(s, pos, B, d_s, e.ws_x.as<float>(), st)) != RID_OK) return r;

@@ -280,10 +280,7 @@ rid_status launch_mcmc(rid_ensemble_impl& e, float* s, int W, long long n_steps,
   if ((r = e.ws_cons.ensure(off_h + sizeof(unsigned) * per_copy * copies + 256)) != RID_OK)
     return r;
   if ((r = e.ws_A.ensure(sizeof(float) * K * (size_t)W)) != RID_OK) return r;
-  if (e.frag_dirty) {
-    if ((r = pack_ensemble_weights(e, st)) != RID_OK) return r;
-    e.frag_dirty = false;
-  }
+  if ((r = ensure_packed(e, st)) != RID_OK) return r;
   unsigned char* base = e.ws_cons.as<unsigned char>();
   McmcArgs a{};
   a.s = s;

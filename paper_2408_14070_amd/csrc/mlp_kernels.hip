@@ -106,7 +106,6 @@ struct Plan {
   using PB = PB_;
   using S = S_;
 };
-using PlanF32 = Plan<F32, F32, F32, float>;
 using PlanBF16 = Plan<F16, BF16, F16, _Float16>;      // the BF16 precision form
 using PlanF16 = Plan<F16, F16, F16, _Float16>;
 using PlanBF16All = Plan<BF16, BF16, BF16, __bf16>;   // every operand BF16
@@ -187,7 +186,6 @@ struct MlpArgs {
   float* g_out;        // [K][B][n]
   // LDS layout (byte offsets; activation buffer 0 starts at 0)
   unsigned off_u0, off_red, off_xs, off_ph0, off_wo;
-  int u0p;             // parts of the input-gradient contraction (u0_split or 1)
   int rc;              // walkers per torsion-gather pass (bias path)
   // torsion input (bias path)
   SysView sv;
@@ -412,7 +410,7 @@ __host__ __device__ constexpr int u0_split() {
 
 // GRAD = false: the free energies only (the forward sweep, no tanh' stash,
 // no reverse sweep, no g output).
-template <class PL, int NP, int RT, int NW, int LM, bool FROM_POS, bool GRAD, bool RES>
+template <class PL, int NP, int RT, int NW, int LM, bool FROM_POS, bool GRAD>
 __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
   using P = typename PL::PH;         // hidden-layer forward GEMMs
   using P1 = typename PL::P1;        // first layer
@@ -425,7 +423,6 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
   using SP = Pack4<T>;               // hidden activations
   using SB = Pack4<TB>;              // reverse vectors
   using SS = Pack4<typename PL::S>;  // tanh' between the sweeps
-  static_assert(!RES || sizeof(T) == 4, "residual form: FP32 tiles");
   constexpr int KF = P::KF;
   constexpr int CT = NP / (16 * NW);
   constexpr int R = 16 * RT;
@@ -457,13 +454,11 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 
   // first forward layer's weights and biases go in flight before the input
   // tile is built
-  constexpr int PD = sizeof(T) == 4 ? RID_PD_FP32 : RID_PD_16;
-  constexpr bool WIDE = sizeof(T) == 4;
-  constexpr int NPASS = WIDE ? RID_NPASS_FP32 : RID_NPASS_16;
+  constexpr int PD = RID_PD_16;
+  constexpr int NPASS = RID_NPASS_16;
   constexpr int CH = CT / NPASS;     // unit tiles per pass of a hidden-layer GEMM
   constexpr int NK = NP / KF;        // k-steps of a hidden-layer GEMM
-  constexpr int U0_SPLIT = u0_split<P, NP>();
-  constexpr int PDW = WIDE ? RID_PDH_FP32 : RID_PDH_16;
+  constexpr int PDW = RID_PDH_16;
   constexpr int PDH = (NPASS * NK) % (PDW + 1) == 0 ? PDW : 1;   // its weight pipeline depth
   const int jt0 = wave * CT;
   const int uq = 4 * (lane >> 4);    // first of this lane's 4 units in a tile
@@ -588,20 +583,13 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 
   const int wl = lane & 15;          // walker within a 16-walker tile
   SS st[LM - 1][RT][CT];             // tanh' of hidden layers 1..L-1
-  // 16-bit plans: the packed w_o carries a per-member power-of-two scale
-  // (exact), so the reverse vectors start scaled; the scale is undone where
-  // A and g are written (uniform loads of its inverse there)
-  constexpr bool SCALED = sizeof(T) == 2;
+  // the packed w_o carries a per-member power-of-two scale (exact), so the
+  // reverse vectors start scaled; the scale is undone where A and g are
+  // written (uniform loads of its inverse there)
   auto a_total = [&](int i) {
-    if constexpr (SCALED) {
-      float a = 0.f;
-      for (int w = 0; w < NW; ++w) a += red[w * R + i];
-      return __builtin_fmaf(a, p.vscale[2 * k + 1], p.bo[k]);
-    } else {
-      float a = p.bo[k];
-      for (int w = 0; w < NW; ++w) a += red[w * R + i];
-      return a;
-    }
+    float a = 0.f;
+    for (int w = 0; w < NW; ++w) a += red[w * R + i];
+    return __builtin_fmaf(a, p.vscale[2 * k + 1], p.bo[k]);
   };
   int cur = 0;
 
@@ -609,17 +597,10 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
   // tile epilogues: tanh and its derivative; a layer before the last stores
   // h_l into the other buffer and stashes tanh'; the last layer stores
   // v_L = w_o * tanh' and accumulates the lane's part of A = w_o . h_L.
-  // Residual form (RES): hidden layers after the first add their input,
-  // h_l = h_{l-1} + tanh(z_l), read from the layer's input buffer at the
-  // lane's own four units (all hidden layers share the padded width).
   float apart[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) apart[rt] = 0.f;
-  f4 ares[RT][CT];                   // RES: dA/dh of the layer being reversed
-  auto skip_in = [&](const T* in, int rt, int c) {
-    return *reinterpret_cast<const f4*>(in + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq);
-  };
-  auto mid_tile = [&](int l, int rt, int c, const f4& z, const T* in, T* out) {
+  auto mid_tile = [&](int l, int rt, int c, const f4& z, T* out) {
     f4 h, d;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -627,15 +608,12 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
       h[q] = tanh_and_grad(z[q], dq);
       d[q] = dq;
     }
-    if constexpr (RES) {
-      if (l >= 1) h += skip_in(in, rt, c);
-    }
     SP o;
     o.set(h);
     o.store(out + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq);
     if constexpr (GRAD) st[l][rt][c].set(d);
   };
-  auto last_tile = [&](int rt, int c, const f4& z, const T* in, bool skip, T* out) {
+  auto last_tile = [&](int rt, int c, const f4& z, T* out) {
     const int u = (jt0 + c) * 16 + uq;
     const f4 w4 = *reinterpret_cast<const f4*>(wos + u);
     f4 h, d;
@@ -644,10 +622,6 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
       float dq;
       h[q] = tanh_and_grad(z[q], dq);
       d[q] = dq;
-    }
-    if constexpr (RES) {
-      if (skip) h += skip_in(in, rt, c);
-      ares[rt][c] = w4;              // dA/dh_L = w_o
     }
     apart[rt] += w4[0] * h[0] + w4[1] * h[1] + w4[2] * h[2] + w4[3] * h[3];
     if constexpr (GRAD) {
@@ -680,12 +654,12 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 #pragma unroll
       for (int c = 0; c < CT; ++c)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) mid_tile(0, rt, c, acc[rt][c], act, out);
+        for (int rt = 0; rt < RT; ++rt) mid_tile(0, rt, c, acc[rt][c], out);
     } else {
 #pragma unroll
       for (int c = 0; c < CT; ++c)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) last_tile(rt, c, acc[rt][c], act, false, out);
+        for (int rt = 0; rt < RT; ++rt) last_tile(rt, c, acc[rt][c], out);
     }
     cur = 1;
     __syncthreads();
@@ -707,7 +681,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 #pragma unroll
       for (int c = 0; c < CT; ++c)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) mid_tile(l, rt, c, acc[rt][c], in, out);
+        for (int rt = 0; rt < RT; ++rt) mid_tile(l, rt, c, acc[rt][c], out);
       cur ^= 1;
       __syncthreads();
     }
@@ -725,7 +699,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) last_tile(rt, c, acc[rt][c], in, true, out);
+      for (int rt = 0; rt < RT; ++rt) last_tile(rt, c, acc[rt][c], out);
     cur ^= 1;
     __syncthreads();
   }
@@ -748,17 +722,9 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
   }
 
   // ------------- reverse sweep: v_{l-1} = (W_l^T v_l) * tanh'_{l-1} -------------
-  // Residual form: the skip of layer l carries dA/dh_l on, so
-  // dA/dh_{l-1} = W_l^T v_l + dA/dh_l (kept per lane in ares) and
-  // v_{l-1} = dA/dh_{l-1} * tanh'_{l-1}.
   auto bwd_tile = [&](int l, int rt, int c, const f4& y, T* out) {
     SB o;
-    if constexpr (RES) {
-      ares[rt][c] += y;
-      o.set(ares[rt][c] * st[l - 1][rt][c].get());
-    } else {
-      o.set(y * st[l - 1][rt][c].get());
-    }
+    o.set(y * st[l - 1][rt][c].get());
     o.store(reinterpret_cast<TB*>(out) + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq);
   };
 #pragma unroll
@@ -782,110 +748,42 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
       __syncthreads();
     }
   }
-  // layer 1 backward: u0 = W_1^T v_1.  Its XP/16 column tiles are too few
-  // to spread evenly over the waves, so each tile's contraction is cut into
-  // p.u0p parts (U0_SPLIT, or 1 when that many partial tiles would not fit
-  // the LDS); the parts' partial sums go to LDS (u0 part q at
-  // u0 + q * R * US) and are added in part order when u0 is read.
-  // v_1 sits in buffer 1 (2L-1 buffer flips), so u0 may alias buffer 0.
-  if constexpr (U0_SPLIT == 1) {
-    // one part (16-bit tiles): the plain form
-    {
-      const T* in = act + cur * BUF;
-      const int JT0 = XP / 16;
-      for (int t = wave; t < JT0; t += NW) {
-        f4 a1[RT][1];
+  // layer 1 backward: u0 = W_1^T v_1.  v_1 sits in buffer 1 (2L-1 buffer
+  // flips), so u0 may alias buffer 0.
+  {
+    const T* in = act + cur * BUF;
+    const int JT0 = XP / 16;
+    for (int t = wave; t < JT0; t += NW) {
+      f4 a1[RT][1];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) a1[rt][0] = f4{0.f, 0.f, 0.f, 0.f};
-        gemm_tiles<PB, RT, 1, 7>(
-            a1, reinterpret_cast<const TB*>(in), AS,
-            WSrc{rsrc, (int)p.bwd_off[0] + t * kFragBytes, JT0 * kFragBytes}, NK, lane);
+      for (int rt = 0; rt < RT; ++rt) a1[rt][0] = f4{0.f, 0.f, 0.f, 0.f};
+      gemm_tiles<PB, RT, 1, 7>(
+          a1, reinterpret_cast<const TB*>(in), AS,
+          WSrc{rsrc, (int)p.bwd_off[0] + t * kFragBytes, JT0 * kFragBytes}, NK, lane);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          *reinterpret_cast<f4*>(u0 + (rt * 16 + wl) * US + t * 16 + uq) = a1[rt][0];
-      }
+      for (int rt = 0; rt < RT; ++rt)
+        *reinterpret_cast<f4*>(u0 + (rt * 16 + wl) * US + t * 16 + uq) = a1[rt][0];
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < R; i += NW * 64) {
-      const float a = a_total(i);
-      if (row0 + i < p.B) p.A_out[(size_t)k * p.B + row0 + i] = a;
-    }
-    const float ivs = SCALED ? p.vscale[2 * k + 1] : 1.f;
-    for (int e = threadIdx.x; e < R * n; e += NW * 64) {
-      const int i = e / n, c = e - i * n;
-      const int row = row0 + i;
-      if (row < p.B) {
-        const float cs = xs[i * X2 + c];
-        const float sn = xs[i * X2 + n + c];
-        float gv = -sn * u0[i * US + c] + cs * u0[i * US + n + c];
-        if constexpr (!FROM_POS) {
-          if (p.raw && p.raw[c]) gv = u0[i * US + c];
-        }
-        p.g_out[((size_t)k * p.B + row) * n + c] = SCALED ? gv * ivs : gv;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < R; i += NW * 64) {
+    const float a = a_total(i);
+    if (row0 + i < p.B) p.A_out[(size_t)k * p.B + row0 + i] = a;
+  }
+  // chain to the angles: g_i = -sin s_i u0[i] + cos s_i u0[n+i]
+  const float ivs = p.vscale[2 * k + 1];
+  for (int e = threadIdx.x; e < R * n; e += NW * 64) {
+    const int i = e / n, c = e - i * n;
+    const int row = row0 + i;
+    if (row < p.B) {
+      const float cs = xs[i * X2 + c];
+      const float sn = xs[i * X2 + n + c];
+      float gv = -sn * u0[i * US + c] + cs * u0[i * US + n + c];
+      if constexpr (!FROM_POS) {
+        if (p.raw && p.raw[c]) gv = u0[i * US + c];
       }
+      p.g_out[((size_t)k * p.B + row) * n + c] = gv * ivs;
     }
-  } else {
-    // PARTS is U0_SPLIT (the common case, compile-time loops) or 1
-    auto u0_stage = [&](auto parts_c) {
-      constexpr int PARTS = decltype(parts_c)::value;
-      const T* in = act + cur * BUF;
-      const int JT0 = XP / 16;
-      constexpr int KQ = NK / PARTS;            // k-steps per part
-      for (int it = wave; it < JT0 * PARTS; it += NW) {
-        const int t = it / PARTS, q = it - t * PARTS;
-        f4 a1[RT][1];
-  #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) a1[rt][0] = f4{0.f, 0.f, 0.f, 0.f};
-        gemm_tiles<PB, RT, 1, 7>(
-            a1, reinterpret_cast<const TB*>(in) + q * KQ * KF, AS,
-            WSrc{rsrc, (int)p.bwd_off[0] + t * kFragBytes + q * KQ * JT0 * kFragBytes,
-                 JT0 * kFragBytes},
-            KQ, lane);
-        float* uq0 = u0 + q * R * US;
-  #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          *reinterpret_cast<f4*>(uq0 + (rt * 16 + wl) * US + t * 16 + uq) = a1[rt][0];
-      }
-    };
-    const bool full = U0_SPLIT == 1 || p.u0p == U0_SPLIT;
-    if (full)
-      u0_stage(std::integral_constant<int, U0_SPLIT>{});
-    else
-      u0_stage(std::integral_constant<int, 1>{});
-    __syncthreads();
-    // A = sum of the waves' partial dot products + b_o
-    for (int i = threadIdx.x; i < R; i += NW * 64) {
-      const float a = a_total(i);
-      if (row0 + i < p.B) p.A_out[(size_t)k * p.B + row0 + i] = a;
-    }
-    // chain to the angles: g_i = -sin s_i u0[i] + cos s_i u0[n+i]
-    auto chain = [&](auto parts_c) {
-      constexpr int PARTS = decltype(parts_c)::value;
-      auto u0_at = [&](int i, int c) {
-        float v = u0[i * US + c];
-  #pragma unroll
-        for (int q = 1; q < PARTS; ++q) v += u0[q * R * US + i * US + c];
-        return v;
-      };
-      const float ivs = SCALED ? p.vscale[2 * k + 1] : 1.f;
-      for (int e = threadIdx.x; e < R * n; e += NW * 64) {
-        const int i = e / n, c = e - i * n;
-        const int row = row0 + i;
-        if (row < p.B) {
-          const float cs = xs[i * X2 + c];
-          const float sn = xs[i * X2 + n + c];
-          float gv = -sn * u0_at(i, c) + cs * u0_at(i, n + c);
-          if constexpr (!FROM_POS) {
-            if (p.raw && p.raw[c]) gv = u0_at(i, c);
-          }
-          p.g_out[((size_t)k * p.B + row) * n + c] = SCALED ? gv * ivs : gv;
-        }
-      }
-    };
-    if (full)
-      chain(std::integral_constant<int, U0_SPLIT>{});
-    else
-      chain(std::integral_constant<int, 1>{});
   }
 }
 
@@ -1628,10 +1526,10 @@ inline unsigned align16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
 
 // LDS layout of one instantiation; returns the total bytes.
 size_t mlp_layout(int R, int NW, int AS, size_t tsize, int XP, int n, int U,
-                  bool from_pos, int NPw, int u0_parts, MlpArgs& a) {
+                  bool from_pos, int NPw, MlpArgs& a) {
   const size_t buf = (size_t)R * AS * tsize;
   size_t off = 2 * buf;
-  const size_t u0_bytes = (size_t)u0_parts * R * (XP + 4) * 4;
+  const size_t u0_bytes = (size_t)R * (XP + 4) * 4;
   if (u0_bytes <= buf) {
     a.off_u0 = 0;                       // buffer 0 is free in the last GEMM
   } else {
@@ -1662,10 +1560,10 @@ size_t lds_bytes(const rid_ensemble_impl& e, const TorsionInput* tin) {
   const int AW = NP > e.XP ? NP : e.XP;
   const int AS = AW + RID_ACT_PAD_BYTES / (int)sizeof(T);
   return mlp_layout(16 * RT, NW, AS, sizeof(T), e.XP, e.n_cv,
-                    tin ? tin->sys->n_uniq : 0, tin != nullptr, NP, u0_split<P, NP>(), a);
+                    tin ? tin->sys->n_uniq : 0, tin != nullptr, NP, a);
 }
 
-template <class PL, int NP, int RT, int NW, int LM, bool RES = false>
+template <class PL, int NP, int RT, int NW, int LM>
 rid_status run_mlp(const rid_ensemble_impl& e, const float* x, int B,
                    float* A_out, float* g_out, const TorsionInput* tin,
                    hipStream_t st) {
@@ -1677,16 +1575,8 @@ rid_status run_mlp(const rid_ensemble_impl& e, const float* x, int B,
   const int AW = NP > e.XP ? NP : e.XP;
   const int AS = AW + RID_ACT_PAD_BYTES / (int)sizeof(T);
   MlpArgs a{};
-  a.u0p = u0_split<P, NP>();
-  size_t lds = mlp_layout(R, NW, AS, sizeof(T), e.XP, e.n_cv,
-                          from_pos ? tin->sys->n_uniq : 0, from_pos, NP, a.u0p, a);
-  if (lds > 160 * 1024 && a.u0p > 1) {
-    // wide inputs: one part, which fits the free activation buffer
-    a = MlpArgs{};
-    a.u0p = 1;
-    lds = mlp_layout(R, NW, AS, sizeof(T), e.XP, e.n_cv,
-                     from_pos ? tin->sys->n_uniq : 0, from_pos, NP, 1, a);
-  }
+  const size_t lds = mlp_layout(R, NW, AS, sizeof(T), e.XP, e.n_cv,
+                                from_pos ? tin->sys->n_uniq : 0, from_pos, NP, a);
   if (lds > 160 * 1024)
     return fail(RID_EUNSUPPORTED, "shape too large for the MLP kernel's LDS");
   if (from_pos && a.rc < 1)
@@ -1694,9 +1584,9 @@ rid_status run_mlp(const rid_ensemble_impl& e, const float* x, int B,
   // without g_out only the free energies are computed (plain input only)
   const bool grad = g_out != nullptr;
   if (!grad && from_pos) return fail(RID_EUNSUPPORTED, "energy-only path takes the encoding");
-  auto kern = !grad    ? mlp_kernel<PL, NP, RT, NW, LM, false, false, RES>
-              : from_pos ? mlp_kernel<PL, NP, RT, NW, LM, true, true, RES>
-                         : mlp_kernel<PL, NP, RT, NW, LM, false, true, RES>;
+  auto kern = !grad    ? mlp_kernel<PL, NP, RT, NW, LM, false, false>
+              : from_pos ? mlp_kernel<PL, NP, RT, NW, LM, true, true>
+                         : mlp_kernel<PL, NP, RT, NW, LM, false, true>;
   const int ki = grad ? (from_pos ? 1 : 0) : 2;
   if (lds > 64 * 1024 && lds > attr_bytes[ki]) {
     RID_HIP(hipFuncSetAttribute((const void*)kern,
@@ -1765,40 +1655,10 @@ rid_status launch_16bit(const rid_ensemble_impl& e, const float* x, int B,
   return fail(RID_EUNSUPPORTED, "no kernel for this padded width");
 }
 
-// FP32 at width 256: 16 waves of one unit tile each (4 per SIMD) hide the
-// latencies of the short stages better than 8 waves of two tiles.
-#ifndef RID_F32_NW256
-#define RID_F32_NW256 16
-#endif
-
 rid_status dispatch(const rid_ensemble_impl& e, const float* x, int B, float* A_out,
                     float* g_out, const TorsionInput* t, hipStream_t st) {
-  if (e.resnet) {
-    // residual connections: FP32, 16-walker tiles
-    if (e.prec != RID_FP32)
-      return fail(RID_EUNSUPPORTED, "residual connections need an FP32 ensemble");
-    switch (e.NP) {
-      case 64:  return run_mlp<PlanF32, 64, 1, 1, 6, true>(e, x, B, A_out, g_out, t, st);
-      case 128: return run_mlp<PlanF32, 128, 1, 2, 6, true>(e, x, B, A_out, g_out, t, st);
-      case 256: return run_mlp<PlanF32, 256, 1, RID_F32_NW256, 6, true>(e, x, B, A_out, g_out, t, st);
-      case 512: return run_mlp<PlanF32, 512, 1, 8, 6, true>(e, x, B, A_out, g_out, t, st);
-    }
-    return fail(RID_EUNSUPPORTED, "no kernel for this padded width");
-  }
-  if (e.prec == RID_FP32) {
-    switch (e.NP) {
-      case 64:  return run_mlp<PlanF32, 64, 1, 1, 6>(e, x, B, A_out, g_out, t, st);
-      case 128: return run_mlp<PlanF32, 128, 1, 2, 6>(e, x, B, A_out, g_out, t, st);
-      case 256:
-        // free energies only (MCMC): 32-walker tiles feed two MFMA tiles from
-        // each weight fragment, taken while they still keep 3/4 of the CUs busy
-        if (!g_out && !t && (long long)((B + 31) / 32) * e.K >= 192)
-          return run_mlp<PlanF32, 256, 2, RID_F32_NW256, 6>(e, x, B, A_out, g_out, t, st);
-        return run_mlp<PlanF32, 256, 1, RID_F32_NW256, 6>(e, x, B, A_out, g_out, t, st);
-      case 512: return run_mlp<PlanF32, 512, 1, 8, 6>(e, x, B, A_out, g_out, t, st);
-    }
-    return fail(RID_EUNSUPPORTED, "no kernel for this padded width");
-  }
+  if (e.prec == RID_FP32) return dispatch_mlp_f32(e, x, B, A_out, g_out, t, st);
+  if (e.resnet) return fail(RID_EUNSUPPORTED, "residual connections need an FP32 ensemble");
   switch (e.prec) {
     case RID_BF16:     return launch_16bit<PlanBF16>(e, x, B, A_out, g_out, t, st);
     case RID_FP16:     return launch_16bit<PlanF16>(e, x, B, A_out, g_out, t, st);
@@ -1979,7 +1839,7 @@ rid_status launch_mlp_from_pos(const rid_ensemble_impl& e, const TorsionInput& t
   return dispatch(e, nullptr, B, A_out, g_out, &tin, st);
 }
 
-rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
+static rid_status pack_frag_weights(rid_ensemble_impl& e, hipStream_t st) {
   ++e.master_gen;     // the masters may have changed: copies made from them are stale
   const int L = e.L;
   PackAll pa{};
@@ -2026,7 +1886,24 @@ rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
   hipLaunchKernelGGL(pack_kernel, grid, block, 0, st, e.d_master, e.per_model, pa, e.d_frag,
                      e.frag_bytes_per_model, e.d_bias, e.d_wo, e.d_bo, e.d_vscale);
   RID_HIP(hipGetLastError());
+  e.frag_dirty = false;
+  e.split_dirty = e.prec == RID_FP32;
   return RID_OK;
+}
+
+rid_status ensure_packed(rid_ensemble_impl& e, hipStream_t st, bool mlp) {
+  rid_status r;
+  if (e.frag_dirty && (r = pack_frag_weights(e, st)) != RID_OK) return r;
+  if (mlp && e.split_dirty) {
+    if ((r = pack_split_weights(e, st)) != RID_OK) return r;
+    e.split_dirty = false;
+  }
+  return RID_OK;
+}
+
+rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
+  e.frag_dirty = true;
+  return ensure_packed(e, st);
 }
 
 }  // namespace rid

@@ -1,0 +1,255 @@
+// FP32 ensembles: packing of the split-FP16 weights and the choice of the MLP
+// kernel's instantiation (kernel: mlp_kernels_f32.h; number format:
+// mlp_split.h).
+#include "mlp_kernels_f32.h"
+
+#include "mlp_f32_decl.h"
+
+namespace rid {
+namespace {
+
+using namespace dev;
+
+struct SplitPackArgs {
+  const float* master;
+  unsigned long long per_model;
+  unsigned w_off[kMaxHidden], b_off[kMaxHidden], fwd_off[kMaxHidden], bwd_off[kMaxHidden];
+  int in[kMaxHidden], out[kMaxHidden], kin_pad[kMaxHidden];
+  unsigned wo_off;
+  int L, K, NP, RW;
+  unsigned char* frag;
+  unsigned long long frag_bytes;
+  float *bias, *rs, *bound, *wo, *bo;
+};
+
+// One block per (16-row tile, layer and direction, member): its waves hold
+// the tile's whole contraction in registers (at most 16 k-chunks, 4 a wave),
+// so the row maxima and absolute sums, the scales and the split fragments
+// come from one read of the masters.  Block row 2L writes the biases and
+// output weights.  Rows and contraction: forward, units x inputs (weights
+// times 2/ln 2); backward, inputs x units.
+__global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
+  const int k = blockIdx.z, y = blockIdx.y, jt = blockIdx.x;
+  const float* m = p.master + (size_t)k * p.per_model;
+  const int NP = p.NP;
+  if (y == 2 * p.L) {
+    for (int e = jt * 256 + threadIdx.x; e < (p.L + 1) * NP; e += gridDim.x * 256) {
+      const int l = e / NP, j = e - l * NP;
+      if (l < p.L)
+        p.bias[((size_t)k * p.L + l) * NP + j] =
+            j < p.out[l] ? kTanhPrescale * m[p.b_off[l] + j] : 0.f;
+      else
+        p.wo[(size_t)k * NP + j] = j < p.out[p.L - 1] ? m[p.wo_off + j] : 0.f;
+    }
+    if (jt == 0 && threadIdx.x == 0) p.bo[k] = m[p.wo_off + p.out[p.L - 1]];
+    return;
+  }
+  const int l = y >> 1, dir = y & 1;
+  const int kc = dir == 0 ? p.kin_pad[l] : NP;      // contraction
+  const int nr = dir == 0 ? NP : p.kin_pad[l];      // rows
+  if (jt * 16 >= nr) return;
+  const int in = p.in[l], outw = p.out[l];
+  const float* W = m + p.w_off[l];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = jt * 16 + (lane & 15), g = lane >> 4;
+  const int KT = kc / kSplitKF;
+  float v[4][8];
+  float mx = 0.f, sum = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int kt = wave + 4 * q;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int kk = kt * kSplitKF + 8 * g + e;
+      const int o = dir == 0 ? row : kk, i = dir == 0 ? kk : row;
+      const bool ok = kt < KT && o < outw && i < in;
+      const float w = W[ok ? (size_t)o * in + i : 0];
+      v[q][e] = ok ? (dir == 0 ? w * kTanhPrescale : w) : 0.f;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      mx = fmaxf(mx, fabsf(v[q][e]));
+      sum += fabsf(v[q][e]);
+    }
+  __shared__ float rm[4][16], rsum[4][16];
+  mx = fmaxf(mx, __shfl_xor(mx, 16));
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  sum += __shfl_xor(sum, 16);
+  sum += __shfl_xor(sum, 32);
+  if (lane < 16) {
+    rm[wave][lane] = mx;
+    rsum[wave][lane] = sum;
+  }
+  __syncthreads();
+  const int r = lane & 15;
+  mx = fmaxf(fmaxf(rm[0][r], rm[1][r]), fmaxf(rm[2][r], rm[3][r]));
+  sum = (rsum[0][r] + rsum[1][r]) + (rsum[2][r] + rsum[3][r]);
+  // the row's largest weight to [2^9, 2^10); rows of zeros, infinities or
+  // NaNs keep a scale that stays a normal number
+  const int ex = min(max(split_exp(__float_as_uint(mx)), -100), 126);
+  const float sc = __uint_as_float((unsigned)(127 + 10 - ex) << 23);
+  if (wave == 0) {
+    if (lane < 16) {
+      const float inv = __uint_as_float((unsigned)(127 - 10 + ex) << 23);
+      p.rs[(((size_t)k * p.L + l) * 2 + dir) * p.RW + row] =
+          dir == 0 && l > 0 ? inv * kActUnscale : inv;
+    }
+    // a hair above the true sum, so that its rounding cannot undercut it
+    float b = sum * 1.0001f;
+#pragma unroll
+    for (int s = 8; s >= 1; s >>= 1) b = fmaxf(b, __shfl_xor(b, s));
+    if (lane == 0) p.bound[(((size_t)k * p.L + l) * 2 + dir) * 32 + jt] = b;
+  }
+  unsigned char* base = p.frag + (size_t)k * p.frag_bytes + (dir == 0 ? p.fwd_off[l] : p.bwd_off[l]);
+  const int JT = nr / 16;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int kt = wave + 4 * q;
+    if (kt >= KT) break;
+    h8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float x = v[q][e] * sc;
+      hi[e] = (_Float16)x;
+      lo[e] = (_Float16)(x - (float)hi[e]);
+    }
+    unsigned char* dst = base + ((size_t)kt * JT + jt) * kSplitFrag + lane * 16;
+    *reinterpret_cast<uint4*>(dst) = __builtin_bit_cast(uint4, hi);
+    *reinterpret_cast<uint4*>(dst + kFragBytes) = __builtin_bit_cast(uint4, lo);
+  }
+}
+
+// Row tiles (16 walkers each) per workgroup, at most `most`.  A workgroup
+// streams all of its member's weights whatever its rows, so its time grows
+// slowly with them; the call takes ceil(workgroups / 256 CUs) rounds, each
+// slowed by up to 0.3 when every CU streams.  Measured (4 members, 38 CVs,
+// 4 layers, us): width 256, 16 walkers 18.8 / 22.6 / 35.5 with 1 / 2 / 4
+// tiles, 1024 walkers 24.2 / 25.5 / 38.8, 1300: 39.6 / 25.9 / 38.7, 4096:
+// 90 / 59 / 48, 20000: 395 / 274 / 224; width 512, 600 walkers 66.8 / 70.3
+// with 1 / 2 tiles, 1024: 77.9 / 71.8, 2000: 146 / 96.  The cheapest wins,
+// the smaller tile on a tie.  Widths 64 and 128 keep several workgroups on a
+// CU: there two tiles pay from 2048 workgroups (16384 walkers 44.7 / 36.9,
+// 4096: 14.3 / 15.0) and past one workgroup a CU (2000: 15.9 / 14.4, 1024:
+// 11.5 / 13.4); four never did (16384: 57 and 97 against 37 and 81).
+int split_rows(int NP, int B, int K, int most) {
+  auto wgs = [&](int rt) { return (long long)((B + 16 * rt - 1) / (16 * rt)) * K; };
+  if (NP <= 128) return most > 1 && wgs(1) > (NP == 64 ? 2048 : 256) ? 2 : 1;
+  const double t[3] = {1.0, NP > 384 ? 1.08 : 1.25, 2.0};
+  int best = 1;
+  double cost = 0.0;
+  for (int i = 0, rt = 1; rt <= most; rt *= 2, ++i) {
+    const long long w = wgs(rt);
+    const double c = t[i] * (double)((w + 255) / 256) * (1.0 + 0.3 * std::min(1.0, w / 256.0));
+    if (rt == 1 || c < cost) {
+      cost = c;
+      best = rt;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+int split_width(int wmax) {
+  for (int v : {64, 128, 192, 256, 320, 384})
+    if (wmax <= v) return v;
+  return 512;
+}
+
+void split_layout(rid_ensemble_impl& e) {
+  SplitDev& s = e.split;
+  int wmax = 0;
+  for (int w : e.widths) wmax = std::max(wmax, w);
+  s.NP = split_width(wmax);
+  s.XP = round_up(2 * e.n_cv, kSplitKF);
+  s.RW = std::max(s.NP, s.XP);
+  s.layers.resize(e.L);
+  size_t off = 0;
+  for (int l = 0; l < e.L; ++l) {
+    LayerDev& ld = s.layers[l];
+    ld.kin_pad = l == 0 ? s.XP : s.NP;
+    const size_t bytes = (size_t)(ld.kin_pad / kSplitKF) * (s.NP / 16) * kSplitFrag;
+    ld.fwd_off = off;
+    ld.bwd_off = off + bytes;
+    off += 2 * bytes;
+  }
+  s.frag_bytes = off;
+}
+
+SplitView split_view(const rid_ensemble_impl& e) {
+  const SplitDev& s = e.split;
+  SplitView v{};
+  v.frag = s.frag;
+  v.frag_bytes = s.frag_bytes;
+  for (int l = 0; l < e.L; ++l) {
+    v.fwd_off[l] = (unsigned)s.layers[l].fwd_off;
+    v.bwd_off[l] = (unsigned)s.layers[l].bwd_off;
+  }
+  v.bias = s.bias;
+  v.rs = s.rs;
+  v.bound = s.bound;
+  v.wo = s.wo;
+  v.bo = s.bo;
+  v.RW = s.RW;
+  return v;
+}
+
+rid_status pack_split_weights(rid_ensemble_impl& e, hipStream_t st) {
+  SplitDev& s = e.split;
+  SplitPackArgs p{};
+  p.master = e.d_master;
+  p.per_model = e.per_model;
+  unsigned off = 0;
+  int prev = 2 * e.n_cv;
+  for (int l = 0; l < e.L; ++l) {
+    p.in[l] = prev;
+    p.out[l] = e.widths[l];
+    p.w_off[l] = off;
+    off += (unsigned)(prev * e.widths[l]);
+    p.b_off[l] = off;
+    off += (unsigned)e.widths[l];
+    p.kin_pad[l] = s.layers[l].kin_pad;
+    p.fwd_off[l] = (unsigned)s.layers[l].fwd_off;
+    p.bwd_off[l] = (unsigned)s.layers[l].bwd_off;
+    prev = e.widths[l];
+  }
+  p.wo_off = off;
+  p.L = e.L; p.K = e.K; p.NP = s.NP; p.RW = s.RW;
+  p.frag = s.frag; p.frag_bytes = s.frag_bytes;
+  p.bias = s.bias; p.rs = s.rs; p.bound = s.bound; p.wo = s.wo; p.bo = s.bo;
+  hipLaunchKernelGGL(pack_split_kernel, dim3(s.RW / 16, 2 * e.L + 1, e.K), dim3(256), 0, st, p);
+  RID_HIP(hipGetLastError());
+  return RID_OK;
+}
+
+rid_status dispatch_mlp_f32(const rid_ensemble_impl& e, const float* x, int B, float* A_out,
+                            float* g_out, const TorsionInput* t, hipStream_t st) {
+  const SplitDev& s = e.split;
+  // up to 64 rows at widths 192 and 256 (32 above: registers and LDS; 32
+  // below: more never paid), 32 for residual networks (16 at the widest), 16
+  // for more than 4 hidden layers (the tanh' stash)
+  int most = e.L > 4 || (e.resnet && s.NP > 384) ? 1
+             : e.resnet || s.NP < 192 || s.NP > 256 ? 2 : 4;
+  for (; most > 1; most /= 2) {
+    MlpF32Args a{};
+    if (mlp_f32_layout(s.NP, 16 * most, 4, s.XP, e.n_cv, t ? t->sys->n_uniq : 0, t != nullptr, a) <=
+        160 * 1024)
+      break;
+  }
+  const int rt = split_rows(s.NP, B, e.K, most);
+  switch (s.NP) {
+    case 64: return mlp_f32_w64(rt, e, x, B, A_out, g_out, t, st);
+    case 128: return mlp_f32_w128(rt, e, x, B, A_out, g_out, t, st);
+    case 192: return mlp_f32_w192(rt, e, x, B, A_out, g_out, t, st);
+    case 256: return mlp_f32_w256(rt, e, x, B, A_out, g_out, t, st);
+    case 320: return mlp_f32_w320(rt, e, x, B, A_out, g_out, t, st);
+    case 384: return mlp_f32_w384(rt, e, x, B, A_out, g_out, t, st);
+    case 512: return mlp_f32_w512(rt, e, x, B, A_out, g_out, t, st);
+  }
+  return fail(RID_EUNSUPPORTED, "no kernel for this padded width");
+}
+
+}  // namespace rid

@@ -1,0 +1,279 @@
+// FP32 matrix products on the FP16 matrix units: every operand is split into
+// two FP16 values, x = hi + lo with hi = fp16(x), lo = fp16(x - hi), and a
+// product is three MFMAs into one FP32 accumulator, w_lo h_hi + w_hi h_lo +
+// w_hi h_hi (the dropped w_lo h_lo is below 2^-23 of the product).
+//
+// Why: FP32 MFMA runs at 1/16 of the FP16 rate, so three FP16 products take
+// 3/16 of its matrix time, and hi and lo together are the four bytes an FP32
+// weight takes.  On 256-long dot products of tanh activations and Xavier
+// weights the error against FP64 is 1.8e-7 rms of the result, that of the
+// FP32 MFMA chain 2.9e-7: the split keeps 22-23 bits of each operand, and
+// 24 accumulator roundings (one per 32 products) replace 256.
+//
+// Range: FP16 spans 2^-24 .. 2^16, so every operand row is scaled by a power
+// of two (exact) before it is split, and the result is scaled back:
+//  * weights: one scale per row of the product (an output unit), from the
+//    row's largest weight, which lands in [2^9, 2^10); lo's resolution is
+//    then 2^-34 of the row's maximum;
+//  * activations h of the forward sweep: |h| <= 6 (tanh, up to 6 residual
+//    layers), scaled by 2^10; an input row with raw CVs by its own maximum;
+//  * vectors with no fixed range (reverse, tangent, adjoint sweeps): one
+//    scale per row (a walker's vector), from a bound that cannot overflow:
+//    the largest entry of the previous layer's vector (tracked in LDS) times
+//    the largest absolute row sum of the layer's weights (from the packer).
+//    The bound is typically 2^4 to 2^6 above the true maximum; FP16 pairs
+//    keep full precision 2^28 below it.
+#pragma once
+
+#include "device_common.h"
+
+namespace rid {
+namespace dev {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+constexpr int kSplitKF = 32;             // contraction indices per MFMA
+constexpr int kSplitFrag = 2 * kFragBytes;   // hi block, then lo block
+constexpr float kActScale = 1024.f;      // scale of forward activations
+constexpr float kActUnscale = 1.f / 1024.f;
+constexpr int kTargetExp = 14;           // scaled vectors stay below 2^14
+
+// Activation rows in LDS: [hi: AW halfs][lo: AW halfs][pad 16 bytes]; AW a
+// multiple of 32, so row starts are spread over the banks like 16-byte
+// padded rows of 4 AW bytes.
+__host__ __device__ constexpr int split_row_halfs(int AW) { return 2 * AW + 8; }
+
+// Where a wave's weight fragments come from: a buffer resource over one
+// member's fragments (range-checked by the hardware), the byte offset of
+// k-chunk 0 of the wave's first unit tile, and the bytes per k-chunk.  A
+// load is one buffer_load_dwordx4 with the lane's 16 bytes as the only
+// vector offset, the k-chunk in the scalar offset, tile and half in the
+// instruction's immediate.
+struct SplitSrc {
+  __amdgpu_buffer_rsrc_t r;
+  int soff, kstride;
+  __device__ inline uint4 ld(int kk, int c, int half, int lane) const {
+    return __builtin_bit_cast(
+        uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                   r, lane * 16 + c * kSplitFrag + half * kFragBytes, soff + kk * kstride, 0));
+  }
+};
+
+// Weight ring: slot kt % (PD+1) holds the fragments (hi, lo) of k-step kt.
+template <int PD, int CT>
+struct SplitRing {
+  uint4 w[PD + 1][CT][2];
+};
+
+template <int PD, int CT>
+__device__ inline void split_ring_load(SplitRing<PD, CT>& wr, int slot, const SplitSrc& src,
+                                       int kk, int lane) {
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) wr.w[slot][c][h] = src.ld(kk, c, h, lane);
+}
+
+// Issue the loads of k-steps 0..PD-1 of a layer into the ring.
+template <int PD, int CT>
+__device__ inline void split_preload(SplitRing<PD, CT>& wr, const SplitSrc& src, int n_kt,
+                                     int lane) {
+#pragma unroll
+  for (int s = 0; s < PD; ++s)
+    if (s < n_kt) split_ring_load(wr, s, src, s, lane);
+}
+
+__device__ inline void split_mfma(f4& c, const uint4& a, const uint4& b) {
+  c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b),
+                                             c, 0, 0, 0);
+}
+
+// Fragments of the activation rows (hi, lo) of k-step kt.
+template <int RT>
+__device__ inline void split_act(uint4 (&a)[RT][2], const _Float16* arow, int as, int lo_off,
+                                 int kt) {
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      a[rt][h] = *reinterpret_cast<const uint4*>(arow + rt * 16 * as + h * lo_off +
+                                                 kt * kSplitKF);
+}
+
+// The three products of one k-step, small ones first.
+template <int RT, int CT>
+__device__ inline void split_step(f4 (&acc)[RT][CT], const uint4 (&w)[CT][2],
+                                  const uint4 (&a)[RT][2]) {
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) split_mfma(acc[rt][c], w[c][1], a[rt][0]);
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) split_mfma(acc[rt][c], w[c][0], a[rt][1]);
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) split_mfma(acc[rt][c], w[c][0], a[rt][0]);
+}
+
+// The scheduling barrier that pins "issue next loads -> MFMAs of this step":
+// without it the compiler sinks a load next to its first use.
+__device__ inline void split_fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// acc[rt][c] += W(tile c of src) act(rows of rt)^T, run-time contraction
+// (first layer, input-gradient product).  On entry the ring holds the first
+// PD k-steps.
+template <int RT, int CT, int PD>
+__device__ inline void split_gemm_run(f4 (&acc)[RT][CT], SplitRing<PD, CT>& wr,
+                                      const _Float16* act, int as, int lo_off,
+                                      const SplitSrc& src, int n_kt, int lane) {
+  constexpr int S = PD + 1;
+  const _Float16* arow = act + (lane & 15) * as + (lane >> 4) * 8;
+  for (int kb = 0; kb < n_kt; kb += S) {
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      const int kt = kb + i;
+      if (kt < n_kt) {
+        if (kt + PD < n_kt) split_ring_load(wr, (i + PD) % S, src, kt + PD, lane);
+        uint4 a[RT][2];
+        split_act<RT>(a, arow, as, lo_off, kt);
+        split_fence();
+        split_step<RT, CT>(acc, wr.w[i], a);
+        split_fence();
+      }
+    }
+  }
+}
+
+// The same with a compile-time contraction of NK k-steps (hidden layers):
+// the activation fragments are read one k-step ahead (ADB) or with their
+// use, and after the last MFMA the next layer's first PD weight steps are
+// already issued, so a layer starts with its weights in flight through the
+// previous epilogue and barrier.  Ring slots line up across layers because
+// PD + 1 divides NK.
+template <int RT, int CT, int PD, int NK, bool ADB>
+__device__ inline void split_gemm_hidden(f4 (&acc)[RT][CT], SplitRing<PD, CT>& wr,
+                                         const _Float16* act, int as, int lo_off,
+                                         const SplitSrc& src, bool has_next,
+                                         const SplitSrc& next, int lane) {
+  constexpr int S = PD + 1;
+  static_assert(NK % S == 0, "ring slots must line up across layers");
+  const _Float16* arow = act + (lane & 15) * as + (lane >> 4) * 8;
+  uint4 a[ADB ? 2 : 1][RT][2];
+  if constexpr (ADB) split_act<RT>(a[0], arow, as, lo_off, 0);
+#pragma unroll
+  for (int v = 0; v < NK; ++v) {
+    if (v + PD < NK) {
+      split_ring_load(wr, (v + PD) % S, src, v + PD, lane);
+    } else if (has_next) {
+      split_ring_load(wr, (v + PD) % S, next, v + PD - NK, lane);
+    }
+    if constexpr (ADB) {
+      if (v + 1 < NK) split_act<RT>(a[(v + 1) % 2], arow, as, lo_off, v + 1);
+    } else {
+      split_act<RT>(a[0], arow, as, lo_off, v);
+    }
+    split_fence();
+    split_step<RT, CT>(acc, wr.w[v % S], a[ADB ? v % 2 : 0]);
+    split_fence();
+  }
+}
+
+// Weight pipeline depth of the hidden-layer products: deep enough to keep
+// the L2 stream in flight, a divisor constraint (PD + 1 | NK) and registers.
+__host__ __device__ constexpr int split_depth(int NK, int CT) {
+  return CT == 1 && NK % 4 == 0 ? 3 : 1;
+}
+
+// Four scaled values into an activation row: hi and lo, 8 bytes each.
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float fl2 __attribute__((ext_vector_type(2)));
+__device__ inline void split_store4(_Float16* dst, int lo_off, const f4& x) {
+  const h2 a = __builtin_convertvector((fl2{x[0], x[1]}), h2);
+  const h2 b = __builtin_convertvector((fl2{x[2], x[3]}), h2);
+  const h2 c = __builtin_convertvector((fl2{x[0] - (float)a[0], x[1] - (float)a[1]}), h2);
+  const h2 d = __builtin_convertvector((fl2{x[2] - (float)b[0], x[3] - (float)b[1]}), h2);
+  *reinterpret_cast<uint2*>(dst) =
+      make_uint2(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b));
+  *reinterpret_cast<uint2*>(dst + lo_off) =
+      make_uint2(__builtin_bit_cast(unsigned, c), __builtin_bit_cast(unsigned, d));
+}
+__device__ inline void split_store2(_Float16* dst, int lo_off, float x, float y) {
+  const h2 a = __builtin_convertvector((fl2{x, y}), h2);
+  const h2 c = __builtin_convertvector((fl2{x - (float)a[0], y - (float)a[1]}), h2);
+  *reinterpret_cast<h2*>(dst) = a;
+  *reinterpret_cast<h2*>(dst + lo_off) = c;
+}
+__device__ inline void split_store1(_Float16* dst, int lo_off, float x) {
+  const _Float16 a = (_Float16)x;
+  dst[0] = a;
+  dst[lo_off] = (_Float16)(x - (float)a);
+}
+
+// The exponent e with x < 2^e for finite x >= 0 given as float bits (129 for
+// an infinity or a NaN, -126 for 0).
+__device__ inline int split_exp(unsigned bits) { return (int)((bits >> 23) & 255u) - 126; }
+// Power-of-two scale that takes values below 2^e to below 2^kTargetExp, and
+// its inverse; e is held inside a range where both are normal numbers.
+__device__ inline int split_clamp_exp(int e) { return min(max(e, -100), 126); }
+__device__ inline float split_scale(int e) {
+  return __uint_as_float((unsigned)(127 + kTargetExp - e) << 23);
+}
+__device__ inline float split_unscale(int e) {
+  return __uint_as_float((unsigned)(127 - kTargetExp + e) << 23);
+}
+// Largest |v| of a row, gathered by every wave of the workgroup.
+__device__ inline void split_track(unsigned* m, const f4& v) {
+  const float a = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+  atomicMax(m, __float_as_uint(a));
+}
+
+// Forward weights and biases are stored multiplied by 2/ln 2, so a forward
+// product yields y = 2 z / ln 2 and exp(2z) = 2^y takes no multiply.
+constexpr float kTanhPrescale = 2.8853900817779268f;
+
+// tanh and its derivative from one exponential and one reciprocal, given the
+// pre-scaled pre-activation y: with r = 1 / (1 + 2^y):  tanh z = 1 - 2r,
+// 1 - tanh^2 z = (1 - h)(1 + h).  Saturates cleanly (2^y -> inf gives r = 0;
+// 2^y -> 0 gives r = 1).  Absolute error of a few 1e-7.
+__device__ inline float tanh_and_grad(float y, float& d) {
+  const float e = __builtin_amdgcn_exp2f(y);
+  const float r = __builtin_amdgcn_rcpf(1.f + e);
+  const float h = __builtin_fmaf(-2.f, r, 1.f);
+  d = __builtin_fmaf(-h, h, 1.f);
+  return h;
+}
+
+// Block -> (member, tile), XCD-aware: when K divides 8 (grp = 8 / K), member
+// k runs on XCDs {k grp, ...}, so each XCD's L2 holds only its members'
+// weights.
+__device__ inline void map_block(int b, int K, int grp, int& k, int& tile) {
+  if (grp > 0) {
+    int x = b & 7;
+    k = x / grp;
+    tile = (b >> 3) * grp + (x % grp);
+  } else {
+    k = b % K;
+    tile = b / K;
+  }
+}
+
+}  // namespace dev
+
+// Kernel-side view of an ensemble's split weights (rid_split in the handle).
+struct SplitView {
+  const unsigned char* frag;          // [K][frag_bytes]
+  unsigned long long frag_bytes;
+  unsigned fwd_off[kMaxHidden], bwd_off[kMaxHidden];
+  const float* bias;                  // [K][L][NP], times 2/ln 2
+  const float* rs;                    // [K][L][2][RW] inverse row scales, forward | backward
+  const float* bound;                 // [K][L][2][32] largest absolute row sum per unit tile
+  const float* wo;                    // [K][NP]
+  const float* bo;                    // [K]
+  int RW;                             // row stride of rs: max(NP, XP)
+};
+
+}  // namespace rid

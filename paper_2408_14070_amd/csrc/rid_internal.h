@@ -106,6 +106,20 @@ struct LayerDev {
   int kin_pad = 0;                   // padded input width of this layer
 };
 
+// Weights of an FP32 ensemble in split-FP16 fragments (layout and scales:
+// mlp_split.h): per member and layer a forward and a backward set, each with
+// one power-of-two scale per row and the largest absolute row sum per
+// 16-row tile.
+struct SplitDev {
+  int NP = 0, XP = 0;                // padded hidden and input widths
+  int RW = 0;                        // row stride of rs: max(NP, XP)
+  size_t frag_bytes = 0;             // bytes of one member's fragments
+  std::vector<LayerDev> layers;
+  unsigned char* frag = nullptr;     // [K][frag_bytes]
+  float* vec = nullptr;              // one allocation: bias | rs | bound | wo | bo
+  float *bias = nullptr, *rs = nullptr, *bound = nullptr, *wo = nullptr, *bo = nullptr;
+};
+
 struct rid_system_impl {
   int n_atoms = 0, n_cv = 0;
   std::vector<int32_t> quads;        // host copy [n_cv][4]
@@ -164,6 +178,7 @@ struct rid_ensemble_impl {
   float* d_wo = nullptr;             // [K][NP]
   float* d_bo = nullptr;             // [K]
   float* d_vscale = nullptr;         // [K][2] reverse-vector scale (a power of two), inverse
+  SplitDev split;                    // FP32 ensembles: the MLP kernel's weights
   // the layer weights again, each member's block and each layer's matrix
   // starting on 16 bytes (the general training sweeps read their weight
   // operand from it with float4 loads); rebuilt when master_gen moves on
@@ -173,6 +188,7 @@ struct rid_ensemble_impl {
   unsigned long long master_gen = 1, wpad_gen = 0;
   // scratch
   bool frag_dirty = false;           // masters changed since the last pack
+  bool split_dirty = false;          // the split fragments are older than d_frag
   DevBuf ws_x, ws_A, ws_g, ws_train, ws_cons;
 };
 
@@ -255,6 +271,16 @@ rid_status launch_bias_scatter(const rid_system_impl& s, int K, const float* pos
 // rec_stride > 0: walker records -- walker w's forces start at
 // force + w * rec_stride and energy/eps/sigma use the same stride.
 rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st);
+// Packs what the masters have left behind; mlp = false leaves the split
+// fragments (a training step reads d_frag only).
+rid_status ensure_packed(rid_ensemble_impl& e, hipStream_t st, bool mlp = true);
+// FP32 ensembles: padded widths and layout of the split fragments (host
+// side), their packing, and the MLP kernel that reads them.
+int split_width(int wmax);
+void split_layout(rid_ensemble_impl& e);
+rid_status pack_split_weights(rid_ensemble_impl& e, hipStream_t st);
+rid_status dispatch_mlp_f32(const rid_ensemble_impl& e, const float* x, int B, float* A_out,
+                            float* g_out, const TorsionInput* t, hipStream_t st);
 // Input mode of the mean-force sweeps: with an upstream gradient rho
 // [B][K][n], J_k = sum_b rho_kb . g_k(s_b) differentiated in the network
 // input x with rho_x held fixed.  Results point into the ensemble's training

@@ -453,11 +453,10 @@ rid_status rid_server_register(rid_server srv, rid_system sys, rid_ensemble ens,
     return fail(RID_EINVAL, "the ensemble's angular mask does not match the system's CV kinds");
   Server& s = srv->s;
   rid_ensemble_impl& e = ens->impl;
-  if (e.frag_dirty) {
-    rid_status rs = pack_ensemble_weights(e, nullptr);
+  if (e.frag_dirty || e.split_dirty) {
+    rid_status rs = ensure_packed(e, nullptr);
     if (rs != RID_OK) return rs;
     RID_HIP(hipStreamSynchronize(nullptr));
-    e.frag_dirty = false;
   }
   std::lock_guard<std::mutex> lk(s.mu);
   ServeModel m{&sys->impl, &e, eps0, eps1, {}};

@@ -993,10 +993,7 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
   float* G = grad_out ? grad_out : W + grad;
   if (grad_used) *grad_used = G;
   ProfScope ps(kProfTrain, st);
-  if (e.frag_dirty) {
-    if ((rs = pack_ensemble_weights(e, st)) != RID_OK) return rs;
-    e.frag_dirty = false;
-  }
+  if ((rs = ensure_packed(e, st, false)) != RID_OK) return rs;
   TrainIo io{};
   io.loss_ld = B;
   io.B_norm = B;
