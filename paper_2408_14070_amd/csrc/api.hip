@@ -138,6 +138,47 @@ static void free_ensemble(rid_ensemble_impl& e) {
   e.ws_cons.release();
 }
 
+// The weights in the layout the kernels read: split fragments of FP32
+// ensembles, 16-bit fragments of the others.
+static rid_status alloc_kernel_weights(rid_ensemble_impl& e, int wmax) {
+  const size_t K = e.K, KL = K * e.L;
+  rid_status st;
+  if (e.prec == RID_FP32) {
+    split_layout(e);
+    SplitDev& s = e.split;
+    const size_t n_bias = KL * s.NP, n_rs = KL * 2 * s.RW, n_bound = KL * 2 * 32, n_wo = K * s.NP;
+    if ((st = dev_alloc(&s.frag, s.frag_bytes * K)) != RID_OK) return st;
+    if ((st = dev_alloc(&s.vec, n_bias + n_rs + n_bound + n_wo + K)) != RID_OK) return st;
+    s.bias = s.vec;
+    s.rs = s.bias + n_bias;
+    s.bound = s.rs + n_rs;
+    s.wo = s.bound + n_bound;
+    s.bo = s.wo + n_wo;
+    return RID_OK;
+  }
+  // the 16-bit MLP kernels exist for padded widths 64, 128, 256 and 512 (zero
+  // units pad the rest: their weights, biases and outputs stay 0)
+  e.NP = wmax <= 64 ? 64 : wmax <= 128 ? 128 : wmax <= 256 ? 256 : 512;
+  e.XP = round_up(2 * e.n_cv, e.KF);
+  e.layers.resize(e.L);
+  size_t off = 0;
+  for (int l = 0; l < e.L; ++l) {
+    LayerDev& ld = e.layers[l];
+    ld.kin_pad = l == 0 ? e.XP : e.NP;
+    ld.fwd_off = off;
+    off += (size_t)(ld.kin_pad / e.KF) * (e.NP / 16) * kFragBytes;
+    ld.bwd_off = off;
+    off += (size_t)(e.NP / e.KF) * (ld.kin_pad / 16) * kFragBytes;
+  }
+  e.frag_bytes_per_model = off;
+  if ((st = dev_alloc(&e.d_frag, e.frag_bytes_per_model * K)) != RID_OK ||
+      (st = dev_alloc(&e.d_bias, KL * e.NP)) != RID_OK ||
+      (st = dev_alloc(&e.d_wo, K * e.NP)) != RID_OK || (st = dev_alloc(&e.d_bo, K)) != RID_OK ||
+      (st = dev_alloc(&e.d_vscale, 2 * K)) != RID_OK)
+    return st;
+  return RID_OK;
+}
+
 }  // namespace rid
 
 using namespace rid;
@@ -329,51 +370,13 @@ rid_status rid_ensemble_create(int n_cv, int n_models, int n_hidden,
   e.L = n_hidden;
   e.widths.assign(widths, widths + n_hidden);
   e.prec = prec;
-  e.KF = kf_of(prec);
-  // the MLP kernels exist for padded widths 64, 128, 256 and 512 (zero
-  // units pad the rest: their weights, biases and outputs stay 0)
-  e.NP = wmax <= 64 ? 64 : wmax <= 128 ? 128 : wmax <= 256 ? 256 : 512;
-  e.XP = round_up(2 * n_cv, e.KF);
   e.per_model = per_model_count(n_cv, n_hidden, widths);
   e.n_params = e.per_model * n_models;
-  e.layers.resize(n_hidden);
-  size_t off = 0;
-  for (int l = 0; l < n_hidden; ++l) {
-    LayerDev& ld = e.layers[l];
-    ld.kin_pad = l == 0 ? e.XP : e.NP;
-    ld.fwd_off = off;
-    off += (size_t)(ld.kin_pad / e.KF) * (e.NP / 16) * kFragBytes;
-    ld.bwd_off = off;
-    off += (size_t)(e.NP / e.KF) * (ld.kin_pad / 16) * kFragBytes;
-  }
-  e.frag_bytes_per_model = off;
   rid_status st = RID_OK;
-  if (prec == RID_FP32) {
-    split_layout(e);
-    SplitDev& s = e.split;
-    const size_t KL = (size_t)n_models * n_hidden;
-    const size_t n_bias = KL * s.NP, n_rs = KL * 2 * s.RW, n_bound = KL * 2 * 32,
-                 n_wo = (size_t)n_models * s.NP;
-    if ((st = dev_alloc(&s.frag, s.frag_bytes * n_models)) != RID_OK ||
-        (st = dev_alloc(&s.vec, n_bias + n_rs + n_bound + n_wo + n_models)) != RID_OK) {
-      free_ensemble(e);
-      delete h;
-      return st;
-    }
-    s.bias = s.vec;
-    s.rs = s.bias + n_bias;
-    s.bound = s.rs + n_rs;
-    s.wo = s.bound + n_bound;
-    s.bo = s.wo + n_wo;
-  }
   if ((st = dev_alloc(&e.d_master, e.n_params)) != RID_OK ||
       (st = dev_alloc(&e.d_m, e.n_params)) != RID_OK ||
       (st = dev_alloc(&e.d_v, e.n_params)) != RID_OK ||
-      (st = dev_alloc(&e.d_frag, e.frag_bytes_per_model * n_models)) != RID_OK ||
-      (st = dev_alloc(&e.d_bias, (size_t)n_models * n_hidden * e.NP)) != RID_OK ||
-      (st = dev_alloc(&e.d_wo, (size_t)n_models * e.NP)) != RID_OK ||
-      (st = dev_alloc(&e.d_bo, (size_t)n_models)) != RID_OK ||
-      (st = dev_alloc(&e.d_vscale, (size_t)2 * n_models)) != RID_OK) {
+      (st = alloc_kernel_weights(e, wmax)) != RID_OK) {
     free_ensemble(e);
     delete h;
     return st;

@@ -3,11 +3,11 @@
 // the walker through the model deviation:
 //   f = sigma gbar + Abar sigma'(eps) d eps/ds,
 //   d eps/ds = sum_k H_k w_k,  w_k = (g_k - gbar) / (K eps),
-// with H_k the Hessian of member k's free energy in s.  FP32 ensembles of
-// padded width <= 256 get H_k w_k from one fused forward-over-reverse
-// kernel (hvp_kernel: primal and tangent rows share every weight fragment).
-// Other ensembles (wider, 16-bit, residual, raw CVs) use the mean-force
-// sweeps of the training path in input mode: with rho_x = (dx/ds) w_k held
+// with H_k the Hessian of member k's free energy in s.  FP32 ensembles get
+// H_k w_k from one fused forward-over-reverse kernel (hvp_f32.h: primal and
+// tangent rows share every weight fragment).  16-bit ensembles, and the few
+// FP32 forms its registers or LDS do not hold (hvp_fused_supported), use the
+// mean-force sweeps of the training path in input mode: with rho_x = (dx/ds) w_k held
 // fixed, the tangent and adjoint sweeps give d(rho_x . dA_k/dx)/dx; the
 // angle chain adds (d rho_x/ds)^T dA_k/dx (zero for a raw CV).
 // The frozen-switch path (rid_bias_force) is the same where sigma' = 0.

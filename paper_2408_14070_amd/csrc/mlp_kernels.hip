@@ -57,21 +57,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
-struct F32 {
-  using T = float;
-  static constexpr int KF = 16;
-  // a: 16 rows x 16 contraction, b: 16 contraction x 16 columns (4 steps)
-  __device__ static inline void mma(const uint4& a, const uint4& b, f4& c) {
-    f4 av = __builtin_bit_cast(f4, a);
-    f4 bv = __builtin_bit_cast(f4, b);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[0], bv[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[1], bv[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[2], bv[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[3], bv[3], c, 0, 0, 0);
-  }
-  __device__ static inline T from_float(float v) { return v; }
-};
-
 struct BF16 {
   using T = __bf16;
   static constexpr int KF = 32;
@@ -112,12 +97,6 @@ using PlanBF16All = Plan<BF16, BF16, BF16, __bf16>;   // every operand BF16
 
 // Four consecutive elements of type T as one register group.
 template <class T> struct Pack4;
-template <> struct Pack4<float> {
-  f4 v;
-  __device__ inline void set(const f4& x) { v = x; }
-  __device__ inline f4 get() const { return v; }
-  __device__ inline void store(float* dst) const { *reinterpret_cast<f4*>(dst) = v; }
-};
 template <class H> struct Pack16 {
   typedef H h2 __attribute__((ext_vector_type(2)));
   typedef float fl2 __attribute__((ext_vector_type(2)));
@@ -145,11 +124,6 @@ template <class T> struct Pack2 {
   typedef float fl2 __attribute__((ext_vector_type(2)));
   __device__ static inline void store(T* dst, float a, float b) {
     *reinterpret_cast<t2*>(dst) = __builtin_convertvector((fl2{a, b}), t2);
-  }
-};
-template <> struct Pack2<float> {
-  __device__ static inline void store(float* dst, float a, float b) {
-    *reinterpret_cast<float2*>(dst) = make_float2(a, b);
   }
 };
 template <> struct Pack4<_Float16> : Pack16<_Float16> {};
@@ -215,14 +189,8 @@ __device__ inline void map_block(int b, int K, int grp, int& k, int& tile) {
 // Scheduling barriers pin "issue next loads -> MFMAs of this step", so the
 // compiler cannot sink a global load next to its first use and expose the
 // memory latency; without ADB they let LDS reads and ALU work move freely.
-#ifndef RID_PD_FP32
-#define RID_PD_FP32 2
-#endif
 #ifndef RID_PD_16
 #define RID_PD_16 1
-#endif
-#ifndef RID_ADB_FP32
-#define RID_ADB_FP32 1
 #endif
 #ifndef RID_ADB_16
 #define RID_ADB_16 1
@@ -247,14 +215,8 @@ __device__ inline void sched_fence() {
 
 // Hidden-layer GEMMs: passes over the contraction and weight pipeline depth
 // (PD+1 must divide passes * k-steps: 1 or 3).
-#ifndef RID_NPASS_FP32
-#define RID_NPASS_FP32 1
-#endif
 #ifndef RID_NPASS_16
 #define RID_NPASS_16 1
-#endif
-#ifndef RID_PDH_FP32
-#define RID_PDH_FP32 3
 #endif
 #ifndef RID_PDH_16
 #define RID_PDH_16 1
@@ -303,8 +265,7 @@ __device__ inline void gemm_run(f4 (&acc)[RT][CT], WRing<PD, CT>& wr,
                                 const typename P::T* act, int as, const WSrc& src, int n_kt,
                                 int lane) {
   constexpr int KF = P::KF;
-  constexpr bool WIDE = sizeof(typename P::T) == 4;
-  constexpr bool ADB = WIDE ? RID_ADB_FP32 : RID_ADB_16;
+  constexpr bool ADB = RID_ADB_16;
   constexpr int S = PD + 1;
   constexpr int U = (S % 2) ? 2 * S : S;      // unroll: static ring indices
   const int r = lane & 15, g = lane >> 4;
@@ -398,14 +359,6 @@ __device__ inline void gemm_hidden(f4 (&acc)[RT][CT], WRing<PD, CT / NPASS>& wr,
       for (int c = 0; c < CH; ++c) P::mma(wr.w[v % S][c], a[v % 2][rt], acc[rt][cb + c]);
     sched_fence<true>();
   }
-}
-
-// Parts the input-gradient GEMM's contraction is cut into: 4 for FP32 (it
-// divides the NP/16 k-steps of every padded width); the 16-bit kernels keep
-// one (their tiles are 4x wider, and the partials would cost registers).
-template <class P, int NP>
-__host__ __device__ constexpr int u0_split() {
-  return sizeof(typename P::T) == 4 ? 4 : 1;
 }
 
 // GRAD = false: the free energies only (the forward sweep, no tanh' stash,
@@ -788,619 +741,6 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Hessian-vector products for conservative switching (FP32 ensembles).
-// For walker w and member k, with rho_x = (dx/ds) w_k (w_k the walker's
-// deviation direction, zero outside the switching band):
-//   u0  = dA_k/dx                          (reverse sweep, as in mlp_kernel)
-//   u0d = H_x rho_x = d/dt u0(x + t rho_x)  (forward-over-reverse)
-// and the member's term of d eps/ds, chained to the angles:
-//   T_k[i] = -sin s_i u0d[i] + cos s_i u0d[n+i] - w_ki (cos s_i u0[i] + sin s_i u0[n+i]).
-// Tangent recurrences: zd_1 = W_1 rho_x, hd_l = tanh'_l zd_l,
-// zd_{l+1} = W_{l+1} hd_l, dd_l = -2 h_l hd_l (tangent of tanh'),
-// vd_L = w_o dd_L, vd_{l-1} = (W_l^T vd_l) tanh'_{l-1} + (W_l^T v_l) dd_{l-1},
-// u0d = W_1^T vd_1.
-// One workgroup owns 16 walkers of one member.  Rows 0-15 of its activation
-// tile are the walkers' primal vectors and rows 16-31 their tangents, so
-// every weight fragment streamed from L2 feeds both (the MFMA B operand
-// spans two 16-row tiles), and tanh' and its tangent stay in registers
-// between the sweeps.  One 16-unit tile per wave.
-// ---------------------------------------------------------------------------
-struct HvpArgs {
-  const float* x;      // [B][2n] encoding cos s | sin s
-  const float* rho;    // [B][K][n] w_k
-  const float* coef;   // [B] Abar sigma'(eps): a tile whose walkers are all 0 is skipped
-  float* T_out;        // [K][B][n]
-  int B, n, K, L, XP, n_tiles, xcd_grp;
-  const unsigned char* frag;
-  unsigned long long frag_model_bytes;
-  unsigned fwd_off[kMaxHidden];
-  unsigned bwd_off[kMaxHidden];
-  const float* bias;   // [K][L][NP], pre-scaled like the forward weights
-  const float* wo;     // [K][NP]
-  unsigned off_u0, off_xs, off_rs, off_wo;   // LDS byte offsets
-};
-
-// ln 2 / 2: undoes the forward pre-scale on the tangent rows (no bias there)
-constexpr float kTanhUnscale = 0.34657359027997264f;
-
-template <int NP, int NW, int LM>
-__global__ __launch_bounds__(NW * 64) void hvp_kernel(HvpArgs p) {
-  using P = F32;
-  constexpr int KF = P::KF;
-  constexpr int RT = 2;                       // primal rows, tangent rows
-  constexpr int CT = NP / (16 * NW);
-  static_assert(CT == 1 && 16 * NW == NP, "one unit tile per wave");
-  constexpr int R = 16 * RT;
-  constexpr int JT = NP / 16;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int k, tile;
-  map_block(blockIdx.x, p.K, p.xcd_grp, k, tile);
-  if (tile >= p.n_tiles) return;
-  const int row0 = tile * 16;
-  // every wave takes the same vote, so a skipped tile leaves as a whole
-  if (!__any(p.coef[min(row0 + (lane & 15), p.B - 1)] != 0.f)) return;
-
-  const int n = p.n, L = p.L, XP = p.XP, X2 = 2 * p.n;
-  const int AW = NP > XP ? NP : XP;
-  const int AS = AW + RID_ACT_PAD_BYTES / 4;
-  const int BUF = R * AS;
-  float* act = reinterpret_cast<float*>(smem);
-  float* u0 = reinterpret_cast<float*>(smem + p.off_u0);
-  const int US = XP + 4;
-  float* xs = reinterpret_cast<float*>(smem + p.off_xs);    // [16][2n]
-  float* rs = reinterpret_cast<float*>(smem + p.off_rs);    // [16][n] w_k
-  float* wos = reinterpret_cast<float*>(smem + p.off_wo);   // [NP]
-
-  const unsigned char* fbase = p.frag + (size_t)k * p.frag_model_bytes;
-  const float* bias = p.bias + (size_t)k * L * NP;
-  const float* wo = p.wo + (size_t)k * NP;
-  constexpr int PD = RID_PD_FP32;
-  constexpr int NK = NP / KF;
-  constexpr int U0_SPLIT = u0_split<P, NP>();
-  constexpr int PDH = NK % (RID_PDH_FP32 + 1) == 0 ? RID_PDH_FP32 : 1;
-  const int jt0 = wave;
-  const int wl = lane & 15;
-  const int uq = 4 * (lane >> 4);
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<unsigned char*>(fbase), (short)0, (int)p.frag_model_bytes, 0x00020000);
-  auto wsrc = [&](unsigned off) {
-    return WSrc{rsrc, (int)off + jt0 * kFragBytes, JT * kFragBytes};
-  };
-  WRing<PD, 1> wr;
-  WRing<PDH, 1> wh;
-  ring_preload<PD, 1>(wr, wsrc(p.fwd_off[0]), XP / KF, lane);
-  f4 bnext = *reinterpret_cast<const f4*>(bias + jt0 * 16 + uq);
-  for (int i = threadIdx.x; i < NP; i += NW * 64) wos[i] = wo[i];
-
-  // input tile: rows 0-15 x, rows 16-31 rho_x = [-sin s w | cos s w],
-  // columns [2n, XP) zero; walkers past B are zero rows
-  for (int e = threadIdx.x; e < 16 * XP; e += NW * 64) {
-    const int i = e / XP, c = e - i * XP;
-    const int row = row0 + i;
-    float xv = 0.f, tv = 0.f;
-    if (row < p.B && c < X2) {
-      const int ci = c < n ? c : c - n;
-      xv = p.x[(size_t)row * X2 + c];
-      const float other = p.x[(size_t)row * X2 + (c < n ? c + n : c - n)];
-      const float w = p.rho[((size_t)row * p.K + k) * n + ci];
-      tv = c < n ? -other * w : other * w;
-      xs[i * X2 + c] = xv;
-      if (c < n) rs[i * n + c] = w;
-    }
-    act[i * AS + c] = xv;
-    act[(16 + i) * AS + c] = tv;
-  }
-  __syncthreads();
-
-  f4 sd[LM - 1], sdd[LM - 1];   // tanh' and its tangent, hidden layers 1..L-1
-  int cur = 0;
-  auto store_pair = [&](float* out, const f4& prim, const f4& tang) {
-    *reinterpret_cast<f4*>(out + wl * AS + jt0 * 16 + uq) = prim;
-    *reinterpret_cast<f4*>(out + (16 + wl) * AS + jt0 * 16 + uq) = tang;
-  };
-  // forward epilogue: y, yd are the pre-scaled GEMM outputs of the two rows
-  auto fwd_core = [&](const f4& y, const f4& yd, f4& h, f4& d, f4& hd, f4& dd) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float dq;
-      h[q] = tanh_and_grad(y[q], dq);
-      d[q] = dq;
-      hd[q] = dq * (yd[q] * kTanhUnscale);
-      dd[q] = -2.f * h[q] * hd[q];
-    }
-  };
-  auto mid_epi = [&](int l, const f4& y, const f4& yd, float* out) {
-    f4 h, d, hd, dd;
-    fwd_core(y, yd, h, d, hd, dd);
-    store_pair(out, h, hd);
-    sd[l] = d;
-    sdd[l] = dd;
-  };
-  auto last_epi = [&](const f4& y, const f4& yd, float* out) {
-    const f4 w4 = *reinterpret_cast<const f4*>(wos + jt0 * 16 + uq);
-    f4 h, d, hd, dd;
-    fwd_core(y, yd, h, d, hd, dd);
-    store_pair(out, w4 * d, w4 * dd);    // v_L, vd_L
-  };
-  auto next_after_fwd = [&](int l) {
-    return wsrc(l + 1 < L ? p.fwd_off[l + 1] : p.bwd_off[L > 1 ? L - 1 : 0]);
-  };
-  auto init_fwd = [&](f4 (&acc)[RT][1]) {
-    acc[0][0] = bnext;
-    acc[1][0] = f4{0.f, 0.f, 0.f, 0.f};
-  };
-
-  {  // layer 1
-    float* out = act + BUF;
-    f4 acc[RT][1];
-    init_fwd(acc);
-    gemm_run<P, RT, 1, PD>(acc, wr, act, AS, wsrc(p.fwd_off[0]), XP / KF, lane);
-    if (L > 1) {
-      ring_preload<PDH, 1>(wh, next_after_fwd(0), NK, lane);
-      bnext = *reinterpret_cast<const f4*>(bias + NP + jt0 * 16 + uq);
-      mid_epi(0, acc[0][0], acc[1][0], out);
-    } else {
-      last_epi(acc[0][0], acc[1][0], out);
-    }
-    cur = 1;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int l = 1; l < LM - 1; ++l) {
-    if (l < L - 1) {
-      const float* in = act + cur * BUF;
-      float* out = act + (cur ^ 1) * BUF;
-      f4 acc[RT][1];
-      init_fwd(acc);
-      gemm_hidden<P, RT, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.fwd_off[l]), true,
-                                        next_after_fwd(l), lane);
-      bnext = *reinterpret_cast<const f4*>(bias + (l + 1) * NP + jt0 * 16 + uq);
-      mid_epi(l, acc[0][0], acc[1][0], out);
-      cur ^= 1;
-      __syncthreads();
-    }
-  }
-  if (L > 1) {
-    const float* in = act + cur * BUF;
-    float* out = act + (cur ^ 1) * BUF;
-    f4 acc[RT][1];
-    init_fwd(acc);
-    gemm_hidden<P, RT, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.fwd_off[L - 1]), true,
-                                      wsrc(p.bwd_off[L - 1]), lane);
-    last_epi(acc[0][0], acc[1][0], out);
-    cur ^= 1;
-    __syncthreads();
-  }
-  // reverse: v_{l-1} = y tanh'_{l-1}, vd_{l-1} = yd tanh'_{l-1} + y dd_{l-1}
-#pragma unroll
-  for (int l = LM - 1; l >= 1; --l) {
-    if (l < L) {
-      const float* in = act + cur * BUF;
-      float* out = act + (cur ^ 1) * BUF;
-      f4 acc[RT][1];
-      acc[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-      acc[1][0] = f4{0.f, 0.f, 0.f, 0.f};
-      gemm_hidden<P, RT, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.bwd_off[l]), l >= 2,
-                                        wsrc(p.bwd_off[l >= 2 ? l - 1 : l]), lane);
-      const f4 y = acc[0][0], yd = acc[1][0];
-      store_pair(out, y * sd[l - 1], yd * sd[l - 1] + y * sdd[l - 1]);
-      cur ^= 1;
-      __syncthreads();
-    }
-  }
-  // u0 | u0d = W_1^T [v_1 | vd_1], contraction split as in mlp_kernel; the
-  // vectors sit in buffer 1 (2L-1 flips), so u0 may alias buffer 0
-  {
-    const float* in = act + cur * BUF;
-    const int JT0 = XP / 16;
-    constexpr int KQ = NK / U0_SPLIT;
-    for (int it = wave; it < JT0 * U0_SPLIT; it += NW) {
-      const int t = it / U0_SPLIT, q = it - t * U0_SPLIT;
-      f4 a1[RT][1];
-      a1[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-      a1[1][0] = f4{0.f, 0.f, 0.f, 0.f};
-      gemm_tiles<P, RT, 1, 7>(
-          a1, in + q * KQ * KF, AS,
-          WSrc{rsrc, (int)p.bwd_off[0] + t * kFragBytes + q * KQ * JT0 * kFragBytes,
-               JT0 * kFragBytes},
-          KQ, lane);
-      float* uq0 = u0 + q * R * US;
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-        *reinterpret_cast<f4*>(uq0 + (rt * 16 + wl) * US + t * 16 + uq) = a1[rt][0];
-    }
-  }
-  __syncthreads();
-  auto u0_at = [&](int i, int c) {
-    float v = u0[i * US + c];
-#pragma unroll
-    for (int q = 1; q < U0_SPLIT; ++q) v += u0[q * R * US + i * US + c];
-    return v;
-  };
-  for (int e = threadIdx.x; e < 16 * n; e += NW * 64) {
-    const int i = e / n, c = e - i * n;
-    const int row = row0 + i;
-    if (row < p.B) {
-      const float cs = xs[i * X2 + c], sn = xs[i * X2 + n + c];
-      const float hv = -sn * u0_at(16 + i, c) + cs * u0_at(16 + i, n + c);
-      const float cu = cs * u0_at(i, c) + sn * u0_at(i, n + c);
-      p.T_out[((size_t)k * p.B + row) * n + c] = hv - rs[i * n + c] * cu;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Mean-force training sweeps (FP32 ensembles), one workgroup per 16 samples
-// and member.  Loss L = (1/B) sum_b |g(s_b) - F_b|^2 with g = dA/ds.  Its
-// parameter gradient is the gradient of J = sum_b rho_b . g(s_b), with
-// rho = 2 (g - F) / B held fixed (or an upstream rho given by the caller),
-// and J is the tangent of A along rho_x = (dx/ds) rho.  The kernel runs,
-// from LDS and registers:
-//   primal forward      h_l = tanh(W_l h_{l-1} + b_l)            rows 0-15
-//   primal reverse      v_L = w_o tanh'_L, v_{l-1} = (W_l^T v_l) tanh'_{l-1},
-//                       u0 = W_1^T v_1, g, residual, rho_x       rows 0-15
-//   tangent forward     zd_l = W_l hd_{l-1}, hd_l = tanh'_l zd_l  rows 16-31
-//   adjoint of J        lam_zd = tanh' lam_hd,
-//                       lam_z = tanh' (lam_h - 2 h zd lam_hd),
-//                       [lam_h ; lam_hd]_{l-1} = W_l^T [lam_z ; lam_zd]_l,
-//                       top: lam_hd = w_o, lam_h = 0             rows 0-31
-// and writes what the batch-reduced weight gradients need: [h ; hd] of
-// every layer input (x ; rho_x first) and [lam_z ; lam_zd] of every layer,
-// each as [K][2B][width], plus the samples' squared residuals.  h and zd
-// of this lane's units stay in VGPRs between the sweeps.
-// Dropout (training only): hidden unit j of layer l of sample b is kept with
-// probability 1 - p and then scaled by 1/(1 - p): word j mod 4 of the
-// Philox4x32-10 block with counter (b, step, 16 member + l, j div 4), kept
-// when its uniform is >= p.  The scaled output S tanh(z) has derivative
-// S (1 - tanh^2) in every sweep; the second-order term keeps the unscaled
-// tanh.  Without dropout S = 1.
-// ---------------------------------------------------------------------------
-struct TrainArgs {
-  const float* s;      // [B][n]
-  const float* F;      // [B][n] labels (null when rho is given)
-  const float* rho;    // [B][K][n] upstream gradient of g, or null
-  float* hh[kMaxHidden + 1];   // [K][2B][wd[j]]
-  float* sl[kMaxHidden];       // [K][2B][wd[j+1]]
-  float* loss_rows;    // row b of member k at loss_rows[k * loss_ld + b], or null
-  long long loss_ld;
-  int row_base;        // batch index of row 0 (dropout counters)
-  int B_norm;          // the whole batch's size (rho scale)
-  int B, n, K, L, XP, n_tiles, xcd_grp;
-  int wd[kMaxHidden + 1];      // 2n, then the hidden widths
-  const unsigned char* frag;
-  unsigned long long frag_model_bytes;
-  unsigned fwd_off[kMaxHidden];
-  unsigned bwd_off[kMaxHidden];
-  const float* bias;   // [K][L][NP], pre-scaled
-  const float* wo;     // [K][NP]
-  unsigned off_u0, off_xs, off_wo;
-  float drop_p, drop_inv;       // rate and 1/(1 - rate); 0 and 1 without dropout
-  unsigned long long drop_seed;
-  uint32_t step;
-};
-
-template <int NP, int NW, int LM>
-__global__ __launch_bounds__(NW * 64) void train_kernel(TrainArgs p) {
-  using P = F32;
-  constexpr int KF = P::KF;
-  static_assert(16 * NW == NP, "one unit tile per wave");
-  constexpr int JT = NP / 16;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int k, tile;
-  map_block(blockIdx.x, p.K, p.xcd_grp, k, tile);
-  if (tile >= p.n_tiles) return;
-  const int row0 = tile * 16;
-  const int n = p.n, L = p.L, XP = p.XP, X2 = 2 * p.n, B = p.B;
-  const int AW = NP > XP ? NP : XP;
-  const int AS = AW + RID_ACT_PAD_BYTES / 4;
-  const int BUF = 32 * AS;
-  float* act = reinterpret_cast<float*>(smem);
-  float* u0 = reinterpret_cast<float*>(smem + p.off_u0);
-  const int US = XP + 4;
-  float* xs = reinterpret_cast<float*>(smem + p.off_xs);    // [16][2n]
-  float* wos = reinterpret_cast<float*>(smem + p.off_wo);   // [NP]
-
-  const unsigned char* fbase = p.frag + (size_t)k * p.frag_model_bytes;
-  const float* bias = p.bias + (size_t)k * L * NP;
-  const float* wo = p.wo + (size_t)k * NP;
-  constexpr int PD = RID_PD_FP32;
-  constexpr int NK = NP / KF;
-  constexpr int U0_SPLIT = u0_split<P, NP>();
-  constexpr int PDH = NK % (RID_PDH_FP32 + 1) == 0 ? RID_PDH_FP32 : 1;
-  const int jt0 = wave;
-  const int wl = lane & 15;
-  const int uq = 4 * (lane >> 4);
-  const int u = jt0 * 16 + uq;       // this lane's first unit
-  const int brow = row0 + wl;        // this lane's sample
-  const bool in_b = brow < B;
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<unsigned char*>(fbase), (short)0, (int)p.frag_model_bytes, 0x00020000);
-  auto wsrc = [&](unsigned off) {
-    return WSrc{rsrc, (int)off + jt0 * kFragBytes, JT * kFragBytes};
-  };
-  WRing<PD, 1> wr;
-  WRing<PDH, 1> wh;
-  ring_preload<PD, 1>(wr, wsrc(p.fwd_off[0]), XP / KF, lane);
-  f4 bnext = *reinterpret_cast<const f4*>(bias + u);
-  for (int i = threadIdx.x; i < NP; i += NW * 64) wos[i] = wo[i];
-  // dropout keep bits of this lane's 4 units, 4 bits per hidden layer
-  unsigned mbits = 0xFFFFFFFFu;
-  if (p.drop_p > 0.f) {
-    mbits = 0u;
-    for (int j = 0; j < L; ++j) {
-      uint32_t c[4] = {(uint32_t)(p.row_base + brow), p.step, (uint32_t)(16 * k + j + 1),
-                       (uint32_t)(u >> 2)};
-      philox4x32_10(c, (uint32_t)(p.drop_seed & 0xFFFFFFFFull), (uint32_t)(p.drop_seed >> 32));
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (philox_uniform(c[q]) >= p.drop_p) mbits |= 1u << (4 * j + q);
-    }
-  }
-  auto dsc = [&](int j) {       // the dropout factors of hidden layer j (0-based)
-    f4 r;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) r[q] = ((mbits >> (4 * j + q)) & 1u) ? p.drop_inv : 0.f;
-    return r;
-  };
-
-  // 4 units of row r (0 .. 2B-1) of a [K][2B][w] array; units past w are
-  // padding and stay unwritten
-  auto put4 = [&](float* base, int w, int r, const f4& v) {
-    if (u >= w) return;
-    float* dst = base + ((size_t)k * 2 * B + r) * w + u;
-    if ((w & 3) == 0) {
-      *reinterpret_cast<f4*>(dst) = v;
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (u + q < w) dst[q] = v[q];
-    }
-  };
-  auto lds4 = [&](float* buf, int r, const f4& v) {
-    *reinterpret_cast<f4*>(buf + r * AS + u) = v;
-  };
-
-  // input tile: x = [cos s | sin s] in rows 0-15 (and to hh[0]), zeros past
-  // 2n and past B
-  for (int e = threadIdx.x; e < 16 * XP; e += NW * 64) {
-    const int i = e / XP, c = e - i * XP;
-    const int row = row0 + i;
-    float v = 0.f;
-    if (row < B && c < X2) {
-      float sn, cs;
-      sincosf(p.s[(size_t)row * n + (c < n ? c : c - n)], &sn, &cs);
-      v = c < n ? cs : sn;
-      xs[i * X2 + c] = v;
-      p.hh[0][((size_t)k * 2 * B + row) * X2 + c] = v;
-    }
-    act[i * AS + c] = v;
-  }
-  __syncthreads();
-
-  f4 hs[LM];        // h of layers 0..L-1
-  f4 zs[LM - 1];    // zd of layers 0..L-2
-  int cur = 0;
-  auto next_after_fwd = [&](int j) {
-    return wsrc(j + 1 < L ? p.fwd_off[j + 1] : p.bwd_off[L > 1 ? L - 1 : 0]);
-  };
-  // primal forward epilogue of layer j: h to the next buffer (and HBM), or
-  // v_L = w_o tanh'_L at the top
-  auto fwd_epi = [&](int j, f4& hj, const f4& y, float* out) {
-    f4 h, d;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float dq;
-      h[q] = tanh_and_grad(y[q], dq);
-      d[q] = dq;
-    }
-    hj = h;
-    const f4 sc = dsc(j);
-    if (j < L - 1) {
-      const f4 hsc = h * sc;
-      lds4(out, wl, hsc);
-      if (in_b) put4(p.hh[j + 1], p.wd[j + 1], brow, hsc);
-    } else {
-      lds4(out, wl, *reinterpret_cast<const f4*>(wos + u) * d * sc);
-    }
-  };
-
-  // ---------------- primal forward ----------------
-  {
-    float* out = act + BUF;
-    f4 acc[1][1];
-    acc[0][0] = bnext;
-    gemm_run<P, 1, 1, PD>(acc, wr, act, AS, wsrc(p.fwd_off[0]), XP / KF, lane);
-    if (L > 1) {
-      ring_preload<PDH, 1>(wh, next_after_fwd(0), NK, lane);
-      bnext = *reinterpret_cast<const f4*>(bias + NP + u);
-    }
-    fwd_epi(0, hs[0], acc[0][0], out);
-    cur = 1;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int j = 1; j < LM; ++j) {
-    if (j < L) {
-      const float* in = act + cur * BUF;
-      float* out = act + (cur ^ 1) * BUF;
-      f4 acc[1][1];
-      acc[0][0] = bnext;
-      gemm_hidden<P, 1, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.fwd_off[j]), true,
-                                       next_after_fwd(j), lane);
-      if (j + 1 < L) bnext = *reinterpret_cast<const f4*>(bias + (j + 1) * NP + u);
-      fwd_epi(j, hs[j], acc[0][0], out);
-      cur ^= 1;
-      __syncthreads();
-    }
-  }
-  // ---------------- primal reverse to u0 ----------------
-#pragma unroll
-  for (int j = LM - 1; j >= 1; --j) {
-    if (j < L) {
-      const float* in = act + cur * BUF;
-      float* out = act + (cur ^ 1) * BUF;
-      f4 acc[1][1];
-      acc[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-      gemm_hidden<P, 1, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.bwd_off[j]), j >= 2,
-                                       wsrc(p.bwd_off[j >= 2 ? j - 1 : j]), lane);
-      const f4 h = hs[j - 1];
-      lds4(out, wl, acc[0][0] * ((1.f - h * h) * dsc(j - 1)));
-      cur ^= 1;
-      __syncthreads();
-    }
-  }
-  // u0 = W_1^T v_1 (v_1 in buffer 1 after 2L-1 flips; the partials may
-  // alias buffer 0)
-  {
-    const float* in = act + cur * BUF;
-    const int JT0 = XP / 16;
-    constexpr int KQ = NK / U0_SPLIT;
-    for (int it = wave; it < JT0 * U0_SPLIT; it += NW) {
-      const int t = it / U0_SPLIT, q = it - t * U0_SPLIT;
-      f4 a1[1][1];
-      a1[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-      gemm_tiles<P, 1, 1, 7>(
-          a1, in + q * KQ * KF, AS,
-          WSrc{rsrc, (int)p.bwd_off[0] + t * kFragBytes + q * KQ * JT0 * kFragBytes,
-               JT0 * kFragBytes},
-          KQ, lane);
-      *reinterpret_cast<f4*>(u0 + q * 16 * US + wl * US + t * 16 + uq) = a1[0][0];
-    }
-  }
-  ring_preload<PD, 1>(wr, wsrc(p.fwd_off[0]), XP / KF, lane);   // tangent layer 1
-  __syncthreads();
-  auto u0_at = [&](int i, int c) {
-    float v = u0[i * US + c];
-#pragma unroll
-    for (int q = 1; q < U0_SPLIT; ++q) v += u0[q * 16 * US + i * US + c];
-    return v;
-  };
-  // ---------------- residual and rho_x (a wave per sample) ----------------
-  // rho_x goes to rows 16-31 of the buffer holding v_1 (its rows 0-15 are
-  // dead after the u0 GEMM) and to the tangent half of hh[0]
-  float* tin = act + cur * BUF + 16 * AS;
-  for (int i = wave; i < 16; i += NW) {
-    const int row = row0 + i;
-    float acc = 0.f;
-    for (int c = lane; c < n; c += 64) {
-      float rx0 = 0.f, rx1 = 0.f;
-      if (row < B) {
-        const float cs = xs[i * X2 + c], sn = xs[i * X2 + n + c];
-        float rho;
-        if (p.rho) {
-          rho = p.rho[((size_t)row * p.K + k) * n + c];
-        } else {
-          const float gi = -sn * u0_at(i, c) + cs * u0_at(i, n + c);
-          const float ri = gi - p.F[(size_t)row * n + c];
-          acc += ri * ri;
-          rho = 2.f * ri / (float)p.B_norm;
-        }
-        rx0 = -sn * rho;
-        rx1 = cs * rho;
-        float* h0 = p.hh[0] + ((size_t)k * 2 * B + B + row) * X2;
-        h0[c] = rx0;
-        h0[n + c] = rx1;
-      }
-      tin[i * AS + c] = rx0;
-      tin[i * AS + n + c] = rx1;
-    }
-    for (int c = X2 + lane; c < XP; c += 64) tin[i * AS + c] = 0.f;
-    if (p.loss_rows && row < B) {
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
-      if (lane == 0) p.loss_rows[(size_t)k * p.loss_ld + row] = acc;
-    }
-  }
-  __syncthreads();
-
-  // ---------------- tangent forward, then the adjoint's top ----------------
-  // layer j epilogue: hd = tanh'_j zd; below the top hd goes on (rows 16-31)
-  // and zd is kept; at the top the adjoint starts:
-  // lam_zd = tanh'_L w_o, lam_z = tanh'_L (-2 h_L zd_L w_o)
-  auto tan_epi = [&](int j, const f4& h, f4& zj, const f4& y, float* out) {
-    const f4 zd = y * kTanhUnscale;
-    const f4 d = (1.f - h * h) * dsc(j);
-    const f4 hd = d * zd;
-    if (in_b) put4(p.hh[j + 1], p.wd[j + 1], B + brow, hd);
-    if (j < L - 1) {
-      lds4(out, 16 + wl, hd);
-      zj = zd;
-    } else {
-      const f4 w4 = *reinterpret_cast<const f4*>(wos + u);
-      const f4 lzd = d * w4;
-      const f4 lz = d * (-2.f * h * zd * w4);
-      lds4(out, wl, lz);
-      lds4(out, 16 + wl, lzd);
-      if (in_b) {
-        put4(p.sl[j], p.wd[j + 1], brow, lz);
-        put4(p.sl[j], p.wd[j + 1], B + brow, lzd);
-      }
-    }
-  };
-  {
-    const float* in = act + cur * BUF + 16 * AS;
-    float* out = act + (cur ^ 1) * BUF;
-    f4 acc[1][1];
-    acc[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-    gemm_run<P, 1, 1, PD>(acc, wr, in, AS, wsrc(p.fwd_off[0]), XP / KF, lane);
-    if (L > 1) ring_preload<PDH, 1>(wh, next_after_fwd(0), NK, lane);
-    f4 dummy;
-    tan_epi(0, hs[0], L > 1 ? zs[0] : dummy, acc[0][0], out);
-    cur ^= 1;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int j = 1; j < LM; ++j) {
-    if (j < L) {
-      const float* in = act + cur * BUF + 16 * AS;
-      float* out = act + (cur ^ 1) * BUF;
-      f4 acc[1][1];
-      acc[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-      gemm_hidden<P, 1, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.fwd_off[j]), true,
-                                       next_after_fwd(j), lane);
-      f4 dummy;
-      tan_epi(j, hs[j], j < LM - 1 ? zs[j < LM - 1 ? j : 0] : dummy, acc[0][0], out);
-      cur ^= 1;
-      __syncthreads();
-    }
-  }
-  // ---------------- adjoint reverse (primal and tangent rows together) ----------------
-#pragma unroll
-  for (int j = LM - 1; j >= 1; --j) {
-    if (j < L) {
-      const float* in = act + cur * BUF;
-      float* out = act + (cur ^ 1) * BUF;
-      f4 acc[2][1];
-      acc[0][0] = f4{0.f, 0.f, 0.f, 0.f};
-      acc[1][0] = f4{0.f, 0.f, 0.f, 0.f};
-      gemm_hidden<P, 2, 1, 1, PDH, NK>(acc, wh, in, AS, wsrc(p.bwd_off[j]), j >= 2,
-                                       wsrc(p.bwd_off[j >= 2 ? j - 1 : j]), lane);
-      const f4 h = hs[j - 1], zd = zs[j - 1];
-      const f4 d = (1.f - h * h) * dsc(j - 1);
-      const f4 lhd = acc[1][0];
-      const f4 lzd = d * lhd;
-      const f4 lz = d * (acc[0][0] - 2.f * h * zd * lhd);
-      if (j >= 2) {
-        lds4(out, wl, lz);
-        lds4(out, 16 + wl, lzd);
-      }
-      if (in_b) {
-        put4(p.sl[j - 1], p.wd[j], brow, lz);
-        put4(p.sl[j - 1], p.wd[j], B + brow, lzd);
-      }
-      cur ^= 1;
-      __syncthreads();
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // weight packer: FP32 masters (packed layout) -> MFMA fragments, biases
 // ---------------------------------------------------------------------------
 struct PackLayer {
@@ -1412,7 +752,7 @@ struct PackLayer {
 };
 
 // element format of a set of MFMA fragments
-enum FragFmt { kFmtF32 = 0, kFmtBF16 = 1, kFmtF16 = 2 };
+enum FragFmt { kFmtBF16 = 1, kFmtF16 = 2 };
 
 struct VecArgs {
   unsigned b_off[kMaxHidden];
@@ -1478,8 +818,8 @@ __global__ void pack_kernel(const float* master, size_t per_model, PackAll pa,
   const PackLayer& pl = pa.layer[blockIdx.y >> 1];
   const int dir = blockIdx.y & 1;
   const int fmt = dir == 0 ? pl.fmt_fwd : pl.fmt_bwd;
-  const int KF = fmt == kFmtF32 ? 16 : 32;
-  const int E = fmt == kFmtF32 ? 4 : 8;       // elements per lane (16 bytes)
+  constexpr int KF = 32;
+  constexpr int E = 8;                        // elements per lane (16 bytes)
   const int kc = dir == 0 ? pl.kin_pad : NP;
   const int nc = dir == 0 ? NP : pl.kin_pad;
   const int JT = nc / 16, KT = kc / KF;
@@ -1493,7 +833,7 @@ __global__ void pack_kernel(const float* master, size_t per_model, PackAll pa,
     const int k = (int)(f / KT);
     const float* W = master + (size_t)k * per_model + pl.w_off;
     const int col = jt * 16 + (lane & 15);
-    float v[8];
+    float v[E];
     for (int e = 0; e < E; ++e) {
       const int kk = kt * KF + (KF / 4) * (lane >> 4) + e;
       // W is [out][in]; forward: (unit col = out, contraction kk = in);
@@ -1503,18 +843,12 @@ __global__ void pack_kernel(const float* master, size_t per_model, PackAll pa,
       v[e] = (o < pl.out && i < pl.in) ? W[(size_t)o * pl.in + i] : 0.f;
       if (dir == 0) v[e] *= kTanhPrescale;
     }
-    uint4 out;
-    if (fmt == kFmtF32) {
-      out = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
-                       __float_as_uint(v[3]));
-    } else {
-      unsigned short hv[8];
-      for (int e = 0; e < 8; ++e)
-        hv[e] = fmt == kFmtBF16 ? __builtin_bit_cast(unsigned short, (__bf16)v[e])
-                                : __builtin_bit_cast(unsigned short, (_Float16)v[e]);
-      out = make_uint4(hv[0] | (unsigned)hv[1] << 16, hv[2] | (unsigned)hv[3] << 16,
-                       hv[4] | (unsigned)hv[5] << 16, hv[6] | (unsigned)hv[7] << 16);
-    }
+    unsigned short hv[E];
+    for (int e = 0; e < E; ++e)
+      hv[e] = fmt == kFmtBF16 ? __builtin_bit_cast(unsigned short, (__bf16)v[e])
+                              : __builtin_bit_cast(unsigned short, (_Float16)v[e]);
+    const uint4 out = make_uint4(hv[0] | (unsigned)hv[1] << 16, hv[2] | (unsigned)hv[3] << 16,
+                                 hv[4] | (unsigned)hv[5] << 16, hv[6] | (unsigned)hv[7] << 16);
     unsigned char* dst = frag + (size_t)k * frag_model_bytes +
                          (dir == 0 ? pl.fwd_off : pl.bwd_off) +
                          (((size_t)kt * JT + jt) * 64 + lane) * 16;
@@ -1668,167 +1002,15 @@ rid_status dispatch(const rid_ensemble_impl& e, const float* x, int B, float* A_
   return fail(RID_EUNSUPPORTED, "unknown precision");
 }
 
-size_t hvp_layout(int NP, int XP, int n, HvpArgs& a) {
-  constexpr int R = 32;
-  const int AS = (NP > XP ? NP : XP) + RID_ACT_PAD_BYTES / 4;
-  const size_t buf = (size_t)R * AS * 4;
-  size_t off = 2 * buf;
-  // the u0 partials (u0_split gives 4 parts at every FP32 width)
-  const size_t u0_bytes = (size_t)u0_split<F32, 64>() * R * (XP + 4) * 4;
-  if (u0_bytes <= buf) {
-    a.off_u0 = 0;                       // buffer 0 is free in the last GEMM
-  } else {
-    a.off_u0 = align16(off);
-    off = a.off_u0 + u0_bytes;
-  }
-  a.off_xs = align16(off);
-  off = a.off_xs + (size_t)16 * 2 * n * 4;
-  a.off_rs = align16(off);
-  off = a.off_rs + (size_t)16 * n * 4;
-  a.off_wo = align16(off);
-  return a.off_wo + (size_t)NP * 4;
-}
-
-template <int NP>
-rid_status run_hvp(const rid_ensemble_impl& e, const float* x, const float* rho,
-                   const float* coef, int B, float* T, hipStream_t st) {
-  constexpr int NW = NP / 16;
-  static size_t attr = 0;
-  HvpArgs a{};
-  const size_t lds = hvp_layout(NP, e.XP, e.n_cv, a);
-  if (lds > 160 * 1024) return fail(RID_EUNSUPPORTED, "shape too large for the HVP kernel");
-  auto kern = hvp_kernel<NP, NW, kMaxHidden>;
-  if (lds > 64 * 1024 && lds > attr) {
-    RID_HIP(hipFuncSetAttribute((const void*)kern,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = lds;
-  }
-  a.x = x; a.rho = rho; a.coef = coef; a.T_out = T;
-  a.B = B; a.n = e.n_cv; a.K = e.K; a.L = e.L; a.XP = e.XP;
-  a.n_tiles = (B + 15) / 16;
-  a.xcd_grp = (8 % e.K == 0) ? 8 / e.K : 0;
-  a.frag = e.d_frag; a.frag_model_bytes = e.frag_bytes_per_model;
-  for (int l = 0; l < e.L; ++l) {
-    a.fwd_off[l] = (unsigned)e.layers[l].fwd_off;
-    a.bwd_off[l] = (unsigned)e.layers[l].bwd_off;
-  }
-  a.bias = e.d_bias; a.wo = e.d_wo;
-  const int grid = a.xcd_grp > 0 ? 8 * ((a.n_tiles + a.xcd_grp - 1) / a.xcd_grp)
-                                  : a.n_tiles * e.K;
-  launch_timed(kProfHvp, kern, dim3(grid), dim3(NW * 64), (uint32_t)lds, st, a);
-  RID_HIP(hipGetLastError());
-  return RID_OK;
-}
-
-size_t train_layout(int NP, int XP, int n, TrainArgs& a) {
-  const int AS = (NP > XP ? NP : XP) + RID_ACT_PAD_BYTES / 4;
-  const size_t buf = (size_t)32 * AS * 4;
-  size_t off = 2 * buf;
-  // the u0 partials of 16 rows (4 parts at every FP32 width)
-  const size_t u0_bytes = (size_t)u0_split<F32, 64>() * 16 * (XP + 4) * 4;
-  if (u0_bytes <= buf) {
-    a.off_u0 = 0;                       // buffer 0 is free in the u0 GEMM
-  } else {
-    a.off_u0 = align16(off);
-    off = a.off_u0 + u0_bytes;
-  }
-  a.off_xs = align16(off);
-  off = a.off_xs + (size_t)16 * 2 * n * 4;
-  a.off_wo = align16(off);
-  return a.off_wo + (size_t)NP * 4;
-}
-
-template <int NP>
-rid_status run_train(const rid_ensemble_impl& e, const TrainIo& io, int B, hipStream_t st) {
-  constexpr int NW = NP / 16;
-  static size_t attr = 0;
-  TrainArgs a{};
-  const size_t lds = train_layout(NP, e.XP, e.n_cv, a);
-  if (lds > 160 * 1024) return fail(RID_EUNSUPPORTED, "shape too large for the training kernel");
-  auto kern = train_kernel<NP, NW, kMaxHidden>;
-  if (lds > 64 * 1024 && lds > attr) {
-    RID_HIP(hipFuncSetAttribute((const void*)kern,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = lds;
-  }
-  a.s = io.s; a.F = io.F; a.rho = io.rho; a.loss_rows = io.loss_rows;
-  a.loss_ld = io.loss_ld; a.row_base = io.row_base; a.B_norm = io.B_norm;
-  for (int j = 0; j <= e.L; ++j) a.hh[j] = io.hh[j];
-  for (int j = 0; j < e.L; ++j) a.sl[j] = io.sl[j];
-  a.B = B; a.n = e.n_cv; a.K = e.K; a.L = e.L; a.XP = e.XP;
-  a.n_tiles = (B + 15) / 16;
-  a.xcd_grp = (8 % e.K == 0) ? 8 / e.K : 0;
-  a.wd[0] = 2 * e.n_cv;
-  for (int j = 0; j < e.L; ++j) a.wd[j + 1] = e.widths[j];
-  a.frag = e.d_frag; a.frag_model_bytes = e.frag_bytes_per_model;
-  for (int l = 0; l < e.L; ++l) {
-    a.fwd_off[l] = (unsigned)e.layers[l].fwd_off;
-    a.bwd_off[l] = (unsigned)e.layers[l].bwd_off;
-  }
-  a.bias = e.d_bias; a.wo = e.d_wo;
-  a.drop_p = io.drop_p;
-  a.drop_inv = io.drop_p > 0.f ? 1.f / (1.f - io.drop_p) : 1.f;
-  a.drop_seed = io.drop_seed;
-  a.step = io.step;
-  const int grid = a.xcd_grp > 0 ? 8 * ((a.n_tiles + a.xcd_grp - 1) / a.xcd_grp)
-                                  : a.n_tiles * e.K;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), (uint32_t)lds, st, a);
-  RID_HIP(hipGetLastError());
-  return RID_OK;
-}
-
 }  // namespace
 
-// Kernel family: (precision, padded width, depth) -> instantiation.
-// FP32: 16 walkers per workgroup, the units split over the waves (16 waves of
-// one 16-unit tile at width 256).  16-bit: 64 walkers per workgroup (32 for
-// deep networks or wide inputs) to cut the L2 weight stream per FLOP; 64
-// units per wave.  g_out == nullptr: free energies only.
+// Kernel family: (precision, padded width, depth) -> instantiation.  FP32
+// ensembles: dispatch_mlp_f32.  16-bit: 64 walkers per workgroup (32 for deep
+// networks or wide inputs) to cut the L2 weight stream per FLOP; 64 units per
+// wave.  g_out == nullptr: free energies only.
 rid_status launch_mlp(const rid_ensemble_impl& e, const float* x, int B,
                       float* A_out, float* g_out, hipStream_t st) {
   return dispatch(e, x, B, A_out, g_out, nullptr, st);
-}
-
-bool hvp_fused_supported(const rid_ensemble_impl& e) {
-  // plain MLPs on periodic inputs (residual and raw-CV ensembles take the
-  // training sweeps in input mode)
-  if (e.prec != RID_FP32 || e.NP > 256 || e.L > kMaxHidden || e.resnet || !e.raw.empty())
-    return false;
-  HvpArgs a{};
-  return hvp_layout(e.NP, e.XP, e.n_cv, a) <= 160 * 1024;
-}
-
-rid_status launch_hvp(const rid_ensemble_impl& e, const float* x, const float* rho,
-                      const float* coef, int B, float* T, hipStream_t st) {
-  if (e.prec == RID_FP32) {
-    switch (e.NP) {
-      case 64:  return run_hvp<64>(e, x, rho, coef, B, T, st);
-      case 128: return run_hvp<128>(e, x, rho, coef, B, T, st);
-      case 256: return run_hvp<256>(e, x, rho, coef, B, T, st);
-    }
-  }
-  return fail(RID_EUNSUPPORTED, "no fused HVP kernel for this ensemble");
-}
-
-bool train_fused_supported(const rid_ensemble_impl& e) {
-  // plain MLPs on periodic inputs (residual and raw-CV ensembles take the
-  // sweeps as separate GEMMs)
-  if (e.prec != RID_FP32 || e.NP > 256 || e.L > kMaxHidden || e.resnet || !e.raw.empty())
-    return false;
-  TrainArgs a{};
-  return train_layout(e.NP, e.XP, e.n_cv, a) <= 160 * 1024;
-}
-
-rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, int B,
-                               hipStream_t st) {
-  if (e.prec == RID_FP32) {
-    switch (e.NP) {
-      case 64:  return run_train<64>(e, io, B, st);
-      case 128: return run_train<128>(e, io, B, st);
-      case 256: return run_train<256>(e, io, B, st);
-    }
-  }
-  return fail(RID_EUNSUPPORTED, "no fused training kernel for this ensemble");
 }
 
 rid_status launch_mlp_from_pos(const rid_ensemble_impl& e, const TorsionInput& tin,
@@ -1839,8 +1021,10 @@ rid_status launch_mlp_from_pos(const rid_ensemble_impl& e, const TorsionInput& t
   return dispatch(e, nullptr, B, A_out, g_out, &tin, st);
 }
 
-static rid_status pack_frag_weights(rid_ensemble_impl& e, hipStream_t st) {
+rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
   ++e.master_gen;     // the masters may have changed: copies made from them are stale
+  e.frag_dirty = false;
+  if (e.prec == RID_FP32) return pack_split_weights(e, st);
   const int L = e.L;
   PackAll pa{};
   pa.L = L;
@@ -1870,11 +1054,8 @@ static rid_status pack_frag_weights(rid_ensemble_impl& e, hipStream_t st) {
       case RID_FP16:
         pl.fmt_fwd = pl.fmt_bwd = kFmtF16;
         break;
-      case RID_BF16_ALL:
+      default:                         // RID_BF16_ALL
         pl.fmt_fwd = pl.fmt_bwd = kFmtBF16;
-        break;
-      default:
-        pl.fmt_fwd = pl.fmt_bwd = kFmtF32;
         break;
     }
     prev = pl.out;
@@ -1886,24 +1067,7 @@ static rid_status pack_frag_weights(rid_ensemble_impl& e, hipStream_t st) {
   hipLaunchKernelGGL(pack_kernel, grid, block, 0, st, e.d_master, e.per_model, pa, e.d_frag,
                      e.frag_bytes_per_model, e.d_bias, e.d_wo, e.d_bo, e.d_vscale);
   RID_HIP(hipGetLastError());
-  e.frag_dirty = false;
-  e.split_dirty = e.prec == RID_FP32;
   return RID_OK;
-}
-
-rid_status ensure_packed(rid_ensemble_impl& e, hipStream_t st, bool mlp) {
-  rid_status r;
-  if (e.frag_dirty && (r = pack_frag_weights(e, st)) != RID_OK) return r;
-  if (mlp && e.split_dirty) {
-    if ((r = pack_split_weights(e, st)) != RID_OK) return r;
-    e.split_dirty = false;
-  }
-  return RID_OK;
-}
-
-rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
-  e.frag_dirty = true;
-  return ensure_packed(e, st);
 }
 
 }  // namespace rid

@@ -33,9 +33,7 @@ struct MlpF32Args {
   SplitView w;
   float* A_out;        // [K][B]
   float* g_out;        // [K][B][n]
-  // LDS byte offsets (activation buffer 0 starts at 0; the partials of the
-  // input-gradient product reuse it)
-  unsigned off_red, off_mx, off_xs, off_ph0, off_wo;
+  unsigned off_red, off_mx, off_xs, off_wo;   // LDS byte offsets
   int u0_parts;        // parts of the input-gradient contraction (1, 2 or 4)
   int rc;              // walkers per torsion-gather pass (bias path)
   dev::SysView sv;          // torsion input (bias path)
@@ -69,11 +67,13 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
   if (tile >= p.n_tiles) return;
   const int row0 = tile * R;
   const int n = p.n, L = p.L, XP = p.XP, X2 = 2 * p.n;
-  const int AW = NP > XP ? NP : XP;            // activation width
-  const int AS = split_row_halfs(AW);          // row stride (halfs)
-  const int BUF = R * AS;                      // halfs per ping-pong buffer
-  _Float16* act = reinterpret_cast<_Float16*>(smem);
-  float* u0 = reinterpret_cast<float*>(smem);                // aliases buffer 0
+  constexpr int AS = split_row_halfs(NP);      // row stride (halfs)
+  constexpr int BUF = R * AS;                  // halfs per ping-pong buffer
+  const int AX = split_row_halfs(XP);          // row stride of the input tile
+  _Float16* const buf1 = reinterpret_cast<_Float16*>(smem);
+  _Float16* const buf0 = buf1 + BUF;
+  auto buf = [&](int i) { return i & 1 ? buf1 : buf0; };
+  float* u0 = reinterpret_cast<float*>(buf0);                // partials of u0
   const int US = XP + 4;
   float* red = reinterpret_cast<float*>(smem + p.off_red);   // [JT][R]
   unsigned* mx = reinterpret_cast<unsigned*>(smem + p.off_mx);   // [LM][R] row maxima
@@ -114,17 +114,17 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
   SplitRing<PDH, CT> wh;             // hidden layers
   split_preload<PD, CT>(wr, wsrc(p.w.fwd_off[0]), XP / kSplitKF, lane);
   f4 bnext[CT], rnext[CT];           // bias and row scales of the coming epilogue
+  const VecSrc vrs = vec_src(rs, L * 2 * p.w.RW), vbias = vec_src(bias, L * NP);
   auto load_fwd = [&](int l) {
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-      bnext[c] = *reinterpret_cast<const f4*>(bias + l * NP + (jt0 + c) * 16 + uq);
-      rnext[c] = *reinterpret_cast<const f4*>(rs + (l * 2) * p.w.RW + (jt0 + c) * 16 + uq);
+      bnext[c] = vbias.ld4(l * NP + (jt0 + c) * 16, uq);
+      rnext[c] = vrs.ld4(l * 2 * p.w.RW + (jt0 + c) * 16, uq);
     }
   };
   auto load_bwd = [&](int l) {
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
-      rnext[c] = *reinterpret_cast<const f4*>(rs + (l * 2 + 1) * p.w.RW + (jt0 + c) * 16 + uq);
+    for (int c = 0; c < CT; ++c) rnext[c] = vrs.ld4((l * 2 + 1) * p.w.RW + (jt0 + c) * 16, uq);
   };
   load_fwd(0);
   for (int i = threadIdx.x; i < NP; i += NW * 64) wos[i] = p.w.wo[(size_t)k * NP + i];
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
     // stores.  Slots past the end are clamped to the last coordinate or
     // walker of the pass (they store that slot's own value again), so no
     // load sits behind a branch; walkers past B get zeros.
-    float* sp = reinterpret_cast<float*>(smem + p.off_ph0);   // [rc][U][3]
+    float* sp = reinterpret_cast<float*>(buf1);   // [rc][U][3]
     const int U3 = 3 * p.sv.U;
     constexpr int WPW = (R + NW - 1) / NW;    // walkers per wave and pass, at most
     constexpr int QB = WPW < 4 ? WPW : 4;     // walkers per batch of loads
@@ -203,14 +203,14 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
           }
           xs[i * X2 + c] = cs;
           xs[i * X2 + n + c] = sn;
-          split_store1(act + i * AS + c, AW, cs * kActScale);
-          split_store1(act + i * AS + n + c, AW, sn * kActScale);
+          split_store1(buf0 + i * AX + c, XP, cs * kActScale);
+          split_store1(buf0 + i * AX + n + c, XP, sn * kActScale);
         }
       }
       __syncthreads();
     }
     for (int i = wave; i < R; i += NW)
-      for (int c = X2 + lane; c < XP; c += 64) split_store1(act + i * AS + c, AW, 0.f);
+      for (int c = X2 + lane; c < XP; c += 64) split_store1(buf0 + i * AX + c, XP, 0.f);
     if (threadIdx.x < R) sx[threadIdx.x] = kActUnscale;
   } else {
     // the column batches of the tile (the first one is already in xv);
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
             v.x = fabsf(v.x) > kMax ? copysignf(kMax, v.x) : v.x;
             v.y = fabsf(v.y) > kMax ? copysignf(kMax, v.y) : v.y;
           }
-          if (i < R) split_store2(act + i * AS + 2 * col, AW, v.x * scl[j], v.y * scl[j]);
+          if (i < R) split_store2(buf0 + i * AX + 2 * col, XP, v.x * scl[j], v.y * scl[j]);
         }
       }
     }
@@ -267,7 +267,6 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
   f4 st[LM - 1][RT][CT];             // tanh' of hidden layers 1..L-1
   f4 ares[RT][CT];                   // RES: the layer's input h, then dA/dh (FP32)
   float apart[RT][CT];               // the lane's part of A = w_o . h_L, per unit tile
-  int cur = 0;
 
   // ---------------- forward: h_l = tanh(W_l h_{l-1} + b_l) ----------------
   // tile epilogues: y = acc * rs + b, tanh and its derivative; a layer
@@ -290,7 +289,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
       if (l >= 1) h += ares[rt][c];  // the lane's own units of h_{l-1}
       ares[rt][c] = h;
     }
-    split_store4(out + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq, AW, h);
+    split_store4(out + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq, NP, h);
     if constexpr (GRAD) st[l][rt][c] = d;
   };
   auto last_tile = [&](int rt, int c, const f4& z, float iv, bool skip, _Float16* out) {
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
       const f4 v = w4 * d;
       if constexpr (!RES)
         split_track(mx + (L - 1) * R + rt * 16 + wl, v);
-      split_store4(out + (rt * 16 + wl) * AS + u, AW, v * split_scale(split_clamp_exp(ec[0])));
+      split_store4(out + (rt * 16 + wl) * AS + u, NP, v * split_scale(split_clamp_exp(ec[0])));
     }
   };
   // the product after forward layer l: forward layer l+1, or the first backward
@@ -322,10 +321,10 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
   };
 
   {  // layer 1 (input width XP)
-    _Float16* out = act + BUF;
+    _Float16* out = buf1;
     f4 acc[RT][CT];
     zero(acc);
-    split_gemm_run<RT, CT, PD>(acc, wr, act, AS, AW, wsrc(p.w.fwd_off[0]), XP / kSplitKF, lane);
+    split_gemm_run<RT, CT, PD>(acc, wr, buf0, AX, XP, wsrc(p.w.fwd_off[0]), XP / kSplitKF, lane);
     if (L > 1) split_preload<PDH, CT>(wh, next_after_fwd(0), NK, lane);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -336,43 +335,40 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
         else last_tile(rt, c, acc[rt][c], iv, false, out);
       }
     }
-    cur = 1;
     __syncthreads();
   }
   // hidden layers before the last
-#pragma unroll
-  for (int l = 1; l < LM - 1; ++l) {
+  layers_up<1, LM - 1>([&](auto lc) __attribute__((always_inline)) {
+    constexpr int l = decltype(lc)::value;
     if (l < L - 1) {
-      const _Float16* in = act + cur * BUF;
-      _Float16* out = act + (cur ^ 1) * BUF;
+      const _Float16* in = buf(l);
+      _Float16* out = buf(l + 1);
       f4 acc[RT][CT];
       zero(acc);
       if constexpr (EARLY) load_fwd(l);
-      split_gemm_hidden<RT, CT, PDH, NK, ADB>(acc, wh, in, AS, AW, wsrc(p.w.fwd_off[l]), true,
+      split_gemm_hidden<RT, CT, PDH, NK, ADB>(acc, wh, in, AS, NP, wsrc(p.w.fwd_off[l]), true,
                                               next_after_fwd(l), lane);
       if constexpr (!EARLY) load_fwd(l);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int c = 0; c < CT; ++c) mid_tile(l, rt, c, acc[rt][c], 1.f, out);
-      cur ^= 1;
       __syncthreads();
     }
-  }
+  });
   if (L > 1) {  // the last hidden layer (index L-1)
-    const _Float16* in = act + cur * BUF;
-    _Float16* out = act + (cur ^ 1) * BUF;
+    const _Float16* in = buf(L - 1);
+    _Float16* out = buf(L);
     f4 acc[RT][CT];
     zero(acc);
     if constexpr (EARLY) load_fwd(L - 1);
-    split_gemm_hidden<RT, CT, PDH, NK, ADB>(acc, wh, in, AS, AW, wsrc(p.w.fwd_off[L - 1]), GRAD,
+    split_gemm_hidden<RT, CT, PDH, NK, ADB>(acc, wh, in, AS, NP, wsrc(p.w.fwd_off[L - 1]), GRAD,
                                             wsrc(p.w.bwd_off[L - 1]), lane);
     if constexpr (!EARLY) load_fwd(L - 1);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int c = 0; c < CT; ++c) last_tile(rt, c, acc[rt][c], 1.f, true, out);
-    cur ^= 1;
     __syncthreads();
   }
   // A = w_o . h_L + b_o: the lanes' partials over the 4 unit groups, then
@@ -407,15 +403,15 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
   float iv[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) iv[rt] = split_unscale(split_clamp_exp(ec[0]));
-#pragma unroll
-  for (int l = LM - 1; l >= 1; --l) {
+  layers_down<LM - 1, 1>([&](auto lc) __attribute__((always_inline)) {
+    constexpr int l = decltype(lc)::value;
     if (l < L) {
-      const _Float16* in = act + cur * BUF;
-      _Float16* out = act + (cur ^ 1) * BUF;
+      const _Float16* in = buf(l + 1);
+      _Float16* out = buf(l);
       f4 acc[RT][CT];
       zero(acc);
       if constexpr (EARLY) load_bwd(l);
-      split_gemm_hidden<RT, CT, PDH, NK, ADB>(acc, wh, in, AS, AW, wsrc(p.w.bwd_off[l]), l >= 2,
+      split_gemm_hidden<RT, CT, PDH, NK, ADB>(acc, wh, in, AS, NP, wsrc(p.w.bwd_off[l]), l >= 2,
                                               wsrc(p.w.bwd_off[l >= 2 ? l - 1 : l]), lane);
       if constexpr (!EARLY) load_bwd(l);
 #pragma unroll
@@ -433,38 +429,36 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
           }
           const f4 v = y * st[l - 1][rt][c];
           if (l >= 2) split_track(mx + (l - 1) * R + rt * 16 + wl, RES ? y : v);
-          split_store4(out + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq, AW, v * sc);
+          split_store4(out + (rt * 16 + wl) * AS + (jt0 + c) * 16 + uq, NP, v * sc);
         }
         iv[rt] = split_unscale(e);
       }
-      cur ^= 1;
       __syncthreads();
     }
-  }
+  });
   // ------------- layer 1 backward: u0 = W_1^T v_1 -------------
   // XP/16 column tiles, each tile's contraction cut into parts so that they
   // spread over the waves; partial sums to LDS (part q at u0 + q * R * US),
-  // added in part order when u0 is read.  v_1 sits in buffer 1 (2L-1 buffer
-  // flips), so the partials take buffer 0.
-  const float* rs0 = rs + p.w.RW;              // backward row scales of layer 1
+  // added in part order when u0 is read.  v_1 sits in buffer 1, the partials
+  // in buffer 0.
   auto u0_stage = [&](auto parts_c) {
     constexpr int PARTS = decltype(parts_c)::value;
     constexpr int KQ = NK / PARTS;             // k-steps per part
-    const _Float16* in = act + cur * BUF;
+    const _Float16* in = buf1;
     const int JT0 = XP / 16;
     for (int it = wave; it < JT0 * PARTS; it += NW) {
       const int t = it / PARTS, q = it - t * PARTS;
       const SplitSrc src{rsrc,
                          (int)p.w.bwd_off[0] + t * kSplitFrag + q * KQ * JT0 * kSplitFrag,
                          JT0 * kSplitFrag};
-      const f4 r4 = *reinterpret_cast<const f4*>(rs0 + t * 16 + uq);
+      const f4 r4 = vrs.ld4(p.w.RW + t * 16, uq);   // backward row scales of layer 1
       constexpr int PU = KQ < 4 ? KQ : 4;      // loads in flight
       SplitRing<PU, 1> w0;
       split_preload<PU, 1>(w0, src, KQ, lane);
       f4 a1[RT][1];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) a1[rt][0] = f4{0.f, 0.f, 0.f, 0.f};
-      split_gemm_run<RT, 1, PU>(a1, w0, in + q * KQ * kSplitKF, AS, AW, src, KQ, lane);
+      split_gemm_run<RT, 1, PU>(a1, w0, in + q * KQ * kSplitKF, AS, NP, src, KQ, lane);
       float* uq0 = u0 + q * R * US;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
@@ -515,24 +509,14 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
 SplitView split_view(const rid_ensemble_impl& e);
 inline unsigned align16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
 
-// Parts of the input-gradient contraction: more parts spread its few column
-// tiles over the waves; the partials must fit the free activation buffer, a
-// condition on the widths alone (rows cancel), so every row tile sums in the
-// same order.
-inline int split_u0_parts(int NP, int XP) {
-  const int AW = NP > XP ? NP : XP;
-  for (int q = 4; q > 1; q /= 2)
-    if ((NP / dev::kSplitKF) % q == 0 && q * (XP + 4) <= AW + 4 && (XP / 16) * (q / 2) < NP / 16)
-      return q;
-  return 1;
-}
+int split_u0_parts(int NP, int XP);
 
 // LDS layout of one instantiation; returns the total bytes.
 inline size_t mlp_f32_layout(int NP, int R, int LM, int XP, int n, int U, bool from_pos,
                              MlpF32Args& a) {
-  const int AW = NP > XP ? NP : XP;
-  const size_t buf = (size_t)R * dev::split_row_halfs(AW) * 2;
-  size_t off = 2 * buf;
+  const size_t buf = (size_t)R * dev::split_row_halfs(NP) * 2;
+  // buffer 0 also holds the input rows and the partials of u0 (XP > NP: one part)
+  size_t off = buf + std::max(buf, (size_t)R * dev::split_row_halfs(XP) * 2);
   a.off_red = align16(off);
   off = a.off_red + (size_t)(NP / 16) * R * 4;
   a.off_mx = align16(off);
@@ -543,7 +527,6 @@ inline size_t mlp_f32_layout(int NP, int R, int LM, int XP, int n, int U, bool f
   off = a.off_wo + (size_t)NP * 4;
   if (from_pos) {
     // gather scratch in buffer 1 (free before layer 1), in passes of rc walkers
-    a.off_ph0 = (unsigned)buf;
     a.rc = (int)std::min<size_t>((size_t)R, buf / ((size_t)12 * U));
   }
   return off;

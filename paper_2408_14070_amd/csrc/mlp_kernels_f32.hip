@@ -153,6 +153,18 @@ int split_rows(int NP, int B, int K, int most) {
 
 }  // namespace
 
+// Parts of the input-gradient contraction: more parts spread its few column
+// tiles over the waves; the partials must fit the free activation buffer, a
+// condition on the widths alone (rows cancel), so every row tile sums in the
+// same order.
+int split_u0_parts(int NP, int XP) {
+  const int AW = NP > XP ? NP : XP;
+  for (int q = 4; q > 1; q /= 2)
+    if ((NP / kSplitKF) % q == 0 && q * (XP + 4) <= AW + 4 && (XP / 16) * (q / 2) < NP / 16)
+      return q;
+  return 1;
+}
+
 int split_width(int wmax) {
   for (int v : {64, 128, 192, 256, 320, 384})
     if (wmax <= v) return v;

@@ -25,6 +25,8 @@
 //    keep full precision 2^28 below it.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace rid {
@@ -32,6 +34,24 @@ namespace dev {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+// f(integral_constant i) for i = I .. N-1, or I down to N: layer loops whose
+// index must be a compile-time constant (the per-layer register arrays) however
+// large the body is; an unroll pragma gives up on the larger ones.
+template <int I, int N, class F>
+__device__ __attribute__((always_inline)) inline void layers_up(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    layers_up<I + 1, N>(f);
+  }
+}
+template <int I, int N, class F>
+__device__ __attribute__((always_inline)) inline void layers_down(F&& f) {
+  if constexpr (I >= N) {
+    f(std::integral_constant<int, I>{});
+    layers_down<I - 1, N>(f);
+  }
+}
 
 constexpr int kSplitKF = 32;             // contraction indices per MFMA
 constexpr int kSplitFrag = 2 * kFragBytes;   // hi block, then lo block
@@ -41,7 +61,10 @@ constexpr int kTargetExp = 14;           // scaled vectors stay below 2^14
 
 // Activation rows in LDS: [hi: AW halfs][lo: AW halfs][pad 16 bytes]; AW a
 // multiple of 32, so row starts are spread over the banks like 16-byte
-// padded rows of 4 AW bytes.
+// padded rows of 4 AW bytes.  Hidden vectors take AW = NP, the input tile its
+// own XP.  The two ping-pong buffers lie [buffer 1][buffer 0, input tile,
+// partials of u0], so that every hidden address is a constant offset; layer
+// j reads buffer j & 1.
 __host__ __device__ constexpr int split_row_halfs(int AW) { return 2 * AW + 8; }
 
 // Where a wave's weight fragments come from: a buffer resource over one
@@ -117,6 +140,20 @@ __device__ inline void split_step(f4 (&acc)[RT][CT], const uint4 (&w)[CT][2],
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int c = 0; c < CT; ++c) split_mfma(acc[rt][c], w[c][0], a[rt][0]);
+}
+
+// Four consecutive floats of a uniform array (row scales, biases): the
+// array as a scalar resource, the element as a scalar offset plus the lane's.
+struct VecSrc {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ inline f4 ld4(int uniform, int lane_off) const {
+    return __builtin_bit_cast(
+        f4, __builtin_amdgcn_raw_buffer_load_b128(r, 4 * lane_off, 4 * uniform, 0));
+  }
+};
+__device__ inline VecSrc vec_src(const float* p, int count) {
+  return VecSrc{__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, 4 * count,
+                                                  0x00020000)};
 }
 
 // The scheduling barrier that pins "issue next loads -> MFMAs of this step":
@@ -234,6 +271,9 @@ __device__ inline void split_track(unsigned* m, const f4& v) {
 // Forward weights and biases are stored multiplied by 2/ln 2, so a forward
 // product yields y = 2 z / ln 2 and exp(2z) = 2^y takes no multiply.
 constexpr float kTanhPrescale = 2.8853900817779268f;
+
+// ln 2 / 2: undoes the forward pre-scale where no bias is added (tangents)
+constexpr float kTanhUnscale = 0.34657359027997264f;
 
 // tanh and its derivative from one exponential and one reciprocal, given the
 // pre-scaled pre-activation y: with r = 1 / (1 + 2^y):  tanh z = 1 - 2r,

@@ -81,14 +81,12 @@ struct ProfScope {
 
 // ---------------------------------------------------------------------------
 // MFMA fragment geometry shared by the weight packer and the kernels.
-// A "fragment" covers 16 output columns x KF contraction indices and is
-// stored as 64 lanes x 16 bytes: lane l holds column (l % 16) and the KF/4
-// consecutive contraction indices starting at (KF/4) * (l / 16).
-//   FP32 (v_mfma_f32_16x16x4_f32 issued four times): KF = 16, 4 floats/lane
-//   BF16 / FP16 (v_mfma_f32_16x16x32_{bf16,f16}):    KF = 32, 8 values/lane
+// A "fragment" covers 16 output columns x 32 contraction indices of
+// v_mfma_f32_16x16x32_{bf16,f16} and is stored as 64 lanes x 16 bytes: lane l
+// holds column (l % 16) and the 8 consecutive contraction indices starting
+// at 8 * (l / 16).  FP32 ensembles hold two per tile (mlp_split.h).
 // ---------------------------------------------------------------------------
 constexpr int kFragBytes = 1024;
-inline int kf_of(rid_precision p) { return p == RID_FP32 ? 16 : 32; }
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 constexpr int kMaxHidden = 6;
@@ -145,9 +143,9 @@ struct rid_ensemble_impl {
   int n_cv = 0, K = 0, L = 0;
   std::vector<int> widths;
   rid_precision prec = RID_FP32;
-  int NP = 0;        // padded hidden width (multiple of 64)
-  int XP = 0;        // padded input width (multiple of KF)
-  int KF = 16;
+  int NP = 0;        // 16-bit: padded hidden width (multiple of 64)
+  int XP = 0;        // 16-bit: padded input width (multiple of KF)
+  int KF = 32;       // contraction indices of a fragment
   size_t n_params = 0;          // packed count (all models)
   size_t per_model = 0;         // packed count of one model
   // FP32 masters in packed layout + Adam moments (device)
@@ -170,7 +168,7 @@ struct rid_ensemble_impl {
   // MCMC box of the raw CVs: lower [n], then upper [n] (null until set)
   std::vector<float> bounds;
   float* d_bounds = nullptr;
-  // kernel-layout parameters
+  // kernel-layout parameters (16-bit ensembles; FP32: split below)
   std::vector<LayerDev> layers;
   size_t frag_bytes_per_model = 0;
   unsigned char* d_frag = nullptr;   // [K][frag_bytes_per_model]
@@ -188,7 +186,6 @@ struct rid_ensemble_impl {
   unsigned long long master_gen = 1, wpad_gen = 0;
   // scratch
   bool frag_dirty = false;           // masters changed since the last pack
-  bool split_dirty = false;          // the split fragments are older than d_frag
   DevBuf ws_x, ws_A, ws_g, ws_train, ws_cons;
 };
 
@@ -224,12 +221,12 @@ rid_status launch_mlp(const rid_ensemble_impl& e, const float* x, int B,
 // term T [K][B][n] of d eps/ds, from the encoding x [B][2n], w_k in
 // rho [B][K][n] and the walkers' Abar sigma' in coef [B] (tiles with no
 // walker in the band are skipped and their T left unwritten).  FP32
-// ensembles of padded width <= 256 only (hvp_fused_supported).
+// ensembles that hvp_fused_supported accepts.
 bool hvp_fused_supported(const rid_ensemble_impl& e);
 rid_status launch_hvp(const rid_ensemble_impl& e, const float* x, const float* rho,
                       const float* coef, int B, float* T, hipStream_t st);
-// Fused sweeps of one mean-force training step (FP32 ensembles of padded
-// width <= 256, train_fused_supported): from the samples s [B][n] and labels
+// Fused sweeps of one mean-force training step (FP32 ensembles that
+// train_fused_supported accepts): from the samples s [B][n] and labels
 // F [B][n] (or an upstream gradient rho [B][K][n] of the g outputs), writes
 // hh[j] = [h_j ; hd_j] (j = 0: [x ; rho_x]) and sl[j] = [lam_z ; lam_zd] of
 // layer j, each [K][2B][width], and the squared residual per sample
@@ -271,9 +268,10 @@ rid_status launch_bias_scatter(const rid_system_impl& s, int K, const float* pos
 // rec_stride > 0: walker records -- walker w's forces start at
 // force + w * rec_stride and energy/eps/sigma use the same stride.
 rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st);
-// Packs what the masters have left behind; mlp = false leaves the split
-// fragments (a training step reads d_frag only).
-rid_status ensure_packed(rid_ensemble_impl& e, hipStream_t st, bool mlp = true);
+// The same where the masters have changed since (a training step).
+inline rid_status ensure_packed(rid_ensemble_impl& e, hipStream_t st) {
+  return e.frag_dirty ? pack_ensemble_weights(e, st) : RID_OK;
+}
 // FP32 ensembles: padded widths and layout of the split fragments (host
 // side), their packing, and the MLP kernel that reads them.
 int split_width(int wmax);

@@ -453,7 +453,7 @@ rid_status rid_server_register(rid_server srv, rid_system sys, rid_ensemble ens,
     return fail(RID_EINVAL, "the ensemble's angular mask does not match the system's CV kinds");
   Server& s = srv->s;
   rid_ensemble_impl& e = ens->impl;
-  if (e.frag_dirty || e.split_dirty) {
+  if (e.frag_dirty) {
     rid_status rs = ensure_packed(e, nullptr);
     if (rs != RID_OK) return rs;
     RID_HIP(hipStreamSynchronize(nullptr));

@@ -16,8 +16,9 @@
 //   dw_o = sum hd_L, db_o = 0.
 // Then one Adam step on the FP32 masters.
 //
-// General form (the sweeps as separate GEMMs: wide and 16-bit ensembles,
-// residual networks, dropout on them, mixed angular masks).  With t_l =
+// The sweeps run fused (train_sweep_f32.h); 16-bit ensembles, and the few FP32
+// forms the fused kernel does not hold (train_fused_supported), take them as
+// separate GEMMs here, in the same general form.  With t_l =
 // tanh(z_l), dropout factors S_l (1 without dropout) and d_l = S_l (1 - t_l^2):
 //   primal   h_l = S_l t_l (+ h_{l-1} for a residual layer l >= 2)
 //   backward u_L = w_o, v_l = u_l d_l, u_{l-1} = W_l^T v_l (+ u_l, residual)
@@ -33,7 +34,7 @@
 // member's slab, so one GEMM moves both halves, and the weight gradient is a
 // single contraction over 2B rows.  All GEMMs are one hand-written FP32-MFMA
 // kernel (64x64 tiles, LDS double buffering, arbitrary strides, fused
-// epilogues); the weight-gradient GEMM is split along the batch with a
+// epilogues); the weight-gradient GEMM (both forms) is split along the batch with a
 // fixed-order reduction, so the whole step is deterministic.
 #include "device_common.h"
 
@@ -945,7 +946,7 @@ void wgrad_split(int K, int tiles_max, int R, int* ks, int* kchunk) {
   *kchunk = round_up((2 * R + s - 1) / s, BK);
 }
 
-// The training step with the sweeps fused into one kernel (train_kernel):
+// The training step with the sweeps fused into one kernel (train_sweep_f32.h):
 // it writes [h ; hd] of every layer input and [lam_z ; lam_zd] of every
 // layer, then the batch reductions run as before: dW_l = S_l^T [h ; hd]_{l-1}
 // (split over the 2R rows), db_l = column sums of lam_z, dw_o = column sums
@@ -993,7 +994,7 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
   float* G = grad_out ? grad_out : W + grad;
   if (grad_used) *grad_used = G;
   ProfScope ps(kProfTrain, st);
-  if ((rs = ensure_packed(e, st, false)) != RID_OK) return rs;
+  if ((rs = ensure_packed(e, st)) != RID_OK) return rs;
   TrainIo io{};
   io.loss_ld = B;
   io.B_norm = B;

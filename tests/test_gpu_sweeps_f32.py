@@ -1,0 +1,154 @@
+"""GPU parity of the fused FP32 training sweeps and Hessian-vector products at
+every padded width, at the edges of their tiles, with residual layers, raw CVs
+and dropout, against the FP64 oracle; and the operand scales of the split
+products (upstream gradients far from 1, strong dropout).
+
+Tolerances: gradients 1e-4 normwise per member, losses 1e-5 relative, forces
+1e-5 normwise per walker plus the switch's slope (as in the tests of the same
+calls)."""
+import numpy as np
+import pytest
+
+import ridgen
+from oracle import rid_oracle as O
+from tests.gpu_common import FP32_TOL
+from tests.test_gpu_conservative import assert_walkers, walker_bounds
+
+pytestmark = pytest.mark.gpu
+GRAD_TOL = 1e-4
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+@pytest.fixture(scope="module")
+def rid():
+    import paper_2408_14070_amd as r
+    r.lib()
+    return r
+
+
+def _models(params, n, widths, K, resnet):
+    m = ridgen.unpack_params(params, 2 * n, widths, K)
+    return [q + (True,) for q in m] if resnet else m
+
+
+def _err(got, ref):
+    return max(np.abs(got[k] - ref[k]).max() / np.abs(ref[k]).max() for k in range(len(ref)))
+
+
+# (n_cv, widths, K, B, residual, raw, dropout): padded widths 64, 128, 192,
+# 256 (6 hidden layers too), 320, 384, 512; batches of 1, 15, 17, 33 samples
+# and ones that take 32 samples a workgroup (more than 256 workgroups of 16)
+@pytest.mark.parametrize("n,widths,K,B,resnet,raw,drop", [
+    (1, [1], 1, 1, False, False, 0.0), (3, [63, 64], 2, 15, False, False, 0.0),
+    (5, [64] * 6, 2, 33, False, False, 0.0), (20, [64] * 3, 4, 1100, False, True, 0.1),
+    (17, [128] * 4, 3, 17, True, False, 0.1), (9, [100, 128], 5, 850, False, False, 0.0),
+    (12, [192] * 6, 2, 20, False, True, 0.0), (12, [170] * 3, 5, 840, False, False, 0.2),
+    (38, [256] * 4, 4, 1041, False, False, 0.0), (38, [256] * 4, 2, 37, True, True, 0.1),
+    (38, [200] * 5, 2, 37, False, False, 0.1), (60, [200, 256], 4, 1030, False, True, 0.0),
+    (18, [300] * 4, 4, 128, True, False, 0.1), (18, [320] * 4, 2, 47, False, True, 0.0),
+    (18, [384] * 3, 2, 31, True, False, 0.0), (30, [350] * 4, 2, 33, False, False, 0.1),
+    (40, [512] * 4, 2, 18, False, False, 0.0), (40, [512] * 3, 2, 18, True, False, 0.0),
+    (100, [64] * 2, 2, 35, False, False, 0.0)])
+def test_loss_grad_at_tile_edges(torch, rid, n, widths, K, B, resnet, raw, drop):
+    rng = np.random.default_rng(n + B)
+    mask = np.ones(n, np.uint8)
+    if raw:
+        mask[::4] = 0
+    params = ridgen.xavier_ensemble(2 * n, widths, K, 500 + n, bias_std=0.1)
+    s, F, _ = ridgen.mf_training_set(B, n)
+    s = s.copy()
+    s[:, mask == 0] = ridgen.f32(rng.uniform(0.3, 1.5, (B, int((mask == 0).sum()))))
+    E = rid.Ensemble(n, widths, K, params)
+    if resnet:
+        E.set_resnet(True)
+    if raw:
+        E.set_angular_mask(mask)
+    if drop:
+        E.set_dropout(drop, 99)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    loss, grad = rid.mf_loss_grad(E, dev(s), dev(F))
+    torch.cuda.synchronize()
+    ref_l, ref_g = [], []
+    for k, m in enumerate(_models(params, n, widths, K, resnet)):
+        sc = O.dropout_scales(B, widths, drop, 99, 0, k) if drop else None
+        l_, g_ = O.train_loss_grad(m, s, F, sc, mask if raw else None)
+        ref_l.append(l_)
+        ref_g.append(O.flat_grad(g_))
+    gerr = _err(grad.cpu().numpy().reshape(K, -1).astype(np.float64), np.stack(ref_g))
+    lerr = np.abs(loss.cpu().numpy() / np.array(ref_l) - 1.0).max()
+    print(f"n={n} {widths} K={K} B={B} res={resnet} raw={raw} drop={drop}: "
+          f"grad {gerr:.2e} loss {lerr:.2e}", flush=True)
+    assert gerr <= GRAD_TOL and lerr <= 1e-5
+
+
+@pytest.mark.parametrize("factor", [2.0 ** 50, 2.0 ** -50])
+@pytest.mark.parametrize("widths,resnet", [([96] * 4, False), ([300] * 3, True)])
+def test_upstream_gradient_far_from_one(torch, rid, factor, widths, resnet):
+    """The vector-Jacobian product is linear in the upstream gradient."""
+    n, K, B = 10, 2, 40
+    rng = np.random.default_rng(4)
+    s = ridgen.f32(rng.uniform(-np.pi, np.pi, (B, n)))
+    rho = ridgen.f32(rng.normal(size=(B, K, n)) * factor)
+    params = ridgen.xavier_ensemble(2 * n, widths, K, 70, bias_std=0.1)
+    E = rid.Ensemble(n, widths, K, params)
+    if resnet:
+        E.set_resnet(True)
+    grad = rid.mf_grad(E, torch.from_numpy(s).cuda(), torch.from_numpy(rho).cuda())
+    torch.cuda.synchronize()
+    ref = np.stack([O.flat_grad(O.mean_force_vjp(m, s, rho[:, k]))
+                    for k, m in enumerate(_models(params, n, widths, K, resnet))])
+    assert _err(grad.cpu().numpy().reshape(K, -1).astype(np.float64), ref) <= GRAD_TOL
+
+
+def test_strong_dropout(torch, rid):
+    """Kept units scaled by 50 stay inside the split products' range."""
+    n, widths, K, B, p = 8, [128] * 3, 2, 60, 0.98
+    s, F, _ = ridgen.mf_training_set(B, n)
+    params = ridgen.xavier_ensemble(2 * n, widths, K, 71, bias_std=0.1)
+    E = rid.Ensemble(n, widths, K, params)
+    E.set_dropout(p, 5)
+    loss, grad = rid.mf_loss_grad(E, torch.from_numpy(s).cuda(), torch.from_numpy(F).cuda())
+    torch.cuda.synchronize()
+    ref = [O.train_loss_grad(m, s, F, O.dropout_scales(B, widths, p, 5, 0, k))
+           for k, m in enumerate(_models(params, n, widths, K, False))]
+    assert _err(grad.cpu().numpy().reshape(K, -1).astype(np.float64),
+                np.stack([O.flat_grad(g) for _, g in ref])) <= GRAD_TOL
+    assert np.abs(loss.cpu().numpy() / np.array([l for l, _ in ref]) - 1.0).max() <= 1e-5
+
+
+# (residues, distances, widths, K, B, residual)
+@pytest.mark.parametrize("res,dist,widths,K,B,resnet", [
+    (2, 0, [64] * 2, 3, 17, False), (20, 0, [128] * 6, 2, 33, False), (20, 6, [192] * 3, 3, 40, False),
+    (20, 6, [256] * 4, 4, 47, True), (20, 0, [200] * 5, 2, 20, True), (10, 0, [300] * 4, 4, 30, True),
+    (10, 4, [384] * 2, 2, 16, False), (20, 0, [512] * 4, 2, 19, False), (40, 0, [64] * 3, 2, 21, False),
+    (10, 0, [512] * 3, 2, 18, True)])
+def test_conservative_force_at_tile_edges(torch, rid, res, dist, widths, K, B, resnet):
+    sys_ = ridgen.chain_system(res, 10)
+    if dist:
+        sys_ = ridgen.with_distances(sys_, dist)
+    n = sys_.n_cv
+    pos = ridgen.f32(ridgen.chain_coords(sys_, B, 31))
+    params = ridgen.xavier_ensemble(2 * n, widths, K, 41, bias_std=0.1)
+    models = _models(params, n, widths, K, resnet)
+    mask = sys_.mask if dist else None
+    eps = O.bias_force(pos.astype(np.float64), sys_.quads, models, 1e30, 2e30, mask=mask)["eps"]
+    e0, e1 = 0.5 * eps.min(), 2.0 * eps.max()
+    ref = O.bias_force_conservative(pos.astype(np.float64), sys_.quads, models, e0, e1, mask=mask)
+    S = rid.System(sys_.n_atoms, sys_.quads, mask)
+    E = rid.Ensemble(n, widths, K, params)
+    if resnet:
+        E.set_resnet(True)
+    if dist:
+        E.set_angular_mask(mask)
+    out = rid.bias_force(S, E, torch.from_numpy(pos).cuda(), float(e0), float(e1), conservative=True)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in out.items()}
+    bound = walker_bounds(got["eps"].astype(np.float64), ref["eps"], e0, e1)
+    assert_walkers(got["F"], ref["F"], bound, f"{res} residues {widths} res={resnet}")
+    assert np.abs(got["E"] - ref["E"]).max() <= FP32_TOL * max(1.0, np.abs(ref["E"]).max())
