@@ -13,18 +13,30 @@
 // d^2 <= t^2 is taken in FP32 with the squares summed in CV order,
 // contraction off, so the labels do not depend on the launch shape.
 //
-// GPU form of the sequential rule, exact: frames go in chunks.  A parallel
-// kernel compares every frame of the chunk with all leaders founded before
-// it (one wave per frame, lanes over leaders, first hit by ballot); a
-// single workgroup then resolves the chunk's unmatched frames in order
-// against the leaders founded inside the chunk (kept in LDS) and founds new
-// ones.  A frame's
-// first match among the earlier leaders is its first match overall, because
-// later leaders only append.  Chunks grow from 64 frames, so the first
-// leaders are found by the single wave over few frames and most frames are
-// then resolved by the parallel kernel.  With threshold adjustment, one pass
-// clusters up to kSlots thresholds side by side (blockIdx.y = slot, each with
-// its own workspace); select_core.h takes the rule's steps over their counts.
+// GPU form of the sequential rule, exact, in rounds over the frames that no
+// leader has matched yet (a bit each):
+//  * sel_walk_kernel, one workgroup: the first G unmatched frames (a thread
+//    and an LDS row each) are walked in order.  The first still unmatched one
+//    founds a cluster and all later ones are compared with it at once; then
+//    the next one founds, until none is left.
+//  * sel_match_kernel, all CUs: every other unmatched frame (all of them come
+//    later than the window) is compared with the round's new leaders in
+//    founding order, up to the first within the threshold.
+// A frame therefore meets all leaders founded before it, in founding order,
+// and founds exactly when none is within the threshold.  Frames of known
+// clusters leave the mask after one round, so the windows hold mostly frames
+// of new ones, and a call takes a few rounds whatever its length.  A founding
+// costs one barrier and one distance (about 1 us), a round about 25 us beside
+// its foundings; the rounds, not the distances, bound the call.  With
+// threshold adjustment, one pass clusters up to kSlots thresholds side by
+// side (blockIdx.y = slot, each with its own workspace); select_core.h takes
+// the rule's steps over their counts.  20 000 frames of 38 CVs, 24 thresholds, cap 51: a pass took
+// 1.67 ms when windows were runs of consecutive frames, 64 to 8192 long,
+// matched by the walking workgroup itself, and takes 0.36 ms now (six rounds,
+// walks 26-43 us, matches 5-37 us; with two LDS reads per CV and leader and
+// without the limit on a round's foundings 0.66 ms).
+#include <climits>
+
 #include "device_common.h"
 #include "select_core.h"
 
@@ -33,13 +45,13 @@ namespace {
 
 using namespace dev;
 
-constexpr int kPending = -3;       // unmatched after the parallel pass
 constexpr int kFiltered = -2;      // eps below eps0
 constexpr int kOverCap = -1;       // would found a cluster past the cap
-constexpr int kMatchWaves = 4;
-constexpr int kMaxSelCv = 256;
-constexpr int kChunkMax = 8192;
-constexpr int kLdsRows = 16384;    // floats for the new leaders, and again for a frame group
+constexpr int kWalkThreads = 1024; // frames of a window, at most
+constexpr int kWalkWaves = kWalkThreads / kWave;
+constexpr size_t kTileBytes = 144 * 1024;   // LDS for the frames' CVs
+constexpr int kMatchWaves = 4;     // 64-frame words per workgroup, at most
+constexpr int kLeadRows = 16;      // leaders staged in LDS at a time
 constexpr int kSlots = 24;         // thresholds clustered side by side in one pass
 static_assert(kSlots <= selcore::kMaxSlots, "slot count");
 
@@ -47,30 +59,38 @@ struct ClusterArgs {
   const float* s;        // [B][n] frames
   const float* eps;      // [B] or null (no filter)
   float eps0, t2;
-  int B, n, cap, chunk;
-  float* LT;             // [n][cap] leaders' CVs, CV-major
+  int B, n, cap, words;
+  float* LR;             // [cap][n] leaders' CVs
   int* leader;           // [cap] frame index of each leader
-  int* state;            // [0] leaders so far, [1] next frame, [2] over the cap
+  int* state;            // kState* below
   int* labels;           // [B]
   unsigned long long* pend;   // [ceil(B/64)] bit f%64 of word f/64: frame f unmatched
   const uint8_t* raw;    // [n] or null: CVs with raw[i] = 1 are not periodic
   const float* w;        // [n] or null: per-CV weights of the squared differences
 };
+enum {
+  kLeaders = 0,          // leaders so far
+  kDone = 1,             // 1: every frame is labelled once this round ends
+  kOver = 2,             // some frame would have founded past the cap
+  kNew = 3,              // first leader of the current round
+  kWord = 4,             // mask words before this one are empty
+  kStateInts = 8         // ints of state per slot
+};
+constexpr int kAbandoned = 2;      // kDone: more leaders than the window allows
 
 // Thresholds clustered in one pass: slot k (blockIdx.y) clusters at t2[k]
 // into its own workspace, the pointers above advanced by k strides.
 struct ClusterSlots {
   float t2[kSlots];
-  long long sLT, sLabels;   // floats of LT, ints of labels per slot (labels: 0 with one slot)
+  long long sLR, sLabels;   // floats of LR, ints of labels per slot (labels: 0 with one slot)
   int sLeader, sPend;       // ints of leader, words of pend per slot
 };
-constexpr int kStateInts = 4;   // ints of state per slot
 
 __device__ inline ClusterArgs slot_args(const ClusterArgs& a0, const ClusterSlots& sl) {
   const int k = blockIdx.y;
   ClusterArgs a = a0;
   a.t2 = sl.t2[k];
-  a.LT += k * sl.sLT;
+  a.LR += k * sl.sLR;
   a.labels += k * sl.sLabels;
   a.leader += k * sl.sLeader;
   a.pend += (size_t)k * sl.sPend;
@@ -78,274 +98,321 @@ __device__ inline ClusterArgs slot_args(const ClusterArgs& a0, const ClusterSlot
   return a;
 }
 
-// Squared distance leader - frame with non-periodic CVs (raw non-null:
-// raw[i] = 1 leaves the difference unwrapped) and/or per-CV weights (w
-// non-null: each square is multiplied by w[i] before it is added);
-// otherwise as leader_d2.
-__device__ inline float leader_d2_general(const float* lead, long long ls, const float* x, int n,
-                                          const uint8_t* raw, const float* w) {
+// Whether a leader lies within t2 of the lane's frame: FP32, differences
+// wrapped to (-pi, pi] unless raw[i], squares weighted by w[i] where w is
+// given, summed in CV order, no fused multiply-add.  The wrapped difference
+// enters as its magnitude, min(|d|, ||d| - 2 pi|): the same value as
+// subtracting or adding 2 pi outside (-pi, pi] (2 pi is twice the FP32 pi, so
+// the two meet exactly at |d| = pi), in three operations instead of seven.
+// The sum only grows, so a wave stops once no active lane is within t2 (a
+// NaN never is).
+constexpr float kTwoPi = 6.28318530717959f;
+__device__ inline float add_square(float acc, float lead, float x) {
 #pragma clang fp contract(off)
-  constexpr float kPi = 3.14159265358979f;
-  constexpr float kTwoPi = 6.28318530717959f;
+  const float d = lead - x;
+  const float m = __builtin_fminf(__builtin_fabsf(d), __builtin_fabsf(__builtin_fabsf(d) - kTwoPi));
+  const float sq = m * m;
+  return acc + sq;
+}
+
+// Any CV count and metric, both rows in memory (lead the same for every lane).
+__device__ inline bool within_rows(const float* lead, const float* x, const ClusterArgs& a) {
+#pragma clang fp contract(off)
+  const int n = a.n;
   float acc = 0.f;
-  for (int i = 0; i < n; ++i) {
-    float d = lead[i * ls] - x[i];
-    if (!raw || !raw[i]) {
-      if (d > kPi) d = d - kTwoPi;
-      if (d <= -kPi) d = d + kTwoPi;
+  auto add = [&](int i) {
+    if (!a.raw && !a.w) {
+      acc = add_square(acc, lead[i], x[i]);
+      return;
     }
+    float d = __builtin_fabsf(lead[i] - x[i]);
+    if (!a.raw || !a.raw[i]) d = __builtin_fminf(d, __builtin_fabsf(d - kTwoPi));
     float sq = d * d;
-    if (w) sq = sq * w[i];
+    if (a.w) sq = sq * a.w[i];
     acc = acc + sq;
+  };
+  int i = 0;
+  for (; i + 8 <= n; i += 8) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) add(i + j);
+    if (!__any(acc <= a.t2)) return false;
   }
-  return acc;
+  for (; i < n; ++i) add(i);
+  return acc <= a.t2;
 }
 
-// Squared periodic distance leader - frame, the leader's CV i at lead[i * ls],
-// the frame's at x[i]; FP32, CV order, no fused multiply-add.
-__device__ inline float leader_d2(const float* lead, long long ls, const float* x, int n,
-                                  const uint8_t* raw, const float* w) {
-#pragma clang fp contract(off)
-  if (raw || w) return leader_d2_general(lead, ls, x, n, raw, w);
-  constexpr float kPi = 3.14159265358979f;
-  constexpr float kTwoPi = 6.28318530717959f;
-  float acc = 0.f;
-#pragma unroll 8
-  for (int i = 0; i < n; ++i) {   // unrolled: loads issue ahead, sum order unchanged
-    float d = lead[i * ls] - x[i];
-    if (d > kPi) d = d - kTwoPi;
-    if (d <= -kPi) d = d + kTwoPi;
-    acc = acc + d * d;
+// The lane's frame as the comparisons take it.  NV > 0: up to 8 NV CVs of the
+// plain metric in registers, zero past the last CV (zero differences add
+// nothing), the leader's row read 16 bytes at a time (one LDS access for the
+// wave): the row form's two LDS reads a CV bound both kernels.  NV = 0: rows.
+typedef float f4 __attribute__((ext_vector_type(4)));
+template <int NV>
+struct FrameCv {
+  float x[8 * NV];
+  __device__ inline void load(const float* row) {
+#pragma unroll
+    for (int i = 0; i < 2 * NV; ++i) {
+      const f4 v = *reinterpret_cast<const f4*>(row + 4 * i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * i + j] = v[j];
+    }
   }
-  return acc;
+  __device__ inline bool within(const float* lead, const ClusterArgs& a) const {
+    float acc = 0.f;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const f4 l0 = *reinterpret_cast<const f4*>(lead + 8 * v);
+      const f4 l1 = *reinterpret_cast<const f4*>(lead + 8 * v + 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = add_square(acc, l0[j], x[8 * v + j]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = add_square(acc, l1[j], x[8 * v + 4 + j]);
+      if (v + 1 < NV && !__any(acc <= a.t2)) return false;
+    }
+    return acc <= a.t2;
+  }
+};
+template <>
+struct FrameCv<0> {
+  const float* row;
+  __device__ inline void load(const float* r) { row = r; }
+  __device__ inline bool within(const float* lead, const ClusterArgs& a) const {
+    return within_rows(lead, row, a);
+  }
+};
+// Row stride (floats) of a frame in LDS.  NV = 0: odd, so that lanes on
+// consecutive rows fall into different banks.
+__host__ __device__ inline int frame_stride(int n, int NV) { return NV ? 8 * NV : n | 1; }
+
+// The mask of the kept frames, the labels of the others, the state.
+__global__ __launch_bounds__(256) void sel_init_kernel(ClusterArgs a0, ClusterSlots sl) {
+  const ClusterArgs a = slot_args(a0, sl);
+  const int lane = threadIdx.x % kWave;
+  const int w = blockIdx.x * 4 + threadIdx.x / kWave;
+  if (blockIdx.x == 0 && threadIdx.x < kStateInts) a.state[threadIdx.x] = 0;
+  if (w >= a.words) return;
+  const int f = w * 64 + lane;
+  const bool in = f < a.B;
+  const bool keep = in && (!a.eps || a.eps[f] >= a.eps0);
+  const unsigned long long m = __ballot(keep);
+  if (lane == 0) a.pend[w] = m;
+  if (in && !keep) a.labels[f] = kFiltered;
 }
 
-__global__ void sel_init_kernel(int* state, unsigned long long* pend, int words) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  state += blockIdx.y * kStateInts;
-  pend += (size_t)blockIdx.y * words;
-  if (t < 3) state[t] = 0;
-  for (int w = t; w < words; w += gridDim.x * blockDim.x) pend[w] = 0ull;
+// One round's walk (see the head of the file), at most max_new foundings:
+// the frames still unmatched then go back into the mask.  A slot with more
+// than `enough` leaders is abandoned (done, its labels incomplete).  LDS: the
+// window's frames [G][stride], their indices [G].
+template <int NV>
+__global__ __launch_bounds__(kWalkThreads) void sel_walk_kernel(ClusterArgs a0, ClusterSlots sl,
+                                                                int G, int max_new, int enough) {
+  const ClusterArgs a = slot_args(a0, sl);
+  extern __shared__ __attribute__((aligned(16))) float tile[];
+  __shared__ int wsum[kWalkWaves], firsts[2][kWalkWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int n = a.n, st = frame_stride(n, NV);
+  int* list = reinterpret_cast<int*>(tile + (size_t)G * st);
+  const int n_start = a.state[kLeaders];
+  if (a.state[kDone]) {
+    if (tid == 0) a.state[kNew] = n_start;
+    return;
+  }
+  // the first G unmatched frames: a thread per mask word, ranks by a prefix
+  // sum; words are cleared of the bits taken
+  int g = 0, w0 = a.state[kWord];
+  bool rest = false;                        // unmatched frames beyond the window
+  for (; w0 < a.words && !rest; w0 += kWalkThreads) {
+    const int w = w0 + tid;
+    unsigned long long m = w < a.words ? a.pend[w] : 0ull;
+    const int cnt = __popcll(m);
+    int scan = cnt;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int v = __shfl_up(scan, o);
+      if (lane >= o) scan += v;
+    }
+    if (lane == kWave - 1) wsum[wave] = scan;
+    __syncthreads();
+    int base = g, tot = 0;
+    for (int q = 0; q < kWalkWaves; ++q) {
+      if (q < wave) base += wsum[q];
+      tot += wsum[q];
+    }
+    int rank = base + scan - cnt;
+    const unsigned long long m0 = m;
+    for (; m && rank < G; ++rank) {
+      const int b = __ffsll((long long)m) - 1;
+      m &= m - 1;
+      list[rank] = w * 64 + b;
+    }
+    if (m != m0) a.pend[w] = m;
+    g = min(G, g + tot);
+    // everything up to here is taken unless the window is full
+    rest = __syncthreads_or(m != 0ull);
+  }
+  // (the last batch may hold words with bits left: the next round starts there)
+  const int w_next = rest ? w0 - kWalkThreads : a.words;
+  // a full window may leave whole words unread behind it
+  const bool last = !rest && w0 >= a.words;
+  // the window's CVs, kBatch loads in flight per thread (element e = q n + i
+  // stepped by the thread count without divisions; past the end, q is clamped
+  // to the last frame and the value is not stored)
+  constexpr int kBatch = 16;
+  const int tot = g * n, dq = kWalkThreads / n, di = kWalkThreads % n;
+  for (int e0 = 0; e0 < tot; e0 += kBatch * kWalkThreads) {
+    int q = (e0 + tid) / n, i = (e0 + tid) - q * n;
+    float v[kBatch];
+    int o[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      v[j] = a.s[(size_t)list[min(q, g - 1)] * n + i];
+      o[j] = q < g ? q * st + i : -1;
+      q += dq;
+      i += di;
+      if (i >= n) {
+        i -= n;
+        ++q;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (o[j] >= 0) tile[o[j]] = v[j];
+  }
+  if (NV > 0)
+    for (int e = tid; e < g * (st - n); e += kWalkThreads)
+      tile[(size_t)(e / (st - n)) * st + n + e % (st - n)] = 0.f;
+  __syncthreads();
+  // the ordered walk
+  FrameCv<NV> fr;
+  fr.load(tile + (size_t)min(tid, max(g - 1, 0)) * st);
+  int label = tid < g ? -2 : 0;             // -2: not matched yet
+  int n_new = 0, over = 0;
+  for (int it = 0;; ++it) {
+    const unsigned long long m = __ballot(label == -2);
+    if (lane == 0)
+      firsts[it & 1][wave] = m ? wave * kWave + __ffsll((long long)m) - 1 : kWalkThreads;
+    __syncthreads();
+    int first = kWalkThreads;
+#pragma unroll
+    for (int q = 0; q < kWalkWaves; ++q) first = min(first, firsts[it & 1][q]);
+    if (first == kWalkThreads) break;
+    const int out = n_start + n_new;
+    if (out >= a.cap) {                     // no room: what is left is over the cap
+      if (label == -2) label = kOverCap;
+      over = 1;
+      break;
+    }
+    const float* xl = tile + (size_t)first * st;
+    for (int i = tid; i < n; i += kWalkThreads) a.LR[(size_t)out * n + i] = xl[i];
+    if (tid == first) {
+      label = out;
+      a.leader[out] = list[first];
+    }
+    if (label == -2 && fr.within(xl, a)) label = out;
+    if (++n_new == max_new) break;
+  }
+  // (the mask words of the window were stored before the barriers above)
+  const bool back = tid < g && label == -2;
+  if (back) atomicOr(&a.pend[list[tid] >> 6], 1ull << (list[tid] & 63));
+  else if (tid < g) a.labels[list[tid]] = label;
+  const bool all = !__syncthreads_or(back);
+  if (tid == 0) {
+    a.state[kLeaders] = n_start + n_new;
+    a.state[kNew] = n_start;
+    a.state[kWord] = all ? w_next : list[0] >> 6;
+    if (over) a.state[kOver] = 1;
+    // a full cap: the match kernel of this round labels every frame left
+    const int now = n_start + n_new;
+    a.state[kDone] = now > enough ? kAbandoned : (last && all) || now >= a.cap;
+  }
 }
 
-// Frames [f_next, f_next + chunk): filtered, matched to the first earlier
-// leader within the threshold, over the cap (no match and no room for a new
-// cluster), or marked unmatched in the bit mask.
+// One round's matching: a wave per mask word, a lane per frame, the round's
+// leaders staged in LDS kLeadRows at a time.  LDS: leaders
+// [kLeadRows][stride], then each wave's frames [64][stride].
+template <int NV>
 __global__ __launch_bounds__(kMatchWaves * kWave) void sel_match_kernel(ClusterArgs a0,
                                                                         ClusterSlots sl) {
   const ClusterArgs a = slot_args(a0, sl);
-  __shared__ float xs[kMatchWaves][kMaxSelCv];
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int f0 = a.state[1];
-  const int f = f0 + blockIdx.x * kMatchWaves + wave;
-  if (f >= min(a.B, f0 + a.chunk)) return;
-  if (a.eps && !(a.eps[f] >= a.eps0)) {
-    if (lane == 0) a.labels[f] = kFiltered;
-    return;
-  }
-  const int n = a.n;
-  for (int i = lane; i < n; i += kWave) xs[wave][i] = a.s[(size_t)f * n + i];
-  __builtin_amdgcn_wave_barrier();
-  const int nl = a.state[0];
-  int lab = kPending;
-  for (int j0 = 0; j0 < nl; j0 += kWave) {
-    const int j = j0 + lane;
-    const bool hit = j < nl && leader_d2(a.LT + j, a.cap, xs[wave], n, a.raw, a.w) <= a.t2;
-    const unsigned long long m = __ballot(hit);
-    if (m) {
-      lab = j0 + __ffsll((long long)m) - 1;
-      break;
+  extern __shared__ __attribute__((aligned(16))) float tile[];
+  const int nt = blockDim.x, tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int n = a.n, st = frame_stride(n, NV);
+  const int w = blockIdx.x * (nt / kWave) + wave;
+  const int l0 = a.state[kNew], l1 = a.state[kLeaders];
+  if (a.state[kDone] == kAbandoned) return;
+  const bool full = l1 >= a.cap;
+  const unsigned long long m0 = w < a.words ? a.pend[w] : 0ull;
+  if (!__syncthreads_or(m0 != 0ull && (l1 > l0 || full))) return;
+  float* lead = tile;
+  float* fr = tile + (size_t)(kLeadRows + wave * kWave) * st;
+  // the word's frames: all 64 rows are one stretch of memory (rows past B are
+  // not read), eight loads in flight per lane
+  if (m0 && l1 > l0) {
+    const int rows = min(64, a.B - w * 64), tot = rows * n;
+    const float* src = a.s + (size_t)w * 64 * n;
+    const int dq = kWave / n, di = kWave % n;
+    for (int e0 = 0; e0 < tot; e0 += 8 * kWave) {
+      int q = (e0 + lane) / n, i = (e0 + lane) - q * n;
+      float v[8];
+      int o[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int e = e0 + j * kWave + lane;
+        v[j] = src[min(e, tot - 1)];
+        o[j] = e < tot ? q * st + i : -1;
+        q += dq;
+        i += di;
+        if (i >= n) {
+          i -= n;
+          ++q;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (o[j] >= 0) fr[o[j]] = v[j];
     }
   }
-  if (lane == 0) {
-    if (lab == kPending && nl >= a.cap) {   // the cap is full: nothing left to found
-      lab = kOverCap;
-      a.state[2] = 1;
+  if (NV > 0 && m0 && l1 > l0)
+    for (int e = lane; e < kWave * (st - n); e += kWave)
+      fr[(e / (st - n)) * st + n + e % (st - n)] = 0.f;
+  bool open = (m0 >> lane) & 1ull;
+  int label = kOverCap;
+  FrameCv<NV> x;
+  for (int j0 = l0; j0 < l1; j0 += kLeadRows) {
+    const int rows = min(kLeadRows, l1 - j0);
+    __syncthreads();                         // the frames, and the last leaders' readers
+    for (int e = tid; e < rows * st; e += nt) {
+      const int r = e / st, i = e - r * st;
+      lead[e] = i < n ? a.LR[(size_t)(j0 + r) * n + i] : 0.f;
     }
-    a.labels[f] = lab;
-    if (lab == kPending) atomicOr(&a.pend[f >> 6], 1ull << (f & 63));
+    if (j0 == l0) x.load(fr + lane * st);
+    __syncthreads();
+    for (int j = 0; j < rows; ++j)
+      if (open && x.within(lead + j * st, a)) {
+        label = j0 + j;
+        open = false;
+      }
+  }
+  const unsigned long long left = __ballot(open);
+  const int f = w * 64 + lane;
+  if (((m0 >> lane) & 1ull) && (!open || full)) a.labels[f] = label;
+  if (lane == 0 && m0) {
+    a.pend[w] = full ? 0ull : left;
+    if (full && left) a.state[kOver] = 1;
   }
 }
 
-// The chunk's unmatched frames, in order, against the leaders founded in
-// this chunk (LDS, nlmax at most); new leaders are founded here.  The chunk's
-// mask words come in one batch of loads, the unmatched frames' CVs in groups
-// of up to gmax frames.  Per group, each thread first matches a frame
-// against the chunk's leaders founded before the group (its first match
-// overall if any, since later leaders only append); the walk then founds a
-// leader at the first frame still unmatched, after which the rest of the
-// group is matched in parallel against that leader before the walk
-// resumes, so every frame meets the leaders founded before it in founding
-// order.  If the cap is full or the LDS holds nlmax new leaders when
-// another is due, the walk stops at that frame and the next chunk starts
-// there.  The mask words read are cleared for the next round.
-constexpr int kResolveWaves = 4;
-constexpr int kXbBatch = 16;
-__global__ __launch_bounds__(kResolveWaves * kWave) void sel_resolve_kernel(ClusterArgs a0,
-                                                                            ClusterSlots sl,
-                                                                            int nlmax, int gmax) {
-  const ClusterArgs a = slot_args(a0, sl);
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int sh[6];   // new leaders so far, stop frame, over the cap, walk start,
-                          // end of the matched run, the frame founding a leader
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int f0 = a.state[1];
-  if (f0 >= a.B) return;
-  const int n = a.n;
-  const int f_end = min(a.B, f0 + a.chunk);
-  const int n_start = a.state[0];
-  const int w0 = f0 >> 6, w1 = (f_end - 1) >> 6;     // mask words of the chunk
-  const int nw = w1 - w0 + 1;                         // <= kChunkMax / 64 + 1
-  unsigned long long* pm = reinterpret_cast<unsigned long long*>(smem);   // [nw]
-  int* grp = reinterpret_cast<int*>(pm + (kChunkMax / 64 + 2));          // [gmax]
-  int* gm = grp + gmax;                                                  // [gmax]
-  float* NL = reinterpret_cast<float*>(gm + gmax);                      // [nlmax][n]
-  float* XB = NL + (size_t)nlmax * n;                                    // [gmax][n]
-  for (int w = tid; w < nw; w += kResolveWaves * kWave) {
-    unsigned long long m = a.pend[w0 + w];
-    const int lo = (w0 + w) << 6;
-    if (lo < f0) m &= ~0ull << (f0 - lo);                   // frames before the chunk
-    if (lo + 64 > f_end) m &= (f_end - lo >= 64) ? ~0ull : ((1ull << (f_end - lo)) - 1ull);
-    pm[w] = m;
-    a.pend[w0 + w] = 0ull;
-  }
-  if (tid == 0) {
-    sh[0] = 0;
-    sh[1] = f_end;
-    sh[2] = a.state[2];
-  }
-  __syncthreads();
-  // every thread walks the mask words identically
-  int wi = 0;
-  unsigned long long cur = pm[0];
-  for (;;) {
-    const int n_new0 = sh[0];
-    if (sh[1] != f_end) break;
-    int g = 0;
-    while (g < gmax) {
-      while (cur == 0ull && wi + 1 < nw) cur = pm[++wi];
-      if (cur == 0ull) break;
-      const int b = __ffsll((long long)cur) - 1;
-      cur &= cur - 1;
-      if (tid == 0) grp[g] = ((w0 + wi) << 6) + b;
-      ++g;
-    }
-    if (g == 0) break;
-    __syncthreads();
-    // the group's CVs into LDS, kXbBatch loads in flight per thread (element
-    // e = q n + i stepped by the thread count without divisions; past the
-    // end, q is clamped to the last frame and the value is not stored)
-    {
-      constexpr int kNT = kResolveWaves * kWave;
-      const int tot = g * n, dq = kNT / n, di = kNT % n;
-      for (int e0 = 0; e0 < tot; e0 += kXbBatch * kNT) {
-        int q = (e0 + tid) / n, i = (e0 + tid) - q * n;
-        float v[kXbBatch];
-#pragma unroll
-        for (int j = 0; j < kXbBatch; ++j) {
-          v[j] = a.s[(size_t)grp[min(q, g - 1)] * n + i];
-          q += dq;
-          i += di;
-          if (i >= n) {
-            i -= n;
-            ++q;
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < kXbBatch; ++j) {
-          const int e = e0 + tid + j * kNT;
-          if (e < tot) XB[e] = v[j];
-        }
-      }
-    }
-    __syncthreads();
-    // a thread per frame, the chunk's leaders in founding order up to the
-    // first within the threshold (few leaders: lanes over them would idle)
-    for (int q = tid; q < g; q += kResolveWaves * kWave) {
-      int hitj = -1;
-      for (int j = 0; j < n_new0; ++j)
-        if (leader_d2(NL + (size_t)j * n, 1, XB + (size_t)q * n, n, a.raw, a.w) <= a.t2) {
-          hitj = j;
-          break;
-        }
-      gm[q] = hitj;
-    }
-    __syncthreads();
-    // ordered walk: wave 0 finds the first frame at or after the walk's
-    // start that no leader matches (a ballot per 64 frames); the frames
-    // before it are labelled in parallel, and it founds a leader, after
-    // which the rest of the group is matched in parallel against that
-    // leader before the walk goes on.  With no room for another leader
-    // (the cap is full, or this launch's LDS rows are) the walk stops at
-    // that frame instead, and the next round starts there: its match kernel
-    // then labels every remaining frame against all leaders, in parallel.
-    int start = 0;
-    for (;;) {
-      if (wave == 0) {
-        int first = g;
-        for (int q0 = start; q0 < g; q0 += kWave) {
-          const int q = q0 + lane;
-          const unsigned long long m = __ballot(q < g && gm[q] < 0);
-          if (m) {
-            first = q0 + __ffsll((long long)m) - 1;
-            break;
-          }
-        }
-        if (lane == 0) {
-          const int n_new = sh[0];
-          int next = g, lead = -1;
-          if (first < g) {
-            if (n_start + n_new >= a.cap || n_new >= nlmax) {
-              sh[1] = grp[first];
-              next = first;
-            } else {
-              lead = first;
-              next = first + 1;
-              sh[0] = n_new + 1;
-            }
-          }
-          sh[3] = next;
-          sh[4] = first;
-          sh[5] = lead;
-        }
-      }
-      __syncthreads();
-      const int mend = sh[4], lead = sh[5], jn = sh[0] - 1;
-      for (int q = start + tid; q < mend; q += kResolveWaves * kWave)
-        a.labels[grp[q]] = n_start + gm[q];
-      if (lead >= 0) {
-        const int out = n_start + jn;
-        const float* xl = XB + (size_t)lead * n;
-        for (int i = tid; i < n; i += kResolveWaves * kWave) {
-          NL[(size_t)jn * n + i] = xl[i];
-          a.LT[(size_t)i * a.cap + out] = xl[i];
-        }
-        if (tid == 0) {
-          a.leader[out] = grp[lead];
-          a.labels[grp[lead]] = out;
-        }
-      }
-      start = sh[3];
-      if (sh[1] != f_end || start >= g) break;
-      // (the new leader's CVs are read from the group tile, where they are
-      // already in place for every thread)
-      const float* xl = XB + (size_t)lead * n;
-      for (int q = start + tid; q < g; q += kResolveWaves * kWave)
-        if (gm[q] < 0 && leader_d2(xl, 1, XB + (size_t)q * n, n, a.raw, a.w) <= a.t2) gm[q] = jn;
-      __syncthreads();
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    a.state[0] = n_start + sh[0];
-    a.state[1] = sh[1];
-    a.state[2] = sh[2];
-  }
+// Frames of a walk's window.
+int walk_frames(int n, int NV) {
+  const int g = (int)(kTileBytes / (sizeof(float) * frame_stride(n, NV) + sizeof(int)));
+  return std::min(kWalkThreads, g / kWave * kWave);
 }
-
-size_t resolve_lds(int n, int nlmax, int gmax) {
-  return sizeof(unsigned long long) * (kChunkMax / 64 + 2) + 2 * sizeof(int) * (size_t)gmax +
-         sizeof(float) * ((size_t)nlmax + gmax) * n;
+size_t walk_lds(int n, int NV, int G) {
+  return (size_t)G * (sizeof(float) * frame_stride(n, NV) + sizeof(int));
+}
+size_t match_lds(int n, int NV, int waves) {
+  return sizeof(float) * (size_t)(kLeadRows + waves * kWave) * frame_stride(n, NV);
 }
 
 // Device memory of one clustering call (one allocation): `slots` copies of
@@ -359,47 +426,63 @@ struct ClusterWs {
 };
 
 // One clustering pass at thresholds t[0..T) side by side (slot k at t[k]);
-// synchronises the stream.  On return st_h[k * kStateInts + 0..2] = {leaders,
-// next frame, over the cap} of slot k.
-rid_status cluster_pass(ClusterArgs a, ClusterSlots sl, const float* t, int T, int nlmax,
-                        int gmax, hipStream_t st, int* st_h) {
-  for (int k = 0; k < T; ++k) sl.t2[k] = t[k] * t[k];
-  const int words = (a.B + 63) / 64;
-  hipLaunchKernelGGL(sel_init_kernel, dim3(std::min((words + 255) / 256 + 1, 1024), T), dim3(256),
-                     0, st, a.state, a.pend, words);
-  RID_HIP(hipGetLastError());
-  const size_t lds = resolve_lds(a.n, nlmax, gmax);
-  static size_t attr = 0;
-  if (lds > 64 * 1024 && lds > attr) {
-    RID_HIP(hipFuncSetAttribute((const void*)sel_resolve_kernel,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = lds;
+// synchronises the stream.  On return st_h[k * kStateInts ...] is the state of
+// slot k.  enough: slots with more leaders are abandoned.  Rounds are launched
+// kRounds at a time: the first ones take most calls to the end, and a look at
+// the state costs more than two idle rounds.
+constexpr int kRounds = 8;
+template <int NV>
+rid_status cluster_pass_nv(const ClusterArgs& a, const ClusterSlots& sl, int T, int enough,
+                           hipStream_t st, int* st_h) {
+  const int G = walk_frames(a.n, NV);
+  const size_t wlds = walk_lds(a.n, NV, G);
+  int mw = kMatchWaves;
+  while (match_lds(a.n, NV, mw) > 150 * 1024) --mw;
+  const size_t mlds = match_lds(a.n, NV, mw);
+  static size_t attr[2] = {0, 0};
+  if (wlds > 64 * 1024 && wlds > attr[0]) {
+    RID_HIP(hipFuncSetAttribute((const void*)sel_walk_kernel<NV>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)wlds));
+    attr[0] = wlds;
   }
-  // rounds: chunks growing from 64 frames until they cover B, then one full
-  // chunk per possible stop: one per nlmax leaders founded (a launch's LDS
-  // rows), one where the cap fills, and one more
-  long long covered = 0;
-  int c = 64;
-  std::vector<int> chunks;
-  while (covered < a.B) {
-    chunks.push_back(c);
-    covered += c;
-    c = std::min(2 * c, kChunkMax);
+  if (mlds > 64 * 1024 && mlds > attr[1]) {
+    RID_HIP(hipFuncSetAttribute((const void*)sel_match_kernel<NV>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds));
+    attr[1] = mlds;
   }
-  const int stops = (a.cap + nlmax - 1) / nlmax;
-  for (int i = 0; i <= stops + 1; ++i) chunks.push_back(kChunkMax);
-  for (int ch : chunks) {
-    a.chunk = ch;
-    hipLaunchKernelGGL(sel_match_kernel, dim3((ch + kMatchWaves - 1) / kMatchWaves, T),
-                       dim3(kMatchWaves * kWave), 0, st, a, sl);
-    RID_HIP(hipGetLastError());
-    hipLaunchKernelGGL(sel_resolve_kernel, dim3(1, T), dim3(kResolveWaves * kWave), (uint32_t)lds,
-                       st, a, sl, nlmax, gmax);
-    RID_HIP(hipGetLastError());
+  // side by side, a round lasts as long as its slot with the most foundings:
+  // a quarter of the cap each (the slots with few need several rounds anyway)
+  const int max_new = T > 1 ? std::max(16, (a.cap + 3) / 4) : kWalkThreads;
+  // a round labels a whole window or founds max_new clusters
+  const long long most = (a.B + G - 1) / G + a.cap / max_new + 1;
+  for (long long r = 0; r < most;) {
+    for (int i = 0; i < kRounds && r < most; ++i, ++r) {
+      hipLaunchKernelGGL(sel_walk_kernel<NV>, dim3(1, T), dim3(kWalkThreads), (uint32_t)wlds, st, a,
+                         sl, G, max_new, enough);
+      RID_HIP(hipGetLastError());
+      hipLaunchKernelGGL(sel_match_kernel<NV>, dim3((a.words + mw - 1) / mw, T), dim3(mw * kWave),
+                         (uint32_t)mlds, st, a, sl);
+      RID_HIP(hipGetLastError());
+    }
+    RID_HIP(hipMemcpyAsync(st_h, a.state, sizeof(int) * kStateInts * T, hipMemcpyDeviceToHost, st));
+    RID_HIP(hipStreamSynchronize(st));
+    bool done = true;
+    for (int k = 0; k < T; ++k) done = done && st_h[k * kStateInts + kDone];
+    if (done) break;
   }
-  RID_HIP(hipMemcpyAsync(st_h, a.state, sizeof(int) * kStateInts * T, hipMemcpyDeviceToHost, st));
-  RID_HIP(hipStreamSynchronize(st));
   return RID_OK;
+}
+
+rid_status cluster_pass(const ClusterArgs& a, ClusterSlots sl, const float* t, int T, int enough,
+                        hipStream_t st, int* st_h) {
+  for (int k = 0; k < T; ++k) sl.t2[k] = t[k] * t[k];
+  hipLaunchKernelGGL(sel_init_kernel, dim3((a.words + 3) / 4, T), dim3(256), 0, st, a, sl);
+  RID_HIP(hipGetLastError());
+  // registers hold up to 64 CVs of the plain metric
+  if (a.raw || a.w || a.n > 64) return cluster_pass_nv<0>(a, sl, T, enough, st, st_h);
+  if (a.n <= 16) return cluster_pass_nv<2>(a, sl, T, enough, st, st_h);
+  if (a.n <= 40) return cluster_pass_nv<5>(a, sl, T, enough, st, st_h);
+  return cluster_pass_nv<8>(a, sl, T, enough, st, st_h);
 }
 
 }  // namespace
@@ -413,22 +496,22 @@ rid_status launch_cluster(const float* s, int B, int n, const uint8_t* raw, cons
   // slots: one without adaptation; with it as many as fit in 256 MiB, at most kSlots
   const size_t per_slot = sizeof(float) * (size_t)n * cap + sizeof(int) * (size_t)cap +
                           sizeof(int) * (size_t)B + sizeof(unsigned long long) * words +
-                          sizeof(int) * kStateInts;
+                          sizeof(int) * 4;
   const int T = adapt ? (int)std::max<size_t>(1, std::min<size_t>(kSlots, (256u << 20) / per_slot))
                       : 1;
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-  const size_t b_lt = al(sizeof(float) * (size_t)n * cap * T), b_ld = al(sizeof(int) * (size_t)cap * T),
+  const size_t b_lr = al(sizeof(float) * (size_t)n * cap * T), b_ld = al(sizeof(int) * (size_t)cap * T),
                b_st = al(sizeof(int) * kStateInts * T),
                b_pd = al(sizeof(unsigned long long) * (size_t)words * T),
                b_lb = T > 1 ? al(sizeof(int) * (size_t)B * T) : 0;
   ClusterWs ws;
-  RID_HIP(hipMalloc(&ws.buf, b_lt + b_ld + b_st + b_pd + b_lb));
+  RID_HIP(hipMalloc(&ws.buf, b_lr + b_ld + b_st + b_pd + b_lb));
   unsigned char* wp = static_cast<unsigned char*>(ws.buf);
-  float* ws_LT = reinterpret_cast<float*>(wp);
-  int* ws_leader = reinterpret_cast<int*>(wp + b_lt);
-  int* ws_state = reinterpret_cast<int*>(wp + b_lt + b_ld);
-  unsigned long long* ws_pend = reinterpret_cast<unsigned long long*>(wp + b_lt + b_ld + b_st);
-  int* ws_labels = T > 1 ? reinterpret_cast<int*>(wp + b_lt + b_ld + b_st + b_pd) : nullptr;
+  float* ws_LR = reinterpret_cast<float*>(wp);
+  int* ws_leader = reinterpret_cast<int*>(wp + b_lr);
+  int* ws_state = reinterpret_cast<int*>(wp + b_lr + b_ld);
+  unsigned long long* ws_pend = reinterpret_cast<unsigned long long*>(wp + b_lr + b_ld + b_st);
+  int* ws_labels = T > 1 ? reinterpret_cast<int*>(wp + b_lr + b_ld + b_st + b_pd) : nullptr;
   ClusterArgs a{};
   a.s = s;
   a.raw = raw;
@@ -438,27 +521,28 @@ rid_status launch_cluster(const float* s, int B, int n, const uint8_t* raw, cons
   a.B = B;
   a.n = n;
   a.cap = cap;
-  a.LT = ws_LT;
+  a.words = words;
+  a.LR = ws_LR;
   a.leader = ws_leader;
   a.state = ws_state;
   a.labels = T > 1 ? ws_labels : labels;
   a.pend = ws_pend;
   ClusterSlots sl{};
-  sl.sLT = (long long)n * cap;
+  sl.sLR = (long long)n * cap;
   sl.sLabels = T > 1 ? B : 0;
   sl.sLeader = cap;
   sl.sPend = words;
-  const int nlmax = kLdsRows / n;                       // >= 64 for n <= 256
-  const int gmax = std::min(256, kLdsRows / n);
   // threshold adjustment (first iteration of the workflow), T thresholds
   // per pass (select_core.h)
   std::vector<int> st_h((size_t)kStateInts * T);
   auto pass = [&](const float* ts, int nts, int* counts) -> int {
-    const rid_status r = cluster_pass(a, sl, ts, nts, nlmax, gmax, st, st_h.data());
+    // a slot past the window needs its count no further: the rule goes on
+    const int enough = nts > 1 ? upper : INT_MAX;
+    const rid_status r = cluster_pass(a, sl, ts, nts, enough, st, st_h.data());
     if (r != RID_OK) return r;
     for (int j = 0; j < nts; ++j) {
       const int* sj = st_h.data() + (size_t)j * kStateInts;
-      counts[j] = sj[1] < B ? -1 : sj[0] + (sj[2] ? 1 : 0);
+      counts[j] = !sj[kDone] ? -1 : sj[kLeaders] + (sj[kOver] ? 1 : 0);
     }
     return 0;
   };
@@ -467,13 +551,22 @@ rid_status launch_cluster(const float* s, int B, int n, const uint8_t* raw, cons
   if (rr == selcore::kIncomplete)
     return fail(RID_EDEVICE, "clustering did not reach the last frame");
   if (rr != 0) return (rid_status)rr;
-  const int k = res.slot, count = res.count;
+  int k = res.slot, count = res.count;
   const float t = res.t;
+  if (st_h[(size_t)k * kStateInts + kDone] == kAbandoned) {
+    // the rule ran out of adjustments on a slot past the window: cluster its
+    // threshold alone, to the end
+    k = 0;
+    const rid_status r = cluster_pass(a, sl, &t, 1, INT_MAX, st, st_h.data());
+    if (r != RID_OK) return r;
+    if (!st_h[kDone]) return fail(RID_EDEVICE, "clustering did not reach the last frame");
+    count = st_h[kLeaders] + (st_h[kOver] ? 1 : 0);
+  }
   const int* sk = st_h.data() + (size_t)k * kStateInts;
   if (T > 1)
     RID_HIP(hipMemcpyAsync(labels, ws_labels + (size_t)k * B, sizeof(int) * (size_t)B,
                            hipMemcpyDeviceToDevice, st));
-  const int nl = std::min(sk[0], leaders_out);
+  const int nl = std::min(sk[kLeaders], leaders_out);
   if (leaders && nl > 0)
     RID_HIP(hipMemcpyAsync(leaders, ws_leader + (size_t)k * cap, sizeof(int) * (size_t)nl,
                            hipMemcpyDeviceToDevice, st));
