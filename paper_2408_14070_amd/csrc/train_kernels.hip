@@ -36,6 +36,7 @@
 // kernel (64x64 tiles, LDS double buffering, arbitrary strides, fused
 // epilogues); the weight-gradient GEMM (both forms) is split along the batch with a
 // fixed-order reduction, so the whole step is deterministic.
+#include "mlp_split.h"
 #include "device_common.h"
 
 namespace rid {
@@ -478,114 +479,10 @@ __global__ void adjoint_kernel(const float* Tl, const float* Dl, const float* Zd
   }
 }
 
-// Column sums out[k][j] = sum_b X[k][b][j] in two fixed-order stages.
-// Stage 1: block (column tile of 64, row chunk of kColRows, member); lanes
-// are columns (coalesced rows), the 4 waves take interleaved rows and are
-// combined in wave order -> part[chunk][k][j].
-constexpr int kColRows = 64;     // 4 row chunks per 256 rows: enough workgroups in flight
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const float* X, long long slab,
-                                                             int B, int w, float* part, int K) {
-  __shared__ float red[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  const int chunk = blockIdx.y, k = blockIdx.z;
-  const int r0 = chunk * kColRows, r1 = min(B, r0 + kColRows);
-  float acc = 0.f;
-  if (j < w) {
-    const float* p = X + k * slab + j;
-#pragma unroll 4
-    for (int b = r0 + wave; b < r1; b += 4) acc += p[(long long)b * w];
-  }
-  red[wave][lane] = acc;
-  __syncthreads();
-  if (wave == 0 && j < w)
-    part[((long long)chunk * K + k) * w + j] =
-        ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-}
-
-// Stage 2: out[k][j] = the chunk partials summed in chunk order, into the
-// gradient buffer at grad + k*per_model + dst_off + j (added to what it
-// holds when accumulate is set).  A block covers 64 outputs; each of its 4
-// waves sums a quarter of the chunks (in order) and the quarters are
-// combined in wave order.
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float* part, int chunks, int w,
-                                                           int K, float* grad,
-                                                           long long per_model, int dst_off,
-                                                           int accumulate) {
-  __shared__ float red[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int e = blockIdx.x * 64 + lane;     // output k*w + j
-  const int cq = (chunks + 3) / 4;
-  const int c0 = wave * cq, c1 = min(chunks, c0 + cq);
-  float acc = 0.f;
-  if (e < K * w) {
-#pragma unroll 4
-    for (int c = c0; c < c1; ++c) acc += part[(long long)c * K * w + e];
-  }
-  red[wave][lane] = acc;
-  __syncthreads();
-  if (wave == 0 && e < K * w) {
-    const int k = e / w, j = e - k * w;
-    const float v = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-    float* o = grad + k * per_model + dst_off + j;
-    *o = accumulate ? *o + v : v;
-  }
-}
-
-// dW[k] = sum over split-K slabs (fixed order) -> gradient buffer (added to
-// what it holds when accumulate is set); with bpart, also db[k] = the
-// slabs' bias partials bpart[s][k][out] summed in slab order, to b_off
-__global__ void splitk_reduce_kernel(const float* part, long long slab_s, int ks,
-                                     int out, int in, int K, float* grad,
-                                     long long per_model, int w_off, int accumulate,
-                                     const float* bpart, int b_off) {
-  const long long total = (long long)K * out * in;
-  const long long all = total + (bpart ? (long long)K * out : 0);
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < all;
-       e += (long long)gridDim.x * blockDim.x) {
-    float* o;
-    const float* src;
-    long long stride;
-    if (e < total) {
-      src = part + e;
-      stride = slab_s;
-      const int k = (int)(e / ((long long)out * in));
-      const long long r = e - (long long)k * out * in;
-      o = grad + k * per_model + w_off + r;
-    } else {
-      const long long eb = e - total;                 // k * out + j
-      src = bpart + eb;
-      stride = (long long)K * out;
-      const int k = (int)(eb / out);
-      o = grad + k * per_model + b_off + (eb - (long long)k * out);
-    }
-    // slabs added in order, eight loads in flight
-    float acc = 0.f;
-    int s = 0;
-    for (; s + 8 <= ks; s += 8) {
-      float v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = src[(s + j) * stride];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc += v[j];
-    }
-    for (; s < ks; ++s) acc += src[s * stride];
-    *o = accumulate ? *o + acc : acc;
-  }
-}
-
-// The step's last launch, one block per member k: the loss, the mean of the
-// member's per-row losses rows[k][0:B] (each thread adds its rows in row
-// order, eight loads in flight, then a fixed pairwise tree), and the output
-// bias's gradient set to zero (it never reaches grad_s A).
-__global__ __launch_bounds__(256) void train_finish_kernel(const float* rows, int B, float* loss,
-                                                           float* grad, long long per_model,
-                                                           int zero_off) {
-  __shared__ float red[256];
-  const int k = blockIdx.x;
-  if (threadIdx.x == 0 && grad) grad[k * per_model + zero_off] = 0.f;
-  if (!rows || !loss) return;     // uniform over the block
-  const float* r = rows + (long long)k * B;
+// The loss of one member: the mean of its per-row losses r[0:B] (each thread
+// adds its rows in row order, eight loads in flight, then a fixed pairwise
+// tree over red[256]).  One block of 256 threads.
+__device__ inline void member_loss(const float* r, int B, float* loss, float* red) {
   float acc = 0.f;
   int b = threadIdx.x;
   for (; b + 7 * 256 < B; b += 8 * 256) {
@@ -602,7 +499,7 @@ __global__ __launch_bounds__(256) void train_finish_kernel(const float* rows, in
     if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) loss[k] = red[0] / (float)B;
+  if (threadIdx.x == 0) *loss = red[0] / (float)B;
 }
 
 __global__ void adam_kernel(float* theta, float* m, float* v, const float* g,
@@ -618,124 +515,333 @@ __global__ void adam_kernel(float* theta, float* m, float* v, const float* g,
   }
 }
 
-// Weight-gradient GEMM: C_s[b] = sum over the k-chunk s of A[b][k][m] B[b][k][n]
-// (A: [Kc][M] rows, m contiguous; B: [Kc][N] rows, n contiguous -- the
-// stacked lam and activation slabs, whose contraction index is the row).
-// The 32x32x2 FP32 MFMA takes A as 32 m x 2 k with lane l holding
-// (m = l % 32, k = l / 32), and B likewise, so each lane loads one float of
-// each operand straight from the row-major slabs with coalesced 128-byte
-// row segments: no LDS staging, no transposes, no barriers in the loop.
-// A workgroup owns a 64 x 64 tile of one member and one k-chunk; its four
-// waves take consecutive quarters of the chunk (two rows per k-step, 2 x 2
-// MFMA tiles per wave, loads issued WG_PF k-steps ahead) and their partial
-// tiles are added through LDS in a fixed order ((w0 + w2) + (w1 + w3)), so
-// the result does not depend on timing.  With csum, the workgroups of the
-// first column tile also sum A over the rows below csum_rows (the bias
-// gradient: lam_z over the primal rows), per split slab.
-struct WgradArgs {
+// Weight gradients of all layers of one pass over a batch, in one launch.
+// Layer l, member b, split s: C = sum over the rows k of chunk s of
+// A[b][k][m] B[b][k][n]; A holds [lam_z ; lam_zd], B [h ; hd] (2R rows each,
+// primal then tangent: the contraction runs over their rows).  A workgroup
+// owns a 64 x 64 tile of one chunk; its four waves take every fourth step of
+// 16 rows and their partial tiles are added through LDS in a fixed order
+// ((w0 + w2) + (w1 + w3)), so the result does not depend on timing.
+// Workgroups of the first column tile also sum A over the primal rows (the
+// bias gradient).
+//
+// The products run on the 16-bit matrix units at 16 times the FP32 rate, the
+// operands split in registers.  A lane holds 8 consecutive rows of one column
+// (the 32x32x16 MFMA's layout), loaded straight from the row-major slabs
+// (128-byte row segments, two steps ahead, no LDS, no barriers in the loop):
+//  * FP16, x = hi + lo and three products, for the fused sweeps, which leave
+//    bounds of the slabs' largest entries.  One power-of-two scale per slab
+//    half: hi and lo keep 22 bits of every entry down to 2^-28 of the half's
+//    largest.  The products of both halves must carry one scale; the half
+//    whose products are smaller gives way (half of the difference on each
+//    operand), which costs nothing the larger half's rounding does not cover.
+//  * BF16, x = x1 + x2 + x3 and six products (the others are below 2^-26),
+//    for the general sweeps: BF16 has FP32's range and needs no scales.
+// On 256-long dots the error against FP64 is 1.8e-7 rms of the result with
+// FP16, 0.8e-7 with BF16, 2.9e-7 with the FP32 MFMA chain.
+//
+// What bounds it: the slabs, 235 MB at 4096 samples of 4 x [256 x 4], read at
+// 2.5 to 3 TB/s (359 MB with the L2's misses); the matrix units are busy a
+// fifth of the time.  Measured per pass there: 205 us with FP32 MFMA and a
+// launch per layer (and 38 us of column sums, partial sums and losses in
+// seven more), 120 us with BF16 alone, 99 us now; 128 samples of residual
+// 4 x [300 x 4]: 41 (and 14) us before, 18 us now.  8-byte loads of column
+// pairs take 103 us; 128 x 128 tiles split once through LDS take 90 us at
+// 4096 samples and 5 % off a step of 16384, but 15 % longer below 500 samples.
+// The launch also covers what else the batch reductions need: the column sums
+// of hd_L (the output weights' gradient, per chunk of kColRows rows) and, on
+// the last pass, the members' losses.
+struct WgradLayer {
+  const uint4* mx;                 // [batch][n_mx] bounds: lam_z, lam_zd, h, hd (FP16)
   const float* A;
-  long long sAb;
-  int lda;
   const float* B;
-  long long sBb;
-  int ldb;
+  long long sAb, sBb;
+  int lda, ldb, M, N, tn, tile0;   // tn: column tiles; tile0: first tile of the layer
   float* C;           // tile of split s, member b: C + s*sCs + b*sCb, [M][N]
   long long sCs, sCb;
-  float* csum;        // bias sums of split s, member b: csum + s*csum_ss + b*csum_sb, [M]
+  float* csum;        // bias sums: csum + s*csum_ss + b*csum_sb, [M]
   long long csum_ss, csum_sb;
-  int csum_rows;
-  int M, N, Kc, batch, ksplit, kchunk;
+};
+constexpr int kColRows = 128;      // rows of a partial column sum
+struct WgradArgs {
+  WgradLayer l[kMaxHidden];
+  int nl, tiles;                   // layers, tiles of all layers
+  int R, batch, ksplit, kchunk, xcd;   // rows of a half; chunks, whole steps of each
+  int n_mx;
+  int main_blocks;                 // workgroups of the products
+  // column sums of X [batch][.][w] (member stride sXb) over its R rows, part c of
+  // member b at out + c*s_part + b*s_mem; null: none
+  const float* X;
+  long long sXb;
+  int w, col_parts;
+  float* col_out;
+  long long col_part, col_mem;
+  // losses from rows [batch][B] (null: none), and the zero of the output bias
+  const float* rows;
+  int B;
+  float* loss;
+  float* zero;
+  long long s_zero;
 };
 
 typedef float f16v __attribute__((ext_vector_type(16)));
-#ifndef RID_WG_PF
-#define RID_WG_PF 6
-#endif
-constexpr int kWgPF = RID_WG_PF;   // k-steps of loads in flight per wave
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+using dev::fl2;
+using dev::h2;
+using dev::h8;
 constexpr int kWgLdsStride = 65;   // padded row of a partial tile in LDS
+constexpr int kWgTile = 64;        // tile edge of a workgroup
+constexpr int kWgStep = 16;        // contraction rows of a step
 
+// The parts of eight values: P = 3 BF16, P = 2 FP16 (of x scale).
+template <int P>
+struct Split8 {
+  uint4 p[P];
+  __device__ inline void set(const float (&x)[8], float scale) {
+    unsigned q[P][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float a = x[2 * i], b = x[2 * i + 1];
+      if constexpr (P == 2) {
+        a *= scale;
+        b *= scale;
+        const h2 hi = __builtin_convertvector((fl2{a, b}), h2);
+        const h2 lo = __builtin_convertvector((fl2{a - (float)hi[0], b - (float)hi[1]}), h2);
+        q[0][i] = __builtin_bit_cast(unsigned, hi);
+        q[1][i] = __builtin_bit_cast(unsigned, lo);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector((fl2{a, b}), bf2));
+          q[t][i] = u;
+          if (t < 2) {
+            a -= __uint_as_float(u << 16);
+            b -= __uint_as_float(u & 0xFFFF0000u);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < P; ++t) p[t] = make_uint4(q[t][0], q[t][1], q[t][2], q[t][3]);
+  }
+};
+
+template <int P>
+__device__ inline void wg_mfma(f16v& c, const uint4& a, const uint4& b) {
+  if constexpr (P == 2)
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b),
+                                               c, 0, 0, 0);
+  else
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a),
+                                                __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+
+// The workgroups past the products: column sums, then losses (red: 256 floats).
+__device__ inline void wgrad_extra(const WgradArgs& g, int blk, float* red) {
+  const int ct = (g.w + 63) / 64, n_col = g.X ? ct * g.col_parts * g.batch : 0;
+  if (blk >= n_col) {
+    const int b = blk - n_col;
+    if (threadIdx.x == 0 && g.zero) g.zero[b * g.s_zero] = 0.f;
+    if (g.rows && g.loss) member_loss(g.rows + (long long)b * g.B, g.B, g.loss + b, red);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = blk / (ct * g.col_parts), r = blk - b * ct * g.col_parts;
+  const int c = r / ct, j = (r - c * ct) * 64 + lane;
+  const int r0 = c * kColRows, r1 = min(g.R, r0 + kColRows);
+  const float* x = g.X + b * g.sXb + min(j, g.w - 1);
+  float acc = 0.f;
+  int k = r0 + wave;
+  for (; k + 28 < r1; k += 32) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = x[(long long)(k + 4 * q) * g.w];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc += v[q];
+  }
+  for (; k < r1; k += 4) acc += x[(long long)k * g.w];
+  red[64 * wave + lane] = acc;
+  __syncthreads();
+  if (wave == 0 && j < g.w)
+    g.col_out[c * g.col_part + b * g.col_mem + j] =
+        ((red[lane] + red[64 + lane]) + red[128 + lane]) + red[192 + lane];
+}
+
+// The tile of a workgroup: its layer, member, split and tile in the layer.
+struct WgradTile {
+  int li, b, s, m0, n0;
+};
+__device__ inline bool wgrad_tile(const WgradArgs& g, int blk, WgradTile& w) {
+  int chunk, tile;
+  if (g.xcd) {                     // all tiles of a chunk on one XCD
+    const int q = blk >> 3;
+    tile = q % g.tiles;
+    chunk = (q / g.tiles) * 8 + (blk & 7);
+  } else {
+    tile = blk % g.tiles;
+    chunk = blk / g.tiles;
+  }
+  if (chunk >= g.batch * g.ksplit) return false;
+  w.b = chunk / g.ksplit;
+  w.s = chunk - w.b * g.ksplit;
+  w.li = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxHidden; ++i)
+    if (i < g.nl && tile >= g.l[i].tile0) w.li = i;
+  const int t2 = tile - g.l[w.li].tile0, tn = g.l[w.li].tn;
+  w.m0 = (t2 / tn) * kWgTile;
+  w.n0 = (t2 % tn) * kWgTile;
+  return true;
+}
+
+template <int P>
 __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
   __shared__ float red[2][64][kWgLdsStride];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x >= g.main_blocks) {
+    wgrad_extra(g, blockIdx.x - g.main_blocks, &red[0][0][0]);
+    return;
+  }
+  WgradTile wt;
+  if (!wgrad_tile(g, blockIdx.x, wt)) return;
+  const int b = wt.b, s = wt.s, m0 = wt.m0, n0 = wt.n0;
+  const WgradLayer& L = g.l[wt.li];
   const int lo = lane & 31, hi = lane >> 5;
-  const int b = blockIdx.z / g.ksplit, s = blockIdx.z % g.ksplit;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int c_begin = s * g.kchunk, c_end = min(g.Kc, c_begin + g.kchunk);
-  // this wave's quarter of the chunk, in whole k-steps of two rows
-  const int steps = (c_end - c_begin + 1) / 2;
-  const int q = (steps + 3) / 4;
-  const int k_begin = c_begin + 2 * min(steps, wave * q);
-  const int k_end = min(c_end, c_begin + 2 * min(steps, (wave + 1) * q));
-  const float* A = g.A + b * g.sAb;
-  const float* Bp = g.B + b * g.sBb;
-  // the lane's element of a k-step: row k + hi, its column clamped into the
-  // operand.  A lane whose column lies outside only feeds accumulator rows
-  // or columns that are never stored, so its value needs no masking.  Every
-  // wave's range holds an even number of rows (chunks and quarters are
-  // whole k-steps of an even Kc), so row k + hi is always inside it.
-  // Offsets from the (uniform) row start are per-lane constants.
-  // Buffer loads: the lane's byte offset in the vector offset, the row's in
-  // the scalar offset, so the loop does no address arithmetic.
-  const int ma = min(m0 + lo, g.M - 1), mb = min(m0 + 32 + lo, g.M - 1);
-  const int na = min(n0 + lo, g.N - 1), nb = min(n0 + 32 + lo, g.N - 1);
-  const int oa0 = 4 * (hi * g.lda + ma), oa1 = 4 * (hi * g.lda + mb);
-  const int ob0 = 4 * (hi * g.ldb + na), ob1 = 4 * (hi * g.ldb + nb);
-  const __amdgpu_buffer_rsrc_t ra =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), (short)0, 0x7FFFFFF0, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Bp), (short)0, 0x7FFFFFF0, 0x00020000);
-  const bool csum_wg = g.csum && blockIdx.x == 0;
-  const int csum_end = min(k_end, g.csum_rows);
+  // The whole 16-row steps of the primal half, then of the tangent half, are
+  // numbered through; this wave takes every fourth of the chunk's.  The rows
+  // left over in each half (R mod 16) fall to waves 0 and 1 of the last chunk.
+  const int R = g.R, half = R / kWgStep, rest = R - half * kWgStep;
+  const int c_begin = min(2 * half, s * g.kchunk), c_end = min(2 * half, c_begin + g.kchunk);
+  const int n_st = (max(c_end - c_begin - wave, 0) + 3) / 4;
+  auto step = [&](int i) { return c_begin + wave + 4 * min(i, n_st - 1); };
+  // A lane's column is clamped into the operand: one outside only feeds
+  // accumulator rows or columns that are never stored.  Buffer loads: the
+  // lane's byte offset in the vector offset, the row's in the scalar offset.
+  const int lda = L.lda, ldb = L.ldb;
+  const int ca[2] = {min(m0 + lo, L.M - 1), min(m0 + 32 + lo, L.M - 1)};
+  const int cb[2] = {min(n0 + lo, L.N - 1), min(n0 + 32 + lo, L.N - 1)};
+  const int oa[2] = {4 * (8 * hi * lda + ca[0]), 4 * (8 * hi * lda + ca[1])};
+  const int ob[2] = {4 * (8 * hi * ldb + cb[0]), 4 * (8 * hi * ldb + cb[1])};
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(L.A + b * L.sAb), (short)0, 0x7FFFFFF0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(L.B + b * L.sBb), (short)0, 0x7FFFFFF0, 0x00020000);
+  const bool csum_wg = L.csum && n0 == 0;
 
   f16v acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f16v{};
-  float cs0 = 0.f, cs1 = 0.f;
-  // ring of loaded k-steps: [slot][a0, a1, b0, b1]
-  float ring[kWgPF][4];
-  auto issue = [&](int slot, int k) {
-    const int sa = 4 * k * g.lda, sb = 4 * k * g.ldb;   // row byte offsets (uniform)
-    ring[slot][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, oa0, sa, 0));
-    ring[slot][1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, oa1, sa, 0));
-    ring[slot][2] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, ob0, sb, 0));
-    ring[slot][3] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, ob1, sb, 0));
+  float cs[2] = {0.f, 0.f};
+  float sA[2] = {1.f, 1.f}, sB[2] = {1.f, 1.f};   // scales: primal, tangent half
+  int unscale = 0;                                // C = acc 2^unscale
+  auto ldf = [](const __amdgpu_buffer_rsrc_t& r, int vo, int so) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
   };
-  // k-steps of the wave; loads run kWgPF steps ahead through the ring.  The
-  // main loop has no conditional code (a step past the last one re-reads
-  // the last, and is never consumed), so the loads stay in flight.
-  const int nst = (k_end - k_begin) / 2;
-  auto step_row = [&](int t) { return k_begin + 2 * min(t, nst - 1); };
-  auto consume = [&](int p, int t) {
-    const float a0 = ring[p][0], a1 = ring[p][1], b0 = ring[p][2], b1 = ring[p][3];
-    if (csum_wg) {
-      const bool in = k_begin + 2 * t + hi < csum_end;
-      cs0 += in ? a0 : 0.f;
-      cs1 += in ? a1 : 0.f;
+  // loaded steps: [slot][a0, a1, b0, b1][row]
+  float ring[3][4][8];
+  auto issue = [&](float (&v)[4][8], int t) {
+    const int k = kWgStep * t + (t >= half ? rest : 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int sa = 4 * (k + e) * lda, sb = 4 * (k + e) * ldb;
+      v[0][e] = ldf(ra, oa[0], sa);
+      v[1][e] = ldf(ra, oa[1], sa);
+      v[2][e] = ldf(rb, ob[0], sb);
+      v[3][e] = ldf(rb, ob[1], sb);
     }
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
   };
-  if (nst > 0) {
+  auto consume = [&](const float (&v)[4][8], bool tangent) {
+    const float fA = tangent ? sA[1] : sA[0], fB = tangent ? sB[1] : sB[0];
+    if (csum_wg && !tangent) {
 #pragma unroll
-    for (int p = 0; p < kWgPF; ++p) issue(p, step_row(p));
-    const int nfull = nst / kWgPF;
-    for (int blk = 0; blk < nfull; ++blk) {
-#pragma unroll
-      for (int p = 0; p < kWgPF; ++p) {
-        const int t = blk * kWgPF + p;
-        consume(p, t);
-        issue(p, step_row(t + kWgPF));
+      for (int e = 0; e < 8; ++e) {
+        cs[0] += v[0][e];
+        cs[1] += v[1][e];
       }
     }
-    const int rem = nst - nfull * kWgPF;
+    Split8<P> fb[2];
+    fb[0].set(v[2], fB);
+    fb[1].set(v[3], fB);
 #pragma unroll
-    for (int p = 0; p < kWgPF; ++p)
-      if (p < rem) consume(p, nfull * kWgPF + p);
+    for (int i = 0; i < 2; ++i) {
+      Split8<P> fa;
+      fa.set(v[i], fA);
+      constexpr int NT = P == 2 ? 3 : 6;   // small products first
+      constexpr int pa[6] = {P == 2 ? 1 : 0, P == 2 ? 0 : 2, P == 2 ? 0 : 1, 0, 1, 0};
+      constexpr int pb[6] = {P == 2 ? 0 : 2, P == 2 ? 1 : 0, P == 2 ? 0 : 1, 1, 0, 0};
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) wg_mfma<P>(acc[i][j], fa.p[pa[t]], fb[j].p[pb[t]]);
+    }
+  };
+  // (a step past the last one re-reads the last, never consumed)
+  if (n_st > 0) {
+    issue(ring[0], step(0));
+    issue(ring[1], step(1));
+  }
+  if constexpr (P == 2) {
+    // the slab halves' largest entries, over the sweep's tiles
+    uint4 m = make_uint4(0, 0, 0, 0);
+    const uint4* mx = L.mx + (long long)b * g.n_mx;
+    auto mx4 = [](const uint4& a, const uint4& c) {
+      return make_uint4(max(a.x, c.x), max(a.y, c.y), max(a.z, c.z), max(a.w, c.w));
+    };
+    for (int i = threadIdx.x; i < g.n_mx; i += 256) m = mx4(m, mx[i]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+      m = mx4(m, make_uint4(__shfl_xor(m.x, d), __shfl_xor(m.y, d), __shfl_xor(m.z, d),
+                            __shfl_xor(m.w, d)));
+    uint4* mr = reinterpret_cast<uint4*>(&red[0][0][0]);
+    if (lane == 0) mr[wave] = m;
+    __syncthreads();
+    m = mx4(mx4(mr[0], mr[1]), mx4(mr[2], mr[3]));
+    __syncthreads();
+    const int a0 = dev::split_clamp_exp(dev::split_exp(m.x));
+    const int a1 = dev::split_clamp_exp(dev::split_exp(m.y));
+    const int b0 = dev::split_clamp_exp(dev::split_exp(m.z));
+    const int b1 = dev::split_clamp_exp(dev::split_exp(m.w));
+    const int top = max(a0 + b0, a1 + b1);
+    // (a half 2^-80 below the other is nothing beside it: the exponents stay
+    // inside FP32's range)
+    const int d0 = min(top - (a0 + b0), 80), d1 = min(top - (a1 + b1), 80);
+    auto pow2 = [](int e) { return __uint_as_float((unsigned)(127 + max(e, -126)) << 23); };
+    sA[0] = pow2(dev::kTargetExp - a0 - (d0 + 1) / 2);
+    sB[0] = pow2(dev::kTargetExp - b0 - d0 / 2);
+    sA[1] = pow2(dev::kTargetExp - a1 - (d1 + 1) / 2);
+    sB[1] = pow2(dev::kTargetExp - b1 - d1 / 2);
+    unscale = top - 2 * dev::kTargetExp;
+  }
+  for (int i = 0; i < n_st; i += 3) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      if (i + p < n_st) {
+        issue(ring[(p + 2) % 3], step(i + p + 2));
+        __builtin_amdgcn_sched_barrier(0);
+        consume(ring[p], step(i + p) >= half);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  }
+  if (rest > 0 && s == g.ksplit - 1 && wave < 2) {   // the rest of a half; zeros past it
+    const int k0 = wave * R + half * kWgStep, k1 = (wave + 1) * R;
+    float v[4][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = k0 + 8 * hi + e, kc = min(k, k1 - 1);
+      const bool in = k < k1;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float x = ldf(ra, 4 * (kc * lda + ca[i]), 0);
+        const float y = ldf(rb, 4 * (kc * ldb + cb[i]), 0);
+        v[i][e] = in ? x : 0.f;
+        v[2 + i][e] = in ? y : 0.f;
+      }
+    }
+    consume(v, wave == 1);
   }
   // accumulator element v of a 32 x 32 tile: row 8 (v / 4) + 4 hi + v % 4,
   // column lo.  Waves 2, 3 park their tiles; waves 0, 1 add them; wave 1
@@ -764,15 +870,14 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
         __builtin_amdgcn_sched_barrier(0);
       }
   };
-  // the bias sums: combine the two row parities of a lane pair, then the
-  // waves in the same fixed order through LDS (column 64 of the tile rows)
+  // the bias sums: combine the two row halves of a lane pair, then the
+  // waves in the same fixed order through LDS
   __shared__ float cred[4][64];
   if (csum_wg) {
-    cs0 += __shfl_xor(cs0, 32);
-    cs1 += __shfl_xor(cs1, 32);
-    if (hi == 0) {
-      cred[wave][lo] = cs0;
-      cred[wave][32 + lo] = cs1;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      cs[i] += __shfl_xor(cs[i], 32);
+      if (hi == 0) cred[wave][32 * i + lo] = cs[i];
     }
   }
   if (wave >= 2) park(wave - 2);
@@ -788,13 +893,84 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
   __syncthreads();
   // the summed tile, stored by all waves: a row per wave and store, one
   // column per lane (256-byte row segments)
-  float* Ct = g.C + s * g.sCs + b * g.sCb + (long long)m0 * g.N + n0;
-  for (int r = wave; r < 64 && m0 + r < g.M; r += 4)
-    if (n0 + lane < g.N) Ct[(long long)r * g.N + lane] = red[1][r][lane];
+  float* Ct = L.C + s * L.sCs + b * L.sCb + (long long)m0 * L.N + n0;
+  for (int r = wave; r < 64 && m0 + r < L.M; r += 4)
+    if (n0 + lane < L.N)
+      Ct[(long long)r * L.N + lane] = P == 2 ? ldexpf(red[1][r][lane], unscale) : red[1][r][lane];
   if (csum_wg && wave == 0) {
     const int m = m0 + lane;
     const float v = (cred[0][lane] + cred[2][lane]) + (cred[1][lane] + cred[3][lane]);
-    if (m < g.M) g.csum[s * g.csum_ss + b * g.csum_sb + m] = v;
+    if (m < L.M) L.csum[s * L.csum_ss + b * L.csum_sb + m] = v;
+  }
+}
+
+// The gradient from the partials of one pass: dW_l and db_l over the split
+// slabs, dw_o over the column sums' parts, each in part order (added to what
+// the gradient holds when accumulate is set); on the last pass the output
+// bias's zero and the losses.  Block row y < nl: layer y; y == nl: the rest.
+struct ReduceLayer {
+  const float* part;               // [ks][K][M][N]
+  const float* bpart;              // [ks][K][M]
+  int M, N;
+  long long w_off, b_off;
+};
+struct ReduceArgs {
+  ReduceLayer l[kMaxHidden];
+  int nl, ks, K, accumulate;
+  float* grad;
+  long long pm;
+  const float* cpart;              // [cparts][K][w], null: none
+  int cparts, w;
+  long long wo_off;
+  const float* rows;               // [K][B]: losses (last pass), or null
+  int B;
+  float* loss;
+  int last;                        // zero the output bias's gradient
+};
+__device__ inline float sum_parts(const float* src, long long stride, int n) {
+  // parts added in order, eight loads in flight
+  float acc = 0.f;
+  int s = 0;
+  for (; s + 8 <= n; s += 8) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = src[(s + j) * stride];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc += v[j];
+  }
+  for (; s < n; ++s) acc += src[s * stride];
+  return acc;
+}
+__global__ __launch_bounds__(256) void grad_reduce_kernel(ReduceArgs g) {
+  __shared__ float red[256];
+  const long long step = (long long)gridDim.x * 256, first = blockIdx.x * 256LL + threadIdx.x;
+  if ((int)blockIdx.y < g.nl) {
+    const ReduceLayer& L = g.l[blockIdx.y];
+    const long long mn = (long long)L.M * L.N, total = g.K * mn, all = total + (long long)g.K * L.M;
+    for (long long e = first; e < all; e += step) {
+      const bool wt = e < total;
+      const long long x = wt ? e : e - total, per = wt ? mn : L.M;
+      const int k = (int)(x / per);
+      float* o = g.grad + k * g.pm + (wt ? L.w_off : L.b_off) + (x - k * per);
+      const float v = sum_parts((wt ? L.part : L.bpart) + x, wt ? total : (long long)g.K * L.M, g.ks);
+      *o = g.accumulate ? *o + v : v;
+    }
+    return;
+  }
+  if (g.cpart) {
+    const long long all = (long long)g.K * g.w;
+    for (long long e = first; e < all; e += step) {
+      const int k = (int)(e / g.w);
+      float* o = g.grad + k * g.pm + g.wo_off + (e - (long long)k * g.w);
+      const float v = sum_parts(g.cpart + e, all, g.cparts);
+      *o = g.accumulate ? *o + v : v;
+    }
+  }
+  if (!g.last) return;
+  for (int k = blockIdx.x; k < g.K; k += gridDim.x) {
+    if (threadIdx.x == 0) g.grad[k * g.pm + g.wo_off + g.w] = 0.f;
+    if (g.rows && g.loss) member_loss(g.rows + (long long)k * g.B, g.B, g.loss + k, red);
+    __syncthreads();
   }
 }
 
@@ -861,56 +1037,101 @@ rid_status gemm(const GemmArgs& g0, hipStream_t st) {
   return RID_OK;
 }
 
-rid_status wgrad(const WgradArgs& a, hipStream_t st) {
-  // the kernel reads two rows per k-step inside each wave's range: chunks
-  // and the contraction must hold whole k-steps
-  if (a.kchunk % 2 != 0 || a.Kc % 2 != 0 || a.M < 1 || a.N < 1 || a.Kc < 1)
-    return fail(RID_EINVAL, "weight-gradient GEMM: bad shape");
-  // row byte offsets are 32-bit scalar offsets (passes are sized to fit)
-  if ((long long)a.Kc * std::max(a.lda, a.ldb) * 4 > 0x7FFFFFFFLL)
-    return fail(RID_EUNSUPPORTED, "weight-gradient GEMM: slab too large for 32-bit offsets");
-  const dim3 grid((a.N + 63) / 64, (a.M + 63) / 64, a.batch * a.ksplit);
-  hipLaunchKernelGGL(wgrad_kernel, grid, dim3(256), 0, st, a);
-  RID_HIP(hipGetLastError());
-  return RID_OK;
-}
+// The batch reductions of one pass of R rows (contraction over 2R stacked
+// rows): the layers' products, and what g says of column sums and losses.
+// Where one split, one column part and no earlier pass make the partials the
+// result, the kernel writes the gradient itself; else it writes partials
+// (region part, bias partials bpart, column parts cpart) and a second launch
+// adds them up.  Layers: operands, shapes and offsets in the packed layout.
+struct GradLayer {
+  const float* A;                  // lam slab [K][2R][M]
+  const float* B;                  // activation slab [K][2R][N]
+  int M, N;
+  long long w_off, b_off;
+  const uint4* mx;                 // [K][n_mx] the sweep tiles' bounds, or null
+};
+struct GradPass {
+  GradLayer l[kMaxHidden];
+  int nl, K, R, ks, kchunk, n_mx;  // n_mx: tiles of the fused sweeps (0: no bounds)
+  float *part, *bpart, *cpart;
+  float* grad;
+  long long pm;
+  bool accumulate, last;
+  const float* X;                  // hd_L rows (member stride sXb), or null
+  long long sXb, wo_off;
+  int w;
+  const float* rows;               // last pass: [K][B] row losses, or null
+  int B;
+  float* loss;
+};
+int col_parts(int R) { return (R + kColRows - 1) / kColRows; }
 
-// dW_l and db_l of one chunk of rows into the gradient (member k at
-// G + k*pm, dW_l at w_off, db_l at b_off).  With one split and no earlier
-// chunk to add to, the kernel writes the gradient itself; otherwise it
-// writes one slab per split (part, bpart) and splitk_reduce_kernel adds them
-// in split order, onto the gradient when accumulate is set.  The operands,
-// shape and split of g are set by the caller.
-rid_status wgrad_into_grad(WgradArgs g, float* part, float* bpart, float* G, long long pm,
-                           long long w_off, long long b_off, bool accumulate, hipStream_t st) {
-  rid_status rs;
-  const long long mn = (long long)g.M * g.N;
-  if (g.ksplit == 1 && !accumulate) {
-    g.C = G + w_off; g.sCs = 0; g.sCb = pm;
-    g.csum = G + b_off; g.csum_ss = 0; g.csum_sb = pm;
-    return wgrad(g, st);
+rid_status grad_pass(const GradPass& g, hipStream_t st) {
+  WgradArgs a{};
+  ReduceArgs r{};
+  const int Kc = 2 * g.R;
+  if (g.kchunk < 1 || g.nl < 1 || g.R < 1)
+    return fail(RID_EINVAL, "weight-gradient pass: bad shape");
+  const bool direct = g.ks == 1 && !g.accumulate && (!g.X || col_parts(g.R) == 1);
+  a.nl = r.nl = g.nl;
+  a.R = g.R; a.batch = g.K; a.ksplit = g.ks; a.kchunk = g.kchunk; a.n_mx = g.n_mx;
+  long long off = 0, boff = 0;
+  for (int i = 0; i < g.nl; ++i) {
+    const GradLayer& s = g.l[i];
+    WgradLayer& d = a.l[i];
+    const long long mn = (long long)s.M * s.N;
+    // row byte offsets are 32-bit scalar offsets (passes are sized to fit)
+    if ((long long)Kc * std::max(s.M, s.N) * 4 > 0x7FFFFFFFLL)
+      return fail(RID_EUNSUPPORTED, "weight-gradient pass: slab too large for 32-bit offsets");
+    d.mx = s.mx;
+    d.A = s.A; d.lda = s.M; d.sAb = (long long)Kc * s.M;
+    d.B = s.B; d.ldb = s.N; d.sBb = (long long)Kc * s.N;
+    d.M = s.M; d.N = s.N;
+    d.tn = (s.N + kWgTile - 1) / kWgTile;
+    d.tile0 = a.tiles;
+    a.tiles += d.tn * ((s.M + kWgTile - 1) / kWgTile);
+    if (direct) {
+      d.C = g.grad + s.w_off; d.sCb = g.pm;
+      d.csum = g.grad + s.b_off; d.csum_sb = g.pm;
+    } else {
+      d.C = g.part + off * g.ks; d.sCs = g.K * mn; d.sCb = mn;
+      d.csum = g.bpart + boff * g.ks; d.csum_ss = (long long)g.K * s.M; d.csum_sb = s.M;
+      r.l[i] = ReduceLayer{d.C, d.csum, s.M, s.N, s.w_off, s.b_off};
+    }
+    off += g.K * mn;
+    boff += (long long)g.K * s.M;
   }
-  g.C = part; g.sCs = g.batch * mn; g.sCb = mn;
-  g.csum = bpart; g.csum_ss = (long long)g.batch * g.M; g.csum_sb = g.M;
-  if ((rs = wgrad(g, st)) != RID_OK) return rs;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid1d(g.batch * (long long)g.M * (g.N + 1))),
-                     dim3(256), 0, st, part, g.batch * mn, g.ksplit, g.M, g.N, g.batch, G, pm,
-                     (int)w_off, accumulate ? 1 : 0, bpart, (int)b_off);
+  const int chunks = g.K * g.ks;
+  a.xcd = chunks >= 8;
+  a.main_blocks = a.xcd ? 8 * a.tiles * ((chunks + 7) / 8) : a.tiles * chunks;
+  int extra = 0;
+  if (g.X) {
+    a.X = g.X; a.sXb = g.sXb; a.w = g.w; a.col_parts = col_parts(g.R);
+    if (direct) {
+      a.col_out = g.grad + g.wo_off; a.col_mem = g.pm;
+    } else {
+      a.col_out = g.cpart; a.col_part = (long long)g.K * g.w; a.col_mem = g.w;
+      r.cpart = g.cpart; r.cparts = a.col_parts;
+    }
+    extra += ((g.w + 63) / 64) * a.col_parts * g.K;
+  }
+  if (direct && g.last) {
+    a.rows = g.rows; a.B = g.B; a.loss = g.loss;
+    a.zero = g.grad + g.wo_off + g.w; a.s_zero = g.pm;
+    extra += g.K;
+  }
+  auto kern = g.n_mx > 0 ? wgrad_kernel<2> : wgrad_kernel<3>;
+  hipLaunchKernelGGL(kern, dim3(a.main_blocks + extra), dim3(256), 0, st, a);
   RID_HIP(hipGetLastError());
-  return RID_OK;
-}
-
-// out[k][j] = sum_{b<B} X[k*slab + b*w + j] -> grad[k*per_model + dst_off + j]
-// (+= when accumulate)
-rid_status colsum(const float* X, long long slab, int B, int w, int K, float* part,
-                  float* grad, long long per_model, int dst_off, bool accumulate,
-                  hipStream_t st) {
-  const int chunks = (B + kColRows - 1) / kColRows;
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((w + 63) / 64, chunks, K), dim3(256), 0, st,
-                     X, slab, B, w, part, K);
-  RID_HIP(hipGetLastError());
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((K * w + 63) / 64), dim3(256), 0, st, part,
-                     chunks, w, K, grad, per_model, dst_off, accumulate ? 1 : 0);
+  if (direct) return RID_OK;
+  r.ks = g.ks; r.K = g.K; r.accumulate = g.accumulate ? 1 : 0;
+  r.grad = g.grad; r.pm = g.pm; r.w = g.w; r.wo_off = g.wo_off;
+  r.last = g.last ? 1 : 0; r.rows = g.rows; r.B = g.B; r.loss = g.loss;
+  long long most = 1;
+  for (int i = 0; i < g.nl; ++i)
+    most = std::max(most, (long long)g.K * g.l[i].M * (g.l[i].N + 1));
+  hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)std::min<long long>((most + 255) / 256, 1024),
+                                              g.nl + 1), dim3(256), 0, st, r);
   RID_HIP(hipGetLastError());
   return RID_OK;
 }
@@ -930,20 +1151,40 @@ int chunk_rows(long long floats_per_row, int B, size_t budget, int wmax) {
   return (int)std::min<long long>(step, (B + chunks - 1) / chunks + 63) / 64 * 64;
 }
 
-// Split of the 2R-row weight-gradient contraction of a pass of R rows:
-// split-K slabs until the tiles times slabs reach RID_WG_TARGET workgroups
-// (512: two per CU; more slabs cost more partial traffic than the extra
-// workgroups gain -- measured 1024 +6 %, 256 +6 %, 128 +31 % per training
-// step), each slab at least 256 rows.
-#ifndef RID_WG_TARGET
-#define RID_WG_TARGET 512
-#endif
-void wgrad_split(int K, int tiles_max, int R, int* ks, int* kchunk) {
-  int s = 1;
-  while (s < 64 && (long long)K * tiles_max * s < RID_WG_TARGET && 2LL * R / (s * 2) >= 256)
-    s *= 2;
-  *ks = s;
-  *kchunk = round_up((2 * R + s - 1) / s, BK);
+// Split of the 2R-row contraction of a pass of R rows over nl layers'
+// products: the number of equal chunks (a power of two, at least 256 rows
+// each) that costs least.  A CU works through `per_cu` tiles of rows + 160
+// (a workgroup's start and its tile's way through LDS cost what 160 rows do);
+// one tile alone on a CU runs at 0.8 of the rate two reach together, and a
+// chunk's partial gradient costs 1 row per 5.7 kB written and read back.
+// Measured per training step (us, 4 members of [256 x 4] unless noted; chunks
+// 1 / 2 / 4): 1024 samples 118 / 114 / 121, 4096 samples 310 / 292 / 298,
+// 16384 samples 1260 / 1173 / 1183, 4096 samples of [300 x 4] 615 / 488 / -,
+// one member and 4096 samples, chunks 4 / 8 / 16: 107 / 104 / 109.
+struct WgradSplit {
+  int ks, kchunk;
+};
+WgradSplit wgrad_split(int K, const int* M, const int* N, int nl, int R) {
+  long long tiles = 0, params = 0;
+  for (int i = 0; i < nl; ++i) {
+    tiles += (long long)((M[i] + kWgTile - 1) / kWgTile) * ((N[i] + kWgTile - 1) / kWgTile);
+    params += (long long)M[i] * N[i];
+  }
+  WgradSplit best{1, 0};
+  double least = 0;
+  for (int ks = 1; ks <= 64 && (ks == 1 || 2LL * R >= 256LL * ks); ks *= 2) {
+    const long long chunks = (long long)K * ks;
+    const double per_cu = chunks >= 8 ? std::ceil(tiles * ((chunks + 7) / 8) / 32.0)
+                                      : std::ceil(tiles * chunks / 256.0);
+    const double cost = per_cu * (2.0 * R / ks + 160) * (per_cu == 1 ? 1.25 : 1.0) +
+                        (ks > 1 ? K * params * 8.0 * ks / 46e3 : 0.0);
+    if (ks == 1 || cost < least) {
+      least = cost;
+      best.ks = ks;
+    }
+  }
+  best.kchunk = std::max(1, (2 * (R / kWgStep) + best.ks - 1) / best.ks);
+  return best;
 }
 
 // The training step with the sweeps fused into one kernel (train_sweep_f32.h):
@@ -959,16 +1200,15 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
                          const float* rho, int B, float* loss, float* grad_out,
                          float** grad_used, hipStream_t st, const std::vector<int>& w,
                          const std::vector<long long>& w_off,
-                         const std::vector<long long>& b_off, long long wo_off,
-                         int tiles_max) {
+                         const std::vector<long long>& b_off, long long wo_off) {
   const int K = e.K, L = e.L, n = e.n_cv;
   int wmax = 0;
   for (int v : w) wmax = std::max(wmax, v);
   long long per_row = 0;
   for (int l = 0; l <= L; ++l) per_row += (long long)K * 2 * w[l] * (l > 0 ? 2 : 1);
   const int Bc = chunk_rows(per_row, B, e.train_budget, wmax);
-  int ks_max, kc;
-  wgrad_split(K, tiles_max, Bc, &ks_max, &kc);
+  std::vector<int> wm(w.begin() + 1, w.end());   // rows of dW_l; w: its columns
+  const int ks_max = wgrad_split(K, wm.data(), w.data(), L, Bc).ks;
   auto al = [](long long v) { return (v + 63) / 64 * 64; };
   std::vector<long long> hh(L + 1), sl(L);
   long long tot = 0;
@@ -980,13 +1220,18 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
     sl[l - 1] = tot;
     tot = al(tot + (long long)K * 2 * Bc * w[l]);
   }
-  long long part_slab = 0;
-  for (int l = 0; l < L; ++l) part_slab = std::max(part_slab, (long long)K * w[l + 1] * w[l]);
-  const long long part = tot; tot = al(tot + part_slab * ks_max);
+  long long parts = 0, bparts = 0;
+  for (int l = 0; l < L; ++l) {
+    parts += (long long)K * w[l + 1] * w[l];
+    bparts += (long long)K * w[l + 1];
+  }
+  const long long part = tot; tot = al(tot + parts * ks_max);
   const long long grad = tot; tot = al(tot + (long long)e.n_params);
   const long long lrows = tot; tot = al(tot + (long long)K * B);
-  const long long cpart = tot; tot = al(tot + (long long)((Bc + kColRows - 1) / kColRows) * K * wmax);
-  const long long bpart = tot; tot = al(tot + (long long)ks_max * K * wmax);
+  const long long cpart = tot; tot = al(tot + (long long)col_parts(Bc) * K * w[L]);
+  const long long bpart = tot; tot = al(tot + bparts * ks_max);
+  // the sweep tiles' bounds, per layer [K][n_tiles] x 16 bytes
+  const long long bnd = tot; tot = al(tot + 4LL * L * K * ((Bc + 15) / 16));
   rid_status rs = e.ws_train.ensure(sizeof(float) * tot);
   if (rs != RID_OK) return rs;
   float* W = e.ws_train.as<float>();
@@ -1006,33 +1251,28 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
   for (int r0 = 0; r0 < B; r0 += Bc) {
     const int R = std::min(Bc, B - r0);
     const bool acc = r0 > 0;
-    int ks, kchunk;
-    wgrad_split(K, tiles_max, R, &ks, &kchunk);
+    const WgradSplit sp = wgrad_split(K, wm.data(), w.data(), L, R);
     io.s = s + (size_t)r0 * n;
     io.F = rho ? nullptr : F + (size_t)r0 * n;
     io.rho = rho ? rho + (size_t)r0 * K * n : nullptr;
     io.loss_rows = rho ? nullptr : W + lrows + r0;
     io.row_base = r0;
-    if ((rs = launch_train_sweeps(e, io, R, st)) != RID_OK) return rs;
-    for (int l = L; l >= 1; --l) {
-      // dW_l = S^T [h ; hd]_{l-1} (contraction over the 2R stacked rows);
-      // db_l = sum over the primal rows of lam_z, in the same pass
-      WgradArgs g{};
-      g.A = W + sl[l - 1]; g.sAb = 2LL * R * w[l]; g.lda = w[l];
-      g.B = W + hh[l - 1]; g.sBb = 2LL * R * w[l - 1]; g.ldb = w[l - 1];
-      g.csum_rows = R;
-      g.M = w[l]; g.N = w[l - 1]; g.Kc = 2 * R; g.batch = K; g.ksplit = ks; g.kchunk = kchunk;
-      if ((rs = wgrad_into_grad(g, W + part, W + bpart, G, pm, w_off[l - 1], b_off[l - 1], acc,
-                                st)) != RID_OK)
-        return rs;
-    }
-    if ((rs = colsum(W + hh[L] + (long long)R * w[L], 2LL * R * w[L], R, w[L], K, W + cpart,
-                     G, pm, (int)wo_off, acc, st)) != RID_OK)
-      return rs;
+    io.bounds = reinterpret_cast<uint4*>(W + bnd);
+    int tiles = 0;
+    if ((rs = launch_train_sweeps(e, io, R, &tiles, st)) != RID_OK) return rs;
+    GradPass g{};
+    g.n_mx = tiles;
+    g.nl = L; g.K = K; g.R = R; g.ks = sp.ks; g.kchunk = sp.kchunk;
+    for (int l = 0; l < L; ++l)      // dW_l = S^T [h ; hd]_{l-1}, db_l = sum of lam_z
+      g.l[l] = GradLayer{W + sl[l], W + hh[l], w[l + 1], w[l], w_off[l], b_off[l],
+                         io.bounds + (long long)l * K * tiles};
+    g.part = W + part; g.bpart = W + bpart; g.cpart = W + cpart;
+    g.grad = G; g.pm = pm;
+    g.accumulate = acc; g.last = r0 + R >= B;
+    g.X = W + hh[L] + (long long)R * w[L]; g.sXb = 2LL * R * w[L]; g.w = w[L]; g.wo_off = wo_off;
+    g.rows = rho ? nullptr : W + lrows; g.B = B; g.loss = loss;
+    if ((rs = grad_pass(g, st)) != RID_OK) return rs;
   }
-  hipLaunchKernelGGL(train_finish_kernel, dim3(K), dim3(256), 0, st,
-                     rho ? nullptr : W + lrows, B, loss, G, pm, (int)(wo_off + w[L]));
-  RID_HIP(hipGetLastError());
   return RID_OK;
 }
 
@@ -1104,13 +1344,9 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
   }
   const long long wo_off = off;
   const long long pm = (long long)e.per_model;
-  int tiles_max = 0;
-  for (int l = 0; l < L; ++l)
-    tiles_max = std::max(tiles_max, ((w[l + 1] + BM - 1) / BM) * ((w[l] + BN - 1) / BN));
-
   if (!input_mode && train_fused_supported(e))
     return mf_grad_fused(e, s, F, rho, B, loss, grad_out, grad_used, st, w, w_off, b_off,
-                         wo_off, tiles_max);
+                         wo_off);
 
   // the general form: residual layers, dropout (training only), raw CVs
   const bool res = e.resnet;
@@ -1123,8 +1359,8 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
   long long per_row = (long long)K * (8 + (res ? 2 : 0)) * wmax;
   for (int l = 0; l <= L; ++l) per_row += (long long)K * w[l] * (l > 0 ? 5 : 2);
   const int Bc = input_mode ? B : chunk_rows(per_row, B, e.train_budget, wmax);
-  int ks_max, kc;
-  wgrad_split(K, tiles_max, Bc, &ks_max, &kc);
+  int ks_max = 1;
+  for (int l = 0; l < L; ++l) ks_max = std::max(ks_max, wgrad_split(K, &w[l + 1], &w[l], 1, Bc).ks);
 
   // workspace (floats), sized for Bc rows; a pass of R <= Bc rows uses the
   // same regions with R-row strides
@@ -1151,7 +1387,7 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
   const long long part = tot; tot += part_slab * ks_max;
   const long long grad = tot; tot += (long long)e.n_params;
   const long long lrows = tot; tot += (long long)K * B;
-  const long long cpart = tot; tot += (long long)((Bc + kColRows - 1) / kColRows) * K * wmax;
+  const long long cpart = tot; tot += (long long)col_parts(Bc) * K * wmax;
   const long long bpart = tot; tot += (long long)ks_max * K * wmax;
   rid_status rs = e.ws_train.ensure(sizeof(float) * tot);
   if (rs != RID_OK) return rs;
@@ -1170,8 +1406,6 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
   for (int r0 = 0; r0 < B; r0 += Bc) {
     const int R = std::min(Bc, B - r0);
     const bool acc = r0 > 0;
-    int ks, kchunk;
-    wgrad_split(K, tiles_max, R, &ks, &kchunk);
     const float* sR = s + (size_t)r0 * n;
     const float* FR = rho ? nullptr : F + (size_t)r0 * n;
     const float* rhoR = rho ? rho + (size_t)r0 * K * n : nullptr;
@@ -1260,18 +1494,24 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
                          st, W + tt[l], W + dd[l], W + zd[l], W + lin, 2LL * R * w[l], w[l], R,
                          K, W + sbuf, 2LL * R * w[l]);
       RID_HIP(hipGetLastError());
-      // dW_l = S^T [h_{l-1}; hd_{l-1}]  (contraction over 2R rows, split)
+      // dW_l = S^T [h_{l-1}; hd_{l-1}]  (contraction over 2R rows, split),
+      // db_l = sum of lam_z; with layer 1, dw_o = sum_b hd_L and, on the last
+      // pass, the losses
       if (!input_mode) {
-        WgradArgs g{};
-        g.A = W + sbuf; g.sAb = 2LL * R * w[l]; g.lda = w[l];
-        g.B = W + hh[l - 1]; g.sBb = slab(l - 1); g.ldb = w[l - 1];
-        // db_l = sum over the primal rows of lam_z, in the same pass
-        g.csum_rows = R;
-        g.M = w[l]; g.N = w[l - 1]; g.Kc = 2 * R; g.batch = K; g.ksplit = ks;
-        g.kchunk = kchunk;
-        if ((rs = wgrad_into_grad(g, W + part, W + bpart, G, pm, w_off[l - 1], b_off[l - 1],
-                                  acc, st)) != RID_OK)
-          return rs;
+        GradPass g{};
+        const WgradSplit sp = wgrad_split(K, &w[l], &w[l - 1], 1, R);
+        g.nl = 1; g.K = K; g.R = R; g.ks = sp.ks; g.kchunk = sp.kchunk;
+        g.l[0] = GradLayer{W + sbuf, W + hh[l - 1], w[l], w[l - 1], w_off[l - 1], b_off[l - 1],
+                           nullptr};
+        g.part = W + part; g.bpart = W + bpart; g.cpart = W + cpart;
+        g.grad = G; g.pm = pm;
+        g.accumulate = acc; g.wo_off = wo_off; g.w = w[L];
+        if (l == 1) {
+          g.last = r0 + R >= B;
+          g.X = W + hh[L] + (long long)R * w[L]; g.sXb = slab(L);
+          g.rows = rho ? nullptr : W + lrows; g.B = B; g.loss = loss;
+        }
+        if ((rs = grad_pass(g, st)) != RID_OK) return rs;
       }
       if (l > 1 || input_mode) {
         // [lam_h ; lam_hd]_{l-1} = [lam_z ; lam_zd] W_l (+ [lam_h ; lam_hd]_l)
@@ -1297,15 +1537,7 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
       hvp->slab_lam = 2LL * B * X;
       return RID_OK;
     }
-    // dw_o = sum_b hd_L
-    if ((rs = colsum(W + hh[L] + (long long)R * w[L], slab(L), R, w[L], K, W + cpart, G, pm,
-                     (int)wo_off, acc, st)) != RID_OK)
-      return rs;
   }
-  // the loss, and db_o = 0 (the output bias never reaches grad_s A)
-  hipLaunchKernelGGL(train_finish_kernel, dim3(K), dim3(256), 0, st,
-                     rho ? nullptr : W + lrows, B, loss, G, pm, (int)(wo_off + w[L]));
-  RID_HIP(hipGetLastError());
   return RID_OK;
 }
 
