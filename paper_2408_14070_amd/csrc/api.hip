@@ -156,9 +156,8 @@ static rid_status alloc_kernel_weights(rid_ensemble_impl& e, int wmax) {
     s.bo = s.wo + n_wo;
     return RID_OK;
   }
-  // the 16-bit MLP kernels exist for padded widths 64, 128, 256 and 512 (zero
-  // units pad the rest: their weights, biases and outputs stay 0)
-  e.NP = wmax <= 64 ? 64 : wmax <= 128 ? 128 : wmax <= 256 ? 256 : 512;
+  // zero units pad the widths: their weights, biases and outputs stay 0
+  e.NP = split_width(wmax);
   e.XP = round_up(2 * e.n_cv, e.KF);
   e.layers.resize(e.L);
   size_t off = 0;

@@ -1,0 +1,17 @@
+// 16-bit MLP kernels at padded widths 64 and 128.
+#include "mlp_16_decl.h"
+#include "mlp_kernels_16.h"
+
+namespace rid {
+
+rid_status mlp_16_w64(int rt, const rid_ensemble_impl& e, const float* x, int B, float* A_out,
+                      float* g_out, const TorsionInput* t, hipStream_t st) {
+  return mlp16::run_width<64, false>(rt, e, x, B, A_out, g_out, t, st);
+}
+
+rid_status mlp_16_w128(int rt, const rid_ensemble_impl& e, const float* x, int B, float* A_out,
+                      float* g_out, const TorsionInput* t, hipStream_t st) {
+  return mlp16::run_width<128, false>(rt, e, x, B, A_out, g_out, t, st);
+}
+
+}  // namespace rid
