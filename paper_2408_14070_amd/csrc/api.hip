@@ -723,8 +723,7 @@ rid_status rid_mf_loss_grad(rid_ensemble ens, const float* d_s, const float* d_F
                             int B, float* d_loss, float* d_grad, rid_stream stream) {
   if (!ens || !d_s || !d_F || !d_grad) return fail(RID_EINVAL, "NULL argument");
   if (B < 1) return fail(RID_EINVAL, "B must be >= 1");
-  float* used = nullptr;
-  return launch_mf_grad(ens->impl, d_s, d_F, nullptr, B, d_loss, d_grad, &used,
+  return launch_mf_grad(ens->impl, d_s, d_F, nullptr, B, d_loss, d_grad,
                         (hipStream_t)stream);
 }
 
@@ -732,8 +731,7 @@ rid_status rid_mf_grad(rid_ensemble ens, const float* d_s, const float* d_rho,
                        int B, float* d_grad, rid_stream stream) {
   if (!ens || !d_s || !d_rho || !d_grad) return fail(RID_EINVAL, "NULL argument");
   if (B < 1) return fail(RID_EINVAL, "B must be >= 1");
-  float* used = nullptr;
-  return launch_mf_grad(ens->impl, d_s, nullptr, d_rho, B, nullptr, d_grad, &used,
+  return launch_mf_grad(ens->impl, d_s, nullptr, d_rho, B, nullptr, d_grad,
                         (hipStream_t)stream);
 }
 

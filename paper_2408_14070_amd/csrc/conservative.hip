@@ -186,7 +186,7 @@ rid_status launch_bias_conservative(const rid_system_impl& s, rid_ensemble_impl&
                                nullptr, nullptr, nullptr, flags, st);
   }
   InputHvp hvp;
-  if ((r = launch_mf_grad(e, d_s, nullptr, d_rho, B, nullptr, nullptr, nullptr, st, &hvp)) !=
+  if ((r = launch_mf_grad(e, d_s, nullptr, d_rho, B, nullptr, nullptr, st, &hvp)) !=
       RID_OK)
     return r;
   hipLaunchKernelGGL(cons_combine_kernel, dim3(grid), dim3(256), 0, st, d_s, d_rho, hvp.lam_x,

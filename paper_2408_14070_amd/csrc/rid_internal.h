@@ -291,9 +291,15 @@ struct InputHvp {
   const float* u0 = nullptr;
   long long slab_lam = 0;
 };
+// Adam's step on the parameters (theta null: none); c1, c2: its bias corrections.
+struct AdamStep {
+  float *theta, *m, *v;
+  float lr, c1, c2;
+};
 rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
                           const float* rho, int B, float* loss, float* grad_out,
-                          float** grad_used, hipStream_t st, InputHvp* hvp = nullptr);
+                          hipStream_t st, InputHvp* hvp = nullptr,
+                          const AdamStep& adam = AdamStep{});
 rid_status launch_mcmc(rid_ensemble_impl& e, float* s, int W, long long n_steps, long long t0,
                        double kT, float step, unsigned long long seed, int proj0, int proj1,
                        int nbins, unsigned* hist1, unsigned* hist2,
