@@ -115,7 +115,8 @@ __global__ void cons_combine_kernel(const float* s, const float* rho, const floa
 }
 
 // The same with the fused kernel's per-member terms T [K][B][n] (read only
-// where coef is nonzero: the kernel skips tiles outside the band).
+// where coef is nonzero: the kernel skips tiles outside the band), for more
+// members or CVs than the scatter sums in registers.
 __global__ void cons_combine_terms_kernel(const float* T, const float* gbar, const float* coef,
                                           const float* sig_w, int K, int B, int n,
                                           float* fcv) {
@@ -125,19 +126,8 @@ __global__ void cons_combine_terms_kernel(const float* T, const float* gbar, con
     const int b = (int)(e / n);
     const float cb = coef[b];
     float de = 0.f;
-    if (cb != 0.f) {
-      if (K <= kRegMembers) {
-        // every member's term in flight at once, added in member order
-        float t[kRegMembers];
-#pragma unroll
-        for (int k = 0; k < kRegMembers; ++k) t[k] = T[min(k, K - 1) * total + e];
-#pragma unroll
-        for (int k = 0; k < kRegMembers; ++k)
-          if (k < K) de += t[k];
-      } else {
-        for (int k = 0; k < K; ++k) de += T[k * total + e];
-      }
-    }
+    if (cb != 0.f)
+      for (int k = 0; k < K; ++k) de += T[k * total + e];
     fcv[e] = sig_w[b] * gbar[e] + cb * de;
   }
 }
@@ -179,6 +169,8 @@ rid_status launch_bias_conservative(const rid_system_impl& s, rid_ensemble_impl&
   if (fused) {
     float* d_T = d_sig + B;
     if ((r = launch_hvp(e, e.ws_x.as<float>(), d_rho, d_coef, B, d_T, st)) != RID_OK) return r;
+    if (scatter_in_regs(K, n))
+      return launch_terms_scatter(s, K, pos, B, d_T, d_gbar, d_coef, d_sig, force, flags, st);
     hipLaunchKernelGGL(cons_combine_terms_kernel, dim3(grid), dim3(256), 0, st, d_T, d_gbar,
                        d_coef, d_sig, K, B, n, d_fcv);
     RID_HIP(hipGetLastError());

@@ -114,6 +114,12 @@ struct ScatterArgs {
   float* sigma;
   uint8_t* flags;
   size_t fstride, ostride;
+  // conservative switching (TERMS): the CV force is
+  // sig_w gbar + coef sum_k terms[k]; terms [K][B][n], read where coef != 0
+  const float* terms;
+  const float* gbar;
+  const float* coef;
+  const float* sig_w;
 };
 
 // The system's small index tables (unique atoms, local quads, CSR inverse
@@ -123,7 +129,10 @@ struct ScatterArgs {
 // issues the loads of its walker's member results (held in registers), the
 // table copy runs while they are in flight, and the atom gather follows the
 // barrier, so a walker waits on memory twice in all; otherwise the members'
-// results are read inside the statistics (any K and n).
+// results are read inside the statistics (any K and n).  TERMS (with REG): the
+// CV force comes from the conservative path's per-member terms, summed here in
+// member order (a launch of its own for that took 4.7 us of a 60 us call at
+// 500 walkers).
 constexpr int kScatterWaves = 4;
 constexpr int kLocalMapMaxAtoms = 4096;
 
@@ -131,7 +140,7 @@ __host__ __device__ inline int scatter_table_ints(int U, int n, int n_atoms) {
   return U + 4 * n + (U + 1) + 4 * n + (n_atoms <= kLocalMapMaxAtoms ? n_atoms : 0);
 }
 
-template <bool REG>
+template <bool REG, bool TERMS>
 __global__ __launch_bounds__(kScatterWaves * kWave) void scatter_kernel(ScatterArgs a) {
   extern __shared__ float sm[];
   const SysView& g = a.sv;
@@ -158,7 +167,18 @@ __global__ __launch_bounds__(kScatterWaves * kWave) void scatter_kernel(ScatterA
     tv[m] = g.uniq[ti[m]];
   }
   WalkerRegs r;
-  if (REG && live) walker_prefetch(r, a.A, a.g, a.fcv, a.K, a.B, n, w, lane);
+  float gb[kRegPasses], coef = 0.f, sw = 0.f;
+  if constexpr (TERMS) {
+    if (live) {
+      walker_prefetch(r, a.terms, a.terms, nullptr, a.K, a.B, n, w, lane);
+#pragma unroll
+      for (int p = 0; p < kRegPasses; ++p) gb[p] = a.gbar[(size_t)w * n + min(lane + p * kWave, n - 1)];
+      coef = a.coef[w];
+      sw = a.sig_w[w];
+    }
+  } else if (REG && live) {
+    walker_prefetch(r, a.A, a.g, a.fcv, a.K, a.B, n, w, lane);
+  }
 #pragma unroll
   for (int m = 0; m < kGatherBatch; ++m) t[ti[m]] = tv[m];
   if (n_tab > kGatherBatch * nt)
@@ -195,7 +215,18 @@ __global__ __launch_bounds__(kScatterWaves * kWave) void scatter_kernel(ScatterA
     gather_atoms(sp, pw, t_uniq, U, lane, kWave);
   }
   float sig = 1.f;
-  if (a.g) {
+  if constexpr (TERMS) {
+#pragma unroll
+    for (int p = 0; p < kRegPasses; ++p) {
+      float de = 0.f;
+      if (coef != 0.f) {
+#pragma unroll
+        for (int k = 0; k < kRegMembers; ++k)
+          if (k < a.K) de += r.g[p][k];
+      }
+      if (lane + p * kWave < n) fc[lane + p * kWave] = sw * gb[p] + coef * de;
+    }
+  } else if (a.g) {
     double abar;
     const double e = scatter_stats_reg(r, a.K, n, fc, abar, lane);
     sig = switch_outputs(e, abar, a.eps0, a.eps1, w, a.energy, a.eps, a.sigma, lane,
@@ -244,27 +275,14 @@ rid_status launch_ensemble_reduce(int K, int n, int B, const float* A,
   return RID_OK;
 }
 
-rid_status launch_bias_scatter(const rid_system_impl& s, int K, const float* pos,
-                               int B, const float* A, const float* g,
-                               const float* fcv, float eps0, float eps1,
-                               float* force, float* energy, float* eps,
-                               float* sigma, uint8_t* flags, hipStream_t st,
-                               int rec_stride) {
-  ScatterArgs a{};
+static rid_status launch_scatter(const rid_system_impl& s, ScatterArgs& a, const float* pos,
+                                 int B, float* force, uint8_t* flags, int rec_stride,
+                                 hipStream_t st) {
   a.sv = SysView{s.n_atoms, s.n_uniq, s.n_cv, s.d_uniq, s.d_lquads, s.d_csr_ptr,
                  s.d_csr_ent, s.d_atom_local};
   a.pos = pos;
-  a.K = K;
   a.B = B;
-  a.A = A;
-  a.g = g;
-  a.fcv = fcv;
-  a.eps0 = eps0;
-  a.eps1 = eps1;
   a.force = force;
-  a.energy = energy;
-  a.eps = eps;
-  a.sigma = sigma;
   a.flags = flags;
   a.fstride = rec_stride > 0 ? (size_t)rec_stride : (size_t)s.n_atoms * 3;
   a.ostride = rec_stride > 0 ? (size_t)rec_stride : 1;
@@ -272,19 +290,57 @@ rid_status launch_bias_scatter(const rid_system_impl& s, int K, const float* pos
       sizeof(float) * (scatter_table_ints(s.n_uniq, s.n_cv, s.n_atoms) +
                        (size_t)kScatterWaves * scatter_lds_floats(s.n_uniq, s.n_cv));
   if (lds > 160 * 1024) return fail(RID_EUNSUPPORTED, "too many torsion atoms for the scatter");
-  static size_t attr[2] = {0, 0};
+  static size_t attr[3] = {0, 0, 0};
   // members' results in registers when they fit (K <= 8, n <= 128)
-  const bool reg = (g == nullptr || K <= kRegMembers) && s.n_cv <= kRegPasses * kWave;
-  auto kern = reg ? scatter_kernel<true> : scatter_kernel<false>;
-  if (lds > 64 * 1024 && lds > attr[reg]) {
+  const bool reg = scatter_in_regs(a.g || a.terms ? a.K : 1, s.n_cv);
+  if (a.terms && !reg) return fail(RID_EUNSUPPORTED, "terms form of the scatter: too many members or CVs");
+  const int ki = a.terms ? 2 : reg;
+  auto kern = a.terms ? scatter_kernel<true, true>
+              : reg   ? scatter_kernel<true, false>
+                      : scatter_kernel<false, false>;
+  if (lds > 64 * 1024 && lds > attr[ki]) {
     RID_HIP(hipFuncSetAttribute((const void*)kern,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr[reg] = lds;
+    attr[ki] = lds;
   }
   launch_timed(kProfScatter, kern, dim3((B + kScatterWaves - 1) / kScatterWaves),
                dim3(kScatterWaves * kWave), (uint32_t)lds, st, a);
   RID_HIP(hipGetLastError());
   return RID_OK;
+}
+
+bool scatter_in_regs(int K, int n) { return K <= kRegMembers && n <= kRegPasses * kWave; }
+
+rid_status launch_bias_scatter(const rid_system_impl& s, int K, const float* pos,
+                               int B, const float* A, const float* g,
+                               const float* fcv, float eps0, float eps1,
+                               float* force, float* energy, float* eps,
+                               float* sigma, uint8_t* flags, hipStream_t st,
+                               int rec_stride) {
+  ScatterArgs a{};
+  a.K = K;
+  a.A = A;
+  a.g = g;
+  a.fcv = fcv;
+  a.eps0 = eps0;
+  a.eps1 = eps1;
+  a.energy = energy;
+  a.eps = eps;
+  a.sigma = sigma;
+  return launch_scatter(s, a, pos, B, force, flags, rec_stride, st);
+}
+
+rid_status launch_terms_scatter(const rid_system_impl& s, int K, const float* pos, int B,
+                                const float* terms, const float* gbar, const float* coef,
+                                const float* sig_w, float* force, uint8_t* flags,
+                                hipStream_t st) {
+  ScatterArgs a{};
+  a.K = K;
+  a.terms = terms;
+  a.gbar = gbar;
+  a.coef = coef;
+  a.sig_w = sig_w;
+  return launch_scatter(s, a, pos, B, force, flags, 0, st);
 }
 
 }  // namespace rid

@@ -261,6 +261,13 @@ rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, in
 rid_status launch_ensemble_reduce(int K, int n, int B, const float* A,
                                   const float* g, float* eps, float* gbar,
                                   float* A_t, float* g_t, hipStream_t st);
+// The scatter of a conservative call: CV force sig_w gbar + coef sum_k terms[k]
+// (terms [K][B][n], read where coef != 0); K and n as scatter_in_regs wants.
+bool scatter_in_regs(int K, int n);
+rid_status launch_terms_scatter(const rid_system_impl& s, int K, const float* pos, int B,
+                                const float* terms, const float* gbar, const float* coef,
+                                const float* sig_w, float* force, uint8_t* flags,
+                                hipStream_t st);
 rid_status launch_bias_scatter(const rid_system_impl& s, int K, const float* pos,
                                int B, const float* A, const float* g,
                                const float* fcv, float eps0, float eps1,

@@ -152,3 +152,10 @@ def test_conservative_force_at_tile_edges(torch, rid, res, dist, widths, K, B, r
     bound = walker_bounds(got["eps"].astype(np.float64), ref["eps"], e0, e1)
     assert_walkers(got["F"], ref["F"], bound, f"{res} residues {widths} res={resnet}")
     assert np.abs(got["E"] - ref["E"]).max() <= FP32_TOL * max(1.0, np.abs(ref["E"]).max())
+
+
+# the scatter sums the members' terms in registers up to 8 members and 128 CVs
+# (64 CVs a pass), a launch of its own does beyond
+@pytest.mark.parametrize("res,K", [(20, 8), (20, 9), (33, 3), (34, 3), (65, 2), (66, 2)])
+def test_conservative_members_and_cvs(torch, rid, res, K):
+    test_conservative_force_at_tile_edges(torch, rid, res, 0, [64] * 2, K, 21, False)
