@@ -182,14 +182,6 @@ static rid_status alloc_kernel_weights(rid_ensemble_impl& e, int wmax) {
 
 using namespace rid;
 
-// Batches up to this many walkers gather torsion atoms inside the MLP kernel
-// (one launch less); larger ones encode the CVs once into HBM first, so the
-// K members' workgroups read a compact [B][2n] encoding instead of each
-// re-reading the positions.
-#ifndef RID_FROM_POS_MAX_B
-#define RID_FROM_POS_MAX_B 4096
-#endif
-
 namespace rid {
 
 rid_status bias_force_check(const rid_system_s* sys, const rid_ensemble_s* ens,
@@ -213,10 +205,9 @@ rid_status bias_force_core(rid_system_impl& s, rid_ensemble_impl& e, const float
   rid_status r;
   if ((r = ensure_packed(e, st)) != RID_OK) return r;
   const TorsionInput tin{&s, d_pos};
-  r = B <= RID_FROM_POS_MAX_B ? launch_mlp_from_pos(e, tin, B, A, g, st) : RID_EUNSUPPORTED;
+  r = launch_mlp_from_pos(e, tin, B, A, g, st);
   if (r == RID_EUNSUPPORTED) {
-    // large batch, or too many torsion atoms for the in-kernel gather:
-    // encode in HBM first
+    // where the in-kernel torsions would cost more: encode in HBM first
     if (!x) {
       if ((r = e.ws_x.ensure(sizeof(float) * 2 * e.n_cv * (size_t)B)) != RID_OK) return r;
       x = e.ws_x.as<float>();

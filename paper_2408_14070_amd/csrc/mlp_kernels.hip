@@ -4,6 +4,7 @@
 #include "device_common.h"
 #include "mlp_16_decl.h"
 #include "mlp_kernels_16.h"
+#include "mlp_kernels_f32.h"
 
 namespace rid {
 namespace {
@@ -137,9 +138,8 @@ __global__ void pack_kernel(const float* master, size_t per_model, PackAll pa,
 // paid (16384 walkers: 22.6 / 22.7 / 27.6 at 64, 44 / 35 / 37 at 128,
 // 84 / 58 / 61 at 192); 32 do past a round (2001 walkers 10.5 / 10.3 and
 // 14.0 / 13.3 at 128 and 192; 1000: 8.3 / 9.0 and 10.9 / 11.2), at 64 only
-// where workgroups outnumber the CUs' places.  The tile must fit LDS, and on
-// the bias path hold the torsion atoms of a walker.
-int rows_16(const rid_ensemble_impl& e, int B, const TorsionInput* t) {
+// where workgroups outnumber the CUs' places.  The tile must fit LDS.
+int rows_16(const rid_ensemble_impl& e, int B) {
   const int NP = e.NP, NW = mlp16::waves(NP);
   auto wgs = [&](int rt) { return (long long)((B + 16 * rt - 1) / (16 * rt)) * e.K; };
   const double round[3] = {1.0, 1.35, NP > 256 ? 2.0 : 2.45};
@@ -148,7 +148,7 @@ int rows_16(const rid_ensemble_impl& e, int B, const TorsionInput* t) {
   bool found = false;
   for (int i = 0, rt = 1; rt <= (NP >= 256 && e.L <= 4 ? 4 : 2); rt *= 2, ++i) {
     int rc = 1;
-    if (mlp16::lds_bytes(e, 16 * rt, NW, t, &rc) > 160 * 1024 || (t && rc < 1)) continue;
+    if (mlp16::lds_bytes(e, 16 * rt, NW, nullptr, &rc) > 160 * 1024) continue;
     double c = round[i] * (double)((wgs(rt) + 255) / 256);
     if (NP <= 192) c = rt == (wgs(1) > (NP == 64 ? 2048 : 256) ? 2 : 1) ? 0.0 : 1.0;
     if (!found || c < least) {
@@ -160,11 +160,39 @@ int rows_16(const rid_ensemble_impl& e, int B, const TorsionInput* t) {
   return best;
 }
 
+// Whether the MLP kernel computes its walkers' torsions itself (a launch less)
+// or the CVs are encoded first: in the kernel every member does it again, a
+// wave at a time.  It pays where the call is one round of 16-walker workgroups,
+// their atoms fit one gather pass, and a wave has few torsions.  Measured, time
+// encoding first over time in the kernel (4 members, 4 hidden layers, 1 to 1000
+// walkers): 2 CVs 1.03 to 1.12 (1.20 for one walker at width 64, where 100 take
+// 0.92); 18 CVs 1.00 to 1.08, but 0.87 to 0.96 at width 64 (72 CVs a wave);
+// 38 CVs, FP32, 1.04 to 1.06 at widths 192 to 320 (38 or 76 a wave), 0.86 at 64
+// (152), and, FP16, 0.93 to 1.00 at 128 to 320 (76); 120 CVs (atoms in several
+// passes) 0.35 to 1.00.  From 1500 walkers on 0.40 to 1.03.
+bool gather_pays(const rid_ensemble_impl& e, const TorsionInput& t, int B) {
+  if ((long long)((B + 15) / 16) * e.K > 256) return false;
+  const bool f32 = e.prec == RID_FP32;
+  int rc = 0, waves;
+  if (f32) {
+    const int NP = e.split.NP;
+    MlpF32Args a{};
+    (void)mlp_f32_layout(NP, 16, 6, e.split.XP, e.n_cv, t.sys->n_uniq, true, a);
+    rc = a.rc;
+    waves = NP <= 256 ? NP / 16 : NP == 512 && !e.resnet ? 16 : NP == 512 ? 8 : NP / 32;
+  } else {
+    waves = mlp16::waves(e.NP);
+    (void)mlp16::lds_bytes(e, 16, waves, &t, &rc);
+  }
+  const int cvs = (16 + waves - 1) / waves * e.n_cv;   // torsions a wave computes
+  return rc >= 16 && cvs <= (f32 ? 80 : 64);
+}
+
 rid_status dispatch(const rid_ensemble_impl& e, const float* x, int B, float* A_out,
                     float* g_out, const TorsionInput* t, hipStream_t st) {
   if (e.prec == RID_FP32) return dispatch_mlp_f32(e, x, B, A_out, g_out, t, st);
   if (e.resnet) return fail(RID_EUNSUPPORTED, "residual connections need an FP32 ensemble");
-  const int rt = rows_16(e, B, t);
+  const int rt = t ? 1 : rows_16(e, B);
   switch (e.NP) {
     case 64: return mlp_16_w64(rt, e, x, B, A_out, g_out, t, st);
     case 128: return mlp_16_w128(rt, e, x, B, A_out, g_out, t, st);
@@ -188,8 +216,8 @@ rid_status launch_mlp(const rid_ensemble_impl& e, const float* x, int B,
 rid_status launch_mlp_from_pos(const rid_ensemble_impl& e, const TorsionInput& tin,
                                int B, float* A_out, float* g_out, hipStream_t st) {
   // the in-kernel gather computes torsions only: systems with distance CVs
-  // take the encoding from cv_eval_kernel
-  if (tin.sys->has_dist) return RID_EUNSUPPORTED;
+  // take the encoding from cv_eval_kernel, as calls do where that is cheaper
+  if (tin.sys->has_dist || !gather_pays(e, tin, B)) return RID_EUNSUPPORTED;
   return dispatch(e, nullptr, B, A_out, g_out, &tin, st);
 }
 

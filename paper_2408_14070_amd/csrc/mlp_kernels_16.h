@@ -815,9 +815,13 @@ rid_status run_mlp(const rid_ensemble_impl& e, const float* x, int B,
   // without g_out only the free energies are computed (plain input only)
   const bool grad = g_out != nullptr;
   if (!grad && from_pos) return fail(RID_EUNSUPPORTED, "energy-only path takes the encoding");
-  auto kern = !grad    ? mlp_kernel<PL, NP, RT, NW, LM, false, false>
-              : from_pos ? mlp_kernel<PL, NP, RT, NW, LM, true, true>
-                         : mlp_kernel<PL, NP, RT, NW, LM, false, true>;
+  auto kern = grad ? mlp_kernel<PL, NP, RT, NW, LM, false, true>
+                   : mlp_kernel<PL, NP, RT, NW, LM, false, false>;
+  if constexpr (RT == 1) {             // (gather_pays: single tiles only)
+    if (from_pos) kern = mlp_kernel<PL, NP, RT, NW, LM, true, true>;
+  } else if (from_pos) {
+    return fail(RID_EUNSUPPORTED, "in-kernel torsions take 16 walkers a workgroup");
+  }
   const int ki = grad ? (from_pos ? 1 : 0) : 2;
   if (lds > 64 * 1024 && lds > attr_bytes[ki]) {
     RID_HIP(hipFuncSetAttribute((const void*)kern,

@@ -548,9 +548,13 @@ rid_status run_mlp_f32(const rid_ensemble_impl& e, const float* x, int B, float*
   if (from_pos && a.rc < 1)
     return fail(RID_EUNSUPPORTED, "too many torsion atoms to gather in-kernel");
   if (!grad && from_pos) return fail(RID_EUNSUPPORTED, "energy-only path takes the encoding");
-  auto kern = !grad      ? dev::mlp_f32_kernel<NP, RT, NW, LM, false, false, RES>
-              : from_pos ? dev::mlp_f32_kernel<NP, RT, NW, LM, true, true, RES>
-                         : dev::mlp_f32_kernel<NP, RT, NW, LM, false, true, RES>;
+  auto kern = grad ? dev::mlp_f32_kernel<NP, RT, NW, LM, false, true, RES>
+                   : dev::mlp_f32_kernel<NP, RT, NW, LM, false, false, RES>;
+  if constexpr (RT == 1) {             // (gather_pays: single tiles only)
+    if (from_pos) kern = dev::mlp_f32_kernel<NP, RT, NW, LM, true, true, RES>;
+  } else if (from_pos) {
+    return fail(RID_EUNSUPPORTED, "in-kernel torsions take 16 walkers a workgroup");
+  }
   const int ki = grad ? (from_pos ? 1 : 0) : 2;
   if (lds > 64 * 1024 && lds > attr_bytes[ki]) {
     RID_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -251,7 +251,7 @@ rid_status dispatch_mlp_f32(const rid_ensemble_impl& e, const float* x, int B, f
         160 * 1024)
       break;
   }
-  const int rt = split_rows(s.NP, B, e.K, most);
+  const int rt = t ? 1 : split_rows(s.NP, B, e.K, most);
   switch (s.NP) {
     case 64: return mlp_f32_w64(rt, e, x, B, A_out, g_out, t, st);
     case 128: return mlp_f32_w128(rt, e, x, B, A_out, g_out, t, st);

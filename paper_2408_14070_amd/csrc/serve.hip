@@ -246,7 +246,7 @@ rid_status Server::launch(const Batch& b, const ServeModel& m) {
   }
   const TorsionInput tin{m.sys, pos};
   rid_status rs = launch_mlp_from_pos(*m.ens, tin, W, A, g, st);
-  if (rs == RID_EUNSUPPORTED) {   // too many torsion atoms for the in-kernel gather
+  if (rs == RID_EUNSUPPORTED) {   // cheaper with the CVs encoded first
     rs = launch_cv_eval(*m.sys, pos, W, nullptr, x, st);
     if (rs == RID_OK) rs = launch_mlp(*m.ens, x, W, A, g, st);
   }

@@ -110,3 +110,28 @@ def test_positions_in_every_row_tile(torch, rid, width, K):
     for lo, hi in ((0, 1), (100, 137), (B - 20, B)):
         for a, b in zip(full, run(dev[lo:hi])):
             assert np.array_equal(a[lo:hi], b)
+
+
+@pytest.mark.parametrize("res,prec,width,K", [
+    (2, "fp32", 64, 4), (2, "fp16", 100, 3), (10, "fp16", 128, 4), (10, "bf16", 300, 4),
+    (10, "fp32", 300, 4), (20, "fp32", 192, 3), (20, "fp32", 256, 4), (16, "bf16_all", 384, 4),
+    (13, "fp16", 512, 8), (10, "fp32", 512, 4)])
+def test_torsions_in_the_kernel_and_encoded_first(torch, rid, res, prec, width, K):
+    """Calls of one round of workgroups with few torsions a wave compute them
+    in the MLP kernel, larger ones encode first: the same bits."""
+    sys_ = ridgen.chain_system(res, 12)
+    n, B, widths = sys_.n_cv, 16 * (256 // K + 2), [width] * 3
+    pos = torch.from_numpy(ridgen.f32(ridgen.chain_coords(sys_, B, 4))).cuda()
+    S = rid.System(sys_.n_atoms, sys_.quads)
+    E = rid.Ensemble(n, widths, K, ridgen.xavier_ensemble(2 * n, widths, K, 6, bias_std=0.1),
+                     getattr(rid, "RID_" + prec.upper()))
+
+    def run(p):
+        out = rid.bias_force(S, E, p.contiguous(), 0.5, 2.0)
+        torch.cuda.synchronize()
+        return [out[q].cpu().numpy() for q in ("F", "E", "eps", "sigma", "flags")]
+
+    full = run(pos)
+    for lo, hi in ((0, 1), (100, 137), (B - 300, B)):
+        for a, b in zip(full, run(pos[lo:hi])):
+            assert np.array_equal(a[lo:hi], b)
