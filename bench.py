@@ -34,8 +34,8 @@ sys.path.insert(0, ROOT)
 import ridgen  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
-FP32_PEAK_TFLOPS = 157.3
 BF16_PEAK_TFLOPS = 2500.0     # dense; FP16 has the same dense peak
+SPLIT_PEAK_TFLOPS = BF16_PEAK_TFLOPS / 3   # FP32 ensembles: three FP16 MFMAs per product
 
 
 def log(msg):
@@ -161,7 +161,7 @@ def kernel_source_hash():
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_2408_14070_amd", "csrc")
     for f in sorted(os.listdir(d)):
-        if f.startswith("mlp_kernels") or f == "device_common.h":
+        if f.startswith("mlp_") or f == "device_common.h":
             h.update(open(os.path.join(d, f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -169,13 +169,15 @@ def kernel_source_hash():
 def train_source_hash():
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_2408_14070_amd", "csrc")
-    for f in ("train_kernels.hip", "mlp_kernels.hip", "device_common.h"):
+    for f in sorted(os.listdir(d)):
+        if not f.startswith("train_") and f not in ("mlp_split.h", "device_common.h"):
+            continue
         h.update(open(os.path.join(d, f), "rb").read())
     return h.hexdigest()[:16]
 
 
 # training kernels the counter passes summarize: key, name test
-TRAIN_PMC_KEYS = (("train_kernel_4x256_b4096", lambda n: "train_kernel<" in n),
+TRAIN_PMC_KEYS = (("train_kernel_4x256_b4096", lambda n: "train_f32_kernel" in n),
                   ("wgrad_kernel_4x256_b4096", lambda n: "wgrad_kernel" in n))
 
 
@@ -292,21 +294,26 @@ def _read_counters(d):
 
 
 def _mlp_signature(name):
-    """(formats, (NP, RT, NW, LM), (FROM_POS, GRAD, RES)) of an mlp_kernel
-    instance from its demangled or mangled name, or None.  Mangled names
-    (the host demangler may not know _Float16): the Plan's first three
-    template arguments are rid::(anonymous)::<format> names, written out
+    """(formats, (NP, RT, NW, LM), (FROM_POS, GRAD, RES)) of an mlp_kernel or
+    mlp_f32_kernel instance from its demangled or mangled name, or None.
+    Mangled names (the host demangler may not know _Float16): the Plan's first
+    three template arguments are rid::mlp16::<format> names, written out
     (NS0_<n><name>E) or as substitutions S<k>_; the names met in the argument
-    list enter the substitution table after rid, the anonymous namespace,
-    mlp_kernel and Plan (indices 0-3), so S<k>_ is the (k - 3)-th of them."""
+    list enter the substitution table after rid, mlp16, mlp_kernel and Plan
+    (indices 0-3), so S<k>_ is the (k - 3)-th of them."""
     import re
-    m = re.search(r"mlp_kernel<[^<>]*Plan<([^<>]*)>\s*,\s*(\d+)\s*,\s*(\d+)\s*,\s*(\d+)\s*,"
-                  r"\s*(\d+)\s*,\s*(true|false)\s*,\s*(true|false)\s*,\s*(true|false)", name)
+    tail = r"\s*(\d+)\s*,\s*(\d+)\s*,\s*(\d+)\s*,\s*(\d+)\s*,\s*(true|false)\s*,\s*(true|false)"
+    m = (re.search(r"mlp_f32_kernel<" + tail + r"\s*,\s*(true|false)", name) or
+         re.search(r"mlp_f32_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELb([01])ELb([01])E",
+                   name))
+    if m:
+        return (["F32"] * 3, tuple(int(m.group(k)) for k in range(1, 5)),
+                tuple(m.group(k) in ("true", "1") for k in range(5, 8)))
+    m = re.search(r"mlp_kernel<[^<>]*Plan<([^<>]*)>\s*," + tail, name)
     if m:
         fmts = [re.sub(r".*::", "", f.strip()) for f in m.group(1).split(",")][:3]
         ints = tuple(int(m.group(k)) for k in range(2, 6))
-        flags = tuple(m.group(k) == "true" for k in range(6, 9))
-        return fmts, ints, flags
+        return fmts, ints, (m.group(6) == "true", m.group(7) == "true", False)
     tag = "mlp_kernelINS0_4PlanI"
     i = name.find(tag)
     if i < 0:
@@ -330,11 +337,11 @@ def _mlp_signature(name):
             return None
         fmts.append(seen[k - 4])
         pos += m.end()
-    m = re.search(r"ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELb([01])ELb([01])E", name[pos:])
+    m = re.search(r"ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELb([01])E", name[pos:])
     if not m:
         return None
     return (fmts, tuple(int(m.group(k)) for k in range(1, 5)),
-            tuple(m.group(k) == "1" for k in range(5, 8)))
+            (m.group(5) == "1", m.group(6) == "1", False))
 
 
 def mlp_display(name):
@@ -449,8 +456,11 @@ def pmc_summary(out_path, *dirs):
             rec["mfma_busy"] = rec["SQ_VALU_MFMA_BUSY_CYCLES"] / (N_SIMD * rec["SQ_BUSY_CU_CYCLES"])
             if rec.get("_duration_ns"):
                 rec["clock_ghz"] = rec["SQ_BUSY_CU_CYCLES"] / N_CU / rec["_duration_ns"]
-        if rec.get("SQ_INSTS_VALU_MFMA_MOPS_F32") is not None:
-            rec["mfma_flop"] = 512.0 * rec["SQ_INSTS_VALU_MFMA_MOPS_F32"]
+        if any(v is not None for v in (rec.get("SQ_INSTS_VALU_MFMA_MOPS_F16"),
+                                       rec.get("SQ_INSTS_VALU_MFMA_MOPS_F32"))):
+            rec["mfma_flop"] = 512.0 * sum(rec.get(c) or 0.0 for c in (
+                "SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_INSTS_VALU_MFMA_MOPS_F16",
+                "SQ_INSTS_VALU_MFMA_MOPS_F32"))
         res[key] = rec
     with open(out_path, "w") as fh:
         json.dump(res, fh, indent=1)
@@ -559,7 +569,8 @@ PRECISION_ARITH = {
             "FP32 switch, FP64 variance",
     "BF16_ALL": "every GEMM operand BF16 (the plain BF16 form, for comparison), FP32 "
                 "accumulate, tanh' stored BF16, FP32 switch, FP64 variance",
-    "FP32": "every GEMM on FP32 MFMA (the FP32 path at the precision form's shape)",
+    "FP32": "every product as three FP16 MFMAs of split FP32 operands (the FP32 path at the "
+            "precision form's shape)",
 }
 
 
@@ -574,10 +585,10 @@ def bench_precision(rid, torch, sys20, prec, name, steps, warmup, samples):
     samples[name.lower()] = sample_outputs(cb, 128)
     fl = mlp_flops_per_walker(sys20.n_cv, wb, Kb) * Bb
     ach = fl / (kern["mlp"] * 1e-3) / 1e12
-    peak = FP32_PEAK_TFLOPS if name == "FP32" else BF16_PEAK_TFLOPS
+    peak = SPLIT_PEAK_TFLOPS if name == "FP32" else BF16_PEAK_TFLOPS
     return {
         "workload": f"same chain; ensemble 8 x [512 x 4], {PRECISION_ARITH[name]}; 16384 "
-                    "walkers (CVs encoded once by cv_eval, then mlp_kernel)",
+                    "walkers (CVs encoded once by cv_eval, then the MLP kernel)",
         "value": Bb * steps / el, "unit": "walker-steps/s", "ms_per_step": 1e3 * el / steps,
         "call_us_percentiles": call_pct,
         "roofline": {"bound": "mfma", "achieved": ach, "peak": peak,
@@ -604,8 +615,8 @@ def bench_variants(rid, torch, sys20, steps, warmup):
         "workload": "headline chain and ensemble with residual connections between the "
                     "hidden layers (h_l = h_{l-1} + tanh(W_l h_{l-1} + b_l), l >= 2)",
         "value": B * steps / el, "unit": "walker-steps/s", "ms_per_step": 1e3 * el / steps,
-        "roofline": {"bound": "mfma", "achieved": ach, "peak": FP32_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": ach / FP32_PEAK_TFLOPS,
+        "roofline": {"bound": "mfma", "achieved": ach, "peak": SPLIT_PEAK_TFLOPS,
+                     "unit": "TFLOP/s", "frac": ach / SPLIT_PEAK_TFLOPS,
                      "avg_launch_us": kern["mlp"] * 1e3, "flop_per_launch": fl},
         "kernels_us": {k: v * 1e3 for k, v in kern.items()},
     }
@@ -619,8 +630,8 @@ def bench_variants(rid, torch, sys20, steps, warmup):
         "workload": "headline chain with 6 CA-CA distance CVs among its 38 torsions (44 CVs, "
                     "angular mask 0 for the distances), headline ensemble shape",
         "value": B * steps / el, "unit": "walker-steps/s", "ms_per_step": 1e3 * el / steps,
-        "roofline": {"bound": "mfma", "achieved": ach, "peak": FP32_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": ach / FP32_PEAK_TFLOPS,
+        "roofline": {"bound": "mfma", "achieved": ach, "peak": SPLIT_PEAK_TFLOPS,
+                     "unit": "TFLOP/s", "frac": ach / SPLIT_PEAK_TFLOPS,
                      "avg_launch_us": kern["mlp"] * 1e3, "flop_per_launch": fl},
         "kernels_us": {k: v * 1e3 for k, v in kern.items()},
     }
@@ -669,7 +680,7 @@ def bench_training(rid, torch, steps=20, warmup=3, samples=None):
     torch.cuda.synchronize()
     big_s = (time.perf_counter() - t2) / big_steps
     # the paper's own Train example (chignolin: 18 torsion CVs, 4 x [300 x 4],
-    # residual connections, dropout 0.1, batch 128): the general sweeps
+    # residual connections, dropout 0.1, batch 128)
     pn, pw, pK, pB = 18, [300] * 4, 4, 128
     ps_all, pF_all, _ = ridgen.mf_training_set(pB * 64, pn)
     PS = torch.from_numpy(ps_all).cuda()
@@ -691,7 +702,7 @@ def bench_training(rid, torch, steps=20, warmup=3, samples=None):
                     "200k resident samples, double backward + Adam, FP32",
         "value": B / step_s, "unit": "samples/s", "ms_per_step": 1e3 * step_s,
         "flop_per_step": fl,
-        "achieved_tflops": fl / step_s / 1e12, "frac_fp32_peak": fl / step_s / 1e12 / FP32_PEAK_TFLOPS,
+        "achieved_tflops": fl / step_s / 1e12, "frac_split_peak": fl / step_s / 1e12 / SPLIT_PEAK_TFLOPS,
         "loss_first_last": [float(losses[0].mean()), float(losses[-1].mean())],
         # MFMA busy and effective clock of the step's two MFMA kernels, from
         # the committed counter passes when they match the current sources
@@ -702,7 +713,7 @@ def bench_training(rid, torch, steps=20, warmup=3, samples=None):
                         "note": "activations of one pass over the batch (~1.1 GB) exceed "
                                 "the 512 MiB training budget: the step runs in row chunks"},
         "paper_train_example": {"workload": "18 torsion CVs, 4 x [300 x 4], residual, "
-                                            "dropout 0.1, batch 128 (separate GEMM sweeps)",
+                                            "dropout 0.1, batch 128",
                                 "value": pB / paper_s, "unit": "samples/s",
                                 "ms_per_step": 1e3 * paper_s},
     }
@@ -743,13 +754,13 @@ def bench_conservative(rid, torch, case, steps=40, warmup=5):
          "value": B / st, "unit": "walker-steps/s", "ms_per_step": 1e3 * st,
          "frozen_ms_per_step": 1e3 * res["frozen"],
          "flop_per_step": fl, "achieved_tflops": fl / st / 1e12,
-         "frac_fp32_peak": fl / st / 1e12 / FP32_PEAK_TFLOPS,
+         "frac_split_peak": fl / st / 1e12 / SPLIT_PEAK_TFLOPS,
          "kernels_us": {k: 1e3 * v for k, v in kern.items()}}
     if "hvp" in kern:
         kf = hvp_kernel_flops_per_walker(sys_.n_cv, case["widths"], case["K"]) * B
         r["hvp_kernel"] = {"flop_per_launch": kf, "avg_launch_us": 1e3 * kern["hvp"],
                            "achieved_tflops": kf / (kern["hvp"] * 1e-3) / 1e12,
-                           "frac_fp32_peak": kf / (kern["hvp"] * 1e-3) / 1e12 / FP32_PEAK_TFLOPS}
+                           "frac_split_peak": kf / (kern["hvp"] * 1e-3) / 1e12 / SPLIT_PEAK_TFLOPS}
     return r
 
 
@@ -1054,11 +1065,11 @@ def main():
     value = B * args.steps / elapsed
     flop_launch = mlp_flops_per_walker(sys20.n_cv, widths, K) * B
     achieved = flop_launch / (kern["mlp"] * 1e-3) / 1e12
-    roof = {"bound": "mfma", "achieved": achieved, "peak": FP32_PEAK_TFLOPS,
-            "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
+    roof = {"bound": "mfma", "achieved": achieved, "peak": SPLIT_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": achieved / SPLIT_PEAK_TFLOPS,
             "traffic": traffic_for("mlp_fp32_4x256_b1024"),
             "mfma_busy": mfma_busy_for("mlp_fp32_4x256_b1024"),
-            "kernel": "mlp_kernel<F32,256> (torsions gathered in-kernel + ensemble "
+            "kernel": "mlp_f32_kernel<256> (torsions gathered in-kernel + ensemble "
                       "forward + input-gradient sweep)",
             "avg_launch_us": kern["mlp"] * 1e3, "flop_per_launch": flop_launch}
     rec = {

@@ -46,7 +46,10 @@ typedef enum {
 } rid_status;
 
 typedef enum {
-  RID_FP32 = 0,     /* every GEMM on FP32 MFMA, FP32 activations            */
+  RID_FP32 = 0,     /* FP32 operands and accumulation: every product as three
+                       FP16 MFMAs of operands split in two (22-23 bits each,
+                       scaled by exact powers of two per row); error against
+                       FP64 no larger than that of FP32 MFMA               */
   RID_BF16 = 1,     /* the precision form: the hidden-layer forward GEMMs on
                        BF16 MFMA with FP32 accumulation (BF16 weights and
                        activations); the first layer (CV encoding -> first
@@ -160,8 +163,7 @@ rid_status rid_ensemble_set_train_budget(rid_ensemble ens, size_t bytes);
  * MLP.  The packed parameters are the same in both forms.  Takes effect on
  * the next call: every evaluation (rid_bias_force, rid_model_dev,
  * rid_select, rid_mcmc_run, the server), conservative switching and the
- * training calls use the residual form (training and conservative
- * switching through the general sweeps: the tangent and both adjoints carry
+ * training calls use the residual form (the tangent and both adjoints carry
  * the skip too).  Errors: RID_EINVAL (NULL, hidden widths not all equal),
  * RID_EUNSUPPORTED (16-bit ensemble: the 16-bit kernels have no skip). */
 rid_status rid_ensemble_set_resnet(rid_ensemble ens, int enable);

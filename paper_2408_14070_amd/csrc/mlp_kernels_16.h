@@ -1,5 +1,11 @@
-// Ensemble MLP free-energy models: the fused forward + input-gradient kernel
-// (fed straight from atom positions on the bias path) and the weight packer.
+// 16-bit ensembles of MLP free-energy models: the fused forward + input-gradient
+// kernel (fed from atom positions on the bias path where that is cheaper).
+// FP32 ensembles: mlp_kernels_f32.h.
+//
+// What bounds it: at width 512 and 16384 walkers of 8 members (393 us, 1.10
+// PFLOP/s) the matrix units, 0.56 busy at 2.0 GHz, beside the weight stream
+// from L2 (64 walkers a workgroup, all that LDS and registers hold); in small
+// calls the latency of the layers, one after the other (rows_16, waves).
 //
 // Method ("Training phase"): each ensemble member is an MLP with tanh hidden
 // layers and a scalar output A(x); the bias needs the mean force
@@ -21,9 +27,8 @@
 //    between two buffers so each layer needs one barrier; it holds x, then
 //    h_1 .. h_L, then the reverse-sweep vectors v_l.
 //  * tanh'(z_l) = 1 - h_l^2 is computed in FP32 and kept in VGPRs for the
-//    reverse sweep (FP32 for the FP32 path; FP16 for the 16-bit plans except
-//    the all-BF16 one, whose 64-walker tiles would not fit an FP32 copy):
-//    nothing goes to HBM between layers.
+//    reverse sweep, in FP16 (BF16 in the all-BF16 plan; 64-walker tiles would
+//    not fit an FP32 copy): nothing goes to HBM between layers.
 //  * 16-bit arithmetic plans (Plan below) choose the operand format of the
 //    first layer, of the hidden-layer forward GEMMs and of the reverse sweep
 //    separately.  The precision form runs the hidden-layer forward GEMMs in
@@ -38,8 +43,8 @@
 //  * Blocks are mapped XCD-aware: when K divides 8, member k runs on XCDs
 //    {k*8/K, ...}, so each XCD's L2 holds only its members' weights.
 //  * On the bias path each workgroup can compute the torsions of its walkers
-//    itself from the positions (small batches: the encoding never goes
-//    through HBM; large batches encode once in a separate kernel).  The
+//    itself from the positions (gather_pays; elsewhere the CVs are encoded
+//    first).  The
 //    FP64 deviation, switch and chain rule run in a second kernel: handing
 //    the members' results to one workgroup inside this launch needs
 //    device-scope fences, which on gfx950 write back and invalidate the

@@ -552,7 +552,7 @@ __global__ void adam_kernel(AdamStep a, const float* g, long long n) {
 // 2.5 to 3 TB/s (359 MB with the L2's misses); the matrix units are busy a
 // fifth of the time.  Measured per pass there: 205 us with FP32 MFMA and a
 // launch per layer (and 38 us of column sums, partial sums and losses in
-// seven more), 120 us with BF16 alone, 99 us now; 128 samples of residual
+// seven more), 120 us with BF16 alone, about 100 us now; 128 samples of residual
 // 4 x [300 x 4]: 41 (and 14) us before, 18 us now.  8-byte loads of column
 // pairs take 103 us; 128 x 128 tiles split once through LDS take 90 us at
 // 4096 samples and 5 % off a step of 16384, but 15 % longer below 500 samples.
