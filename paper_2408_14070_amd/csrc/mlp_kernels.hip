@@ -102,8 +102,10 @@ __global__ void pack_kernel(const float* master, size_t per_model, PackAll pa,
     size_t f = t / 64;
     const int jt = f % JT; f /= JT;
     const int kt = f % KT;
-    const int k = (int)(f / KT);
-    const float* W = master + (size_t)k * per_model + pl.w_off;
+    const int k = __builtin_amdgcn_readfirstlane((int)(f / KT));   // (a wave's fragment)
+    const __amdgpu_buffer_rsrc_t W = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(master + (size_t)k * per_model + pl.w_off), (short)0,
+        4 * pl.in * pl.out, 0x00020000);
     const int col = jt * 16 + (lane & 15);
     float v[E];
     for (int e = 0; e < E; ++e) {
@@ -112,9 +114,13 @@ __global__ void pack_kernel(const float* master, size_t per_model, PackAll pa,
       // backward: (unit col = in, contraction kk = out)
       const int o = dir == 0 ? col : kk;
       const int i = dir == 0 ? kk : col;
-      v[e] = (o < pl.out && i < pl.in) ? W[(size_t)o * pl.in + i] : 0.f;
-      if (dir == 0) v[e] *= kTanhPrescale;
+      // (outside: an offset past the resource, which reads as 0; a branch
+      // around the load made the compiler wait on each)
+      const int off = o < pl.out && i < pl.in ? 4 * (o * pl.in + i) : 0x7FFFFFF0;
+      v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(W, off, 0, 0));
     }
+    if (dir == 0)
+      for (int e = 0; e < E; ++e) v[e] *= kTanhPrescale;
     unsigned short hv[E];
     for (int e = 0; e < E; ++e)
       hv[e] = fmt == kFmtBF16 ? __builtin_bit_cast(unsigned short, (__bf16)v[e])
