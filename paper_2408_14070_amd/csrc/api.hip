@@ -422,10 +422,7 @@ rid_status rid_ensemble_load_params(rid_ensemble ens, const float* d_params,
   hipStream_t st = (hipStream_t)stream;
   if (d_params != e.d_master)
     RID_HIP(hipMemcpyAsync(e.d_master, d_params, e.n_params * 4, hipMemcpyDeviceToDevice, st));
-  rid_status r = pack_ensemble_weights(e, st);
-  if (r != RID_OK) return r;
-  e.frag_dirty = false;
-  return RID_OK;
+  return pack_ensemble_weights(e, st);
 }
 
 int64_t rid_ensemble_step(rid_ensemble ens) { return ens ? ens->impl.step : -1; }

@@ -229,8 +229,12 @@ rid_status launch_mlp_from_pos(const rid_ensemble_impl& e, const TorsionInput& t
 
 rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
   ++e.master_gen;     // the masters may have changed: copies made from them are stale
-  e.frag_dirty = false;
-  if (e.prec == RID_FP32) return pack_split_weights(e, st);
+  e.frag_dirty = true;               // until the packing is launched
+  if (e.prec == RID_FP32) {
+    const rid_status r = pack_split_weights(e, st);
+    e.frag_dirty = r != RID_OK;
+    return r;
+  }
   const int L = e.L;
   PackAll pa{};
   pa.L = L;
@@ -273,6 +277,7 @@ rid_status pack_ensemble_weights(rid_ensemble_impl& e, hipStream_t st) {
   hipLaunchKernelGGL(pack_kernel, grid, block, 0, st, e.d_master, e.per_model, pa, e.d_frag,
                      e.frag_bytes_per_model, e.d_bias, e.d_wo, e.d_bo, e.d_vscale);
   RID_HIP(hipGetLastError());
+  e.frag_dirty = false;
   return RID_OK;
 }
 
