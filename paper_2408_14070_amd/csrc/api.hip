@@ -208,10 +208,6 @@ rid_status bias_force_core(rid_system_impl& s, rid_ensemble_impl& e, const float
   r = launch_mlp_from_pos(e, tin, B, A, g, st);
   if (r == RID_EUNSUPPORTED) {
     // where the in-kernel torsions would cost more: encode in HBM first
-    if (!x) {
-      if ((r = e.ws_x.ensure(sizeof(float) * 2 * e.n_cv * (size_t)B)) != RID_OK) return r;
-      x = e.ws_x.as<float>();
-    }
     if ((r = launch_cv_eval(s, d_pos, B, nullptr, x, st)) != RID_OK) return r;
     r = launch_mlp(e, x, B, A, g, st);
   }
@@ -623,9 +619,12 @@ rid_status rid_bias_force(rid_system sys, rid_ensemble ens, const float* d_pos,
   rid_ensemble_impl& e = ens->impl;
   if ((r = e.ws_A.ensure(sizeof(float) * e.K * (size_t)B)) != RID_OK) return r;
   if ((r = e.ws_g.ensure(sizeof(float) * e.K * (size_t)B * e.n_cv)) != RID_OK) return r;
+  // the encoding's place too, whichever route this call takes: a later call of
+  // this size under graph capture (another system) may need it and cannot allocate
+  if ((r = e.ws_x.ensure(sizeof(float) * 2 * e.n_cv * (size_t)B)) != RID_OK) return r;
   return bias_force_core(sys->impl, e, d_pos, B, eps0, eps1, e.ws_A.as<float>(),
-                         e.ws_g.as<float>(), nullptr, d_force, d_energy, d_eps, d_sigma,
-                         d_flags, (hipStream_t)stream);
+                         e.ws_g.as<float>(), e.ws_x.as<float>(), d_force, d_energy, d_eps,
+                         d_sigma, d_flags, (hipStream_t)stream);
 }
 
 rid_status rid_bias_force_conservative(rid_system sys, rid_ensemble ens,

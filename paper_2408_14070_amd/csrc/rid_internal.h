@@ -319,8 +319,7 @@ rid_status launch_train_step(rid_ensemble_impl& e, const float* s,
                              const float* F, int B, float lr, float* loss,
                              hipStream_t st);
 // The bias path (rid_bias_force) with its scratch given: A [K][B], g
-// [K][B][n], and x [B][2n] for the encoding when it goes through memory
-// (null: taken from the ensemble's workspace, grown on demand).
+// [K][B][n], and x [B][2n] for the encoding when it goes through memory.
 rid_status bias_force_core(rid_system_impl& s, rid_ensemble_impl& e, const float* d_pos,
                            int B, float eps0, float eps1, float* A, float* g, float* x,
                            float* d_force, float* d_energy, float* d_eps, float* d_sigma,
