@@ -245,7 +245,6 @@ struct TrainIo {
   float drop_p;                     // dropout rate (0: none)
   unsigned long long drop_seed;
   uint32_t step;                    // training step (mask counter)
-  uint4* bounds;                    // [L][K][tiles]: largest |lam_z|, |lam_zd|, |h|, |hd| of a tile
 };
 // Threshold clustering of CV frames (selection); synchronises the stream.
 // Copies the first min(leaders, leaders_out) leaders' frame indices.
@@ -255,8 +254,7 @@ rid_status launch_cluster(const float* s, int B, int n, const uint8_t* raw,
                           int* labels, int* leaders, int leaders_out, int* n_leaders,
                           int* n_clusters, float* t_used, hipStream_t st);
 bool train_fused_supported(const rid_ensemble_impl& e);
-// (tiles: the sample tiles of the launch, at most one per 16 rows)
-rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, int B, int* tiles,
+rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, int B,
                                hipStream_t st);
 rid_status launch_ensemble_reduce(int K, int n, int B, const float* A,
                                   const float* g, float* eps, float* gbar,

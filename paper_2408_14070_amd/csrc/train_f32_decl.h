@@ -7,7 +7,7 @@
 namespace rid {
 #define RID_TRAIN_F32(W)                                                                 \
   rid_status train_f32_w##W(int rt, const rid_ensemble_impl& e, const TrainIo& io, int B, \
-                            int* tiles, hipStream_t st);
+                            hipStream_t st);
 RID_TRAIN_F32(64) RID_TRAIN_F32(128) RID_TRAIN_F32(192) RID_TRAIN_F32(256)
 RID_TRAIN_F32(320) RID_TRAIN_F32(384) RID_TRAIN_F32(512)
 #undef RID_TRAIN_F32

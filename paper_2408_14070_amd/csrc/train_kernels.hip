@@ -36,7 +36,6 @@
 // kernel (64x64 tiles, LDS double buffering, arbitrary strides, fused
 // epilogues); the weight-gradient GEMM (both forms) is split along the batch with a
 // fixed-order reduction, so the whole step is deterministic.
-#include "mlp_split.h"
 #include "device_common.h"
 
 namespace rid {
@@ -533,34 +532,31 @@ __global__ void adam_kernel(AdamStep a, const float* g, long long n) {
 // Workgroups of the first column tile also sum A over the primal rows (the
 // bias gradient).
 //
-// The products run on the 16-bit matrix units at 16 times the FP32 rate, the
-// operands split in registers.  A lane holds 8 consecutive rows of one column
-// (the 32x32x16 MFMA's layout), loaded straight from the row-major slabs
-// (128-byte row segments, two steps ahead, no LDS, no barriers in the loop):
-//  * FP16, x = hi + lo and three products, for the fused sweeps, which leave
-//    bounds of the slabs' largest entries.  One power-of-two scale per slab
-//    half: hi and lo keep 22 bits of every entry down to 2^-28 of the half's
-//    largest.  The products of both halves must carry one scale; the half
-//    whose products are smaller gives way (half of the difference on each
-//    operand), which costs nothing the larger half's rounding does not cover.
-//  * BF16, x = x1 + x2 + x3 and six products (the others are below 2^-26),
-//    for the general sweeps: BF16 has FP32's range and needs no scales.
-// On 256-long dots the error against FP64 is 1.8e-7 rms of the result with
-// FP16, 0.8e-7 with BF16, 2.9e-7 with the FP32 MFMA chain.
+// The products run on the BF16 matrix units at 16 times the FP32 rate, the
+// operands split in registers, x = x1 + x2 + x3, six products (the others are
+// below 2^-26).  BF16 has FP32's range and the three parts hold all 24 bits, so
+// every entry of the gradient is as precise as its own terms, however small
+// beside the rest of its layer (Adam normalises each entry by itself).  FP16
+// pairs, three products, need a scale per slab: 99 instead of 120 us at 4096
+// samples below, but a unit whose lam is 2^-12 of the layer's largest lost 4
+// bits, and one at 2^-26 its whole gradient.  A lane holds 8 consecutive rows
+// of one column (the 32x32x16 MFMA's layout), loaded straight from the
+// row-major slabs (128-byte row segments, two steps ahead, no LDS, no barriers
+// in the loop).  On 256-long dots the error against FP64 is 0.8e-7 rms of the
+// result, 2.9e-7 with the FP32 MFMA chain.
 //
 // What bounds it: the slabs, 235 MB at 4096 samples of 4 x [256 x 4], read at
-// 2.5 to 3 TB/s (359 MB with the L2's misses); the matrix units are busy a
-// fifth of the time.  Measured per pass there: 205 us with FP32 MFMA and a
-// launch per layer (and 38 us of column sums, partial sums and losses in
-// seven more), 120 us with BF16 alone, about 100 us now; 128 samples of residual
-// 4 x [300 x 4]: 41 (and 14) us before, 18 us now.  8-byte loads of column
-// pairs take 103 us; 128 x 128 tiles split once through LDS take 90 us at
-// 4096 samples and 5 % off a step of 16384, but 15 % longer below 500 samples.
+// 2 TB/s (359 MB with the L2's misses), and the splits and products beside
+// them.  Measured per pass there: 205 us with FP32 MFMA and a launch per layer
+// (and 38 us of column sums, partial sums and losses in seven more), 118 us
+// now; 128 samples of residual 4 x [300 x 4]: 41 (and 14) us before, 19 us now.
+// With FP16 pairs, 8-byte loads of column pairs took 103 instead of 99 us;
+// 128 x 128 tiles split once through LDS 90 us at 4096 samples and 5 % off a
+// step of 16384, but 15 % longer below 500 samples.
 // The launch also covers what else the batch reductions need: the column sums
 // of hd_L (the output weights' gradient, per chunk of kColRows rows) and, on
 // the last pass, the members' losses.
 struct WgradLayer {
-  const uint4* mx;                 // [batch][n_mx] bounds: lam_z, lam_zd, h, hd (FP16)
   const float* A;
   const float* B;
   long long sAb, sBb;
@@ -575,7 +571,6 @@ struct WgradArgs {
   WgradLayer l[kMaxHidden];
   int nl, tiles;                   // layers, tiles of all layers
   int R, batch, ksplit, kchunk, xcd;   // rows of a half; chunks, whole steps of each
-  int n_mx;
   int main_blocks;                 // workgroups of the products
   // column sums of X [batch][.][w] (member stride sXb) over its R rows, part c of
   // member b at out + c*s_part + b*s_mem; null: none
@@ -595,54 +590,37 @@ struct WgradArgs {
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-using dev::fl2;
-using dev::h2;
-using dev::h8;
+typedef float fl2 __attribute__((ext_vector_type(2)));
 constexpr int kWgLdsStride = 65;   // padded row of a partial tile in LDS
 constexpr int kWgTile = 64;        // tile edge of a workgroup
 constexpr int kWgStep = 16;        // contraction rows of a step
 
-// The parts of eight values: P = 3 BF16, P = 2 FP16 (of x scale).
-template <int P>
+// The three BF16 parts of eight values.
 struct Split8 {
-  uint4 p[P];
-  __device__ inline void set(const float (&x)[8], float scale) {
-    unsigned q[P][4];
+  uint4 p[3];
+  __device__ inline void set(const float (&x)[8]) {
+    unsigned q[3][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float a = x[2 * i], b = x[2 * i + 1];
-      if constexpr (P == 2) {
-        a *= scale;
-        b *= scale;
-        const h2 hi = __builtin_convertvector((fl2{a, b}), h2);
-        const h2 lo = __builtin_convertvector((fl2{a - (float)hi[0], b - (float)hi[1]}), h2);
-        q[0][i] = __builtin_bit_cast(unsigned, hi);
-        q[1][i] = __builtin_bit_cast(unsigned, lo);
-      } else {
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-          const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector((fl2{a, b}), bf2));
-          q[t][i] = u;
-          if (t < 2) {
-            a -= __uint_as_float(u << 16);
-            b -= __uint_as_float(u & 0xFFFF0000u);
-          }
+      for (int t = 0; t < 3; ++t) {
+        const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector((fl2{a, b}), bf2));
+        q[t][i] = u;
+        if (t < 2) {
+          a -= __uint_as_float(u << 16);
+          b -= __uint_as_float(u & 0xFFFF0000u);
         }
       }
     }
 #pragma unroll
-    for (int t = 0; t < P; ++t) p[t] = make_uint4(q[t][0], q[t][1], q[t][2], q[t][3]);
+    for (int t = 0; t < 3; ++t) p[t] = make_uint4(q[t][0], q[t][1], q[t][2], q[t][3]);
   }
 };
 
-template <int P>
 __device__ inline void wg_mfma(f16v& c, const uint4& a, const uint4& b) {
-  if constexpr (P == 2)
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b),
-                                               c, 0, 0, 0);
-  else
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a),
-                                                __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a),
+                                              __builtin_bit_cast(bf8, b), c, 0, 0, 0);
 }
 
 // The workgroups past the products: column sums, then losses (red: 256 floats).
@@ -703,7 +681,6 @@ __device__ inline bool wgrad_tile(const WgradArgs& g, int blk, WgradTile& w) {
   return true;
 }
 
-template <int P>
 __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
   __shared__ float red[2][64][kWgLdsStride];
   const int lane = threadIdx.x & 63;
@@ -744,8 +721,6 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f16v{};
   float cs[2] = {0.f, 0.f};
-  float sA[2] = {1.f, 1.f}, sB[2] = {1.f, 1.f};   // scales: primal, tangent half
-  int unscale = 0;                                // C = acc 2^unscale
   auto ldf = [](const __amdgpu_buffer_rsrc_t& r, int vo, int so) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
   };
@@ -763,7 +738,6 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
     }
   };
   auto consume = [&](const float (&v)[4][8], bool tangent) {
-    const float fA = tangent ? sA[1] : sA[0], fB = tangent ? sB[1] : sB[0];
     if (csum_wg && !tangent) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -771,58 +745,25 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
         cs[1] += v[1][e];
       }
     }
-    Split8<P> fb[2];
-    fb[0].set(v[2], fB);
-    fb[1].set(v[3], fB);
+    Split8 fb[2];
+    fb[0].set(v[2]);
+    fb[1].set(v[3]);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      Split8<P> fa;
-      fa.set(v[i], fA);
-      constexpr int NT = P == 2 ? 3 : 6;   // small products first
-      constexpr int pa[6] = {P == 2 ? 1 : 0, P == 2 ? 0 : 2, P == 2 ? 0 : 1, 0, 1, 0};
-      constexpr int pb[6] = {P == 2 ? 0 : 2, P == 2 ? 1 : 0, P == 2 ? 0 : 1, 1, 0, 0};
+      Split8 fa;
+      fa.set(v[i]);
+      constexpr int pa[6] = {0, 2, 1, 0, 1, 0};   // small products first
+      constexpr int pb[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) wg_mfma<P>(acc[i][j], fa.p[pa[t]], fb[j].p[pb[t]]);
+        for (int j = 0; j < 2; ++j) wg_mfma(acc[i][j], fa.p[pa[t]], fb[j].p[pb[t]]);
     }
   };
   // (a step past the last one re-reads the last, never consumed)
   if (n_st > 0) {
     issue(ring[0], step(0));
     issue(ring[1], step(1));
-  }
-  if constexpr (P == 2) {
-    // the slab halves' largest entries, over the sweep's tiles
-    uint4 m = make_uint4(0, 0, 0, 0);
-    const uint4* mx = L.mx + (long long)b * g.n_mx;
-    auto mx4 = [](const uint4& a, const uint4& c) {
-      return make_uint4(max(a.x, c.x), max(a.y, c.y), max(a.z, c.z), max(a.w, c.w));
-    };
-    for (int i = threadIdx.x; i < g.n_mx; i += 256) m = mx4(m, mx[i]);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1)
-      m = mx4(m, make_uint4(__shfl_xor(m.x, d), __shfl_xor(m.y, d), __shfl_xor(m.z, d),
-                            __shfl_xor(m.w, d)));
-    uint4* mr = reinterpret_cast<uint4*>(&red[0][0][0]);
-    if (lane == 0) mr[wave] = m;
-    __syncthreads();
-    m = mx4(mx4(mr[0], mr[1]), mx4(mr[2], mr[3]));
-    __syncthreads();
-    const int a0 = dev::split_clamp_exp(dev::split_exp(m.x));
-    const int a1 = dev::split_clamp_exp(dev::split_exp(m.y));
-    const int b0 = dev::split_clamp_exp(dev::split_exp(m.z));
-    const int b1 = dev::split_clamp_exp(dev::split_exp(m.w));
-    const int top = max(a0 + b0, a1 + b1);
-    // (a half 2^-80 below the other is nothing beside it: the exponents stay
-    // inside FP32's range)
-    const int d0 = min(top - (a0 + b0), 80), d1 = min(top - (a1 + b1), 80);
-    auto pow2 = [](int e) { return __uint_as_float((unsigned)(127 + max(e, -126)) << 23); };
-    sA[0] = pow2(dev::kTargetExp - a0 - (d0 + 1) / 2);
-    sB[0] = pow2(dev::kTargetExp - b0 - d0 / 2);
-    sA[1] = pow2(dev::kTargetExp - a1 - (d1 + 1) / 2);
-    sB[1] = pow2(dev::kTargetExp - b1 - d1 / 2);
-    unscale = top - 2 * dev::kTargetExp;
   }
   for (int i = 0; i < n_st; i += 3) {
 #pragma unroll
@@ -904,7 +845,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
   float* Ct = L.C + s * L.sCs + b * L.sCb + (long long)m0 * L.N + n0;
   for (int r = wave; r < 64 && m0 + r < L.M; r += 4)
     if (n0 + lane < L.N)
-      Ct[(long long)r * L.N + lane] = P == 2 ? ldexpf(red[1][r][lane], unscale) : red[1][r][lane];
+      Ct[(long long)r * L.N + lane] = red[1][r][lane];
   if (csum_wg && wave == 0) {
     const int m = m0 + lane;
     const float v = (cred[0][lane] + cred[2][lane]) + (cred[1][lane] + cred[3][lane]);
@@ -1073,11 +1014,10 @@ struct GradLayer {
   const float* B;                  // activation slab [K][2R][N]
   int M, N;
   long long w_off, b_off;
-  const uint4* mx;                 // [K][n_mx] the sweep tiles' bounds, or null
 };
 struct GradPass {
   GradLayer l[kMaxHidden];
-  int nl, K, R, ks, kchunk, n_mx;  // n_mx: tiles of the fused sweeps (0: no bounds)
+  int nl, K, R, ks, kchunk;
   float *part, *bpart, *cpart;
   float* grad;
   long long pm;
@@ -1100,7 +1040,7 @@ rid_status grad_pass(const GradPass& g, hipStream_t st) {
     return fail(RID_EINVAL, "weight-gradient pass: bad shape");
   const bool direct = g.ks == 1 && !g.accumulate && (!g.X || col_parts(g.R) == 1);
   a.nl = r.nl = g.nl;
-  a.R = g.R; a.batch = g.K; a.ksplit = g.ks; a.kchunk = g.kchunk; a.n_mx = g.n_mx;
+  a.R = g.R; a.batch = g.K; a.ksplit = g.ks; a.kchunk = g.kchunk;
   long long off = 0, boff = 0;
   for (int i = 0; i < g.nl; ++i) {
     const GradLayer& s = g.l[i];
@@ -1109,7 +1049,6 @@ rid_status grad_pass(const GradPass& g, hipStream_t st) {
     // row byte offsets are 32-bit scalar offsets (passes are sized to fit)
     if ((long long)Kc * std::max(s.M, s.N) * 4 > 0x7FFFFFFFLL)
       return fail(RID_EUNSUPPORTED, "weight-gradient pass: slab too large for 32-bit offsets");
-    d.mx = s.mx;
     d.A = s.A; d.lda = s.M; d.sAb = (long long)Kc * s.M;
     d.B = s.B; d.ldb = s.N; d.sBb = (long long)Kc * s.N;
     d.M = s.M; d.N = s.N;
@@ -1146,8 +1085,7 @@ rid_status grad_pass(const GradPass& g, hipStream_t st) {
     a.zero = g.grad + g.wo_off + g.w; a.s_zero = g.pm;
     extra += g.K;
   }
-  auto kern = g.n_mx > 0 ? wgrad_kernel<2> : wgrad_kernel<3>;
-  hipLaunchKernelGGL(kern, dim3(a.main_blocks + extra), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(wgrad_kernel, dim3(a.main_blocks + extra), dim3(256), 0, st, a);
   RID_HIP(hipGetLastError());
   if (direct) {
     if (g.adam.theta) {
@@ -1192,9 +1130,9 @@ int chunk_rows(long long floats_per_row, int B, size_t budget, int wmax) {
 // one tile alone on a CU runs at 0.8 of the rate two reach together, and a
 // chunk's partial gradient costs 1 row per 5.7 kB written and read back.
 // Measured per training step (us, 4 members of [256 x 4] unless noted; chunks
-// 1 / 2 / 4): 1024 samples 118 / 114 / 121, 4096 samples 310 / 292 / 298,
-// 16384 samples 1260 / 1173 / 1183, 4096 samples of [300 x 4] 615 / 488 / -,
-// one member and 4096 samples, chunks 4 / 8 / 16: 107 / 104 / 109.
+// 1 / 2 / 4): 1024 samples 114 / 111 / 117, 4096 samples 299 / 287 / 292,
+// 16384 samples 1254 / 1174 / 1175, 4096 samples of [300 x 4] 611 / 480 / 472,
+// one member and 4096 samples, chunks 4 / 8 / 16: 103 / 99 / 103.
 struct WgradSplit {
   int ks, kchunk;
 };
@@ -1265,8 +1203,6 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
   const long long lrows = tot; tot = al(tot + (long long)K * B);
   const long long cpart = tot; tot = al(tot + (long long)col_parts(Bc) * K * w[L]);
   const long long bpart = tot; tot = al(tot + bparts * ks_max);
-  // the sweep tiles' bounds, per layer [K][n_tiles] x 16 bytes
-  const long long bnd = tot; tot = al(tot + 4LL * L * K * ((Bc + 15) / 16));
   rid_status rs = e.ws_train.ensure(sizeof(float) * tot);
   if (rs != RID_OK) return rs;
   float* W = e.ws_train.as<float>();
@@ -1291,15 +1227,11 @@ rid_status mf_grad_fused(rid_ensemble_impl& e, const float* s, const float* F,
     io.rho = rho ? rho + (size_t)r0 * K * n : nullptr;
     io.loss_rows = rho ? nullptr : W + lrows + r0;
     io.row_base = r0;
-    io.bounds = reinterpret_cast<uint4*>(W + bnd);
-    int tiles = 0;
-    if ((rs = launch_train_sweeps(e, io, R, &tiles, st)) != RID_OK) return rs;
+    if ((rs = launch_train_sweeps(e, io, R, st)) != RID_OK) return rs;
     GradPass g{};
-    g.n_mx = tiles;
     g.nl = L; g.K = K; g.R = R; g.ks = sp.ks; g.kchunk = sp.kchunk;
     for (int l = 0; l < L; ++l)      // dW_l = S^T [h ; hd]_{l-1}, db_l = sum of lam_z
-      g.l[l] = GradLayer{W + sl[l], W + hh[l], w[l + 1], w[l], w_off[l], b_off[l],
-                         io.bounds + (long long)l * K * tiles};
+      g.l[l] = GradLayer{W + sl[l], W + hh[l], w[l + 1], w[l], w_off[l], b_off[l]};
     g.part = W + part; g.bpart = W + bpart; g.cpart = W + cpart;
     g.grad = G; g.pm = pm;
     g.accumulate = acc; g.last = r0 + R >= B;
@@ -1535,8 +1467,7 @@ rid_status launch_mf_grad(rid_ensemble_impl& e, const float* s, const float* F,
         GradPass g{};
         const WgradSplit sp = wgrad_split(K, &w[l], &w[l - 1], 1, R);
         g.nl = 1; g.K = K; g.R = R; g.ks = sp.ks; g.kchunk = sp.kchunk;
-        g.l[0] = GradLayer{W + sbuf, W + hh[l - 1], w[l], w[l - 1], w_off[l - 1], b_off[l - 1],
-                           nullptr};
+        g.l[0] = GradLayer{W + sbuf, W + hh[l - 1], w[l], w[l - 1], w_off[l - 1], b_off[l - 1]};
         g.part = W + part; g.bpart = W + bpart; g.cpart = W + cpart;
         g.grad = G; g.pm = pm;
         g.accumulate = acc; g.wo_off = wo_off; g.w = w[L];

@@ -28,8 +28,9 @@
 // every fragment.  38 CVs, 4 x [256 x 4], 4096 samples: 330 us with FP32 MFMA
 // (16 samples a workgroup), 172 us now; 18 CVs, residual 4 x [300 x 4] with
 // dropout, 128 samples (the separate GEMM sweeps before, 29 launches): about
-// 150 us, 72 us now, 32 workgroups each streaming its member once a sweep.  t and zd of the lane's units stay in VGPRs in FP32; the
-// slabs are written from the FP32 values.  Row scales of the vectors with no
+// 150 us, 72 us now, 32 workgroups each streaming its member once a sweep.  t
+// and zd of the lane's units stay in VGPRs in FP32; the slabs are written from
+// the FP32 values.  Row scales of the vectors with no
 // fixed range come from bounds on the largest row entries (tracked in LDS):
 //   |u_{l-1}|  <= C_l S max|u_l| [+ max|u_l|]           C: column sums of |W|
 //   |hd_l|     <= S R_l max|hd_{l-1}| [+ max|hd_{l-1}|]  R: row sums of |W|
@@ -52,7 +53,6 @@ struct TrainF32Args {
   const uint8_t* raw;  // [n] 1: raw CV (null: every CV angular)
   float* hh[kMaxHidden + 1];   // [K][2B][wd[j]]
   float* sl[kMaxHidden];       // [K][2B][wd[j+1]]
-  uint4* bounds;       // [L][K][n_tiles] float bits: largest |lam_z|, |lam_zd|, |h|, |hd|
   float* loss_rows;    // row b of member k at loss_rows[k * loss_ld + b], or null
   long long loss_ld;
   int row_base;        // batch index of row 0 (dropout counters)
@@ -627,40 +627,6 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
       __syncthreads();
     }
   });
-  // ---------------- bounds of this tile's slab rows ----------------
-  // (what the weight-gradient products are scaled by; the entries of layer j:
-  // lam_z, lam_zd there, h and hd of its input)
-  if (wave != 0) return;
-  uint4* const bounds = p.bounds + (size_t)k * p.n_tiles + row0 / R;
-  const size_t step = (size_t)p.K * p.n_tiles;
-  const int r = lane & (R - 1);
-  layers_up<0, LM>([&](auto jc) __attribute__((always_inline)) {
-    constexpr int j = decltype(jc)::value;
-    if (j < L) {
-      // lam_h, lam_hd: tracked in layers 1 .. L - 2; layer 0's from layer 1's
-      float mh = 0.f, mhd = cb[0];
-      if (j < L - 1) {
-        constexpr int l = j >= 1 ? j : 1;
-        mh = l < L - 1 ? __uint_as_float(m_lh[l * R + r]) : 0.f;
-        mhd = l < L - 1 ? __uint_as_float(m_lhd[l * R + r]) : cb[0];
-        if (j == 0) {
-          const float res = RES ? 1.f : 0.f;
-          mh = cb[1] * (mh + 2.f * __uint_as_float(m_zd[R + r]) * mhd) + res * mh;
-          mhd = (cb[1] + res) * mhd;
-        }
-      }
-      const float mz = __uint_as_float(m_zd[j * R + r]);
-      unsigned m[4] = {__float_as_uint(S * (mh + 2.f * mz * mhd)) & 0x7FFFFFFFu,
-                       __float_as_uint(S * mhd) & 0x7FFFFFFFu,
-                       __float_as_uint(j == 0 ? sx[r] * (2.f * kActScale) : S * (RES ? (float)j : 1.f)),
-                       m_hd[j * R + r]};
-#pragma unroll
-      for (int d = R / 2; d >= 1; d >>= 1)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) m[q] = max(m[q], (unsigned)__shfl_xor(m[q], d));
-      if (lane == 0) bounds[j * step] = make_uint4(m[0], m[1], m[2], m[3]);
-    }
-  });
 }
 
 }  // namespace dev
@@ -686,8 +652,7 @@ inline size_t train_f32_layout(int NP, int R, int LM, int XP, int n, TrainF32Arg
 }
 
 template <int NP, int RT, int NW, int LM, bool RES>
-rid_status run_train_f32(const rid_ensemble_impl& e, const TrainIo& io, int B, int* tiles,
-                         hipStream_t st) {
+rid_status run_train_f32(const rid_ensemble_impl& e, const TrainIo& io, int B, hipStream_t st) {
   static size_t attr = 0;
   constexpr int R = 16 * RT;
   const SplitDev& s = e.split;
@@ -706,8 +671,7 @@ rid_status run_train_f32(const rid_ensemble_impl& e, const TrainIo& io, int B, i
   for (int j = 0; j <= e.L; ++j) a.hh[j] = io.hh[j];
   for (int j = 0; j < e.L; ++j) a.sl[j] = io.sl[j];
   a.B = B; a.n = e.n_cv; a.K = e.K; a.L = e.L; a.XP = s.XP;
-  a.n_tiles = *tiles = (B + R - 1) / R;
-  a.bounds = io.bounds;
+  a.n_tiles = (B + R - 1) / R;
   a.xcd_grp = (8 % e.K == 0) ? 8 / e.K : 0;
   a.u0_parts = split_u0_parts(NP, s.XP);
   a.wd[0] = 2 * e.n_cv;

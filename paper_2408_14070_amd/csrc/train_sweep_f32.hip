@@ -26,7 +26,7 @@ bool train_fused_supported(const rid_ensemble_impl& e) {
   return e.prec == RID_FP32 && e.L <= train_depth(e.split.NP, e.resnet) && train_fits(e, 16);
 }
 
-rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, int B, int* tiles,
+rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, int B,
                                hipStream_t st) {
   if (!train_fused_supported(e))
     return fail(RID_EUNSUPPORTED, "no fused training kernel for this ensemble");
@@ -37,13 +37,13 @@ rid_status launch_train_sweeps(const rid_ensemble_impl& e, const TrainIo& io, in
                     (long long)((B + 15) / 16) * e.K > 256;
   const int rt = wide ? 2 : 1;
   switch (s.NP) {
-    case 64: return train_f32_w64(rt, e, io, B, tiles, st);
-    case 128: return train_f32_w128(rt, e, io, B, tiles, st);
-    case 192: return train_f32_w192(rt, e, io, B, tiles, st);
-    case 256: return train_f32_w256(rt, e, io, B, tiles, st);
-    case 320: return train_f32_w320(rt, e, io, B, tiles, st);
-    case 384: return train_f32_w384(rt, e, io, B, tiles, st);
-    case 512: return train_f32_w512(rt, e, io, B, tiles, st);
+    case 64: return train_f32_w64(rt, e, io, B, st);
+    case 128: return train_f32_w128(rt, e, io, B, st);
+    case 192: return train_f32_w192(rt, e, io, B, st);
+    case 256: return train_f32_w256(rt, e, io, B, st);
+    case 320: return train_f32_w320(rt, e, io, B, st);
+    case 384: return train_f32_w384(rt, e, io, B, st);
+    case 512: return train_f32_w512(rt, e, io, B, st);
   }
   return fail(RID_EUNSUPPORTED, "no kernel for this padded width");
 }

@@ -5,8 +5,8 @@
 namespace rid {
 
 rid_status train_f32_w512(int, const rid_ensemble_impl& e, const TrainIo& io, int B,
-                         int* tiles, hipStream_t st) {
-  return run_train_f32<512, 1, 8, 4, false>(e, io, B, tiles, st);
+                         hipStream_t st) {
+  return run_train_f32<512, 1, 8, 4, false>(e, io, B, st);
 }
 
 }  // namespace rid
