@@ -276,20 +276,28 @@ constexpr float kTanhPrescale = 2.8853900817779268f;
 constexpr float kTanhUnscale = 0.34657359027997264f;
 
 // tanh and its derivative from one exponential and one reciprocal, given the
-// pre-scaled pre-activation y: with e = 2^-|y| <= 1 and q = 2 e / (1 + e),
-// |tanh z| = 1 - q and tanh' = q (2 - q).  q keeps its relative precision as
-// the unit saturates, and so does tanh'; 1 - tanh^2 carries tanh's rounding.
-// Small values take |tanh z| = (1 - e) / (1 + e) instead (1 - e is exact
-// there); e > 1/3 is |z| < 0.55.  y of any size and either infinity saturate, a
-// NaN stays one.  |z| from 6 to 14, largest errors: tanh' 1e-11, tanh 3e-8
-// (3e-7 and 1.5e-7 as 1 - h^2 with h = (e^2z - 1) / (e^2z + 1)), tanh' formed
-// from tanh in the training sweeps 6e-8 (2.8e-7); 0.1 to 0.9 % of a call.
+// pre-scaled pre-activation y: with e = 2^-|y| <= 1, r = 1 / (1 + e) and
+// s = e r, |tanh z| = r - s and tanh' = 4 s (1 - s).  s keeps its relative
+// precision as the unit saturates, and so does tanh'; 1 - tanh^2 carries tanh's
+// rounding.  TANH_ONLY (the training sweeps, which form tanh' from tanh again):
+// |tanh z| = 1 - 2 s from |z| = 0.55 on (e = 1/3), which leaves the reciprocal's
+// rounding out; below it r - s is the more precise.  y of any size and either
+// infinity saturate, a NaN stays one.  |z| from 6 to 14, largest errors: tanh'
+// 1e-11, in the training sweeps 6e-8 (3e-7 as 1 - h^2 with
+// h = (e^2z - 1) / (e^2z + 1)).
+template <bool TANH_ONLY = false>
 __device__ inline float tanh_and_grad(float y, float& d) {
   const float e = __builtin_amdgcn_exp2f(-__builtin_fabsf(y));
   const float r = __builtin_amdgcn_rcpf(1.f + e);
-  const float q = (e + e) * r;
-  d = __builtin_fmaf(-q, q, q + q);
-  const float h = e > 1.f / 3.f ? __builtin_fmaf(-e, r, r) : 1.f - q;
+  const float s = e * r;
+  float h = __builtin_fmaf(-e, r, r);
+  if constexpr (TANH_ONLY) {
+    h = e > 1.f / 3.f ? h : __builtin_fmaf(-2.f, s, 1.f);
+    d = __builtin_fmaf(-h, h, 1.f);
+  } else {
+    const float s4 = 4.f * s;
+    d = __builtin_fmaf(-s4, s, s4);
+  }
   return __builtin_copysignf(h, y);
 }
 

@@ -310,7 +310,8 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           float dq;
-          t[q] = tanh_and_grad(__builtin_fmaf(acc[rt][c][q] * iv, rnext[c][q], bnext[c][q]), dq);
+          t[q] = tanh_and_grad<true>(__builtin_fmaf(acc[rt][c][q] * iv, rnext[c][q], bnext[c][q]),
+                                     dq);
           d[q] = dq;
         }
         ts[j][rt][c] = t;
