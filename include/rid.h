@@ -46,10 +46,16 @@ typedef enum {
 } rid_status;
 
 typedef enum {
-  RID_FP32 = 0,     /* FP32 operands and accumulation: every product as three
-                       FP16 MFMAs of operands split in two (22-23 bits each,
-                       scaled by exact powers of two per row); error against
-                       FP64 no larger than that of FP32 MFMA               */
+  RID_FP32 = 0,     /* FP32 operands and accumulation: the layers' products as
+                       three FP16 MFMAs of operands split in two, each row
+                       scaled by an exact power of two: 22-23 bits of every
+                       entry down to 2^-16 of its row's bound (a bit less for
+                       each power of two below); raw CVs' part of layer 1 on
+                       FP32 MFMA, whatever their size; weight gradients on
+                       BF16 in three parts (all 24 bits, FP32's range).  Error
+                       against FP64 measured no larger than that of FP32 MFMA
+                       throughout (networks of ordinary scaling, saturated
+                       units, raw CVs of 1e-6 to 1e7)                      */
   RID_BF16 = 1,     /* the precision form: the hidden-layer forward GEMMs on
                        BF16 MFMA with FP32 accumulation (BF16 weights and
                        activations); the first layer (CV encoding -> first

@@ -116,6 +116,31 @@ static void free_system(rid_system_impl& s) {
   s.d_uniq = s.d_lquads = s.d_csr_ptr = s.d_csr_ent = s.d_atom_local = nullptr;
 }
 
+static void free_raw(rid_ensemble_impl& e) {
+  dev_free(e.d_raw);
+  dev_free(e.split.raw_w);
+  e.split.raw_max = nullptr;
+  e.split.raw_sets = 0;
+  e.raw.clear();
+}
+
+// The raw CVs' device tables (raw: [n_cv], some of it set).
+static rid_status alloc_raw(rid_ensemble_impl& e, const std::vector<uint8_t>& raw) {
+  rid_status st = dev_alloc(&e.d_raw, (size_t)e.n_cv);
+  if (st != RID_OK) return st;
+  RID_HIP(hipMemcpy(e.d_raw, raw.data(), (size_t)e.n_cv, hipMemcpyHostToDevice));
+  if (e.prec == RID_FP32) {
+    SplitDev& s = e.split;
+    const size_t n_w = (size_t)e.K * s.NP * round_up(e.n_cv, 16);
+    if ((st = dev_alloc(&s.raw_w, n_w + (size_t)e.K * e.n_cv)) != RID_OK) return st;
+    s.raw_max = s.raw_w + n_w;
+    for (int i = 0; i < e.n_cv; ++i)
+      if (raw[i]) s.raw_sets |= 1u << (i / 16);
+  }
+  e.raw = raw;
+  return RID_OK;
+}
+
 static void free_ensemble(rid_ensemble_impl& e) {
   dev_free(e.d_master);
   dev_free(e.d_m);
@@ -127,7 +152,7 @@ static void free_ensemble(rid_ensemble_impl& e) {
   dev_free(e.d_vscale);
   dev_free(e.split.frag);
   dev_free(e.split.vec);
-  dev_free(e.d_raw);
+  free_raw(e);
   dev_free(e.d_cvw);
   dev_free(e.d_bounds);
   e.ws_x.release();
@@ -478,13 +503,15 @@ rid_status rid_ensemble_set_angular_mask(rid_ensemble ens, const uint8_t* angula
     }
   }
   RID_HIP(hipDeviceSynchronize());   // calls in flight may still read the old mask
-  dev_free(e.d_raw);
-  e.raw.clear();
-  if (!any) return RID_OK;
-  rid_status st = dev_alloc(&e.d_raw, (size_t)e.n_cv);
-  if (st != RID_OK) return st;
-  RID_HIP(hipMemcpy(e.d_raw, raw.data(), (size_t)e.n_cv, hipMemcpyHostToDevice));
-  e.raw = raw;
+  const bool had = !e.raw.empty();
+  free_raw(e);
+  rid_status st = RID_OK;
+  if (any && (st = alloc_raw(e, raw)) != RID_OK) free_raw(e);
+  if (e.prec != RID_FP32 || !(had || any)) return st;
+  // raw columns leave the FP32 fragments, or come back
+  const rid_status r = pack_ensemble_weights(e, nullptr);
+  if (st != RID_OK || r != RID_OK) return st != RID_OK ? st : r;
+  RID_HIP(hipStreamSynchronize(nullptr));
   return RID_OK;
 }
 

@@ -45,8 +45,8 @@ struct HvpF32Args {
 
 namespace dev {
 
-// tracked row maxima (hd, td, u, ud per layer), the input rows' inverse
-// scales, the tangent input's exponents, the layer bounds
+// tracked row maxima (hd, td, u, ud per layer), the raw CVs' bounds on layer
+// 1's tangents, the layer bounds
 __host__ __device__ constexpr int hvp_track_words(int LM, int R) {
   return 4 * (LM + 1) * R + R + 2 * (kMaxHidden + 1);
 }
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(NW * 64) void hvp_f32_kernel(HvpF32Args p) {
   unsigned* m_td = m_hd + (LM + 1) * R;
   unsigned* m_u = m_td + (LM + 1) * R;
   unsigned* m_ud = m_u + (LM + 1) * R;
-  float* sx = reinterpret_cast<float*>(m_ud + (LM + 1) * R);   // [R]
-  float* cb = sx + R;                          // C_l (slot 0: max |w_o|)
+  float* m_raw = reinterpret_cast<float*>(m_ud + (LM + 1) * R);   // [R]
+  float* cb = m_raw + R;                       // C_l (slot 0: max |w_o|)
   float* rb = cb + kMaxHidden + 1;             // R_l
 
   const unsigned char* fbase = p.w.frag + (size_t)k * p.w.frag_bytes;
@@ -137,12 +137,12 @@ __global__ __launch_bounds__(NW * 64) void hvp_f32_kernel(HvpF32Args p) {
     }
   }
   // input rows, a wave per walker: x (primal) and rho_x = (dx/ds) w (tangent),
-  // columns [2n, XP) zero; walkers past B are zero rows
+  // columns [2n, XP) and the raw CVs' (added in FP32) zero; walkers past B are
+  // zero rows
   constexpr int kCvq = 4;                      // n <= 256: CVs per lane
-  constexpr float kMax = 3.4028234663852886e38f;
   for (int i = wave; i < R; i += NW) {
     const int row = row0 + i;
-    float x0[kCvq], x1[kCvq], r0[kCvq], r1[kCvq], m = 1.f, mr = 0.f;
+    float x0[kCvq], x1[kCvq], r0[kCvq], r1[kCvq], mraw = 0.f, mr = 0.f;
 #pragma unroll
     for (int q = 0; q < kCvq; ++q) {
       const int c = lane + 64 * q;
@@ -151,33 +151,32 @@ __global__ __launch_bounds__(NW * 64) void hvp_f32_kernel(HvpF32Args p) {
         x0[q] = p.x[(size_t)row * X2 + c];
         x1[q] = p.x[(size_t)row * X2 + n + c];
         const float w = p.rho[((size_t)row * p.K + k) * n + c];
-        const bool is_raw = p.raw && p.raw[c];
-        r0[q] = is_raw ? w : -x1[q] * w;
-        r1[q] = is_raw ? 0.f : x0[q] * w;
-        if (is_raw && fabsf(x0[q]) > kMax) x0[q] = copysignf(kMax, x0[q]);
-        m = fmaxf(m, fabsf(x0[q]));
+        if (p.raw && p.raw[c]) {
+          x0[q] = x1[q] = 0.f;
+          mraw += p.w.raw_max[(size_t)k * n + c] * fabsf(w);
+        } else {
+          r0[q] = -x1[q] * w;
+          r1[q] = x0[q] * w;
+        }
         mr = fmaxf(mr, fmaxf(fabsf(r0[q]), fabsf(r1[q])));
       }
     }
 #pragma unroll
     for (int q = 32; q >= 1; q >>= 1) {
-      m = fmaxf(m, __shfl_xor(m, q));
+      mraw += __shfl_xor(mraw, q);
       mr = fmaxf(mr, __shfl_xor(mr, q));
     }
-    // rows of cosines and sines keep 2^10 (m may pass 1 by an ulp)
-    const int e = p.raw ? min(split_exp(__float_as_uint(m)), 126) - 1 : 0;
-    const float scl = __uint_as_float((unsigned)(127 + 10 - e) << 23);
     const float sr = split_scale(split_clamp_exp(split_exp(__float_as_uint(mr))));
     if (lane == 0) {
-      sx[i] = __uint_as_float((unsigned)(127 - 10 + e) << 23);
+      m_raw[i] = 1.0001f * mraw;       // (the sum's rounding cannot undercut it)
       m_hd[i] = __float_as_uint(mr);
     }
 #pragma unroll
     for (int q = 0; q < kCvq; ++q) {
       const int c = lane + 64 * q;
       if (c < n) {
-        split_store1(buf0 + i * AX + c, XP, x0[q] * scl);
-        split_store1(buf0 + i * AX + n + c, XP, x1[q] * scl);
+        split_store1(buf0 + i * AX + c, XP, x0[q] * kActScale);
+        split_store1(buf0 + i * AX + n + c, XP, x1[q] * kActScale);
         split_store1(buf0 + (R + i) * AX + c, XP, r0[q] * sr);
         split_store1(buf0 + (R + i) * AX + n + c, XP, r1[q] * sr);
       }
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(NW * 64) void hvp_f32_kernel(HvpF32Args p) {
   };
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    iv[rt] = sx[rt * 16 + wl];
+    iv[rt] = kActUnscale;
     ivd[rt] = split_unscale(split_clamp_exp(split_exp(m_hd[rt * 16 + wl])));
   }
   // forward epilogue of layer j (0-based): h and hd to the next buffer, or
@@ -214,7 +213,7 @@ __global__ __launch_bounds__(NW * 64) void hvp_f32_kernel(HvpF32Args p) {
     for (int rt = 0; rt < RT; ++rt) {
       const int r = rt * 16 + wl;
       const float mh = __uint_as_float(m_hd[j * R + r]);
-      const float tb = rb[j] * mh;              // >= |td_j|
+      const float tb = rb[j] * mh + (j == 0 ? m_raw[r] : 0.f);   // >= |td_j|
       const bool top = j == L - 1;
       const int e0 = split_clamp_exp(split_exp(__float_as_uint(cb[0])));
       const int e1 = split_clamp_exp(split_exp(
@@ -263,6 +262,27 @@ __global__ __launch_bounds__(NW * 64) void hvp_f32_kernel(HvpF32Args p) {
     f4 acc[2 * RT][CT];
     zero(acc);
     split_gemm_run<2 * RT, CT, PD>(acc, wr, buf0, AX, XP, wfwd(0), XP / kSplitKF, lane);
+    if (p.raw) {            // acc becomes the pre-activation and its tangent, raw CVs on top
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          acc[rt][c] = acc[rt][c] * iv[rt] * rnext[c] + bnext[c];
+          acc[RT + rt][c] *= ivd[rt] * rnext[c];
+        }
+        rnext[c] = f4{1.f, 1.f, 1.f, 1.f};
+        bnext[c] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) iv[rt] = ivd[rt] = 1.f;
+      const int rows = min(R, p.B - row0), ks = p.K * n;
+      const __amdgpu_buffer_rsrc_t xr = row_src(p.x + (size_t)row0 * X2, rows, X2),
+                                   rr = row_src(p.rho + (size_t)row0 * ks, rows, ks);
+      raw_gemm<2 * RT, CT>(acc, raw_src(p.w, k, NP, n), jt0, lane, [&](int rt, int i) {
+        return rt < RT ? raw_value(row_ld(xr, (rt * 16 + wl) * X2 + i))
+                       : row_ld(rr, ((rt - RT) * 16 + wl) * ks + k * n + i);
+      });
+    }
     if (L > 1) split_preload<PDH, CT>(wh, wfwd(1), NK, lane);
     fwd_epi(0, acc, buf1);
     __syncthreads();

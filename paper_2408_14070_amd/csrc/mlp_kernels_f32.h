@@ -77,8 +77,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
   const int US = XP + 4;
   float* red = reinterpret_cast<float*>(smem + p.off_red);   // [JT][R]
   unsigned* mx = reinterpret_cast<unsigned*>(smem + p.off_mx);   // [LM][R] row maxima
-  float* sx = reinterpret_cast<float*>(mx + LM * R);         // [R] inverse scale of the input row
-  int* ec = reinterpret_cast<int*>(sx + R);                  // [kMaxHidden + 1] bounds (exponents)
+  int* ec = reinterpret_cast<int*>(mx + LM * R);             // [kMaxHidden + 1] bounds (exponents)
   float* xs = reinterpret_cast<float*>(smem + p.off_xs);     // [R][2n] cos|sin (FROM_POS)
   float* wos = reinterpret_cast<float*>(smem + p.off_wo);    // [NP] output weights
 
@@ -211,53 +210,25 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
     }
     for (int i = wave; i < R; i += NW)
       for (int c = X2 + lane; c < XP; c += 64) split_store1(buf0 + i * AX + c, XP, 0.f);
-    if (threadIdx.x < R) sx[threadIdx.x] = kActUnscale;
   } else {
     // the column batches of the tile (the first one is already in xv);
-    // padding columns [X2, XP) get zeros (X2 is even).  With raw CVs a
-    // row's scale comes from its largest entry (infinite ones clamped to
-    // the largest finite value: tanh saturates the same)
+    // padding columns [X2, XP) get zeros (X2 is even), and so do the raw CVs'
+    // (their part of layer 1 is added in FP32)
     const int hp = XP / 2;
-    float scl[RW_];
-#pragma unroll
-    for (int j = 0; j < RW_; ++j) scl[j] = kActScale;
-    if (p.raw) {
-      float m[RW_];
-#pragma unroll
-      for (int j = 0; j < RW_; ++j) m[j] = 1.f;
-      for (int cb = 0; cb < n; cb += 64) {
-        if (cb > 0) load_x(cb);
-#pragma unroll
-        for (int j = 0; j < RW_; ++j) m[j] = fmaxf(m[j], fmaxf(fabsf(xv[j].x), fabsf(xv[j].y)));
-      }
-      if (n > 64) load_x(0);
-#pragma unroll
-      for (int j = 0; j < RW_; ++j) {
-#pragma unroll
-        for (int q = 32; q >= 1; q >>= 1) m[j] = fmaxf(m[j], __shfl_xor(m[j], q));
-        // 2^10 at a maximum of 1, as for angular rows
-        const int e = min(split_exp(__float_as_uint(m[j])), 126) - 1;
-        scl[j] = __uint_as_float((unsigned)(127 + 10 - e) << 23);
-        const int i = wave + j * NW;
-        if (lane == 0 && i < R) sx[i] = __uint_as_float((unsigned)(127 - 10 + e) << 23);
-      }
-    } else if (threadIdx.x < R) {
-      sx[threadIdx.x] = kActUnscale;
-    }
     for (int cb = 0; cb < hp; cb += 64) {
       const int col = cb + lane;               // float2 column
       if (cb > 0) load_x(cb);
       if (col < hp) {
+        bool zx = false, zy = false;
+        if (p.raw) {
+          zx = 2 * col < n && p.raw[min(2 * col, n - 1)];
+          zy = 2 * col + 1 < n && p.raw[min(2 * col + 1, n - 1)];
+        }
 #pragma unroll
         for (int j = 0; j < RW_; ++j) {
           const int i = wave + j * NW;
-          float2 v = xv[j];
-          if (p.raw) {
-            constexpr float kMax = 3.4028234663852886e38f;
-            v.x = fabsf(v.x) > kMax ? copysignf(kMax, v.x) : v.x;
-            v.y = fabsf(v.y) > kMax ? copysignf(kMax, v.y) : v.y;
-          }
-          if (i < R) split_store2(buf0 + i * AX + 2 * col, XP, v.x * scl[j], v.y * scl[j]);
+          const float vx = zx ? 0.f : xv[j].x * kActScale, vy = zy ? 0.f : xv[j].y * kActScale;
+          if (i < R) split_store2(buf0 + i * AX + 2 * col, XP, vx, vy);
         }
       }
     }
@@ -325,16 +296,35 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
     f4 acc[RT][CT];
     zero(acc);
     split_gemm_run<RT, CT, PD>(acc, wr, buf0, AX, XP, wsrc(p.w.fwd_off[0]), XP / kSplitKF, lane);
+    float iv = kActUnscale;
+    if constexpr (!FROM_POS) {
+      if (p.raw) {                     // acc becomes y, the raw CVs' part on top
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[rt][c][q] = __builtin_fmaf(acc[rt][c][q] * iv, rnext[c][q], bnext[c][q]);
+          rnext[c] = f4{1.f, 1.f, 1.f, 1.f};
+          bnext[c] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        iv = 1.f;
+        const __amdgpu_buffer_rsrc_t xr =
+            row_src(p.x + (size_t)row0 * X2, min(R, p.B - row0), X2);
+        raw_gemm<RT, CT>(acc, raw_src(p.w, k, NP, n), jt0, lane, [&](int rt, int i) {
+          return raw_value(row_ld(xr, (rt * 16 + wl) * X2 + i));
+        });
+      }
+    }
     if (L > 1) split_preload<PDH, CT>(wh, next_after_fwd(0), NK, lane);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const float iv = sx[rt * 16 + wl];
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int c = 0; c < CT; ++c) {
         if (L > 1) mid_tile(0, rt, c, acc[rt][c], iv, out);
         else last_tile(rt, c, acc[rt][c], iv, false, out);
       }
-    }
     __syncthreads();
   }
   // hidden layers before the last
@@ -520,7 +510,7 @@ inline size_t mlp_f32_layout(int NP, int R, int LM, int XP, int n, int U, bool f
   a.off_red = align16(off);
   off = a.off_red + (size_t)(NP / 16) * R * 4;
   a.off_mx = align16(off);
-  off = a.off_mx + (size_t)(LM + 1) * R * 4 + (kMaxHidden + 1) * 4;
+  off = a.off_mx + (size_t)LM * R * 4 + (kMaxHidden + 1) * 4;
   a.off_xs = align16(off);
   off = a.off_xs + (from_pos ? (size_t)R * 2 * n * 4 : 0);
   a.off_wo = align16(off);

@@ -20,14 +20,18 @@ struct SplitPackArgs {
   unsigned char* frag;
   unsigned long long frag_bytes;
   float *bias, *rs, *bound, *wo, *bo;
+  const uint8_t* raw;              // [n] or null
+  int n;
+  float *raw_w, *raw_max;
 };
 
 // One block per (16-row tile, layer and direction, member): its waves hold
 // the tile's whole contraction in registers (at most 16 k-chunks, 4 a wave),
 // so the row maxima and absolute sums, the scales and the split fragments
 // come from one read of the masters.  Block row 2L writes the biases and
-// output weights.  Rows and contraction: forward, units x inputs (weights
-// times 2/ln 2); backward, inputs x units.
+// output weights, row 2L + 1 the raw CVs' FP32 weights (zero in layer 1's forward
+// fragments, so that they set no row's scale).  Rows and contraction: forward,
+// units x inputs (weights times 2/ln 2); backward, inputs x units.
 __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
   const int k = blockIdx.z, y = blockIdx.y, jt = blockIdx.x;
   const float* m = p.master + (size_t)k * p.per_model;
@@ -42,6 +46,23 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
         p.wo[(size_t)k * NP + j] = j < p.out[p.L - 1] ? m[p.wo_off + j] : 0.f;
     }
     if (jt == 0 && threadIdx.x == 0) p.bo[k] = m[p.wo_off + p.out[p.L - 1]];
+    return;
+  }
+  if (y == 2 * p.L + 1) {              // a wave per CV, its lanes over the units
+    const int nw = gridDim.x * 4, lane = threadIdx.x & 63, sets = (p.n + 15) / 16;
+    for (int i = jt * 4 + (threadIdx.x >> 6); i < 16 * sets; i += nw) {
+      const bool raw = i < p.n && p.raw[min(i, p.n - 1)];
+      float mx = 0.f;
+      for (int j = lane; j < NP; j += 64) {
+        const float w = raw && j < p.out[0] ? m[p.w_off[0] + j * p.in[0] + i] : 0.f;
+        p.raw_w[(((size_t)k * (NP / 16) + j / 16) * sets + i / 16) * 256 +
+                (((i & 15) >> 2) * 16 + (j & 15)) * 4 + (i & 3)] = kTanhPrescale * w;
+        mx = fmaxf(mx, fabsf(w));
+      }
+#pragma unroll
+      for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s));
+      if (lane == 0 && i < p.n) p.raw_max[(size_t)k * p.n + i] = mx;
+    }
     return;
   }
   const int l = y >> 1, dir = y & 1;
@@ -64,7 +85,8 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
     for (int e = 0; e < 8; ++e) {
       const int kk = kt * kSplitKF + 8 * g + e;
       const int o = dir == 0 ? row : kk, i = dir == 0 ? kk : row;
-      const bool ok = kt < KT && o < outw && i < in;
+      bool ok = kt < KT && o < outw && i < in;
+      if (p.raw && y == 0) ok = ok && !p.raw[min(i < p.n ? i : i - p.n, p.n - 1)];
       // (outside: an offset past the resource, which reads as 0.  As a branch
       // around the load the compiler waited on each of the 32: 12.9 us a pack
       // of 4 x [300 x 4], 8.4 so)
@@ -216,6 +238,9 @@ SplitView split_view(const rid_ensemble_impl& e) {
   v.wo = s.wo;
   v.bo = s.bo;
   v.RW = s.RW;
+  v.raw_w = s.raw_w;
+  v.raw_max = s.raw_max;
+  v.raw_sets = s.raw_sets;
   return v;
 }
 
@@ -242,7 +267,9 @@ rid_status pack_split_weights(rid_ensemble_impl& e, hipStream_t st) {
   p.L = e.L; p.K = e.K; p.NP = s.NP; p.RW = s.RW;
   p.frag = s.frag; p.frag_bytes = s.frag_bytes;
   p.bias = s.bias; p.rs = s.rs; p.bound = s.bound; p.wo = s.wo; p.bo = s.bo;
-  hipLaunchKernelGGL(pack_split_kernel, dim3(s.RW / 16, 2 * e.L + 1, e.K), dim3(256), 0, st, p);
+  p.raw = e.d_raw; p.n = e.n_cv; p.raw_w = s.raw_w; p.raw_max = s.raw_max;
+  hipLaunchKernelGGL(pack_split_kernel, dim3(s.RW / 16, 2 * e.L + (s.raw_sets ? 2 : 1), e.K),
+                     dim3(256), 0, st, p);
   RID_HIP(hipGetLastError());
   return RID_OK;
 }

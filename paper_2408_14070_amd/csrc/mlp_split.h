@@ -16,7 +16,10 @@
 //    row's largest weight, which lands in [2^9, 2^10); lo's resolution is
 //    then 2^-34 of the row's maximum;
 //  * activations h of the forward sweep: |h| <= 6 (tanh, up to 6 residual
-//    layers), scaled by 2^10; an input row with raw CVs by its own maximum;
+//    layers), scaled by 2^10, and so the cosines and sines of the input;
+//  * raw CVs have no range at all (their weights neither, nor their entries
+//    of the tangents' input): layer 1 adds their part in FP32 (raw_gemm), and
+//    the split products get zeros in their columns;
 //  * vectors with no fixed range (reverse, tangent, adjoint sweeps): one
 //    scale per row (a walker's vector), from a bound that cannot overflow:
 //    the largest entry of the previous layer's vector (tracked in LDS) times
@@ -301,6 +304,49 @@ __device__ inline float tanh_and_grad(float y, float& d) {
   return __builtin_copysignf(h, y);
 }
 
+// The raw CVs' part of layer 1 on FP32 MFMA, acc += W x over the CVs in sets of
+// 16 (those that hold a raw one): weights in FP32 fragments, lane l holding unit
+// l % 16 and CVs 4 (l / 16) .. + 3 of the set, zero for angular CVs; x(rt, i) is
+// the lane's walker's value of CV i in row tile rt (i < n; past n the last
+// one's, its weight zero).  A set costs 4 MFMAs a tile and one round trip to
+// L2, below 1 us: 1000 walkers of 4 x [256 x 4], 38 CVs, 26.8 us without, 28.2 with
+// 12 raw ones, 30.0 with 38 (36.1 when every product ran on FP32 MFMA).
+struct RawSrc {
+  __amdgpu_buffer_rsrc_t r;   // one member's fragments
+  unsigned sets;              // bit t: set t holds a raw CV
+  int n_sets, n;
+};
+template <int RT, int CT, class X>
+__device__ inline void raw_gemm(f4 (&acc)[RT][CT], const RawSrc& s, int jt0, int lane, X&& x) {
+  for (unsigned m = s.sets; m; m &= m - 1) {
+    const int t = __builtin_ctz(m);
+    f4 w[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+      w[c] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                        s.r, lane * 16, ((jt0 + c) * s.n_sets + t) * 1024, 0));
+    float v[RT][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = min(16 * t + 4 * (lane >> 4) + e, s.n - 1);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) v[rt][e] = x(rt, i);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+          acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][e], v[rt][e], acc[rt][c], 0, 0, 0);
+  }
+}
+// A raw CV's value; an infinity becomes a number large enough to saturate
+// (padded units have zero weights, and 0 inf is a NaN).
+__device__ inline float raw_value(float s) {
+  return __builtin_isinf(s) ? __builtin_copysignf(1e30f, s) : s;
+}
+
 // Block -> (member, tile), XCD-aware: when K divides 8 (grp = 8 / K), member
 // k runs on XCDs {k grp, ...}, so each XCD's L2 holds only its members'
 // weights.
@@ -328,6 +374,27 @@ struct SplitView {
   const float* wo;                    // [K][NP]
   const float* bo;                    // [K]
   int RW;                             // row stride of rs: max(NP, XP)
+  const float* raw_w;                 // raw CVs' FP32 fragments (RawSrc)
+  const float* raw_max;               // [K][n] largest |weight| of a raw CV
+  unsigned raw_sets;
 };
+
+namespace dev {
+__device__ inline RawSrc raw_src(const SplitView& w, int k, int NP, int n) {
+  const int sets = (n + 15) / 16, floats = NP * 16 * sets;
+  return RawSrc{__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w.raw_w + (size_t)k * floats),
+                                                  (short)0, 4 * floats, 0x00020000),
+                w.raw_sets, sets, n};
+}
+// Rows [0, rows) of a row-major array as a buffer (range-checked: rows past the
+// end read as 0), for the raw CVs' values.
+__device__ inline __amdgpu_buffer_rsrc_t row_src(const float* p, int rows, int stride) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, 4 * rows * stride,
+                                           0x00020000);
+}
+__device__ inline float row_ld(const __amdgpu_buffer_rsrc_t& r, int offset) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, 4 * offset, 0, 0));
+}
+}  // namespace dev
 
 }  // namespace rid

@@ -114,6 +114,12 @@ struct SplitDev {
   size_t frag_bytes = 0;             // bytes of one member's fragments
   std::vector<LayerDev> layers;
   unsigned char* frag = nullptr;     // [K][frag_bytes]
+  // raw CVs (angular mask 0): their layer-1 weights stay FP32, out of the
+  // forward fragments, in FP32 fragments of 16 units x 16 CVs (mlp_split.h); one
+  // allocation: raw_w | raw_max
+  unsigned raw_sets = 0;             // bit t: a raw CV among 16 t .. 16 t + 15
+  float* raw_w = nullptr;            // [K][NP / 16][ceil(n_cv / 16)][256], times 2/ln 2
+  float* raw_max = nullptr;          // [K][n_cv] largest |weight| of a raw CV (angular: 0)
   float* vec = nullptr;              // one allocation: bias | rs | bound | wo | bo
   float *bias = nullptr, *rs = nullptr, *bound = nullptr, *wo = nullptr, *bo = nullptr;
 };

@@ -82,8 +82,8 @@ __device__ inline f4 reread(f4 v) {
   return v;
 }
 
-// rows of tracked maxima: u, hd, zd, lam_h, lam_hd per layer, then the
-// input rows' inverse scales and the layer bounds
+// rows of tracked maxima: u, hd, zd, lam_h, lam_hd per layer, then the raw
+// CVs' bounds on layer 1's tangents and the layer bounds
 __host__ __device__ constexpr int train_track_words(int LM, int R) {
   return 5 * (LM + 1) * R + R + 2 * (kMaxHidden + 1);
 }
@@ -127,8 +127,8 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
   unsigned* m_zd = m_hd + (LM + 1) * R;
   unsigned* m_lh = m_zd + (LM + 1) * R;
   unsigned* m_lhd = m_lh + (LM + 1) * R;
-  float* sx = reinterpret_cast<float*>(m_lhd + (LM + 1) * R);   // [R]
-  float* cb = sx + R;                          // [kMaxHidden + 1] S C_l (slot 0: max |w_o|)
+  float* m_raw = reinterpret_cast<float*>(m_lhd + (LM + 1) * R);   // [R]
+  float* cb = m_raw + R;                       // [kMaxHidden + 1] S C_l (slot 0: max |w_o|)
   float* rb = cb + kMaxHidden + 1;             // [kMaxHidden + 1] S R_l
 
   const unsigned char* fbase = p.w.frag + (size_t)k * p.w.frag_bytes;
@@ -238,47 +238,38 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
   };
   constexpr int kCvq = 4;                  // n <= 256: CVs per lane
   // input tile, a wave per sample: x into the primal rows (and hh[0]),
-  // zeros past 2n and past B; a row with raw CVs is scaled by its largest
-  // entry (infinite ones clamped: tanh saturates the same)
+  // zeros past 2n and past B.  xs keeps cos s | sin s, for a raw CV (zero in
+  // the tile: its part is added in FP32) its value and later its rho.
   for (int i = wave; i < R; i += NW) {
     const int row = row0 + i;
-    float x0[kCvq], x1[kCvq], m = 1.f;
+    float x0[kCvq], x1[kCvq];
 #pragma unroll
     for (int q = 0; q < kCvq; ++q) {
       const int c = lane + 64 * q;
       x0[q] = x1[q] = 0.f;
-      if (c < n && row < B) {
-        const float sv = p.s[(size_t)row * n + c];
+      if (c < n) {
         const bool is_raw = p.raw && p.raw[c];
-        float sn, cs;
-        sincosf(sv, &sn, &cs);
-        x0[q] = is_raw ? sv : cs;
-        x1[q] = is_raw ? 0.f : sn;
-        xs[i * X2 + c] = is_raw ? 0.f : cs;       // dx/ds = (-sin, cos), raw (1, 0)
-        xs[i * X2 + n + c] = is_raw ? -1.f : sn;
-        float* h0 = p.hh[0] + ((size_t)k * 2 * B + row) * X2;
-        h0[c] = x0[q];
-        h0[n + c] = x1[q];
-        m = fmaxf(m, fabsf(x0[q]));
+        float sv = 0.f, sn = 0.f, cs = 0.f;
+        if (row < B) {
+          sv = p.s[(size_t)row * n + c];
+          sincosf(sv, &sn, &cs);
+          if (is_raw) cs = sn = 0.f;
+          float* h0 = p.hh[0] + ((size_t)k * 2 * B + row) * X2;
+          h0[c] = is_raw ? sv : cs;
+          h0[n + c] = sn;
+        }
+        x0[q] = cs;
+        x1[q] = sn;
+        xs[i * X2 + c] = is_raw ? raw_value(sv) : cs;
+        xs[i * X2 + n + c] = sn;
       }
     }
-    float scl = kActScale, iv = kActUnscale;
-    if (p.raw) {
-#pragma unroll
-      for (int q = 32; q >= 1; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
-      const int e = min(split_exp(__float_as_uint(m)), 126) - 1;
-      scl = __uint_as_float((unsigned)(127 + 10 - e) << 23);
-      iv = __uint_as_float((unsigned)(127 - 10 + e) << 23);
-    }
-    if (lane == 0) sx[i] = iv;
 #pragma unroll
     for (int q = 0; q < kCvq; ++q) {
       const int c = lane + 64 * q;
       if (c < n) {
-        constexpr float kMax = 3.4028234663852886e38f;
-        const float v = fabsf(x0[q]) > kMax ? copysignf(kMax, x0[q]) : x0[q];
-        split_store1(buf0 + i * AX + c, XP, v * scl);
-        split_store1(buf0 + i * AX + n + c, XP, x1[q] * scl);
+        split_store1(buf0 + i * AX + c, XP, x0[q] * kActScale);
+        split_store1(buf0 + i * AX + n + c, XP, x1[q] * kActScale);
       }
     }
     for (int c = X2 + lane; c < XP; c += 64) split_store1(buf0 + i * AX + c, XP, 0.f);
@@ -298,11 +289,12 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
 
   // ---------------- primal forward ----------------
   // h to the next buffer (and HBM), or v_L = w_o d_L at the top
+  float iv0 = kActUnscale;  // layer 1's (1 where raw CVs made acc the pre-activation)
   auto fwd_epi = [&](int j, const f4 (&acc)[RT][CT], _Float16* out) __attribute__((always_inline)) {
     const float vsc = split_scale(split_clamp_exp(split_exp(__float_as_uint(cb[0])) + eS));
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      const float iv = j == 0 ? sx[rt * 16 + wl] : aiv;
+      const float iv = j == 0 ? iv0 : aiv;
       const int brow = row0 + rt * 16 + wl;
 #pragma unroll
       for (int c = 0; c < CT; ++c) {
@@ -336,6 +328,21 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
     load_rs(0, 0);
     load_bias(0);
     split_gemm_run<RT, CT, PD>(acc, wr, buf0, AX, XP, wfwd(0), XP / kSplitKF, lane);
+    if (p.raw) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            acc[rt][c][q] = __builtin_fmaf(acc[rt][c][q] * iv0, rnext[c][q], bnext[c][q]);
+        rnext[c] = f4{1.f, 1.f, 1.f, 1.f};
+        bnext[c] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+      iv0 = 1.f;
+      raw_gemm<RT, CT>(acc, raw_src(p.w, k, NP, n), jt0, lane,
+                       [&](int rt, int i) { return xs[(rt * 16 + wl) * X2 + i]; });
+    }
     if (L > 1) split_preload<PDH, CT>(wh, wfwd(1), NK, lane);
     fwd_epi(0, acc, buf1);
     __syncthreads();
@@ -434,17 +441,22 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
   };
   // ---------------- residual and rho_x (a wave per sample) ----------------
   // rho_x goes to tin, scaled by the row's largest entry, and to the tangent
-  // half of hh[0]
+  // half of hh[0]; a raw CV's (rho, 0) to xs instead of tin, with its bound on
+  // layer 1's tangents
   for (int i = wave; i < R; i += NW) {
     const int row = row0 + i;
-    float acc = 0.f, m = 0.f, rx0[kCvq], rx1[kCvq];
+    float acc = 0.f, m = 0.f, mr = 0.f, rx0[kCvq], rx1[kCvq];
 #pragma unroll
     for (int q = 0; q < kCvq; ++q) {
       const int c = lane + 64 * q;
       rx0[q] = rx1[q] = 0.f;
       if (c < n && row < B) {
-        const float cs = xs[i * X2 + c], sn = xs[i * X2 + n + c];
-        float rho;
+        const bool is_raw = p.raw && p.raw[c];
+        float cs = xs[i * X2 + c], sn = xs[i * X2 + n + c], rho;
+        if (is_raw) {                  // dx/ds = (1, 0)
+          cs = 0.f;
+          sn = -1.f;
+        }
         if (p.rho) {
           rho = p.rho[((size_t)row * p.K + k) * n + c];
         } else {
@@ -458,8 +470,18 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
         float* h0 = p.hh[0] + ((size_t)k * 2 * B + B + row) * X2;
         h0[c] = rx0[q];
         h0[n + c] = rx1[q];
+        if (is_raw) {
+          xs[i * X2 + n + c] = rho;
+          mr += p.w.raw_max[(size_t)k * n + c] * fabsf(rho);
+          rx0[q] = rx1[q] = 0.f;
+        }
         m = fmaxf(m, fmaxf(fabsf(rx0[q]), fabsf(rx1[q])));
       }
+    }
+    if (p.raw) {
+#pragma unroll
+      for (int q = 32; q >= 1; q >>= 1) mr += __shfl_xor(mr, q);
+      if (lane == 0) m_raw[i] = S * 1.0001f * mr;   // (the sum's rounding cannot undercut it)
     }
 #pragma unroll
     for (int q = 32; q >= 1; q >>= 1) {
@@ -494,7 +516,8 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
       const int r = rt * 16 + wl;
       const int brow = row0 + r;
       const float mh = __uint_as_float(m_hd[j * R + r]);
-      const float zb = rb[j] * mh;             // >= S |zd_j|
+      float zb = rb[j] * mh;                   // >= S |zd_j|
+      if (j == 0 && p.raw) zb += m_raw[r];
       int e0, e1;
       if (j < L - 1) {
         e0 = e1 = split_clamp_exp(split_exp(__float_as_uint(RES && j >= 1 ? zb + mh : zb)));
@@ -541,8 +564,20 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
     zero1(acc);
     if constexpr (EARLY) load_rs(0, 0);
     split_gemm_run<RT, CT, PD>(acc, wr, tin, AX, XP, wfwd(0), XP / kSplitKF, lane);
-    if (L > 1) split_preload<PDH, CT>(wh, wfwd(1), NK, lane);
     if constexpr (!EARLY) load_rs(0, 0);
+    if (p.raw) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt][c] *= iv[rt] * rnext[c];
+        rnext[c] = f4{1.f, 1.f, 1.f, 1.f};
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) iv[rt] = 1.f;
+      raw_gemm<RT, CT>(acc, raw_src(p.w, k, NP, n), jt0, lane,
+                       [&](int rt, int i) { return xs[(rt * 16 + wl) * X2 + n + i]; });
+    }
+    if (L > 1) split_preload<PDH, CT>(wh, wfwd(1), NK, lane);
     tan_epi(0, acc, buf0);
     __syncthreads();
   }
