@@ -153,8 +153,7 @@ int rows_16(const rid_ensemble_impl& e, int B) {
   double least = 0.0;
   bool found = false;
   for (int i = 0, rt = 1; rt <= (NP >= 256 && e.L <= 4 ? 4 : 2); rt *= 2, ++i) {
-    int rc = 1;
-    if (mlp16::lds_bytes(e, 16 * rt, NW, nullptr, &rc) > 160 * 1024) continue;
+    if (mlp16::lds_bytes(e, 16 * rt, NW) > 160 * 1024) continue;
     double c = round[i] * (double)((wgs(rt) + 255) / 256);
     if (NP <= 192) c = rt == (wgs(1) > (NP == 64 ? 2048 : 256) ? 2 : 1) ? 0.0 : 1.0;
     if (!found || c < least) {
@@ -168,30 +167,23 @@ int rows_16(const rid_ensemble_impl& e, int B) {
 
 // Whether the MLP kernel computes its walkers' torsions itself (a launch less)
 // or the CVs are encoded first: in the kernel every member does it again, a
-// wave at a time.  It pays where the call is one round of 16-walker workgroups,
-// their atoms fit one gather pass, and a wave has few torsions.  Measured, time
+// wave at a time.  It pays where the call is one round of 16-walker workgroups
+// whose atoms fit an activation buffer, and a wave has few torsions.  Measured, time
 // encoding first over time in the kernel (4 members, 4 hidden layers, 1 to 1000
 // walkers): 2 CVs 1.03 to 1.12 (1.20 for one walker at width 64, where 100 take
 // 0.92); 18 CVs 1.00 to 1.08, but 0.87 to 0.96 at width 64 (72 CVs a wave);
 // 38 CVs, FP32, 1.04 to 1.06 at widths 192 to 320 (38 or 76 a wave), 0.86 at 64
-// (152), and, FP16, 0.93 to 1.00 at 128 to 320 (76); 120 CVs (atoms in several
-// passes) 0.35 to 1.00.  From 1500 walkers on 0.40 to 1.03.
+// (152), and, FP16, 0.93 to 1.00 at 128 to 320 (76); 120 CVs (atoms gathered in
+// several passes) 0.35 to 1.00.  From 1500 walkers on 0.40 to 1.03.
 bool gather_pays(const rid_ensemble_impl& e, const TorsionInput& t, int B) {
   if ((long long)((B + 15) / 16) * e.K > 256) return false;
   const bool f32 = e.prec == RID_FP32;
-  int rc = 0, waves;
-  if (f32) {
-    const int NP = e.split.NP;
-    MlpF32Args a{};
-    (void)mlp_f32_layout(NP, 16, 6, e.split.XP, e.n_cv, t.sys->n_uniq, true, a);
-    rc = a.rc;
-    waves = NP <= 256 ? NP / 16 : NP == 512 && !e.resnet ? 16 : NP == 512 ? 8 : NP / 32;
-  } else {
-    waves = mlp16::waves(e.NP);
-    (void)mlp16::lds_bytes(e, 16, waves, &t, &rc);
-  }
+  const int NP = e.split.NP;
+  const int waves = !f32 ? mlp16::waves(e.NP)
+                    : NP <= 256 ? NP / 16 : NP == 512 && !e.resnet ? 16 : NP == 512 ? 8 : NP / 32;
   const int cvs = (16 + waves - 1) / waves * e.n_cv;   // torsions a wave computes
-  return rc >= 16 && cvs <= (f32 ? 80 : 64);
+  if (f32) return mlp_f32_gathers(NP, 16, t.sys->n_uniq) && cvs <= 80;
+  return mlp16::gathers(e, 16, t.sys->n_uniq) && cvs <= 64;
 }
 
 rid_status dispatch(const rid_ensemble_impl& e, const float* x, int B, float* A_out,

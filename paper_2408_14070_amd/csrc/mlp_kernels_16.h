@@ -168,7 +168,6 @@ struct MlpArgs {
   float* g_out;        // [K][B][n]
   // LDS layout (byte offsets; activation buffer 0 starts at 0)
   unsigned off_u0, off_red, off_xs, off_ph0, off_wo;
-  int rc;              // walkers per torsion-gather pass (bias path)
   // torsion input (bias path)
   SysView sv;
   const float* pos;    // [B][n_atoms][3]
@@ -243,9 +242,6 @@ struct WSrc {
     return __builtin_bit_cast(
         uint4, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + c * kFragBytes,
                                                      soff + kk * kstride, 0));
-  }
-  __device__ inline WSrc tiles_from(int c) const {
-    return WSrc{r, soff + c * kFragBytes, kstride};
   }
 };
 
@@ -458,66 +454,58 @@ __global__ __launch_bounds__(NW * 64) void mlp_kernel(MlpArgs p) {
 
   // ---------------- input tile: x = [cos s | sin s] -> buffer 0 ----------------
   if constexpr (FROM_POS) {
-    // torsions of the tile's walkers, p.rc walkers per pass (the gather
-    // scratch lives in buffer 1).  Gather: a lane owns coordinates
-    // j = lane + 64m of the unique-atom list and copies them for the walkers
-    // of its wave (walkers to the waves in turn); then a lane per torsion.
-    // Coordinates go in chunks of kGatherBatch per lane: the chunk's index
-    // loads, then its coordinate loads for all of the wave's walkers, then
-    // the stores.  Slots past the end are clamped to the last coordinate or
-    // walker of the pass (they store that slot's own value again), so no
-    // load sits behind a branch; walkers past B get zeros.
-    float* sp = reinterpret_cast<float*>(smem + p.off_ph0);   // [rc][U][3]
+    // torsions of the tile's walkers (the gather scratch, buffer 1, holds them
+    // all: gather_pays).  Gather: a lane owns coordinates j = lane + 64m of the
+    // unique-atom list and copies them for the walkers of its wave (walkers to
+    // the waves in turn); then a lane per torsion.  Coordinates go in chunks of
+    // kGatherBatch per lane: the chunk's index loads, then its coordinate loads
+    // for the wave's walkers, then the stores.  Slots past the end are clamped to
+    // the last coordinate or walker (they store that slot's own value again), so
+    // no load sits behind a branch; walkers past B get zeros.
+    float* sp = reinterpret_cast<float*>(smem + p.off_ph0);   // [R][U][3]
     const int U3 = 3 * p.sv.U;
-    constexpr int WPW = (R + NW - 1) / NW;    // walkers per wave and pass, at most
+    constexpr int WPW = (R + NW - 1) / NW;    // walkers per wave, at most
     constexpr int QB = WPW < 4 ? WPW : 4;     // walkers per batch of loads
     const size_t wstride = (size_t)p.sv.n_atoms * 3;
-    for (int c0 = 0; c0 < R; c0 += p.rc) {
-      const int rc = R - c0 < p.rc ? R - c0 : p.rc;
-      for (int j0 = lane; j0 < U3; j0 += kGatherBatch * 64) {
-        int jc[kGatherBatch], a[kGatherBatch];
+    for (int j0 = lane; j0 < U3; j0 += kGatherBatch * 64) {
+      int jc[kGatherBatch], a[kGatherBatch];
 #pragma unroll
-        for (int m = 0; m < kGatherBatch; ++m) {
-          jc[m] = min(j0 + m * 64, U3 - 1);
-          const int u = jc[m] / 3;
-          a[m] = 3 * p.sv.uniq[u] + (jc[m] - 3 * u);
-        }
+      for (int m = 0; m < kGatherBatch; ++m) {
+        jc[m] = min(j0 + m * 64, U3 - 1);
+        const int u = jc[m] / 3;
+        a[m] = 3 * p.sv.uniq[u] + (jc[m] - 3 * u);
+      }
 #pragma unroll 1
-        for (int q0 = 0; q0 < WPW && wave + q0 * NW < rc; q0 += QB) {
-          float v[QB][kGatherBatch];
+      for (int q0 = 0; wave + q0 * NW < R; q0 += QB) {
+        float v[QB][kGatherBatch];
 #pragma unroll
-          for (int q = 0; q < QB; ++q) {
-            const int il = min(wave + (q0 + q) * NW, rc - 1);
-            const int row = min(row0 + c0 + il, p.B - 1);
+        for (int q = 0; q < QB; ++q) {
+          const int row = min(row0 + min(wave + (q0 + q) * NW, R - 1), p.B - 1);
 #pragma unroll
-            for (int m = 0; m < kGatherBatch; ++m) v[q][m] = p.pos[row * wstride + a[m]];
-          }
+          for (int m = 0; m < kGatherBatch; ++m) v[q][m] = p.pos[row * wstride + a[m]];
+        }
 #pragma unroll
-          for (int q = 0; q < QB; ++q) {
-            const int il = min(wave + (q0 + q) * NW, rc - 1);
-            const bool in_b = row0 + c0 + il < p.B;
+        for (int q = 0; q < QB; ++q) {
+          const int i = min(wave + (q0 + q) * NW, R - 1);
 #pragma unroll
-            for (int m = 0; m < kGatherBatch; ++m)
-              sp[il * U3 + jc[m]] = in_b ? v[q][m] : 0.f;
-          }
+          for (int m = 0; m < kGatherBatch; ++m)
+            sp[i * U3 + jc[m]] = row0 + i < p.B ? v[q][m] : 0.f;
         }
       }
-      __syncthreads();
-      for (int il = wave; il < rc; il += NW) {
-        const int i = c0 + il;
-        for (int c = lane; c < n; c += 64) {
-          float cs = 0.f, sn = 0.f;
-          if (row0 + i < p.B) {
-            const Torsion t = torsion(sp + il * U3, p.sv.lq + 4 * c);
-            torsion_cos_sin(t, cs, sn);
-          }
-          xs[i * X2 + c] = cs;
-          xs[i * X2 + n + c] = sn;
-          act1[i * AS + c] = P1::from_float(cs);
-          act1[i * AS + n + c] = P1::from_float(sn);
+    }
+    __syncthreads();
+    for (int i = wave; i < R; i += NW) {
+      for (int c = lane; c < n; c += 64) {
+        float cs = 0.f, sn = 0.f;
+        if (row0 + i < p.B) {
+          const Torsion t = torsion(sp + i * U3, p.sv.lq + 4 * c);
+          torsion_cos_sin(t, cs, sn);
         }
+        xs[i * X2 + c] = cs;
+        xs[i * X2 + n + c] = sn;
+        act1[i * AS + c] = P1::from_float(cs);
+        act1[i * AS + n + c] = P1::from_float(sn);
       }
-      __syncthreads();
     }
     for (int i = wave; i < R; i += NW)
       for (int c = X2 + lane; c < XP; c += 64) act1[i * AS + c] = P1::from_float(0.f);
@@ -760,8 +748,7 @@ __host__ __device__ constexpr int waves(int NP) {
 inline unsigned align16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
 
 // LDS layout of one instantiation; returns the total bytes.
-inline size_t mlp_layout(int R, int NW, int AS, size_t tsize, int XP, int n, int U,
-                  bool from_pos, int NPw, MlpArgs& a) {
+inline size_t mlp_layout(int R, int NW, int AS, size_t tsize, int XP, int n, int NPw, MlpArgs& a) {
   const size_t buf = (size_t)R * AS * tsize;
   size_t off = 2 * buf;
   const size_t u0_bytes = (size_t)R * (XP + 4) * 4;
@@ -776,27 +763,21 @@ inline size_t mlp_layout(int R, int NW, int AS, size_t tsize, int XP, int n, int
   a.off_xs = align16(off);
   off = a.off_xs + (size_t)R * 2 * n * 4;
   a.off_wo = align16(off);              // output weights w_o [NP]
-  off = a.off_wo + (size_t)NPw * 4;
-  if (from_pos) {
-    // gather scratch in buffer 1 (free before layer 1), in passes of rc
-    // walkers; a shape with no room for one walker reports 0 passes
-    a.off_ph0 = (unsigned)buf;
-    const size_t per_walker = (size_t)3 * U * 4;
-    a.rc = (int)std::min<size_t>((size_t)R, buf / per_walker);
-  }
-  return off;
+  a.off_ph0 = (unsigned)buf;            // gather scratch: buffer 1, free before layer 1
+  return a.off_wo + (size_t)NPw * 4;
 }
 
-// Bytes of LDS of one shape (NW: waves; R: walkers), and the walkers of a
-// torsion-gather pass in *rc on the bias path.
-inline size_t lds_bytes(const rid_ensemble_impl& e, int R, int NW, const TorsionInput* tin,
-                        int* rc) {
+inline int row_stride(const rid_ensemble_impl& e) {   // elements of an activation row
+  return (e.NP > e.XP ? e.NP : e.XP) + RID_ACT_PAD_BYTES / 2;
+}
+// Bytes of LDS of one shape (NW: waves; R: walkers).
+inline size_t lds_bytes(const rid_ensemble_impl& e, int R, int NW) {
   MlpArgs a{};
-  const int AS = (e.NP > e.XP ? e.NP : e.XP) + RID_ACT_PAD_BYTES / 2;
-  const size_t b = mlp_layout(R, NW, AS, 2, e.XP, e.n_cv, tin ? tin->sys->n_uniq : 0,
-                              tin != nullptr, e.NP, a);
-  *rc = a.rc;
-  return b;
+  return mlp_layout(R, NW, row_stride(e), 2, e.XP, e.n_cv, e.NP, a);
+}
+// Whether buffer 1 (free before layer 1) holds a tile's torsion atoms.
+inline bool gathers(const rid_ensemble_impl& e, int R, int U) {
+  return (size_t)R * row_stride(e) * 2 >= (size_t)R * U * 12;
 }
 
 template <class PL, int NP, int RT, int NW, int LM>
@@ -808,24 +789,19 @@ rid_status run_mlp(const rid_ensemble_impl& e, const float* x, int B,
   using P = typename PL::PH;
   using T = typename P::T;
   const bool from_pos = tin != nullptr;
-  const int AW = NP > e.XP ? NP : e.XP;
-  const int AS = AW + RID_ACT_PAD_BYTES / (int)sizeof(T);
+  static_assert(sizeof(T) == 2, "16-bit activations");
   MlpArgs a{};
-  const size_t lds = mlp_layout(R, NW, AS, sizeof(T), e.XP, e.n_cv,
-                                from_pos ? tin->sys->n_uniq : 0, from_pos, NP, a);
+  const size_t lds = mlp_layout(R, NW, row_stride(e), sizeof(T), e.XP, e.n_cv, NP, a);
   if (lds > 160 * 1024)
     return fail(RID_EUNSUPPORTED, "shape too large for the MLP kernel's LDS");
-  if (from_pos && a.rc < 1)
-    return fail(RID_EUNSUPPORTED, "too many torsion atoms to gather in-kernel");
   // without g_out only the free energies are computed (plain input only)
   const bool grad = g_out != nullptr;
-  if (!grad && from_pos) return fail(RID_EUNSUPPORTED, "energy-only path takes the encoding");
+  if (from_pos && (RT > 1 || !grad || !gathers(e, R, tin->sys->n_uniq)))
+    return fail(RID_EUNSUPPORTED, "in-kernel torsions: not this form (gather_pays)");
   auto kern = grad ? mlp_kernel<PL, NP, RT, NW, LM, false, true>
                    : mlp_kernel<PL, NP, RT, NW, LM, false, false>;
-  if constexpr (RT == 1) {             // (gather_pays: single tiles only)
+  if constexpr (RT == 1) {
     if (from_pos) kern = mlp_kernel<PL, NP, RT, NW, LM, true, true>;
-  } else if (from_pos) {
-    return fail(RID_EUNSUPPORTED, "in-kernel torsions take 16 walkers a workgroup");
   }
   const int ki = grad ? (from_pos ? 1 : 0) : 2;
   if (lds > 64 * 1024 && lds > attr_bytes[ki]) {

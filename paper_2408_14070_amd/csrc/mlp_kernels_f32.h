@@ -35,7 +35,6 @@ struct MlpF32Args {
   float* g_out;        // [K][B][n]
   unsigned off_red, off_mx, off_xs, off_wo;   // LDS byte offsets
   int u0_parts;        // parts of the input-gradient contraction (1, 2 or 4)
-  int rc;              // walkers per torsion-gather pass (bias path)
   dev::SysView sv;          // torsion input (bias path)
   const float* pos;    // [B][n_atoms][3]
   const uint8_t* raw;  // raw[i] = 1: CV i is non-angular, encoded (s_i, 0)
@@ -147,66 +146,58 @@ __global__ __launch_bounds__(NW * 64) void mlp_f32_kernel(MlpF32Args p) {
 
   // ---------------- input tile: x = [cos s | sin s] -> buffer 0 ----------------
   if constexpr (FROM_POS) {
-    // torsions of the tile's walkers, p.rc walkers per pass (the gather
-    // scratch lives in buffer 1).  Gather: a lane owns coordinates
-    // j = lane + 64m of the unique-atom list and copies them for the walkers
-    // of its wave (walkers to the waves in turn); then a lane per torsion.
-    // Coordinates go in chunks of kGatherBatch per lane: the chunk's index
-    // loads, then its coordinate loads for the wave's walkers, then the
-    // stores.  Slots past the end are clamped to the last coordinate or
-    // walker of the pass (they store that slot's own value again), so no
-    // load sits behind a branch; walkers past B get zeros.
-    float* sp = reinterpret_cast<float*>(buf1);   // [rc][U][3]
+    // torsions of the tile's walkers (the gather scratch, buffer 1, holds them
+    // all: gather_pays).  Gather: a lane owns coordinates j = lane + 64m of the
+    // unique-atom list and copies them for the walkers of its wave (walkers to
+    // the waves in turn); then a lane per torsion.  Coordinates go in chunks of
+    // kGatherBatch per lane: the chunk's index loads, then its coordinate loads
+    // for the wave's walkers, then the stores.  Slots past the end are clamped to
+    // the last coordinate or walker (they store that slot's own value again), so
+    // no load sits behind a branch; walkers past B get zeros.
+    float* sp = reinterpret_cast<float*>(buf1);   // [R][U][3]
     const int U3 = 3 * p.sv.U;
-    constexpr int WPW = (R + NW - 1) / NW;    // walkers per wave and pass, at most
+    constexpr int WPW = (R + NW - 1) / NW;    // walkers per wave, at most
     constexpr int QB = WPW < 4 ? WPW : 4;     // walkers per batch of loads
     const size_t wstride = (size_t)p.sv.n_atoms * 3;
-    for (int c0 = 0; c0 < R; c0 += p.rc) {
-      const int rc = R - c0 < p.rc ? R - c0 : p.rc;
-      for (int j0 = lane; j0 < U3; j0 += kGatherBatch * 64) {
-        int jc[kGatherBatch], a[kGatherBatch];
+    for (int j0 = lane; j0 < U3; j0 += kGatherBatch * 64) {
+      int jc[kGatherBatch], a[kGatherBatch];
 #pragma unroll
-        for (int m = 0; m < kGatherBatch; ++m) {
-          jc[m] = min(j0 + m * 64, U3 - 1);
-          const int u = jc[m] / 3;
-          a[m] = 3 * p.sv.uniq[u] + (jc[m] - 3 * u);
-        }
+      for (int m = 0; m < kGatherBatch; ++m) {
+        jc[m] = min(j0 + m * 64, U3 - 1);
+        const int u = jc[m] / 3;
+        a[m] = 3 * p.sv.uniq[u] + (jc[m] - 3 * u);
+      }
 #pragma unroll 1
-        for (int q0 = 0; wave + q0 * NW < rc; q0 += QB) {
-          float v[QB][kGatherBatch];
+      for (int q0 = 0; wave + q0 * NW < R; q0 += QB) {
+        float v[QB][kGatherBatch];
 #pragma unroll
-          for (int q = 0; q < QB; ++q) {
-            const int il = min(wave + (q0 + q) * NW, rc - 1);
-            const int row = min(row0 + c0 + il, p.B - 1);
+        for (int q = 0; q < QB; ++q) {
+          const int row = min(row0 + min(wave + (q0 + q) * NW, R - 1), p.B - 1);
 #pragma unroll
-            for (int m = 0; m < kGatherBatch; ++m) v[q][m] = p.pos[row * wstride + a[m]];
-          }
+          for (int m = 0; m < kGatherBatch; ++m) v[q][m] = p.pos[row * wstride + a[m]];
+        }
 #pragma unroll
-          for (int q = 0; q < QB; ++q) {
-            const int il = min(wave + (q0 + q) * NW, rc - 1);
-            const bool in_b = row0 + c0 + il < p.B;
+        for (int q = 0; q < QB; ++q) {
+          const int i = min(wave + (q0 + q) * NW, R - 1);
 #pragma unroll
-            for (int m = 0; m < kGatherBatch; ++m)
-              sp[il * U3 + jc[m]] = in_b ? v[q][m] : 0.f;
-          }
+          for (int m = 0; m < kGatherBatch; ++m)
+            sp[i * U3 + jc[m]] = row0 + i < p.B ? v[q][m] : 0.f;
         }
       }
-      __syncthreads();
-      for (int il = wave; il < rc; il += NW) {
-        const int i = c0 + il;
-        for (int c = lane; c < n; c += 64) {
-          float cs = 0.f, sn = 0.f;
-          if (row0 + i < p.B) {
-            const Torsion t = torsion(sp + il * U3, p.sv.lq + 4 * c);
-            torsion_cos_sin(t, cs, sn);
-          }
-          xs[i * X2 + c] = cs;
-          xs[i * X2 + n + c] = sn;
-          split_store1(buf0 + i * AX + c, XP, cs * kActScale);
-          split_store1(buf0 + i * AX + n + c, XP, sn * kActScale);
+    }
+    __syncthreads();
+    for (int i = wave; i < R; i += NW) {
+      for (int c = lane; c < n; c += 64) {
+        float cs = 0.f, sn = 0.f;
+        if (row0 + i < p.B) {
+          const Torsion t = torsion(sp + i * U3, p.sv.lq + 4 * c);
+          torsion_cos_sin(t, cs, sn);
         }
+        xs[i * X2 + c] = cs;
+        xs[i * X2 + n + c] = sn;
+        split_store1(buf0 + i * AX + c, XP, cs * kActScale);
+        split_store1(buf0 + i * AX + n + c, XP, sn * kActScale);
       }
-      __syncthreads();
     }
     for (int i = wave; i < R; i += NW)
       for (int c = X2 + lane; c < XP; c += 64) split_store1(buf0 + i * AX + c, XP, 0.f);
@@ -502,7 +493,7 @@ inline unsigned align16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
 int split_u0_parts(int NP, int XP);
 
 // LDS layout of one instantiation; returns the total bytes.
-inline size_t mlp_f32_layout(int NP, int R, int LM, int XP, int n, int U, bool from_pos,
+inline size_t mlp_f32_layout(int NP, int R, int LM, int XP, int n, bool from_pos,
                              MlpF32Args& a) {
   const size_t buf = (size_t)R * dev::split_row_halfs(NP) * 2;
   // buffer 0 also holds the input rows and the partials of u0 (XP > NP: one part)
@@ -514,12 +505,11 @@ inline size_t mlp_f32_layout(int NP, int R, int LM, int XP, int n, int U, bool f
   a.off_xs = align16(off);
   off = a.off_xs + (from_pos ? (size_t)R * 2 * n * 4 : 0);
   a.off_wo = align16(off);
-  off = a.off_wo + (size_t)NP * 4;
-  if (from_pos) {
-    // gather scratch in buffer 1 (free before layer 1), in passes of rc walkers
-    a.rc = (int)std::min<size_t>((size_t)R, buf / ((size_t)12 * U));
-  }
-  return off;
+  return a.off_wo + (size_t)NP * 4;
+}
+// Whether buffer 1 (free before layer 1) holds a tile's torsion atoms.
+inline bool mlp_f32_gathers(int NP, int R, int U) {
+  return (size_t)R * dev::split_row_halfs(NP) * 2 >= (size_t)R * U * 12;
 }
 
 // One instantiation.  RID_EUNSUPPORTED (without a message of its own where
@@ -532,18 +522,14 @@ rid_status run_mlp_f32(const rid_ensemble_impl& e, const float* x, int B, float*
   const bool from_pos = tin != nullptr, grad = g_out != nullptr;
   const SplitDev& s = e.split;
   MlpF32Args a{};
-  const size_t lds = mlp_f32_layout(NP, R, LM, s.XP, e.n_cv, from_pos ? tin->sys->n_uniq : 0,
-                                    from_pos, a);
+  const size_t lds = mlp_f32_layout(NP, R, LM, s.XP, e.n_cv, from_pos, a);
   if (lds > 160 * 1024) return fail(RID_EUNSUPPORTED, "shape too large for the MLP kernel's LDS");
-  if (from_pos && a.rc < 1)
-    return fail(RID_EUNSUPPORTED, "too many torsion atoms to gather in-kernel");
-  if (!grad && from_pos) return fail(RID_EUNSUPPORTED, "energy-only path takes the encoding");
+  if (from_pos && (RT > 1 || !grad || !mlp_f32_gathers(NP, R, tin->sys->n_uniq)))
+    return fail(RID_EUNSUPPORTED, "in-kernel torsions: not this form (gather_pays)");
   auto kern = grad ? dev::mlp_f32_kernel<NP, RT, NW, LM, false, true, RES>
                    : dev::mlp_f32_kernel<NP, RT, NW, LM, false, false, RES>;
-  if constexpr (RT == 1) {             // (gather_pays: single tiles only)
+  if constexpr (RT == 1) {
     if (from_pos) kern = dev::mlp_f32_kernel<NP, RT, NW, LM, true, true, RES>;
-  } else if (from_pos) {
-    return fail(RID_EUNSUPPORTED, "in-kernel torsions take 16 walkers a workgroup");
   }
   const int ki = grad ? (from_pos ? 1 : 0) : 2;
   if (lds > 64 * 1024 && lds > attr_bytes[ki]) {

@@ -284,8 +284,7 @@ rid_status dispatch_mlp_f32(const rid_ensemble_impl& e, const float* x, int B, f
              : e.resnet || s.NP < 192 || s.NP > 256 ? 2 : 4;
   for (; most > 1; most /= 2) {
     MlpF32Args a{};
-    if (mlp_f32_layout(s.NP, 16 * most, 4, s.XP, e.n_cv, t ? t->sys->n_uniq : 0, t != nullptr, a) <=
-        160 * 1024)
+    if (mlp_f32_layout(s.NP, 16 * most, 4, s.XP, e.n_cv, t != nullptr, a) <= 160 * 1024)
       break;
   }
   const int rt = t ? 1 : split_rows(s.NP, B, e.K, most);
