@@ -32,10 +32,10 @@
 // Layout: batched over the K members; "stacked" tensors hold the primal
 // quantity in rows [0, B) and the tangent one in rows [B, 2B) of each
 // member's slab, so one GEMM moves both halves, and the weight gradient is a
-// single contraction over 2B rows.  All GEMMs are one hand-written FP32-MFMA
-// kernel (64x64 tiles, LDS double buffering, arbitrary strides, fused
-// epilogues); the weight-gradient GEMM (both forms) is split along the batch with a
-// fixed-order reduction, so the whole step is deterministic.
+// single contraction over 2B rows.  The general sweeps' GEMMs are one
+// hand-written FP32-MFMA kernel (LDS double buffering, arbitrary strides, fused
+// epilogues); the weight gradients of both forms are wgrad_kernel's, split along
+// the batch with a fixed-order reduction, so the whole step is deterministic.
 #include "device_common.h"
 
 namespace rid {
@@ -43,7 +43,7 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr int BM = 64, BN = 64, BK = 16, LDK = BK + 4;   // BM, BN: split-K sizing
+constexpr int BK = 16;              // contraction block
 constexpr int kThreads = 256;
 
 enum Epi {
@@ -58,7 +58,7 @@ struct GemmArgs {
   const float* Bm;
   long long sBb, sBk, sBn;
   float* C;
-  long long sCb, sCm, sCn, sCs;   // sCs: split-K slab stride
+  long long sCb, sCm, sCn;
   float* C2;                      // second output (EPI_GEN): C's row and
   long long sC2b;                 // column strides, own batch stride
   const float* bias;
@@ -70,7 +70,7 @@ struct GemmArgs {
   long long sMulb;
   const float* add2;
   long long sAdd2b;
-  int M, N, Kc, batch, ksplit, kchunk, mode;
+  int M, N, Kc, batch, mode;
   int modeA, modeB;               // operand load modes (TileLoad), set by gemm()
 };
 
@@ -175,17 +175,15 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) float As[2][TM][BKT + 4];
   __shared__ __attribute__((aligned(16))) float Bs[2][TN][BKT + 4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.z / g.ksplit, s = blockIdx.z % g.ksplit;
+  const int b = blockIdx.z;
   const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  const int k_begin = s * g.kchunk;
-  const int k_end = min(g.Kc, k_begin + g.kchunk);
   const float* A = g.A + b * g.sAb;
   const float* Bp = g.Bm + b * g.sBb;
   TileLoad<TM, BKT> ta;
   TileLoad<TN, BKT> tb;
   auto load = [&](int kb) {
-    ta.template load<VA>(A, g.sAm, g.sAk, g.modeA, m0, g.M, kb, k_end, tid);
-    tb.template load<VB>(Bp, g.sBn, g.sBk, g.modeB, n0, g.N, kb, k_end, tid);
+    ta.template load<VA>(A, g.sAm, g.sAk, g.modeA, m0, g.M, kb, g.Kc, tid);
+    tb.template load<VB>(Bp, g.sBn, g.sBk, g.modeB, n0, g.N, kb, g.Kc, tid);
   };
   auto store = [&](int buf) {
     ta.template store<VA>(As[buf], g.modeA, tid);
@@ -201,11 +199,11 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmArgs g) {
     for (int j = 0; j < TJ; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   int buf = 0;
-  load(k_begin);
+  load(0);
   store(0);
   __syncthreads();
-  for (int kb = k_begin; kb < k_end; kb += BKT) {
-    const bool more = kb + BKT < k_end;
+  for (int kb = 0; kb < g.Kc; kb += BKT) {
+    const bool more = kb + BKT < g.Kc;
     if (more) load(kb + BKT);
 #pragma unroll
     for (int sb = 0; sb < BKT / 16; ++sb) {
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmArgs g) {
   // (bias, add, mul, add2) are loaded for all of the row's elements before
   // any is used (an element outside C reads element 0 and is not stored),
   // so their loads are in flight together.
-  float* C = g.C ? g.C + b * g.sCb + s * g.sCs : nullptr;
+  float* C = g.C ? g.C + b * g.sCb : nullptr;
   constexpr int E = TJ * 4;
 #pragma unroll
   for (int i = 0; i < TI; ++i) {
@@ -970,30 +968,28 @@ void launch_gemm_tile(dim3 grid, const GemmArgs& g, hipStream_t st) {
 #endif
 rid_status gemm(const GemmArgs& g0, hipStream_t st) {
   GemmArgs g = g0;
-  if (g.ksplit < 1) g.ksplit = 1;
-  if (g.kchunk <= 0) g.kchunk = round_up(g.Kc, BK);
   g.modeA = load_mode(g.A, g.sAm, g.sAk, g.sAb, g.M, g.Kc);
   g.modeB = load_mode(g.Bm, g.sBn, g.sBk, g.sBb, g.N, g.Kc);
   // 128 x 128 tiles only when they still give every CU several workgroups
   // (one 4-wave workgroup per CU leaves one wave per SIMD to hide latency);
   // 32 x 64 tiles when 64 x 64 would leave CUs with fewer than two
   const long long tiles128 =
-      (long long)((g.N + 127) / 128) * ((g.M + 127) / 128) * g.batch * g.ksplit;
+      (long long)((g.N + 127) / 128) * ((g.M + 127) / 128) * g.batch;
   const long long tiles64 =
-      (long long)((g.N + 63) / 64) * ((g.M + 63) / 64) * g.batch * g.ksplit;
+      (long long)((g.N + 63) / 64) * ((g.M + 63) / 64) * g.batch;
   if (g.M >= 128 && g.N >= 128 && tiles128 >= 1024) {
-    dim3 grid((g.N + 127) / 128, (g.M + 127) / 128, g.batch * g.ksplit);
+    dim3 grid((g.N + 127) / 128, (g.M + 127) / 128, g.batch);
     launch_gemm_tile<128, 128, BK>(grid, g, st);
   } else if (g.M > 32 && tiles64 < 512) {
-    dim3 grid((g.N + 63) / 64, (g.M + 31) / 32, g.batch * g.ksplit);
+    dim3 grid((g.N + 63) / 64, (g.M + 31) / 32, g.batch);
     // fewer workgroups than CUs: latency-bound, 64-deep contraction blocks
     const long long wgs = (long long)grid.x * grid.y * grid.z;
-    if (wgs < RID_GEMM_DEEP_WGS && g.kchunk >= 64)
+    if (wgs < RID_GEMM_DEEP_WGS && g.Kc > 48)
       launch_gemm_tile<32, 64, 64>(grid, g, st);
     else
       launch_gemm_tile<32, 64, BK>(grid, g, st);
   } else {
-    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, g.batch * g.ksplit);
+    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, g.batch);
     launch_gemm_tile<64, 64, BK>(grid, g, st);
   }
   RID_HIP(hipGetLastError());
