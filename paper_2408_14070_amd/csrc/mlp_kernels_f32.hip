@@ -94,11 +94,7 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
       v[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wr, off, 0, 0));
     }
   }
-  const float pre = dir == 0 ? kTanhPrescale : 1.f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[q][e] *= pre;
+  const float pre = dir == 0 ? kTanhPrescale : 1.f, pre_lo = dir == 0 ? kTanhPrescaleLow : 0.f;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -117,8 +113,8 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
   }
   __syncthreads();
   const int r = lane & 15;
-  mx = fmaxf(fmaxf(rm[0][r], rm[1][r]), fmaxf(rm[2][r], rm[3][r]));
-  sum = (rsum[0][r] + rsum[1][r]) + (rsum[2][r] + rsum[3][r]);
+  mx = pre * fmaxf(fmaxf(rm[0][r], rm[1][r]), fmaxf(rm[2][r], rm[3][r]));
+  sum = pre * ((rsum[0][r] + rsum[1][r]) + (rsum[2][r] + rsum[3][r]));
   // the row's largest weight to [2^9, 2^10); rows of zeros, infinities or
   // NaNs keep a scale that stays a normal number
   const int ex = min(max(split_exp(__float_as_uint(mx)), -100), 126);
@@ -144,9 +140,16 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
     h8 hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float x = v[q][e] * sc;
+      // lo takes what the product with the pre-scale rounds off, and the
+      // pre-scale's own rounding: either is the same for every sample, so that
+      // sums over a batch do not average it out.  (The value as the compiler has
+      // not seen it: it rounded the product to hi in two ways, one for lo.)
+      const float w = v[q][e] * sc;
+      float x = w * pre;
+      asm("" : "+v"(x));
       hi[e] = (_Float16)x;
-      lo[e] = (_Float16)(x - (float)hi[e]);
+      lo[e] = (_Float16)((x - (float)hi[e]) +
+                         __builtin_fmaf(w, pre_lo, __builtin_fmaf(w, pre, -x)));
     }
     unsigned char* dst = base + ((size_t)kt * JT + jt) * kSplitFrag + lane * 16;
     *reinterpret_cast<uint4*>(dst) = __builtin_bit_cast(uint4, hi);

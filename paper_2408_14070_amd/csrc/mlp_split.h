@@ -274,6 +274,7 @@ __device__ inline void split_track(unsigned* m, const f4& v) {
 // Forward weights and biases are stored multiplied by 2/ln 2, so a forward
 // product yields y = 2 z / ln 2 and exp(2z) = 2^y takes no multiply.
 constexpr float kTanhPrescale = 2.8853900817779268f;
+constexpr float kTanhPrescaleLow = 3.8519260e-8f;   // 2/ln 2 less that float
 
 // ln 2 / 2: undoes the forward pre-scale where no bias is added (tangents)
 constexpr float kTanhUnscale = 0.34657359027997264f;

@@ -540,8 +540,12 @@ __global__ void adam_kernel(AdamStep a, const float* g, long long n) {
 // bits, and one at 2^-26 its whole gradient.  A lane holds 8 consecutive rows
 // of one column (the 32x32x16 MFMA's layout), loaded straight from the
 // row-major slabs (128-byte row segments, two steps ahead, no LDS, no barriers
-// in the loop).  On 256-long dots the error against FP64 is 0.8e-7 rms of the
-// result, 2.9e-7 with the FP32 MFMA chain.
+// in the loop).  A step's six products go into a cleared accumulator that is then
+// added to the running one: products far smaller than an MFMA's accumulator
+// are rounded toward minus infinity, and the gradient sums thousands of them
+// (4096 samples: error 1.9e-7 of the gradient, 1.05e-7 so, with FP32 MFMA
+// 0.82e-7; 2.4 % of a step).  For the same reason the sums of rows and of partials
+// add eight values in a tree before they meet the running sum.
 //
 // What bounds it: the slabs, 235 MB at 4096 samples of 4 x [256 x 4], read at
 // 2 TB/s (359 MB with the L2's misses), and the splits and products beside
@@ -593,6 +597,10 @@ constexpr int kWgLdsStride = 65;   // padded row of a partial tile in LDS
 constexpr int kWgTile = 64;        // tile edge of a workgroup
 constexpr int kWgStep = 16;        // contraction rows of a step
 
+__device__ inline float tree8(const float (&v)[8]) {
+  return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+
 // The three BF16 parts of eight values.
 struct Split8 {
   uint4 p[3];
@@ -641,8 +649,7 @@ __device__ inline void wgrad_extra(const WgradArgs& g, int blk, float* red) {
     float v[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) v[q] = x[(long long)(k + 4 * q) * g.w];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc += v[q];
+    acc += tree8(v);
   }
   for (; k < r1; k += 4) acc += x[(long long)k * g.w];
   red[64 * wave + lane] = acc;
@@ -679,7 +686,8 @@ __device__ inline bool wgrad_tile(const WgradArgs& g, int blk, WgradTile& w) {
   return true;
 }
 
-__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
+// (two workgroups a CU: without the bound the compiler took registers for one)
+__global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs g) {
   __shared__ float red[2][64][kWgLdsStride];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -737,11 +745,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
   };
   auto consume = [&](const float (&v)[4][8], bool tangent) {
     if (csum_wg && !tangent) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        cs[0] += v[0][e];
-        cs[1] += v[1][e];
-      }
+      cs[0] += tree8(v[0]);
+      cs[1] += tree8(v[1]);
     }
     Split8 fb[2];
     fb[0].set(v[2]);
@@ -752,10 +757,13 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
       fa.set(v[i]);
       constexpr int pa[6] = {0, 2, 1, 0, 1, 0};   // small products first
       constexpr int pb[6] = {2, 0, 1, 1, 0, 0};
+      f16v sum[2] = {f16v{}, f16v{}};
 #pragma unroll
       for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) wg_mfma(acc[i][j], fa.p[pa[t]], fb[j].p[pb[t]]);
+        for (int j = 0; j < 2; ++j) wg_mfma(sum[j], fa.p[pa[t]], fb[j].p[pb[t]]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] += sum[j];
     }
   };
   // (a step past the last one re-reads the last, never consumed)
@@ -876,15 +884,14 @@ struct ReduceArgs {
   AdamStep adam;
 };
 __device__ inline float sum_parts(const float* src, long long stride, int n) {
-  // parts added in order, eight loads in flight
+  // parts in order, eight loads in flight and added in a tree
   float acc = 0.f;
   int s = 0;
   for (; s + 8 <= n; s += 8) {
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = src[(s + j) * stride];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc += v[j];
+    acc += tree8(v);
   }
   for (; s < n; ++s) acc += src[s * stride];
   return acc;
