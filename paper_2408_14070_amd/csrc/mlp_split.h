@@ -308,10 +308,12 @@ __device__ inline float tanh_and_grad(float y, float& d) {
 // The raw CVs' part of layer 1 on FP32 MFMA, acc += W x over the CVs in sets of
 // 16 (those that hold a raw one): weights in FP32 fragments, lane l holding unit
 // l % 16 and CVs 4 (l / 16) .. + 3 of the set, zero for angular CVs; x(rt, i) is
-// the lane's walker's value of CV i in row tile rt (i < n; past n the last
-// one's, its weight zero).  A set costs 4 MFMAs a tile and one round trip to
-// L2, below 1 us: 1000 walkers of 4 x [256 x 4], 38 CVs, 26.8 us without, 28.2 with
-// 12 raw ones, 30.0 with 38 (36.1 when every product ran on FP32 MFMA).
+// the lane's walker's values of CVs i .. i + 3 in row tile rt (whatever stands
+// past the last CV is not used).  What bounds it is the loads of x: every wave
+// reads the tile's 16 rows, 16 bytes a lane (as four loads a lane 38 raw CVs cost
+// 3.0 us instead of 1.3).  1000 walkers of 4 x [256 x 4]: 27.0 us without, 27.8
+// with 12 of 38 CVs raw, 28.3 with all (36.2 when every product ran on FP32
+// MFMA); 300 walkers, 200 raw CVs, 4 x [512 x 4]: 91 and 101 (135).
 struct RawSrc {
   __amdgpu_buffer_rsrc_t r;   // one member's fragments
   unsigned sets;              // bit t: set t holds a raw CV
@@ -320,32 +322,32 @@ struct RawSrc {
 template <int RT, int CT, class X>
 __device__ inline void raw_gemm(f4 (&acc)[RT][CT], const RawSrc& s, int jt0, int lane, X&& x) {
   for (unsigned m = s.sets; m; m &= m - 1) {
-    const int t = __builtin_ctz(m);
-    f4 w[CT];
+    const int t = __builtin_ctz(m), i = 16 * t + 4 * (lane >> 4);
+    f4 w[CT], v[RT];
 #pragma unroll
     for (int c = 0; c < CT; ++c)
       w[c] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
                                         s.r, lane * 16, ((jt0 + c) * s.n_sets + t) * 1024, 0));
-    float v[RT][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = min(16 * t + 4 * (lane >> 4) + e, s.n - 1);
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) v[rt][e] = x(rt, i);
-    }
+    for (int rt = 0; rt < RT; ++rt) v[rt] = x(rt, i);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
+      for (int rt = 0; rt < RT; ++rt) {
+        const float ve = i + e < s.n ? v[rt][e] : 0.f;
 #pragma unroll
         for (int c = 0; c < CT; ++c)
-          acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][e], v[rt][e], acc[rt][c], 0, 0, 0);
+          acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][e], ve, acc[rt][c], 0, 0, 0);
+      }
   }
 }
 // A raw CV's value; an infinity becomes a number large enough to saturate
 // (padded units have zero weights, and 0 inf is a NaN).
 __device__ inline float raw_value(float s) {
   return __builtin_isinf(s) ? __builtin_copysignf(1e30f, s) : s;
+}
+__device__ inline f4 raw_value(f4 s) {
+  return f4{raw_value(s[0]), raw_value(s[1]), raw_value(s[2]), raw_value(s[3])};
 }
 
 // Block -> (member, tile), XCD-aware: when K divides 8 (grp = 8 / K), member
@@ -393,8 +395,8 @@ __device__ inline __amdgpu_buffer_rsrc_t row_src(const float* p, int rows, int s
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, 4 * rows * stride,
                                            0x00020000);
 }
-__device__ inline float row_ld(const __amdgpu_buffer_rsrc_t& r, int offset) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, 4 * offset, 0, 0));
+__device__ inline f4 row_ld(const __amdgpu_buffer_rsrc_t& r, int offset) {
+  return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, 4 * offset, 0, 0));
 }
 }  // namespace dev
 

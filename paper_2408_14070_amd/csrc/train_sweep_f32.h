@@ -82,6 +82,14 @@ __device__ inline f4 reread(f4 v) {
   return v;
 }
 
+// Four consecutive floats of an LDS array of `count` (none past its end).
+__device__ inline f4 lds_ld4(const float* p, int i, int count) {
+  f4 v;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = p[min(i + q, count - 1)];
+  return v;
+}
+
 // rows of tracked maxima: u, hd, zd, lam_h, lam_hd per layer, then the raw
 // CVs' bounds on layer 1's tangents and the layer bounds
 __host__ __device__ constexpr int train_track_words(int LM, int R) {
@@ -341,7 +349,7 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
       }
       iv0 = 1.f;
       raw_gemm<RT, CT>(acc, raw_src(p.w, k, NP, n), jt0, lane,
-                       [&](int rt, int i) { return xs[(rt * 16 + wl) * X2 + i]; });
+                       [&](int rt, int i) { return lds_ld4(xs, (rt * 16 + wl) * X2 + i, R * X2); });
     }
     if (L > 1) split_preload<PDH, CT>(wh, wfwd(1), NK, lane);
     fwd_epi(0, acc, buf1);
@@ -575,7 +583,7 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) iv[rt] = 1.f;
       raw_gemm<RT, CT>(acc, raw_src(p.w, k, NP, n), jt0, lane,
-                       [&](int rt, int i) { return xs[(rt * 16 + wl) * X2 + n + i]; });
+                       [&](int rt, int i) { return lds_ld4(xs, (rt * 16 + wl) * X2 + n + i, R * X2); });
     }
     if (L > 1) split_preload<PDH, CT>(wh, wfwd(1), NK, lane);
     tan_epi(0, acc, buf0);
