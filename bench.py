@@ -36,6 +36,7 @@ import ridgen  # noqa: E402
 HBM_PEAK_GBS = 8000.0
 BF16_PEAK_TFLOPS = 2500.0     # dense; FP16 has the same dense peak
 SPLIT_PEAK_TFLOPS = BF16_PEAK_TFLOPS / 3   # FP32 ensembles: three FP16 MFMAs per product
+L2_STREAM_TBS = 28.0                       # L2 -> CU reads, measured (a streaming probe)
 
 
 def log(msg):
@@ -179,6 +180,17 @@ def train_source_hash():
 # training kernels the counter passes summarize: key, name test
 TRAIN_PMC_KEYS = (("train_kernel_4x256_b4096", lambda n: "train_f32_kernel" in n),
                   ("wgrad_kernel_4x256_b4096", lambda n: "wgrad_kernel" in n))
+
+
+def fp32_weight_stream(n_cv, widths, K, B, rows, ms):
+    """The FP32 MLP kernel's weight stream from L2 to the CUs: every workgroup
+    (`rows` walkers of one member) reads its member's fragments of both
+    directions once, 4 bytes a weight, widths padded as the kernel pads them."""
+    pad = next(w for w in (64, 128, 192, 256, 320, 384, 512) if w >= max(widths))
+    per_member = 8 * pad * ((2 * n_cv + 31) // 32 * 32 + (len(widths) - 1) * pad)
+    byts = per_member * K * ((B + rows - 1) // rows)
+    return {"bytes": byts, "achieved": byts / (ms * 1e-3) / 1e12, "peak": L2_STREAM_TBS,
+            "unit": "TB/s", "frac": byts / (ms * 1e-3) / 1e12 / L2_STREAM_TBS}
 
 
 def pmc_for(kernel_key):
@@ -345,13 +357,16 @@ def _mlp_signature(name):
 
 
 def mlp_display(name):
-    """A short readable name of an mlp_kernel instance (else None)."""
+    """A short readable name of an mlp_kernel or mlp_f32_kernel instance (else
+    None)."""
     sig = _mlp_signature(name)
     if sig is None:
         return None
     fmts, ints, flags = sig
-    return ("mlp_kernel<Plan<" + ", ".join(fmts) + ">, " + ", ".join(map(str, ints)) + ", "
-            + ", ".join("true" if f else "false" for f in flags) + ">")
+    f32 = fmts[0] == "F32"
+    return (("mlp_f32_kernel<" if f32 else "mlp_kernel<Plan<" + ", ".join(fmts) + ">, ")
+            + ", ".join(map(str, ints)) + ", "
+            + ", ".join("true" if f else "false" for f in (flags if f32 else flags[:2])) + ">")
 
 
 def pmc_kernel_key(name):
@@ -591,8 +606,8 @@ def bench_precision(rid, torch, sys20, prec, name, steps, warmup, samples):
                     "walkers (CVs encoded once by cv_eval, then the MLP kernel)",
         "value": Bb * steps / el, "unit": "walker-steps/s", "ms_per_step": 1e3 * el / steps,
         "call_us_percentiles": call_pct,
-        "roofline": {"bound": "mfma", "achieved": ach, "peak": peak,
-                     "unit": "TFLOP/s", "frac": ach / peak,
+        "roofline": {"bound": "weight stream" if name == "FP32" else "mfma", "achieved": ach,
+                     "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
                      "traffic": traffic_for(f"mlp_{name.lower()}_8x512_b16384"),
                      "mfma_busy": mfma_busy_for(f"mlp_{name.lower()}_8x512_b16384"),
                      "avg_launch_us": kern["mlp"] * 1e3, "flop_per_launch": fl},
@@ -615,8 +630,10 @@ def bench_variants(rid, torch, sys20, steps, warmup):
         "workload": "headline chain and ensemble with residual connections between the "
                     "hidden layers (h_l = h_{l-1} + tanh(W_l h_{l-1} + b_l), l >= 2)",
         "value": B * steps / el, "unit": "walker-steps/s", "ms_per_step": 1e3 * el / steps,
-        "roofline": {"bound": "mfma", "achieved": ach, "peak": SPLIT_PEAK_TFLOPS,
+        "roofline": {"bound": "weight stream", "achieved": ach, "peak": SPLIT_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": ach / SPLIT_PEAK_TFLOPS,
+                     "weight_stream": fp32_weight_stream(c["E"].n_cv, widths, K, B, 16,
+                                                         kern["mlp"]),
                      "avg_launch_us": kern["mlp"] * 1e3, "flop_per_launch": fl},
         "kernels_us": {k: v * 1e3 for k, v in kern.items()},
     }
@@ -630,8 +647,10 @@ def bench_variants(rid, torch, sys20, steps, warmup):
         "workload": "headline chain with 6 CA-CA distance CVs among its 38 torsions (44 CVs, "
                     "angular mask 0 for the distances), headline ensemble shape",
         "value": B * steps / el, "unit": "walker-steps/s", "ms_per_step": 1e3 * el / steps,
-        "roofline": {"bound": "mfma", "achieved": ach, "peak": SPLIT_PEAK_TFLOPS,
+        "roofline": {"bound": "weight stream", "achieved": ach, "peak": SPLIT_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": ach / SPLIT_PEAK_TFLOPS,
+                     "weight_stream": fp32_weight_stream(c["E"].n_cv, widths, K, B, 16,
+                                                         kern["mlp"]),
                      "avg_launch_us": kern["mlp"] * 1e3, "flop_per_launch": fl},
         "kernels_us": {k: v * 1e3 for k, v in kern.items()},
     }
@@ -1065,8 +1084,10 @@ def main():
     value = B * args.steps / elapsed
     flop_launch = mlp_flops_per_walker(sys20.n_cv, widths, K) * B
     achieved = flop_launch / (kern["mlp"] * 1e-3) / 1e12
-    roof = {"bound": "mfma", "achieved": achieved, "peak": SPLIT_PEAK_TFLOPS,
+    # (bound by the weight stream; achieved, peak and frac price the products)
+    roof = {"bound": "weight stream", "achieved": achieved, "peak": SPLIT_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": achieved / SPLIT_PEAK_TFLOPS,
+            "weight_stream": fp32_weight_stream(sys20.n_cv, widths, K, B, 16, kern["mlp"]),
             "traffic": traffic_for("mlp_fp32_4x256_b1024"),
             "mfma_busy": mfma_busy_for("mlp_fp32_4x256_b1024"),
             "kernel": "mlp_f32_kernel<256> (torsions gathered in-kernel + ensemble "

@@ -54,8 +54,11 @@ typedef enum {
                        FP32 MFMA, whatever their size; weight gradients on
                        BF16 in three parts (all 24 bits, FP32's range).  Error
                        against FP64 measured no larger than that of FP32 MFMA
-                       throughout (networks of ordinary scaling, saturated
-                       units, raw CVs of 1e-6 to 1e7)                      */
+                       for forces, energies and training steps (networks of
+                       ordinary scaling, saturated units, raw CVs of 1e-6 to
+                       1e7); the gradient of a batch of 4096, whose sums
+                       average random roundings out: 1.05e-7 of its norm
+                       against 0.82e-7                                     */
   RID_BF16 = 1,     /* the precision form: the hidden-layer forward GEMMs on
                        BF16 MFMA with FP32 accumulation (BF16 weights and
                        activations); the first layer (CV encoding -> first

@@ -10,7 +10,7 @@
 // rows take a third of that time; so a workgroup takes as many 16-walker row
 // tiles (RT) as the LDS and the registers hold without idling CUs
 // (split_rows()).  Against the FP32 MFMA form it replaced (kernel time):
-// 1024 walkers, 38 CVs, 4 x [256 x 4]: 33.1 -> 24.5 us; 20 000: 598 -> 224;
+// 1024 walkers, 38 CVs, 4 x [256 x 4]: 33.1 -> 22.5 us; 20 000: 598 -> 224;
 // 333 walkers, 120 CVs, 4 x [512 x 4]: 120.6 -> 71; 12 walkers, 18 CVs,
 // residual 4 x [300 x 4] (padded to 320 instead of 512): 98.7 -> 38; energies
 // of 2000 MCMC walkers 32.5 -> 15 us; force error against FP64 7.1e-7 -> 5.2e-7.

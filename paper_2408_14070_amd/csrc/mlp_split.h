@@ -24,8 +24,9 @@
 //    scale per row (a walker's vector), from a bound that cannot overflow:
 //    the largest entry of the previous layer's vector (tracked in LDS) times
 //    the largest absolute row sum of the layer's weights (from the packer).
-//    The bound is typically 2^4 to 2^6 above the true maximum; FP16 pairs
-//    keep full precision 2^28 below it.
+//    The bound is typically 2^4 to 2^6 above the true maximum.  lo's smallest
+//    step is 2^-24 and values stay below 2^14, so a pair keeps 22 bits down to
+//    2^-16 of the bound and one less per power of two below (11 at 2^-28).
 #pragma once
 
 #include <type_traits>

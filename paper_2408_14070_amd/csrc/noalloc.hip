@@ -3,12 +3,12 @@
 // capture, tight serving loops, harnesses that forbid allocation).
 //
 // The scratch (per-member free energies A [K][B], mean forces g [K][B][n]
-// and, above the in-kernel gather's batch limit, the CV encoding x [B][2n])
-// lives in `scratch`, a file-scope device array of kScratchFloats floats
-// (32 MiB) that each GPU the library runs on holds until the process ends.
-// Its device address is looked up once per device (hipGetSymbolAddress, with
-// that device current) and kept; kernels receive that address, never the
-// array's name.  Every kernel writes each scratch element it later reads
+// and, for calls whose CVs are encoded first, the CV encoding x [B][2n]) lives
+// in `scratch`, a file-scope device array of kScratchFloats floats (32 MiB)
+// that each GPU the library runs on holds until the process ends.  Its device
+// address is looked up once per device (hipGetSymbolAddress, with that device
+// current) and kept; kernels receive that address, never the array's name.
+// Every kernel writes each scratch element it later reads
 // (A and g for every walker row below B, x likewise), so nothing needs to
 // start at zero.  All calls on one GPU share the array: calls that overlap
 // on one GPU (different streams, or different host threads without ordering)

@@ -548,10 +548,10 @@ __global__ void adam_kernel(AdamStep a, const float* g, long long n) {
 // add eight values in a tree before they meet the running sum.
 //
 // What bounds it: the slabs, 235 MB at 4096 samples of 4 x [256 x 4], read at
-// 2 TB/s (359 MB with the L2's misses), and the splits and products beside
-// them.  Measured per pass there: 205 us with FP32 MFMA and a launch per layer
-// (and 38 us of column sums, partial sums and losses in seven more), 118 us
-// now; 128 samples of residual 4 x [300 x 4]: 41 (and 14) us before, 19 us now.
+// 2 TB/s (293 MB with the L2's misses), and the splits and products beside
+// them (matrix units 0.42 busy).  Measured per pass there: 205 us with FP32
+// MFMA and a launch per layer (and 38 us of column sums, partial sums and
+// losses in seven more), 125 us now; 128 samples of residual 4 x [300 x 4]: 41 (and 14) us before, 19 us now.
 // With FP16 pairs, 8-byte loads of column pairs took 103 instead of 99 us;
 // 128 x 128 tiles split once through LDS 90 us at 4096 samples and 5 % off a
 // step of 16384, but 15 % longer below 500 samples.
@@ -1133,9 +1133,9 @@ int chunk_rows(long long floats_per_row, int B, size_t budget, int wmax) {
 // one tile alone on a CU runs at 0.8 of the rate two reach together, and a
 // chunk's partial gradient costs 1 row per 5.7 kB written and read back.
 // Measured per training step (us, 4 members of [256 x 4] unless noted; chunks
-// 1 / 2 / 4): 1024 samples 114 / 111 / 117, 4096 samples 299 / 287 / 292,
-// 16384 samples 1254 / 1174 / 1175, 4096 samples of [300 x 4] 611 / 480 / 472,
-// one member and 4096 samples, chunks 4 / 8 / 16: 103 / 99 / 103.
+// 1 / 2 / 4): 1024 samples 116 / 110 / 118, 4096 samples 338 / 300 / 308,
+// 16384 samples 1370 / 1233 / 1245, 4096 samples of [300 x 4] 622 / 486 / 474,
+// one member and 4096 samples, chunks 4 / 8 / 16: 104 / 100 / 107.
 struct WgradSplit {
   int ks, kchunk;
 };

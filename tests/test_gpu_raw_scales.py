@@ -192,3 +192,16 @@ def test_infinite_raw_cvs_saturate(torch, rid, inf):
     keep = np.arange(B) != 7
     for p, f, g in zip(plain, far, got):
         assert np.array_equal(f, g) and np.isfinite(g).all() and np.array_equal(p[keep], g[keep])
+
+
+@pytest.mark.parametrize("width,layers,resnet", [(64, 3, False), (256, 4, False), (300, 3, True)])
+def test_same_bits_in_every_row_tile(torch, rid, width, layers, resnet):
+    """Large calls (32 or 64 walkers a workgroup) and slices of them (16)."""
+    n, K, B = 37, 4, 9000 if width == 64 else 4500
+    s, mask, params, _ = _case(n, [width] * layers, K, B, 3.0, 12, resnet, every=3)
+    E = _ensemble(rid, n, [width] * layers, K, params, mask, resnet)
+    full = [o.cpu().numpy() for o in rid.model_dev(E, torch.from_numpy(s).cuda())]
+    for lo, hi in ((0, 1), (37, 96), (B - 33, B)):
+        part = rid.model_dev(E, torch.from_numpy(np.ascontiguousarray(s[lo:hi])).cuda())
+        for a, b in zip(full, part):
+            assert np.array_equal(a[lo:hi], b.cpu().numpy())
