@@ -172,7 +172,7 @@ static rid_status alloc_kernel_weights(rid_ensemble_impl& e, int wmax) {
     split_layout(e);
     SplitDev& s = e.split;
     const size_t n_bias = KL * s.NP, n_rs = KL * 2 * s.RW, n_bound = KL * 2 * 32, n_wo = K * s.NP;
-    if ((st = dev_alloc(&s.frag, s.frag_bytes * K)) != RID_OK) return st;
+    if ((st = dev_alloc(&s.frag, 2 * s.frag_bytes * K)) != RID_OK) return st;
     if ((st = dev_alloc(&s.vec, n_bias + n_rs + n_bound + n_wo + K)) != RID_OK) return st;
     s.bias = s.vec;
     s.rs = s.bias + n_bias;

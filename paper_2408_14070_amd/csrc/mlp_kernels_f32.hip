@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
   for (int q = 0; q < 4; ++q) {
     const int kt = wave + 4 * q;
     if (kt >= KT) break;
-    h8 hi, lo;
+    h8 hi, lo, lo2;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       // lo takes what the product with the pre-scale rounds off, and the
@@ -148,12 +148,21 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
       float x = w * pre;
       asm("" : "+v"(x));
       hi[e] = (_Float16)x;
-      lo[e] = (_Float16)((x - (float)hi[e]) +
-                         __builtin_fmaf(w, pre_lo, __builtin_fmaf(w, pre, -x)));
+      float r = (x - (float)hi[e]) + __builtin_fmaf(w, pre_lo, __builtin_fmaf(w, pre, -x));
+      asm("" : "+v"(r));
+      lo[e] = (_Float16)r;
+      // lo's own rounding is the same for every sample too: the second set's lo
+      // is off by as much the other way (exactly where r fits FP16 but for its
+      // last bit, as all of a backward row's do), and half the tiles of a
+      // training step read it
+      lo2[e] = (_Float16)(r + (r - (float)lo[e]));
     }
     unsigned char* dst = base + ((size_t)kt * JT + jt) * kSplitFrag + lane * 16;
+    unsigned char* dst2 = dst + (size_t)p.K * p.frag_bytes;
     *reinterpret_cast<uint4*>(dst) = __builtin_bit_cast(uint4, hi);
     *reinterpret_cast<uint4*>(dst + kFragBytes) = __builtin_bit_cast(uint4, lo);
+    *reinterpret_cast<uint4*>(dst2) = __builtin_bit_cast(uint4, hi);
+    *reinterpret_cast<uint4*>(dst2 + kFragBytes) = __builtin_bit_cast(uint4, lo2);
   }
 }
 

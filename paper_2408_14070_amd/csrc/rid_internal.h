@@ -113,7 +113,9 @@ struct SplitDev {
   int RW = 0;                        // row stride of rs: max(NP, XP)
   size_t frag_bytes = 0;             // bytes of one member's fragments
   std::vector<LayerDev> layers;
-  unsigned char* frag = nullptr;     // [K][frag_bytes]
+  // [2][K][frag_bytes]: a second set, its lo parts rounded so that the two
+  // sets' errors cancel, for the training sweeps (sums over a batch)
+  unsigned char* frag = nullptr;
   // raw CVs (angular mask 0): their layer-1 weights stay FP32, out of the
   // forward fragments, in FP32 fragments of 16 units x 16 CVs (mlp_split.h); one
   // allocation: raw_w | raw_max

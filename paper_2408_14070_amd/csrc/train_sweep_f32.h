@@ -139,7 +139,9 @@ __global__ __launch_bounds__(NW * 64) void train_f32_kernel(TrainF32Args p) {
   float* cb = m_raw + R;                       // [kMaxHidden + 1] S C_l (slot 0: max |w_o|)
   float* rb = cb + kMaxHidden + 1;             // [kMaxHidden + 1] S R_l
 
-  const unsigned char* fbase = p.w.frag + (size_t)k * p.w.frag_bytes;
+  // odd tiles read the second set of fragments (the weights' rounding errors,
+  // the same for every sample, then cancel in the sums over the batch)
+  const unsigned char* fbase = p.w.frag + (size_t)((tile & 1) * p.K + k) * p.w.frag_bytes;
   const float* bias = p.w.bias + (size_t)k * L * NP;
   const float* rs = p.w.rs + (size_t)k * L * 2 * p.w.RW;
   const int jt0 = wave * CT;

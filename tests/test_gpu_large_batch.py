@@ -58,3 +58,35 @@ def test_gradient_of_a_coherent_batch(torch, rid, n, width, layers, K, B):
         err[name] = max(err[name], np.linalg.norm(x - y) / np.linalg.norm(y))
     print(f"K={K} B={B}: " + ", ".join(f"{k} {v:.2e}" for k, v in err.items()), flush=True)
     assert err["weights"] <= 1.5e-7 and err["output"] <= 1.3e-7
+
+
+def test_weights_that_round_alike(torch, rid):
+    """Every weight's last 13 bits are 0x803: 11 + 11 bits of an FP16 pair leave an
+    odd half unit that rounds the same way in every weight (up, 2^-24 to 2^-23 of
+    it), so the errors of one rounding add up through the layers: FP64 sweeps with
+    weights so rounded are off by 1.4e-7.  With two roundings of opposite error
+    over the batch they are off by 0.33e-7.  The bound: that, FP32 sums (up to
+    6e-8) and the sweeps' own arithmetic (7e-8) in quadrature, and a fifth on top."""
+    n, widths, K, B = 38, [256] * 4, 1, 4096
+    rng = np.random.default_rng(1)
+    s = ridgen.f32(rng.uniform(-np.pi, np.pi, (B, n)))
+    a, b = rng.uniform(0.5, 5.0, n), rng.uniform(-np.pi, np.pi, n)
+    F = ridgen.f32(a * np.sin(s - b) + rng.normal(0.0, 0.5, s.shape))
+    params = np.array(ridgen.xavier_ensemble(2 * n, widths, K, 1000, bias_std=0.05), np.float32)
+    bits = params.view(np.uint32)
+    blocks, off, prev = [], 0, 2 * n
+    for w in widths:
+        blocks.append((off, w * prev))
+        bits[off:off + w * prev] = (bits[off:off + w * prev] & ~np.uint32(0x1FFF)) | np.uint32(0x803)
+        off += w * prev + w
+        prev = w
+    E = rid.Ensemble(n, widths, K, params)
+    _, grad = rid.mf_loss_grad(E, torch.from_numpy(s).cuda(), torch.from_numpy(F).cuda())
+    torch.cuda.synchronize()
+    grad = grad.cpu().numpy().reshape(-1).astype(np.float64)
+    model, = ridgen.unpack_params(params, 2 * n, widths, K)
+    ref = O.flat_grad(O.train_loss_grad(model, s, F)[1])
+    x, y = (np.concatenate([g[o:o + c] for o, c in blocks]) for g in (grad, ref))
+    err = np.linalg.norm(x - y) / np.linalg.norm(y)
+    print(f"weights {err:.2e}", flush=True)
+    assert err <= 1.2e-7
