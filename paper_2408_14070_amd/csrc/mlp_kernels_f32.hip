@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitPackArgs p) {
       if (p.raw && y == 0) ok = ok && !p.raw[min(i < p.n ? i : i - p.n, p.n - 1)];
       // (outside: an offset past the resource, which reads as 0.  As a branch
       // around the load the compiler waited on each of the 32: 12.9 us a pack
-      // of 4 x [300 x 4], 8.4 so)
+      // of 4 x [300 x 4], 8.4 so, and 10.3 with the second set of fragments)
       const int off = ok ? 4 * (o * in + i) : 0x7FFFFFF0;
       v[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wr, off, 0, 0));
     }
